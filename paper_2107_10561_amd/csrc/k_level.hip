@@ -249,27 +249,89 @@ hipError_t launch_spmv(hipStream_t s, int b, const DevLevel& L, const double* r,
 
 // Level residual from the spatial factors of an operator whose blocks are
 // C[i][l] M + delta_il tw[i] A (time-independent coefficients): per block only
-// the two scalars m = M(s, s') and a = A(s, s') are streamed.  SPLIT: a row's
-// blocks come in two lists, those with m != 0 as one 16-byte (m, a) pair,
-// then those with m = 0 (the velocity-pressure couplings of a mass matrix
-// that acts on the velocity only) as a only, 8 bytes; otherwise one list of
-// (m, a) pairs in the level's block order.  LPR lanes per block row
-// (64 / LPR rows per wavefront): lane `sub` of a row takes the list's blocks
-// sub, sub + LPR, ..., U of them per round, with every load of a round issued
-// before the first is used (indices clamped into the list, the blocks past
-// its end weighted by zero, instead of branches), and keeps only the B
-// partial sums of its own row; the row's lanes then add their sums
+// the two scalars m = M(s, s') and a = A(s, s') are streamed.  LPR lanes per
+// block row (64 / LPR rows per wavefront): lane `sub` of a row takes the
+// row's blocks sub, sub + LPR, ..., U of them per round, with every load of a
+// round issued before the first is used (indices clamped into the list, the
+// blocks past its end weighted by zero, instead of branches), and keeps only
+// the B partial sums of its own row; the row's lanes then add their sums
 // (butterfly over the LPR lanes).  LPR x U slots per round are matched to
 // the typical row length by the autotuner.
 struct KronCoef { double C[16]; double tw[4]; };
 
-template <int B, int LPR, int U, bool SPLIT>
-__global__ void __launch_bounds__(256) k_spmv_kron(const int32_t* __restrict__ rp1,
-                                                   const int32_t* __restrict__ col1,
+// Sum of acc[0 .. NV) over the LPR lanes of a row, in every lane of the row.
+template <int LPR, int NV>
+__device__ __forceinline__ void row_sum(double (&acc)[NV]) {
+#pragma unroll
+  for (int off = LPR / 2; off >= 1; off >>= 1)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
+}
+
+// The first nv of NV entries y[o0 ..] = r + sx acc, entry e from lane e % LPR.
+template <int LPR, int NV, int E0 = 0>
+__device__ __forceinline__ void row_store(const double (&acc)[NV], int nv, int sub, int64_t o0,
+                                          const double* __restrict__ r, double* __restrict__ y,
+                                          double sx) {
+  constexpr int CNT = NV - E0 < LPR ? NV - E0 : LPR;
+  // values first, then the choice: a conditional read of acc would be turned
+  // into one read at a run-time index, which moves acc out of registers
+  double v[CNT];
+#pragma unroll
+  for (int e = 0; e < CNT; ++e) v[e] = acc[E0 + e];
+  double s = v[0];
+#pragma unroll
+  for (int e = 1; e < CNT; ++e) s = (sub == e) ? v[e] : s;
+  if (sub < CNT && E0 + sub < nv) {
+    const int64_t o = o0 + E0 + sub;
+    y[o] = r ? fma(sx, s, r[o]) : sx * s;
+  }
+  if constexpr (E0 + LPR < NV) row_store<LPR, NV, E0 + LPR>(acc, nv, sub, o0, r, y, sx);
+}
+
+// acc += the (m, a) blocks [q0, q1) of one row (list position in ma and col).
+template <int B, int LPR, int U, int NV>
+__device__ __forceinline__ void row_pairs(int32_t q0, int32_t q1, int sub,
+                                          const int32_t* __restrict__ col,
+                                          const double2* __restrict__ ma,
+                                          const double* __restrict__ x, const KronCoef& K,
+                                          double (&acc)[NV]) {
+  const int nit = (q1 - q0 + U * LPR - 1) / (U * LPR);
+  for (int it = 0; it < nit; ++it) {
+    const int32_t qb = q0 + it * U * LPR + sub;
+    int64_t c[U];
+    double m[U], a[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t q = qb + u * LPR;
+      const bool v = q < q1;
+      const int32_t qc = v ? q : q1 - 1;
+      c[u] = col[qc];
+      const double2 f = ma[qc];
+      m[u] = v ? f.x : 0.0;
+      a[u] = v ? f.y : 0.0;
+    }
+    double xl[U][B];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int l = 0; l < B; ++l) xl[u][l] = x[c[u] * B + l];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        double ci = 0.0;
+#pragma unroll
+        for (int l = 0; l < B; ++l) ci = fma(K.C[i * B + l], xl[u][l], ci);
+        acc[i] = fma(m[u], ci, fma(a[u] * K.tw[i], xl[u][i], acc[i]));
+      }
+  }
+}
+
+template <int B, int LPR, int U>
+__global__ void __launch_bounds__(256) k_spmv_kron(const int32_t* __restrict__ rowptr,
+                                                   const int32_t* __restrict__ col,
                                                    const double2* __restrict__ ma,
-                                                   const int32_t* __restrict__ rp2,
-                                                   const int32_t* __restrict__ col2,
-                                                   const double* __restrict__ a2,
                                                    const double* __restrict__ r,
                                                    const double* __restrict__ x,
                                                    double* __restrict__ y, int32_t n_rows,
@@ -279,48 +341,161 @@ __global__ void __launch_bounds__(256) k_spmv_kron(const int32_t* __restrict__ r
   const int row = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPWV + lane / LPR;
   const bool live = row < n_rows;
   const int rr = live ? row : n_rows - 1;
-  double rv = 0.0;
-  if (r && live && sub < B) rv = r[(int64_t)rr * B + sub];
   double acc[B];
 #pragma unroll
   for (int i = 0; i < B; ++i) acc[i] = 0.0;
-  // blocks with a mass entry: (m, a)
-  {
-    const int32_t q0 = rp1[rr], q1 = rp1[rr + 1];
-    const int nit = (q1 - q0 + U * LPR - 1) / (U * LPR);
-    for (int it = 0; it < nit; ++it) {
-      const int32_t qb = q0 + it * U * LPR + sub;
-      int64_t c[U];
-      double m[U], a[U];
+  row_pairs<B, LPR, U>(rowptr[rr], rowptr[rr + 1], sub, col, ma, x, K, acc);
+  row_sum<LPR>(acc);
+  if (live) row_store<LPR>(acc, B, sub, (int64_t)row * B, r, y, sx);
+}
+
+// The same residual from row groups (DevLevel::kg).  The velocity rows of
+// one node repeat each other: D consecutive rows whose (m, a) values are
+// equal and whose columns differ by the component only are read once for all
+// D; their coupling blocks (m = 0, the same columns in every row) carry D
+// values per column, and the D + 1 consecutive pressure rows of a cell one
+// column per node and (D + 1) D values.  Rows that fit neither (nodes on a
+// wall, whose normal component has its own boundary terms; operators of
+// another structure) are read singly, their blocks with m != 0 as (m, a),
+// the others as a.  The kernel streams its lists once and is bound by HBM:
+// per node pair 20 bytes instead of 20 D (3d: 1.3 instead of 3.0 GB on the
+// 128x24x24 level), and per pair of loads D rows of work instead of one.
+// The D B sums of a velocity group are M x and A x apart, combined with C and
+// tw once per row instead of once per block.  Blocks of the grid are split
+// over the three kinds; lanes and rounds as in k_spmv_kron.  Measured on one
+// MI355X, best shape, rows read singly -> groups: 3d 128x24x24 dG(1)
+// 648 -> 355 us, 2d 512x128 dG(2) 77 -> 45 us, 2d 256x64 dG(1) 15.4 -> 11.6
+// us; levels under about 10,000 rows are at the launch latency either way.
+template <int B, int D, int LPR, int U>
+__global__ void __launch_bounds__(256) k_spmv_group(KronGroups G, const double* __restrict__ r,
+                                                    const double* __restrict__ x,
+                                                    double* __restrict__ y, double sx,
+                                                    KronCoef K) {
+  constexpr int RPWV = 64 / LPR;
+  const int lane = threadIdx.x & 63, sub = lane % LPR;
+  const int wrow = (threadIdx.x >> 6) * RPWV + lane / LPR;
+  const int blk = blockIdx.x;
+  constexpr int NV = (D + 1) * B;   // entries of the largest group
+  double acc[NV];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int32_t q = qb + u * LPR;
-        const bool v = q < q1;
-        const int32_t qc = v ? q : q1 - 1;
-        c[u] = col1[qc];
-        const double2 f = ma[qc];
-        m[u] = v ? f.x : 0.0;
-        a[u] = v ? f.y : 0.0;
-      }
-      double xl[U][B];
+  for (int e = 0; e < NV; ++e) acc[e] = 0.0;
+  int64_t row;
+  int nv;
+  bool live;
+  if (blk < G.nb_v) {
+    const int g = blk * 4 * RPWV + wrow;
+    live = g < G.n_v;
+    const int gg = live ? g : G.n_v - 1;
+    double am[D * B], aa[D * B];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+    for (int e = 0; e < D * B; ++e) am[e] = aa[e] = 0.0;
+    {
+      const int32_t q0 = G.vp1[gg], q1 = G.vp1[gg + 1];
+      const int nit = (q1 - q0 + U * LPR - 1) / (U * LPR);
+      for (int it = 0; it < nit; ++it) {
+        const int32_t qb = q0 + it * U * LPR + sub;
+        int64_t c[U];
+        double2 f[U];
 #pragma unroll
-        for (int l = 0; l < B; ++l) xl[u][l] = x[c[u] * B + l];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int i = 0; i < B; ++i) {
-          double ci = 0.0;
-#pragma unroll
-          for (int l = 0; l < B; ++l) ci = fma(K.C[i * B + l], xl[u][l], ci);
-          acc[i] = fma(m[u], ci, fma(a[u] * K.tw[i], xl[u][i], acc[i]));
+        for (int u = 0; u < U; ++u) {
+          const int32_t q = qb + u * LPR;
+          const bool v = q < q1;
+          const int32_t qc = v ? q : q1 - 1;
+          c[u] = G.vc1[qc];
+          const double2 w = G.vma[qc];
+          f[u].x = v ? w.x : 0.0;
+          f[u].y = v ? w.y : 0.0;
         }
+        double xl[U][D * B];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < D * B; ++e) xl[u][e] = x[c[u] * B + e];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < D * B; ++e) {
+            am[e] = fma(f[u].x, xl[u][e], am[e]);
+            aa[e] = fma(f[u].y, xl[u][e], aa[e]);
+          }
+      }
     }
-  }
-  // blocks without one: a only
-  if constexpr (SPLIT) {
-    const int32_t q0 = rp2[rr], q1 = rp2[rr + 1];
+    {
+      const int32_t q0 = G.vp2[gg], q1 = G.vp2[gg + 1];
+      const int nit = (q1 - q0 + U * LPR - 1) / (U * LPR);
+      for (int it = 0; it < nit; ++it) {
+        const int32_t qb = q0 + it * U * LPR + sub;
+        int64_t c[U];
+        double f[U][D];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int32_t q = qb + u * LPR;
+          const bool v = q < q1;
+          const int32_t qc = v ? q : q1 - 1;
+          c[u] = G.vc2[qc];
+#pragma unroll
+          for (int e = 0; e < D; ++e) {
+            const double w = G.va2[(int64_t)qc * D + e];
+            f[u][e] = v ? w : 0.0;
+          }
+        }
+        double xl[U][B];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int l = 0; l < B; ++l) xl[u][l] = x[c[u] * B + l];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < D; ++e)
+#pragma unroll
+            for (int l = 0; l < B; ++l) aa[e * B + l] = fma(f[u][e], xl[u][l], aa[e * B + l]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < D; ++e)
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        double s = K.tw[i] * aa[e * B + i];
+#pragma unroll
+        for (int l = 0; l < B; ++l) s = fma(K.C[i * B + l], am[e * B + l], s);
+        acc[e * B + i] = s;
+      }
+    row = G.vrow[gg];
+    nv = D * B;
+  } else if (blk < G.nb_v + G.nb_p) {
+    const int g = (blk - G.nb_v) * 4 * RPWV + wrow;
+    live = g < G.n_p;
+    const int gg = live ? g : G.n_p - 1;
+    const int32_t q0 = G.pp[gg], q1 = G.pp[gg + 1];
+    for (int32_t q = q0 + sub; q < q1; q += LPR) {
+      const int64_t c = G.pc[q];
+      double f[(D + 1) * D], xl[D * B];
+#pragma unroll
+      for (int e = 0; e < (D + 1) * D; ++e) f[e] = G.pa[(int64_t)q * ((D + 1) * D) + e];
+#pragma unroll
+      for (int e = 0; e < D * B; ++e) xl[e] = x[c * B + e];
+#pragma unroll
+      for (int m = 0; m <= D; ++m)
+#pragma unroll
+        for (int e = 0; e < D; ++e)
+#pragma unroll
+          for (int l = 0; l < B; ++l)
+            acc[m * B + l] = fma(f[m * D + e], xl[e * B + l], acc[m * B + l]);
+    }
+#pragma unroll
+    for (int m = 0; m <= D; ++m)
+#pragma unroll
+      for (int i = 0; i < B; ++i) acc[m * B + i] *= K.tw[i];
+    row = G.prow[gg];
+    nv = NV;
+  } else {
+    const int g = (blk - G.nb_v - G.nb_p) * 4 * RPWV + wrow;
+    live = g < G.n_s;
+    const int gg = live ? g : G.n_s - 1;
+    row_pairs<B, LPR, U>(G.sp1[gg], G.sp1[gg + 1], sub, G.sc1, G.sma, x, K, acc);
+    // blocks without a mass entry: a only
+    const int32_t q0 = G.sp2[gg], q1 = G.sp2[gg + 1];
     const int nit = (q1 - q0 + U * LPR - 1) / (U * LPR);
     for (int it = 0; it < nit; ++it) {
       const int32_t qb = q0 + it * U * LPR + sub;
@@ -331,8 +506,8 @@ __global__ void __launch_bounds__(256) k_spmv_kron(const int32_t* __restrict__ r
         const int32_t q = qb + u * LPR;
         const bool v = q < q1;
         const int32_t qc = v ? q : q1 - 1;
-        c[u] = col2[qc];
-        const double f = a2[qc];
+        c[u] = G.sc2[qc];
+        const double f = G.sa2[qc];
         a[u] = v ? f : 0.0;
       }
       double xl[U][B];
@@ -345,24 +520,17 @@ __global__ void __launch_bounds__(256) k_spmv_kron(const int32_t* __restrict__ r
 #pragma unroll
         for (int i = 0; i < B; ++i) acc[i] = fma(a[u] * K.tw[i], xl[u][i], acc[i]);
     }
+    row = G.srow[gg];
+    nv = B;
   }
-#pragma unroll
-  for (int off = LPR / 2; off >= 1; off >>= 1)
-#pragma unroll
-    for (int i = 0; i < B; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
-  if (live && sub < B) {
-    double s = acc[0];
-#pragma unroll
-    for (int i = 1; i < B; ++i) s = (sub == i) ? acc[i] : s;
-    y[(int64_t)row * B + sub] = r ? fma(sx, s, rv) : sx * s;
-  }
+  row_sum<LPR>(acc);
+  if (live) row_store<LPR>(acc, nv, sub, row * B, r, y, sx);
 }
 
-// residual shapes from the factors: (lanes per block row, blocks per lane and round)
-// (shapes 7-12: the same on the split lists)
+// residual shapes from the factors: (lanes per block row, blocks per lane and
+// round), 1-6 on the plain rows, 7-12 the same on the row groups
 static constexpr int kKronShapes = 12;
 static constexpr int kKronLpr[kKronShapes] = {4, 8, 8, 16, 16, 32, 4, 8, 8, 16, 16, 32};
-static constexpr int kKronU[kKronShapes] = {4, 3, 4, 2, 4, 2, 4, 3, 4, 2, 4, 2};
 
 int residual_shapes(const DevLevel& L) { return L.kron_ma ? kKronShapes : 4; }
 
@@ -374,30 +542,39 @@ static hipError_t spmv_kron_b(hipStream_t s, const DevLevel& L, const double* r,
   for (int e = 0; e < B; ++e) K.tw[e] = L.kron_tw[e];
   const int sh = L.spmv_rpw - 1;
   if (sh < 0 || sh >= kKronShapes) return hipErrorInvalidValue;
-  const int lpr = kKronLpr[sh], rows_per_wg = 4 * (64 / lpr);
-  dim3 grid((L.n_s + rows_per_wg - 1) / rows_per_wg), block(256);
-  const bool split = sh >= kKronShapes / 2;
-  if (split && (!L.kx_ptr || !L.kx_col || !L.kx_val)) return hipErrorInvalidValue;
-  const int64_t n1 = L.kx_n1;
-  const int32_t* rp1 = split ? L.kx_ptr : L.rowptr;
-  const int32_t* c1 = split ? L.kx_col : L.col;
-  const double2* ma = (const double2*)(split ? L.kx_val : L.kron_ma);
-  const int32_t* rp2 = split ? L.kx_ptr + (L.n_s + 1) : nullptr;
-  const int32_t* c2 = split ? L.kx_col + n1 : nullptr;
-  const double* a2 = split ? L.kx_val + 2 * n1 : nullptr;
-#define STV_KRON(S, LP, UU, SP)                                                              \
+  const int rows_per_wg = 4 * (64 / kKronLpr[sh]);
+  const double2* ma = (const double2*)L.kron_ma;
+  if (sh < kKronShapes / 2) {
+    const dim3 grid((L.n_s + rows_per_wg - 1) / rows_per_wg), block(256);
+#define STV_KRON(S, LP, UU)                                                                  \
   case S:                                                                                   \
-    launch(k_spmv_kron<B, LP, UU, SP>, dim3(grid), dim3(block), 0, s, rp1, c1, ma, rp2, c2, a2, \
-           r, x, y, L.n_s, sx, K);                                                          \
+    launch(k_spmv_kron<B, LP, UU>, grid, block, 0, s, L.rowptr, L.col, ma, r, x, y, L.n_s,  \
+           sx, K);                                                                          \
+    break;
+    switch (sh) {
+      STV_KRON(0, 4, 4) STV_KRON(1, 8, 3) STV_KRON(2, 8, 4)
+      STV_KRON(3, 16, 2) STV_KRON(4, 16, 4) STV_KRON(5, 32, 2)
+    }
+#undef STV_KRON
+    return hipGetLastError();
+  }
+  KronGroups G = L.kg;
+  if (!G.vp1) return hipErrorInvalidValue;
+  G.nb_v = (G.n_v + rows_per_wg - 1) / rows_per_wg;
+  G.nb_p = (G.n_p + rows_per_wg - 1) / rows_per_wg;
+  const dim3 grid(G.nb_v + G.nb_p + (G.n_s + rows_per_wg - 1) / rows_per_wg), block(256);
+#define STV_GROUP(S, LP, UU)                                                                 \
+  case S:                                                                                   \
+    if (L.n_ls == 21)                                                                       \
+      launch(k_spmv_group<B, 2, LP, UU>, grid, block, 0, s, G, r, x, y, sx, K);             \
+    else                                                                                    \
+      launch(k_spmv_group<B, 3, LP, UU>, grid, block, 0, s, G, r, x, y, sx, K);             \
     break;
   switch (sh) {
-    STV_KRON(0, 4, 4, false) STV_KRON(1, 8, 3, false) STV_KRON(2, 8, 4, false)
-    STV_KRON(3, 16, 2, false) STV_KRON(4, 16, 4, false) STV_KRON(5, 32, 2, false)
-    STV_KRON(6, 4, 4, true) STV_KRON(7, 8, 3, true) STV_KRON(8, 8, 4, true)
-    STV_KRON(9, 16, 2, true) STV_KRON(10, 16, 4, true) STV_KRON(11, 32, 2, true)
-    default: return hipErrorInvalidValue;
+    STV_GROUP(6, 4, 4) STV_GROUP(7, 8, 3) STV_GROUP(8, 8, 4)
+    STV_GROUP(9, 16, 2) STV_GROUP(10, 16, 4) STV_GROUP(11, 32, 2)
   }
-#undef STV_KRON
+#undef STV_GROUP
   return hipGetLastError();
 }
 
@@ -410,6 +587,140 @@ hipError_t launch_spmv_kron(hipStream_t s, int b, const DevLevel& L, const doubl
     case 4: return spmv_kron_b<4>(s, L, r, x, y, sx);
   }
   return hipErrorInvalidValue;
+}
+
+// ma[q] = (m[q], a[q])
+__global__ void k_interleave(const double* __restrict__ m, const double* __restrict__ a,
+                             double2* __restrict__ ma, int64_t n) {
+  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n;
+       q += (int64_t)gridDim.x * blockDim.x)
+    ma[q] = make_double2(m[q], a[q]);
+}
+
+hipError_t launch_interleave(hipStream_t s, const double* m, const double* a, double* ma,
+                             int64_t n) {
+  k_interleave<<<2048, 256, 0, s>>>(m, a, (double2*)ma, n);
+  return hipGetLastError();
+}
+
+// What rows i .. of a level can be grouped as, one wavefront per row i:
+// kind bit 0: rows i .. i + D - 1 are a velocity group; bit 1: rows i .. i + D
+// a pressure group (k_spmv_group); n1[i] = row i's blocks with m != 0.  The
+// conditions are exact (equal values, equal lengths), so a group's rows give
+// the sums that the single rows give.
+template <int D>
+__global__ void __launch_bounds__(256) k_group_classify(const int32_t* __restrict__ rowptr,
+                                                        const int32_t* __restrict__ col,
+                                                        const double2* __restrict__ ma,
+                                                        int32_t n_rows,
+                                                        uint8_t* __restrict__ kind,
+                                                        int32_t* __restrict__ n1) {
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= n_rows) return;
+  const int32_t q0 = rowptr[row], len = rowptr[row + 1] - q0;
+  int cnt = 0;
+  for (int32_t e = lane; e < len; e += 64) cnt += ma[q0 + e].x != 0.0;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
+  bool v = cnt > 0 && row + D <= n_rows;
+  for (int c = 1; c < D && v; ++c) {
+    const int32_t qc = rowptr[row + c];
+    bool ok = rowptr[row + c + 1] - qc == len;
+    for (int32_t e = lane; ok && e < len; e += 64) {
+      const double2 f = ma[q0 + e], g = ma[qc + e];
+      if (f.x != 0.0) ok = col[qc + e] == col[q0 + e] + c && g.x == f.x && g.y == f.y;
+      else ok = col[qc + e] == col[q0 + e] && g.x == 0.0;
+    }
+    v = __all(ok);
+  }
+  bool p = cnt == 0 && row + D + 1 <= n_rows && len % D == 0;
+  for (int c = 0; c <= D && p; ++c) {
+    const int32_t qc = rowptr[row + c];
+    bool ok = rowptr[row + c + 1] - qc == len;
+    for (int32_t e = lane; ok && e < len; e += 64)
+      ok = ma[qc + e].x == 0.0 && col[qc + e] == col[q0 + e] &&
+           col[q0 + e] == col[q0 + e / D * D] + e % D;
+    p = __all(ok);
+  }
+  if (lane == 0) {
+    kind[row] = (uint8_t)((v ? 1 : 0) | (p ? 2 : 0));
+    n1[row] = cnt;
+  }
+}
+
+// Fills the lists of the groups whose rows and pointers are in G, one
+// wavefront per group (velocity groups first, then pressure groups, then
+// single rows); list order is block order.
+template <int D>
+__global__ void __launch_bounds__(256) k_group_fill(const int32_t* __restrict__ rowptr,
+                                                    const int32_t* __restrict__ col,
+                                                    const double2* __restrict__ ma,
+                                                    KronGroups G) {
+  const int lane = threadIdx.x & 63;
+  int g = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (g >= G.n_v + G.n_p + G.n_s) return;
+  if (g >= G.n_v && g < G.n_v + G.n_p) {
+    g -= G.n_v;
+    const int32_t row = G.prow[g], q0 = rowptr[row], len = rowptr[row + 1] - q0, o = G.pp[g];
+    for (int32_t e = lane; e < len; e += 64) {
+      if (e % D == 0) const_cast<int32_t*>(G.pc)[o + e / D] = col[q0 + e];
+      for (int m = 0; m <= D; ++m)
+        const_cast<double*>(G.pa)[((int64_t)o + e / D) * ((D + 1) * D) + m * D + e % D] =
+            ma[rowptr[row + m] + e].y;
+    }
+    return;
+  }
+  const bool vel = g < G.n_v;
+  if (!vel) g -= G.n_v + G.n_p;
+  const int32_t row = vel ? G.vrow[g] : G.srow[g];
+  int32_t o1 = vel ? G.vp1[g] : G.sp1[g], o2 = vel ? G.vp2[g] : G.sp2[g];
+  int32_t* c1 = const_cast<int32_t*>(vel ? G.vc1 : G.sc1);
+  int32_t* c2 = const_cast<int32_t*>(vel ? G.vc2 : G.sc2);
+  double2* m1 = const_cast<double2*>(vel ? G.vma : G.sma);
+  double* a2 = const_cast<double*>(vel ? G.va2 : G.sa2);
+  const int nv = vel ? D : 1;
+  const int32_t q0 = rowptr[row], len = rowptr[row + 1] - q0;
+  for (int32_t e0 = 0; e0 < len; e0 += 64) {
+    const int32_t e = e0 + lane;
+    const bool in = e < len;
+    const double2 f = in ? ma[q0 + e] : make_double2(0.0, 0.0);
+    const bool one = in && f.x != 0.0, two = in && f.x == 0.0;
+    const uint64_t b1 = __builtin_amdgcn_ballot_w64(one), b2 = __builtin_amdgcn_ballot_w64(two);
+    const uint64_t below = (1ull << lane) - 1ull;
+    if (one) {
+      const int32_t q = o1 + __popcll(b1 & below);
+      c1[q] = col[q0 + e];
+      m1[q] = f;
+    }
+    if (two) {
+      const int32_t q = o2 + __popcll(b2 & below);
+      c2[q] = col[q0 + e];
+      for (int c = 0; c < nv; ++c) a2[(int64_t)q * nv + c] = ma[rowptr[row + c] + e].y;
+    }
+    o1 += __popcll(b1);
+    o2 += __popcll(b2);
+  }
+}
+
+hipError_t launch_group_classify(hipStream_t s, const DevLevel& L, const double* ma,
+                                 uint8_t* kind, int32_t* n1) {
+  const dim3 grid((L.n_s + 3) / 4), block(256);
+  if (L.n_ls == 21)
+    k_group_classify<2><<<grid, block, 0, s>>>(L.rowptr, L.col, (const double2*)ma, L.n_s, kind, n1);
+  else
+    k_group_classify<3><<<grid, block, 0, s>>>(L.rowptr, L.col, (const double2*)ma, L.n_s, kind, n1);
+  return hipGetLastError();
+}
+
+hipError_t launch_group_fill(hipStream_t s, const DevLevel& L, const double* ma,
+                             const KronGroups& G) {
+  const dim3 grid((G.n_v + G.n_p + G.n_s + 3) / 4), block(256);
+  if (L.n_ls == 21)
+    k_group_fill<2><<<grid, block, 0, s>>>(L.rowptr, L.col, (const double2*)ma, G);
+  else
+    k_group_fill<3><<<grid, block, 0, s>>>(L.rowptr, L.col, (const double2*)ma, G);
+  return hipGetLastError();
 }
 
 // Largest deviation of the stored blocks from C m + delta tw a, and the

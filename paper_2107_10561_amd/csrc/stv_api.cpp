@@ -165,7 +165,7 @@ void free_level(DevLevel& L) {
   dfree(L.inv_off); dfree(L.inv_store); dfree(L.posmap); dfree(L.dec_tab); dfree(L.dec_code);
   dfree(L.rho); dfree(L.r); dfree(L.d); dfree(L.corr);
   dfree(L.rowptr_t); dfree(L.col_t); dfree(L.val_t);
-  dfree(L.kron_ma); dfree(L.kx_ptr); dfree(L.kx_col); dfree(L.kx_val);
+  dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
   L = DevLevel();
 }
 
@@ -2481,6 +2481,88 @@ int stv_autotune(stv_ctx* ctx, int* choices, int cap) {
   return STV_OK;
 }
 
+// Row groups of a level's factors ma: the device classifies every row, the
+// host takes groups greedily in row order (a velocity group, else a pressure
+// group, else a single row) and lays their lists out, the device fills them.
+static int make_groups(stv_ctx* ctx, const DevLevel& L, const double* ma, KronGroups* out,
+                       int32_t** idx, double** val) {
+  const int D = ctx->dim;
+  const size_t ns = (size_t)L.n_s;
+  uint8_t* dkind = nullptr;
+  int32_t* dn1 = nullptr;
+  std::vector<uint8_t> kind(ns);
+  std::vector<int32_t> n1(ns), rp(ns + 1);
+  int rc = dalloc(ctx, &dkind, ns);
+  if (rc == STV_OK) rc = dalloc(ctx, &dn1, ns);
+  hipError_t e = hipSuccess;
+  if (rc == STV_OK) {
+    e = launch_group_classify(ctx->stream, L, ma, dkind, dn1);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    if (e == hipSuccess) e = hipMemcpy(kind.data(), dkind, ns, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(n1.data(), dn1, 4 * ns, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(rp.data(), L.rowptr, 4 * (ns + 1), hipMemcpyDeviceToHost);
+  }
+  dfree(dkind);
+  dfree(dn1);
+  if (rc != STV_OK) return rc;
+  if (e != hipSuccess)
+    return fail(ctx, STV_EHIP, std::string("row grouping failed: ") + hipGetErrorString(e));
+  std::vector<int32_t> vrow, vp1(1, 0), vp2(1, 0), prow, pp(1, 0), srow, sp1(1, 0), sp2(1, 0);
+  for (size_t i = 0; i < ns;) {
+    const int32_t len = rp[i + 1] - rp[i];
+    if (kind[i] & 1) {
+      vrow.push_back((int32_t)i);
+      vp1.push_back(vp1.back() + n1[i]);
+      vp2.push_back(vp2.back() + len - n1[i]);
+      i += (size_t)D;
+    } else if (kind[i] & 2) {
+      prow.push_back((int32_t)i);
+      pp.push_back(pp.back() + len / D);
+      i += (size_t)D + 1;
+    } else {
+      srow.push_back((int32_t)i);
+      sp1.push_back(sp1.back() + n1[i]);
+      sp2.push_back(sp2.back() + len - n1[i]);
+      i += 1;
+    }
+  }
+  // one index array (rows and pointers, then the columns) and one value array
+  const int64_t nv1 = vp1.back(), nv2 = vp2.back(), np = pp.back(), n_s1 = sp1.back(), n_s2 = sp2.back();
+  std::vector<int32_t> h;
+  auto put = [&](const std::vector<int32_t>& a) { h.insert(h.end(), a.begin(), a.end()); };
+  put(vrow); put(vp1); put(vp2); put(prow); put(pp); put(srow); put(sp1); put(sp2);
+  rc = dalloc(ctx, idx, h.size() + (size_t)(nv1 + nv2 + np + n_s1 + n_s2));
+  if (rc == STV_OK)
+    rc = dalloc(ctx, val, (size_t)(2 * (nv1 + n_s1) + D * nv2 + (D + 1) * D * np + n_s2));
+  if (rc == STV_OK) {
+    KronGroups G{};
+    G.n_v = (int32_t)vrow.size();
+    G.n_p = (int32_t)prow.size();
+    G.n_s = (int32_t)srow.size();
+    const int32_t* q = *idx;
+    auto take = [&](size_t n) { const int32_t* p = q; q += n; return p; };
+    G.vrow = take(vrow.size()); G.vp1 = take(vp1.size()); G.vp2 = take(vp2.size());
+    G.prow = take(prow.size()); G.pp = take(pp.size());
+    G.srow = take(srow.size()); G.sp1 = take(sp1.size()); G.sp2 = take(sp2.size());
+    G.vc1 = take((size_t)nv1); G.vc2 = take((size_t)nv2); G.pc = take((size_t)np);
+    G.sc1 = take((size_t)n_s1); G.sc2 = take((size_t)n_s2);
+    G.vma = (const double2*)*val;
+    G.sma = G.vma + nv1;
+    G.va2 = (const double*)(G.sma + n_s1);
+    G.pa = G.va2 + D * nv2;
+    G.sa2 = G.pa + (D + 1) * D * np;
+    e = hipMemcpy(*idx, h.data(), 4 * h.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = launch_group_fill(ctx->stream, L, ma, G);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess)
+      rc = fail(ctx, STV_EHIP, std::string("row grouping failed: ") + hipGetErrorString(e));
+    else
+      *out = G;
+  }
+  if (rc != STV_OK) { dfree(*idx); dfree(*val); }
+  return rc;
+}
+
 int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const double* aval,
                          const double* C, const double* tw) {
   STV_TRY(check_ctx(ctx, true, false));
@@ -2488,8 +2570,8 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
   DevLevel& L = ctx->lv[level];
   if (!mval && !aval) {   // drop the factors: back to the stored blocks
     STV_HIP(hipStreamSynchronize(ctx->stream));
-    dfree(L.kron_ma); dfree(L.kx_ptr); dfree(L.kx_col); dfree(L.kx_val);
-    L.kx_n1 = 0;
+    dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
+    L.kg = KronGroups{};
     ctx->cgroups_algo = -1;   // the coarse groups may refer to the factors
     ctx->inv_layout = -1;     // and the cell-inverse layout of the level
     ++ctx->generation;
@@ -2503,20 +2585,26 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
   for (int e = 0; e < b; ++e)
     if (!std::isfinite(tw[e])) return fail(ctx, STV_EINVAL, "tw must be finite");
   STV_HIP(hipStreamSynchronize(ctx->stream));
-  double *dma = nullptr, *part = nullptr;
+  double *dma = nullptr, *part = nullptr, *dm = nullptr, *da = nullptr;
   const int nblk = 1024;
   auto drop = [&]() { dfree(dma); dfree(part); };
-  std::vector<double> hma((size_t)2 * L.nnzb);
-  for (int64_t q = 0; q < L.nnzb; ++q) {
-    hma[(size_t)(2 * q)] = mval[q];
-    hma[(size_t)(2 * q + 1)] = aval[q];
-  }
-  int rc = upload(ctx, &dma, hma.data(), hma.size());
+  int rc = upload(ctx, &dm, mval, (size_t)L.nnzb);
+  if (rc == STV_OK) rc = upload(ctx, &da, aval, (size_t)L.nnzb);
+  if (rc == STV_OK) rc = dalloc(ctx, &dma, (size_t)2 * L.nnzb);
   if (rc == STV_OK) rc = dalloc(ctx, &part, (size_t)2 * nblk);
+  hipError_t e = hipSuccess;
+  if (rc == STV_OK) {
+    e = launch_interleave(ctx->stream, dm, da, dma, L.nnzb);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess)
+      rc = fail(ctx, STV_EHIP, std::string("factor upload failed: ") + hipGetErrorString(e));
+  }
+  dfree(dm);
+  dfree(da);
   if (rc != STV_OK) { drop(); return rc; }
   // the factors must reproduce the stored blocks
   std::vector<double> hp((size_t)2 * nblk);
-  hipError_t e = launch_kron_check(ctx->stream, b, L, dma, C, tw, part, nblk);
+  e = launch_kron_check(ctx->stream, b, L, dma, C, tw, part, nblk);
   if (e == hipSuccess) e = hipMemcpyAsync(hp.data(), part, sizeof(double) * hp.size(),
                                           hipMemcpyDeviceToHost, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -2535,54 +2623,16 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
     return fail(ctx, STV_EINVAL, "the factors do not reproduce the level's blocks (max deviation " +
                                      std::to_string(dev) + " of " + std::to_string(mag) + ")");
   }
-  // the residual's split lists: per row the blocks with m != 0, then the
-  // others (row order kept within each list)
-  const int64_t ns = L.n_s;
-  std::vector<int32_t> hrp((size_t)ns + 1), hcol((size_t)L.nnzb);
-  e = hipMemcpy(hrp.data(), L.rowptr, sizeof(int32_t) * hrp.size(), hipMemcpyDeviceToHost);
-  if (e == hipSuccess)
-    e = hipMemcpy(hcol.data(), L.col, sizeof(int32_t) * hcol.size(), hipMemcpyDeviceToHost);
-  if (e != hipSuccess) {
-    drop();
-    return fail(ctx, STV_EHIP, std::string("reading the level pattern failed: ") + hipGetErrorString(e));
-  }
-  std::vector<int32_t> xptr((size_t)(2 * (ns + 1)), 0);
-  int64_t n1 = 0;
-  for (int64_t q = 0; q < L.nnzb; ++q) n1 += mval[q] != 0.0;
-  const int64_t n2 = L.nnzb - n1;
-  std::vector<int32_t> xcol((size_t)L.nnzb);
-  std::vector<double> xval((size_t)(2 * n1 + n2));
-  int64_t p1 = 0, p2 = 0;
-  for (int64_t i = 0; i < ns; ++i) {
-    xptr[(size_t)i] = (int32_t)p1;
-    xptr[(size_t)(ns + 1 + i)] = (int32_t)p2;
-    for (int32_t q = hrp[(size_t)i]; q < hrp[(size_t)i + 1]; ++q) {
-      if (mval[q] != 0.0) {
-        xcol[(size_t)p1] = hcol[(size_t)q];
-        xval[(size_t)(2 * p1)] = mval[q];
-        xval[(size_t)(2 * p1 + 1)] = aval[q];
-        ++p1;
-      } else {
-        xcol[(size_t)(n1 + p2)] = hcol[(size_t)q];
-        xval[(size_t)(2 * n1 + p2)] = aval[q];
-        ++p2;
-      }
-    }
-  }
-  xptr[(size_t)ns] = (int32_t)p1;
-  xptr[(size_t)(2 * ns + 1)] = (int32_t)p2;
-  int32_t *dxp = nullptr, *dxc = nullptr;
-  double* dxv = nullptr;
-  rc = upload(ctx, &dxp, xptr.data(), xptr.size());
-  if (rc == STV_OK) rc = upload(ctx, &dxc, xcol.data(), xcol.size());
-  if (rc == STV_OK) rc = upload(ctx, &dxv, xval.data(), xval.size());
-  if (rc != STV_OK) { drop(); dfree(dxp); dfree(dxc); dfree(dxv); return rc; }
-  dfree(L.kron_ma); dfree(L.kx_ptr); dfree(L.kx_col); dfree(L.kx_val);
+  KronGroups kg{};
+  int32_t* kg_idx = nullptr;
+  double* kg_val = nullptr;
+  rc = make_groups(ctx, L, dma, &kg, &kg_idx, &kg_val);
+  if (rc != STV_OK) { drop(); return rc; }
+  dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
   L.kron_ma = dma;
-  L.kx_ptr = dxp;
-  L.kx_col = dxc;
-  L.kx_val = dxv;
-  L.kx_n1 = n1;
+  L.kg = kg;
+  L.kg_idx = kg_idx;
+  L.kg_val = kg_val;
   ctx->cgroups_algo = -1;   // the coarse groups are regrouped at the next build
   ctx->inv_layout = -1;     // the cell inverses may be stored time-decoupled
   for (int i = 0; i < 16; ++i) L.kron_C[i] = i < b * b ? C[i] : 0.0;

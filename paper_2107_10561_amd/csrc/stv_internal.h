@@ -41,6 +41,23 @@ struct CellSplit {
   double T[16], V[16], W[16];
 };
 
+// The block rows of a level with spatial factors, grouped for the residual
+// (D = space dimension; k_group_classify has the conditions).  A velocity
+// group is D rows from vrow: (m, a) blocks vp1 .. of columns vc1 (the first
+// row's; row c's is c more), then blocks with m = 0 vp2 .. of columns vc2 with
+// D values each.  A pressure group is D + 1 rows from prow: node columns pp ..
+// of first columns pc with (D + 1) x D values each.  Other rows (srow) have an
+// (m, a) list and an a-only list.  Every DoF is in exactly one group.
+struct KronGroups {
+  int32_t n_v, n_p, n_s;          // groups of each kind
+  int32_t nb_v, nb_p;             // grid blocks of the first two kinds (set per launch)
+  const int32_t *vrow, *vp1, *vp2, *vc1, *vc2;
+  const int32_t *prow, *pp, *pc;
+  const int32_t *srow, *sp1, *sp2, *sc1, *sc2;
+  const double2 *vma, *sma;
+  const double *va2, *pa, *sa2;
+};
+
 // Device arrays of one level.
 struct DevLevel {
   int32_t n_s = 0, n_cells = 0, n_ls = 0;
@@ -87,14 +104,10 @@ struct DevLevel {
   int32_t* rowptr_t = nullptr; int32_t* col_t = nullptr; double* val_t = nullptr;
   // spatial factors (optional): blocks = C[i][l] M + delta_il tw[i] A
   double* kron_ma = nullptr;      // spatial factors (m, a), interleaved per block
-  // the factors split per row for the residual: the blocks with m != 0 as
-  // (m, a) pairs, then those with m = 0 as a only; kx_ptr holds both row
-  // pointer arrays (n_s + 1 each), kx_col the two column lists (kx_n1 + the
-  // rest), kx_val the 2 kx_n1 pair values followed by the a-only values
-  int32_t* kx_ptr = nullptr;
-  int32_t* kx_col = nullptr;
-  double* kx_val = nullptr;
-  int64_t kx_n1 = 0;
+  // the factors in row groups for the residual (views into kg_idx, kg_val)
+  KronGroups kg{};
+  int32_t* kg_idx = nullptr;
+  double* kg_val = nullptr;
   int dec = 0;                    // the inverse store holds time-decoupled rows (CellSplit)
   int cx = 0;                     // inverses built from the complex decoupled block (plain store)
   CellSplit split{};
@@ -324,6 +337,12 @@ hipError_t launch_spmv(hipStream_t s, int b, const DevLevel& L, const double* r,
                        const double* x, double* y, double sx, bool transposed = false);
 hipError_t launch_spmv_kron(hipStream_t s, int b, const DevLevel& L, const double* r,
                             const double* x, double* y, double sx);
+hipError_t launch_interleave(hipStream_t s, const double* m, const double* a, double* ma,
+                             int64_t n);
+hipError_t launch_group_classify(hipStream_t s, const DevLevel& L, const double* ma,
+                                 uint8_t* kind, int32_t* n1);
+hipError_t launch_group_fill(hipStream_t s, const DevLevel& L, const double* ma,
+                             const KronGroups& G);
 hipError_t launch_kron_check(hipStream_t s, int b, const DevLevel& L, const double* ma,
                              const double* C, const double* tw, double* partial, int nblk);
 // residual shapes available for a level (factors: lanes per row x blocks per lane)

@@ -244,3 +244,49 @@ def test_store_layout_follows_the_build(stv):
         assert relerr(to_host(dd), ref) <= 1e-12, step
     assert sizes[0] == plain and sizes[2] == plain
     assert sizes[1] * p.b == plain     # one row per owned spatial DoF instead of k+1
+
+
+@pytest.mark.parametrize("change", ["none", "values", "numbering"])
+@pytest.mark.parametrize("name", ["2d_dg0", "2d_dg2", "3d_dg1"])
+def test_residual_row_groups(stv, name, change):
+    """The grouped residual shapes (7..12) where rows group (none), where some
+    nodes' rows do not (values: one row's a, one entry's m), and where no
+    neighbours do (numbering: random).  Tolerance: sums of at most 360 terms."""
+    import scipy.sparse as sp
+    p, _ = problem(name)
+    C, tw = time_factors(p)
+    rng = np.random.default_rng(31)
+    levels = [dict(n_sdofs=L.n_sdofs, rowptr=np.asarray(L.rowptr), col=np.asarray(L.col),
+                   val=np.asarray(L.val), cell_sdofs=np.asarray(L.cell_sdofs), P=L.P)
+              for L in p.levels]
+    F, n = levels[-1], levels[-1]["n_sdofs"]
+    m, a = (np.array(v) for v in spatial_factors(p.levels[-1]))
+    rp, cl = F["rowptr"], F["col"]
+    if change == "values":
+        row = p.dim * (p.levels[-1].mesh.n_vnodes // 2) + 1
+        a[rp[row]:rp[row + 1]] *= 1.5
+        m[rp[5 * p.dim] + 1] = 0.0
+    if change == "numbering":
+        perm = rng.permutation(n)
+        rows = perm[np.repeat(np.arange(n), np.diff(rp))]
+        order = np.lexsort((perm[cl], rows))
+        m, a = m[order], a[order]
+        rp = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))])
+        cl = perm[cl][order]
+        P = sp.csr_matrix((F["P"][2], F["P"][1], F["P"][0]),
+                          shape=(n, levels[-2]["n_sdofs"]))[np.argsort(perm)].tocsr()
+        F.update(cell_sdofs=perm[F["cell_sdofs"]], P=(P.indptr, P.indices, P.data))
+    val = m[:, None, None] * C[None] + a[:, None, None] * np.diag(tw)[None]
+    F.update(rowptr=rp, col=cl, val=val)
+    s = stv.Solver(0)
+    s.set_hierarchy(levels, p.dim, p.k)
+    s.set_kron_factors(len(levels) - 1, m, a, C, tw)
+    J = sp.bsr_matrix((val, cl, rp), shape=(n * p.b, n * p.b))
+    r, d = rng.standard_normal(n * p.b), rng.standard_normal(n * p.b)
+    r *= np.abs(val).max()
+    ref, scale = r - J @ d, np.abs(r) + abs(J) @ np.abs(d)
+    for shape in range(7, 13):
+        s.set_launch(len(levels) - 1, shape, 0)
+        out = to_dev(np.zeros(n * p.b))
+        s.residual(len(levels) - 1, to_dev(r), to_dev(d), out)
+        assert (np.abs(to_host(out) - ref) <= 360 * 2.0 ** -53 * scale).all()
