@@ -1249,6 +1249,7 @@ static hipError_t vanka_bn(hipStream_t s, const DevLevel& L, const double* rho, 
   if constexpr (B == 2 && NLS == 85) {
     if (L.dec && L.cx) {
       if (full) return hipErrorInvalidValue;
+      if (L.comp) return launch_vanka_comp(s, L, rho, d, omega, zero_init, fp32, grid);
       if (fp32)
         launch(k_vanka_cx<NLS, float, cx_group<float>()>, dim3(grid), dim3(256), 0, s, rho, d,
                L.cell_sdofs, L.own_ptr, L.own_loc, L.inv_off, L.inv_ld,

@@ -142,7 +142,11 @@ void free_inverses(stv_ctx* ctx) {
     dfree(ctx->lv[g].inv_store);
     dfree(ctx->lv[g].dec_tab);
     dfree(ctx->lv[g].dec_code);
-    ctx->lv[g].dec = 0;
+    dfree(ctx->lv[g].comp_flags);
+    dfree(ctx->lv[g].comp_cell);
+    dfree(ctx->lv[g].comp_node);
+    dfree(ctx->lv[g].comp_dof);
+    ctx->lv[g].dec = ctx->lv[g].comp = 0;
     ctx->lv[g].inv_elems = 0;
     dfree(ctx->inv_status[g]);
     dfree(ctx->inv_scratch[g]);
@@ -163,6 +167,8 @@ void free_level(DevLevel& L) {
   dfree(L.P_rowptr); dfree(L.P_col); dfree(L.P_val);
   dfree(L.Pt_rowptr); dfree(L.Pt_col); dfree(L.Pt_val);
   dfree(L.inv_off); dfree(L.inv_store); dfree(L.posmap); dfree(L.dec_tab); dfree(L.dec_code);
+  dfree(L.comp_flags); dfree(L.comp_cell); dfree(L.comp_node);
+  dfree(L.comp_dof);
   dfree(L.rho); dfree(L.r); dfree(L.d); dfree(L.corr);
   dfree(L.rowptr_t); dfree(L.col_t); dfree(L.val_t);
   dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
@@ -1373,6 +1379,58 @@ static int make_coarse_groups(stv_ctx* ctx) {
   return STV_OK;
 }
 
+// Whether a level's velocity components do not couple in any cell (k_comp.hip);
+// keeps the per-cell flags on the device when so.
+static int check_components(stv_ctx* ctx, DevLevel& L) {
+  STV_TRY(dalloc(ctx, &L.comp_flags, (size_t)L.n_cells));
+  std::vector<uint8_t> f((size_t)L.n_cells);
+  hipError_t e = launch_comp_flags(ctx->stream, L, L.comp_flags);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e == hipSuccess) e = hipMemcpy(f.data(), L.comp_flags, f.size(), hipMemcpyDeviceToHost);
+  if (e != hipSuccess)
+    return fail(ctx, STV_EHIP, std::string("component check failed: ") + hipGetErrorString(e));
+  L.comp = std::all_of(f.begin(), f.end(), [](uint8_t v) { return (v & 2) != 0; });
+  if (!L.comp) {
+    dfree(L.comp_flags);
+    return STV_OK;
+  }
+  // cells with one distinct V block, for the component store
+  L.h_comp_cell.assign((size_t)L.n_cells, int4{});
+  for (int32_t c = 0; c < L.n_cells; ++c) L.h_comp_cell[(size_t)c].w = (f[(size_t)c] & 1) ? 1 : 3;
+  return STV_OK;
+}
+
+// Owned nodes, offsets and size of the component store of a 3d level
+// (layout in k_comp.hip); h_comp_cell[c].w holds the distinct V blocks.
+static int make_component_store(stv_ctx* ctx, DevLevel& L, int64_t* total) {
+  L.h_comp_node.clear();
+  std::vector<int32_t> dof;
+  int64_t tot = 0;
+  for (int32_t c = 0; c < L.n_cells; ++c) {
+    int4& ci = L.h_comp_cell[(size_t)c];
+    const int nvb = ci.w, first = (int)L.h_comp_node.size();
+    int mask[27] = {}, pm = 0;
+    for (int32_t q = L.h_own_ptr[(size_t)c]; q < L.h_own_ptr[(size_t)c + 1]; ++q) {
+      const int a = L.h_own_loc[(size_t)q];
+      if (a < 81) mask[a % 27] |= 1 << (a / 27);
+      else pm |= 1 << (a - 81);
+    }
+    for (int j = 0; j < 27; ++j) {
+      if (!mask[j]) continue;
+      L.h_comp_node.push_back((uint16_t)(j | mask[j] << 8));
+      for (int k = 0; k < 3; ++k)
+        dof.push_back((mask[j] >> k) & 1 ? L.h_csd[(size_t)c * 85 + 27 * k + j] : -1);
+    }
+    const int R = (int)L.h_comp_node.size() - first;
+    ci = int4{(int)(uint32_t)tot, (int)(tot >> 32), first, R | nvb << 8 | pm << 16};
+    tot += (int64_t)(54 * nvb + 24) * R + 704;
+  }
+  *total = tot;
+  STV_TRY(upload(ctx, &L.comp_cell, L.h_comp_cell.data(), L.h_comp_cell.size()));
+  STV_TRY(upload(ctx, &L.comp_dof, dof.data(), dof.size()));
+  return upload(ctx, &L.comp_node, L.h_comp_node.data(), L.h_comp_node.size());
+}
+
 // Stores of every cell's inverse rows for a layout (all rows or the owned
 // rows) and element type: per-level row offsets and the store itself.
 static int make_inverse_stores(stv_ctx* ctx, int fp32, int full) {
@@ -1383,9 +1441,14 @@ static int make_inverse_stores(stv_ctx* ctx, int fp32, int full) {
     dfree(L.inv_store);
     dfree(L.dec_tab);
     dfree(L.dec_code);
+    dfree(L.comp_flags);
+    dfree(L.comp_cell);
+    dfree(L.comp_node);
+    dfree(L.comp_dof);
     L.inv_elems = 0;
     L.dec = 0;
     L.cx = 0;
+    L.comp = 0;
     if (L.n_cells == 0) continue;
     const int n = L.n_ls * b;
     // with spatial factors, the owned-row layout of a level whose cell
@@ -1468,6 +1531,18 @@ static int make_inverse_stores(stv_ctx* ctx, int fp32, int full) {
       }
       L.cx = 1;
       L.dec = full ? 0 : 1;
+    }
+    if (L.dec && !L.comp_off) STV_TRY(check_components(ctx, L));
+    if (L.comp && L.cx) {
+      int64_t tot = 0;
+      STV_TRY(make_component_store(ctx, L, &tot));
+      void* p = nullptr;
+      const hipError_t e = hipMalloc(&p, (size_t)tot * (fp32 ? 4 : 8));
+      if (e != hipSuccess)
+        return fail(ctx, STV_ENOMEM, std::string("component store: ") + hipGetErrorString(e));
+      L.inv_store = p;
+      L.inv_elems = tot;
+      continue;
     }
     // rows stored densely (padding each row to a 128-byte boundary was
     // measured slower: the sweep reads whole cells as one contiguous stream)
@@ -1652,6 +1727,18 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
     return fail(ctx, STV_EHIP, std::string("inverse build failed: ") + hipGetErrorString(e));
   }
   const int none = 0x7f7f7f7f;
+  // a component-wise elimination met a small pivot: these levels eliminate
+  // the whole cell matrices instead (with these factors, from now on)
+  bool again = false;
+  for (int g = 1; g < ctx->n_levels; ++g)
+    if (ctx->lv[g].n_cells > 0 && ctx->lv[g].comp && ctx->h_report[g] != none) {
+      ctx->lv[g].comp_off = 1;
+      again = true;
+    }
+  if (again) {
+    ctx->inv_layout = -1;
+    return stv_build_cell_inverses(ctx, storage, bad_level, bad_cell);
+  }
   for (int g = 1; g < ctx->n_levels; ++g)
     if (ctx->lv[g].n_cells > 0 && ctx->h_report[g] != none) {
       if (bad_level) *bad_level = g;
@@ -2256,16 +2343,53 @@ int stv_get_cell_inverse(stv_ctx* ctx, int level, int cell, double* out) {
   const int b = ctx->b, nls = L.n_ls, n = nls * b;
   const int o0 = L.h_own_ptr[(size_t)cell], no = L.h_own_ptr[(size_t)cell + 1] - o0;
   const int R = ctx->inv_full ? n : L.dec ? no : no * b;
-  const int ld = L.inv_ld;
-  std::vector<int64_t> off(1);
-  STV_HIP(hipMemcpy(off.data(), L.inv_off + cell, sizeof(int64_t), hipMemcpyDeviceToHost));
-  std::vector<double> blk((size_t)R * ld);
-  if (ctx->inv_fp32) {
-    std::vector<float> f((size_t)R * ld);
-    STV_HIP(hipMemcpy(f.data(), (const float*)L.inv_store + off[0], sizeof(float) * f.size(), hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < f.size(); ++i) blk[i] = f[i];
+  const int ld = L.comp_cell ? 2 * nls : L.inv_ld;
+  auto stored = [&](int64_t off, size_t cnt, std::vector<double>& v) {
+    v.resize(cnt);
+    if (!ctx->inv_fp32)
+      return hipMemcpy(v.data(), (const double*)L.inv_store + off, 8 * cnt, hipMemcpyDeviceToHost);
+    std::vector<float> f(cnt);
+    const hipError_t e = hipMemcpy(f.data(), (const float*)L.inv_store + off, 4 * cnt, hipMemcpyDeviceToHost);
+    std::copy(f.begin(), f.end(), v.begin());
+    return e;
+  };
+  std::vector<double> blk;
+  if (L.comp_cell) {
+    // whole complex rows [V^-1 | 0] + G P from the component store
+    const int4 ci = L.h_comp_cell[(size_t)cell];
+    const int Rn = ci.w & 255, nvb = (ci.w >> 8) & 255;
+    std::vector<double> st;
+    STV_HIP(stored(((int64_t)ci.y << 32) | (uint32_t)ci.x, (size_t)((54 * nvb + 24) * Rn + 704), st));
+    const double* G = st.data() + (size_t)54 * nvb * Rn;
+    const double* P = G + (size_t)24 * Rn;
+    typedef std::complex<double> cd;
+    auto prow = [&](int m, int e) {
+      const int ch = e / 22, k = e % 22;
+      return cd(P[(2 * k) * 16 + 4 * m + ch], P[(2 * k + 1) * 16 + 4 * m + ch]);
+    };
+    blk.assign((size_t)R * ld, 0.0);
+    for (int os = 0; os < no; ++os) {
+      const int a = L.h_own_loc[(size_t)(o0 + os)], c = a / 27, i = a % 27;
+      int o = 0;
+      while (a < 81 && (L.h_comp_node[(size_t)(ci.z + o)] & 255) != i) ++o;
+      for (int e = 0; e < nls; ++e) {
+        cd v = 0.0;
+        if (a >= 81) {
+          v = prow(a - 81, e);
+        } else {
+          const double* Vc = st.data() + (size_t)(nvb == 1 ? 0 : c) * 54 * Rn;
+          if (e < 81 && e / 27 == c) v = cd(Vc[(2 * (e % 27)) * Rn + o], Vc[(2 * (e % 27) + 1) * Rn + o]);
+          for (int m = 0; m < 4; ++m)
+            v += cd(G[(2 * (4 * c + m)) * Rn + o], G[(2 * (4 * c + m) + 1) * Rn + o]) * prow(m, e);
+        }
+        blk[(size_t)os * ld + e] = v.real();
+        blk[(size_t)os * ld + nls + e] = v.imag();
+      }
+    }
   } else {
-    STV_HIP(hipMemcpy(blk.data(), (const double*)L.inv_store + off[0], sizeof(double) * blk.size(), hipMemcpyDeviceToHost));
+    int64_t off = 0;
+    STV_HIP(hipMemcpy(&off, L.inv_off + cell, sizeof(int64_t), hipMemcpyDeviceToHost));
+    STV_HIP(stored(off, (size_t)R * ld, blk));
   }
   for (int64_t e = 0; e < (int64_t)n * n; ++e) out[e] = NAN;
   if (L.dec) {
@@ -2572,6 +2696,7 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
     STV_HIP(hipStreamSynchronize(ctx->stream));
     dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
     L.kg = KronGroups{};
+    L.comp_off = 0;
     ctx->cgroups_algo = -1;   // the coarse groups may refer to the factors
     ctx->inv_layout = -1;     // and the cell-inverse layout of the level
     ++ctx->generation;
@@ -2630,6 +2755,7 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
   if (rc != STV_OK) { drop(); return rc; }
   dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
   L.kron_ma = dma;
+  L.comp_off = 0;
   L.kg = kg;
   L.kg_idx = kg_idx;
   L.kg_val = kg_val;

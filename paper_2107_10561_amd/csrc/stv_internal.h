@@ -111,6 +111,20 @@ struct DevLevel {
   int dec = 0;                    // the inverse store holds time-decoupled rows (CellSplit)
   int cx = 0;                     // inverses built from the complex decoupled block (plain store)
   CellSplit split{};
+  // cells whose velocity components do not couple (k_comp.hip): comp = the
+  // build uses that structure, comp_off = it met a pivot too small for these
+  // factors, comp_flags per cell; comp_cell (set: the store is the component
+  // store) has per cell the store offset (x, y), the first entry of its owned
+  // nodes in comp_node (z) and R | distinct V blocks << 8 | owned pressure
+  // modes << 16 (w); comp_node: node | owned components << 8; comp_dof: the
+  // node's spatial DoF per component (-1: not owned)
+  int comp = 0, comp_off = 0;
+  uint8_t* comp_flags = nullptr;
+  int4* comp_cell = nullptr;
+  uint16_t* comp_node = nullptr;
+  int32_t* comp_dof = nullptr;
+  std::vector<int4> h_comp_cell;
+  std::vector<uint16_t> h_comp_node;
   // per lane j of the decoupled sweep: W[j % B][.] and V[j % B][.] (2B x 64,
   // row-major), and a code word: source lanes of u (bits 0-5, 6-11) and the
   // multipliers (2 bits per output: 0 = 0, 1 = +1, 3 = -1; from bit 12 for
@@ -377,6 +391,12 @@ hipError_t launch_vanka_combine(hipStream_t s, int b, const DevLevel& L, double*
 hipError_t launch_cell_inverses(hipStream_t s, int b, const DevLevel& L, int fp32, int full,
                                 uint8_t* status, double* gscratch, int n_slots, int n_cu,
                                 int reserve, int cu_cap = 0);
+// cell problems with uncoupled velocity components (k_comp.hip)
+hipError_t launch_comp_flags(hipStream_t s, const DevLevel& L, uint8_t* flags);
+hipError_t launch_inverse_comp(hipStream_t s, const DevLevel& L, int fp32, uint8_t* status,
+                               int n_cu, int reserve);
+hipError_t launch_vanka_comp(hipStream_t s, const DevLevel& L, const double* rho, double* d,
+                             double omega, int zero_init, int fp32, unsigned grid);
 // transfers: shapes 1..kTransferShapes take 1, 2, 4, 8, 16 lanes per row;
 // transfer_shape_for picks one from the mean row length
 constexpr int kTransferShapes = 5;
