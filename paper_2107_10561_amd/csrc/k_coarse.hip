@@ -1,0 +1,405 @@
+// The direct coarse solve of a member whose velocity components do not couple
+// (spatial factors, time-decoupled): one time block of the coarse operator is
+//   [ V  B ]   V = blockdiag(V_1 .. V_nc), one block per velocity component,
+//   [ C  D ]   and the rows without a diagonal entry (the pressure) last.
+// The V_c are eliminated as one batch by the complex-pivot chain (k_dense.hip),
+// then the Schur complement S = D - C V^-1 B by a second, smaller one, and the
+// solve is applied in factored form,
+//   p = P (f, g),  P = S^-1 [-C V^-1 | I],   u = V^-1 f + G p,  G = -V^-1 B.
+// In 3d (16x3x3 cells) that is three complex blocks of order 1,617 and one of
+// 576 instead of one of 5,427: 13 times fewer operations, 138 panels in
+// sequence instead of 340, and 220 instead of 471 MB per apply.  All matrices
+// here are complex, row-major, in the member's order (components one after
+// the other, then the pressure); entry x of a real form [[Re, -Im], [Im, Re]].
+#include "stv_internal.h"
+
+namespace stv {
+
+typedef double stv_d4 __attribute__((ext_vector_type(4)));
+
+// complex value of block q of the time block p: t (m) + a, t = al - i be
+__device__ __forceinline__ double2 cc_value(const CompCoarse& M, int p, int64_t q) {
+  const double2 f = reinterpret_cast<const double2*>(M.ma)[q];
+  return make_double2(fma(M.al[p], f.x, f.y), -M.be[p] * f.x);
+}
+
+__device__ __forceinline__ void atomic_max_bits(unsigned long long* at, double v) {
+  // non-negative doubles order as their bit patterns (a NaN above infinity)
+  atomicMax(at, __builtin_bit_cast(unsigned long long, v));
+}
+
+__device__ __forceinline__ double wave_fmax(double v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    const double o = __shfl_xor(v, off, 64);
+    v = (v != v || v > o) ? v : o;   // a NaN wins
+  }
+  return v;
+}
+
+// The dense V_c in real form (A zeroed before): local row blockIdx.x of block
+// blockIdx.y = p * kCcMax + c, member blockIdx.z; one wavefront per row.
+__global__ void __launch_bounds__(64) k_cc_fill(const CompCoarse* __restrict__ cc) {
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y / kCcMax, c = blockIdx.y % kCcMax, i = blockIdx.x;
+  if (p >= M.nblk || c >= M.nc || i >= M.n[c]) return;
+  const int32_t row = M.row_off + M.order[M.off[c] + i];
+  double* A = M.A[p][c];
+  const int64_t ld = M.lda[c];
+  double mx = 0.0;
+  for (int32_t q = M.rowptr[row] + (int)threadIdx.x; q < M.rowptr[row + 1]; q += 64) {
+    const int j = M.where[M.col[q] - M.row_off] - M.off[c];
+    if (j < 0 || j >= M.n[c]) continue;
+    const double2 v = cc_value(M, p, q);
+    *reinterpret_cast<double2*>(&A[2 * (int64_t)i * ld + 2 * j]) = make_double2(v.x, -v.y);
+    *reinterpret_cast<double2*>(&A[(2 * (int64_t)i + 1) * ld + 2 * j]) = make_double2(v.y, v.x);
+    mx = fmax(mx, fabs(v.x) + fabs(v.y));
+  }
+  mx = wave_fmax(mx);
+  if (threadIdx.x == 0) atomic_max_bits(&M.norm[p][c][0], mx);
+}
+
+// Inverse rows out of the eliminated real form, in natural order: row i is S's
+// row rpiv[2i], column 2t belongs to j = rpiv[2t] / 2.  Nothing is read where
+// the pivot record is not a permutation (verdict).
+__device__ __forceinline__ void cc_collect(const double* A, int64_t ld, const int* rpiv, int n,
+                                           int i, double2* out, unsigned long long* norm) {
+  const double* row = A + (int64_t)rpiv[2 * i] * ld;
+  double mx = 0.0;
+  for (int t = threadIdx.x; t < n; t += 256) {
+    const double2 e = *reinterpret_cast<const double2*>(row + 2 * (int64_t)t);
+    out[(int64_t)i * n + (rpiv[2 * t] >> 1)] = make_double2(e.x, -e.y);
+    const double m = fabs(e.x) + fabs(e.y);
+    mx = (m != m || m > mx) ? m : mx;
+  }
+  mx = wave_fmax(mx);
+  if ((threadIdx.x & 63) == 0) atomic_max_bits(norm, mx);
+}
+
+__global__ void __launch_bounds__(256) k_cc_collect_v(const CompCoarse* __restrict__ cc) {
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y / kCcMax, c = blockIdx.y % kCcMax, i = blockIdx.x;
+  if (p >= M.nblk || c >= M.nc || i >= M.n[c] || *M.verdict[p][c]) return;
+  cc_collect(M.A[p][c], M.lda[c], M.rpiv[p][c], M.n[c], i, M.Vi[p][c], &M.norm[p][c][1]);
+}
+
+__global__ void __launch_bounds__(256) k_cc_collect_s(const CompCoarse* __restrict__ cc) {
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y, m = blockIdx.x;
+  if (p >= M.nblk || m >= M.n_p || *M.verdict[p][kCcMax]) return;
+  cc_collect(M.A[p][kCcMax], M.lda[kCcMax], M.rpiv[p][kCcMax], M.n_p, m, M.Si[p],
+             &M.norm[p][kCcMax][1]);
+}
+
+// Z = C V^-1, row m: the pressure row's entries of each component times the
+// rows of V_c^-1 (coalesced over the columns).
+__global__ void __launch_bounds__(256) k_cc_z(const CompCoarse* __restrict__ cc) {
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y / kCcMax, c = blockIdx.y % kCcMax, m = blockIdx.x;
+  if (p >= M.nblk || c >= M.nc || m >= M.n_p) return;
+  const int32_t row = M.row_off + M.order[M.n_v + m];
+  const int n = M.n[c];
+  const double2* Vi = M.Vi[p][c];
+  double2* out = M.Z[p] + (int64_t)m * M.n_v + M.off[c];
+  for (int j = threadIdx.x; j < n; j += 256) {
+    double re = 0.0, im = 0.0;
+    for (int32_t q = M.rowptr[row]; q < M.rowptr[row + 1]; ++q) {
+      const int i = M.where[M.col[q] - M.row_off] - M.off[c];
+      if (i < 0 || i >= n) continue;
+      const double2 a = cc_value(M, p, q), v = Vi[(int64_t)i * n + j];
+      re = fma(a.x, v.x, fma(-a.y, v.y, re));
+      im = fma(a.x, v.y, fma(a.y, v.x, im));
+    }
+    out[j] = make_double2(re, im);
+  }
+}
+
+// One row x (length n, in LDS) times the columns of B_c: column m's entries are
+// listed at bptr[m nc + c].
+__device__ __forceinline__ double2 cc_times_b(const CompCoarse& M, int p, int c, int m,
+                                              const double2* x, double2 acc) {
+  for (int32_t e = M.bptr[m * M.nc + c]; e < M.bptr[m * M.nc + c + 1]; ++e) {
+    const double2 a = cc_value(M, p, M.bq[e]), v = x[M.bi[e]];
+    acc.x = fma(a.x, v.x, fma(-a.y, v.y, acc.x));
+    acc.y = fma(a.x, v.y, fma(a.y, v.x, acc.y));
+  }
+  return acc;
+}
+
+// G = -V^-1 B, row (c, i): the row of V_c^-1 staged in LDS, a pressure column
+// per thread.
+__global__ void __launch_bounds__(256) k_cc_g(const CompCoarse* __restrict__ cc) {
+  extern __shared__ double2 x[];
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y / kCcMax, c = blockIdx.y % kCcMax, i = blockIdx.x;
+  if (p >= M.nblk || c >= M.nc || i >= M.n[c]) return;
+  const int n = M.n[c];
+  for (int j = threadIdx.x; j < n; j += 256) x[j] = M.Vi[p][c][(int64_t)i * n + j];
+  __syncthreads();
+  for (int m = threadIdx.x; m < M.n_p; m += 256) {
+    const double2 v = cc_times_b(M, p, c, m, x, make_double2(0.0, 0.0));
+    M.G[p][(int64_t)(M.off[c] + i) * M.n_p + m] = make_double2(-v.x, -v.y);
+  }
+}
+
+// S = D - Z B, row m, in real form into the Schur block's matrix (zeroed before).
+__global__ void __launch_bounds__(256) k_cc_s(const CompCoarse* __restrict__ cc) {
+  extern __shared__ double2 x[];
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y, m = blockIdx.x;
+  if (p >= M.nblk || m >= M.n_p) return;
+  double* A = M.A[p][kCcMax];
+  const int64_t ld = M.lda[kCcMax];
+  const int32_t row = M.row_off + M.order[M.n_v + m];
+  double mx = 0.0;
+  for (int k0 = 0; k0 < M.n_p; k0 += 256) {
+    const int k = k0 + (int)threadIdx.x;
+    double2 acc = make_double2(0.0, 0.0);
+    for (int c = 0; c < M.nc; ++c) {
+      __syncthreads();
+      for (int j = threadIdx.x; j < M.n[c]; j += 256)
+        x[j] = M.Z[p][(int64_t)m * M.n_v + M.off[c] + j];
+      __syncthreads();
+      if (k < M.n_p) acc = cc_times_b(M, p, c, k, x, acc);
+    }
+    if (k >= M.n_p) continue;
+    double2 d = make_double2(-acc.x, -acc.y);
+    for (int32_t q = M.rowptr[row]; q < M.rowptr[row + 1]; ++q)
+      if (M.where[M.col[q] - M.row_off] - M.n_v == k) {
+        const double2 v = cc_value(M, p, q);
+        d.x += v.x;
+        d.y += v.y;
+      }
+    *reinterpret_cast<double2*>(&A[2 * (int64_t)m * ld + 2 * k]) = make_double2(d.x, -d.y);
+    *reinterpret_cast<double2*>(&A[(2 * (int64_t)m + 1) * ld + 2 * k]) = make_double2(d.y, d.x);
+    const double t = fabs(d.x) + fabs(d.y);
+    mx = (t != t || t > mx) ? t : mx;
+  }
+  mx = wave_fmax(mx);
+  if ((threadIdx.x & 63) == 0) atomic_max_bits(&M.norm[p][kCcMax][0], mx);
+}
+
+// P = S^-1 [-Z | I]: a complex matrix product on FP64 matrix cores, 64 x 64
+// tiles, four wavefronts of 2 x 2 instruction tiles each, 16 columns of S^-1
+// per step staged in LDS.  3d: 12.9 GFLOP.
+__global__ void __launch_bounds__(256) k_cc_p(const CompCoarse* __restrict__ cc, int blocks) {
+  constexpr int KC = 16;
+  __shared__ double2 As[64][KC + 1], Bs[KC][64 + 1];
+  const CompCoarse& M = cc[blockIdx.z / blocks];
+  const int p = blockIdx.z % blocks;
+  if (p >= M.nblk) return;
+  const int n_p = M.n_p, n_v = M.n_v, n_s = n_v + n_p;
+  const int m0 = blockIdx.y * 64, e0 = blockIdx.x * 64;
+  if (m0 >= n_p || e0 >= n_s) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int lr = lane >> 4, lc = lane & 15, wr = 32 * (w >> 1), wc = 32 * (w & 1);
+  const double2 *Si = M.Si[p], *Z = M.Z[p];
+  stv_d4 re[2][2] = {}, im[2][2] = {};
+  if (e0 < n_v) {
+    for (int k0 = 0; k0 < n_p; k0 += KC) {
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = tid + 256 * u, r = e / KC, k = e % KC;
+        As[r][k] = (m0 + r < n_p && k0 + k < n_p) ? Si[(int64_t)(m0 + r) * n_p + k0 + k]
+                                                  : make_double2(0.0, 0.0);
+        const int kb = e / 64, cb = e % 64;
+        Bs[kb][cb] = (k0 + kb < n_p && e0 + cb < n_v) ? Z[(int64_t)(k0 + kb) * n_v + e0 + cb]
+                                                      : make_double2(0.0, 0.0);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < KC; k += 4) {
+        double2 a[2], b[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          a[t] = As[wr + 16 * t + lc][k + lr];
+          b[t] = Bs[k + lr][wc + 16 * t + lc];
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, re[i][j], 0, 0, 0);
+            re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[i].y, b[j].y, re[i][j], 0, 0, 0);
+            im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, im[i][j], 0, 0, 0);
+            im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].x, im[i][j], 0, 0, 0);
+          }
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int m = m0 + wr + 16 * i + 4 * v + lr, e = e0 + wc + 16 * j + lc;
+        if (m >= n_p || e >= n_s) continue;
+        M.P[p][(int64_t)m * n_s + e] =
+            e < n_v ? make_double2(-re[i][j][v], -im[i][j][v]) : Si[(int64_t)m * n_p + e - n_v];
+      }
+}
+
+// A block whose largest entry times its inverse's largest is above 1e10 (or
+// not finite) is not trusted: its verdict is set, and the build then
+// eliminates the whole coarse matrix.
+__global__ void k_cc_verdict(const CompCoarse* __restrict__ cc) {
+  const CompCoarse& M = cc[blockIdx.x];
+  const int p = threadIdx.x / (kCcMax + 1), c = threadIdx.x % (kCcMax + 1);
+  if (p >= M.nblk || (c < kCcMax && c >= M.nc)) return;
+  const double a = __builtin_bit_cast(double, M.norm[p][c][0]);
+  const double i = __builtin_bit_cast(double, M.norm[p][c][1]);
+  if (!(a * i <= 1e10)) *M.verdict[p][c] = 1;
+}
+
+// z_e = (W r)_e of time block p at member position e (its complex pair)
+template <int B>
+__device__ __forceinline__ double2 cc_rhs(const CompCoarse& M, int p, int e,
+                                          const double* __restrict__ r) {
+  const int64_t s = (int64_t)(M.row_off + M.order[e]) * B;
+  const int f = M.first[p];
+  double z0 = 0.0, z1 = 0.0;
+#pragma unroll
+  for (int l = 0; l < B; ++l) z0 = fma(M.W[f * B + l], r[s + l], z0);
+  if (M.sz[p] == 2) {
+#pragma unroll
+    for (int l = 0; l < B; ++l) z1 = fma(M.W[(f + 1) * B + l], r[s + l], z1);
+  }
+  return make_double2(z0, z1);
+}
+
+// First half of the solve: p = P z, one workgroup per pressure row and block.
+template <int B>
+__global__ void __launch_bounds__(256) k_cc_solve_p(const CompCoarse* __restrict__ cc,
+                                                    const double* __restrict__ r) {
+  __shared__ double2 red[4];
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y, m = blockIdx.x;
+  if (p >= M.nblk || m >= M.n_p) return;
+  const int n_s = M.n_v + M.n_p;
+  const double2* row = M.P[p] + (int64_t)m * n_s;
+  double re = 0.0, im = 0.0;
+#pragma unroll 4
+  for (int e = threadIdx.x; e < n_s; e += 256) {
+    const double2 a = row[e], z = cc_rhs<B>(M, p, e, r);
+    re = fma(a.x, z.x, fma(-a.y, z.y, re));
+    im = fma(a.x, z.y, fma(a.y, z.x, im));
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    re += __shfl_xor(re, off, 64);
+    im += __shfl_xor(im, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_double2(re, im);
+  __syncthreads();
+  if (threadIdx.x == 0)
+    M.pw[p * M.n_p + m] = make_double2((red[0].x + red[1].x) + (red[2].x + red[3].x),
+                                       (red[0].y + red[1].y) + (red[2].y + red[3].y));
+}
+
+// Second half: u = V^-1 z + G p and the time recombination, one wavefront per
+// spatial row (a pressure row only copies its p).
+template <int B>
+__global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict__ cc,
+                                                    const double* __restrict__ r,
+                                                    double* __restrict__ d) {
+  const CompCoarse& M = cc[blockIdx.z];
+  const int lane = threadIdx.x & 63;
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (e >= M.n_v + M.n_p) return;
+  int c = 0;
+  while (c < M.nc && e >= M.off[c] + M.n[c]) ++c;
+  double out[B];
+#pragma unroll
+  for (int i = 0; i < B; ++i) out[i] = 0.0;
+  for (int p = 0; p < M.nblk; ++p) {
+    double re = 0.0, im = 0.0;
+    if (c < M.nc) {
+      const int n = M.n[c];
+      const double2* row = M.Vi[p][c] + (int64_t)(e - M.off[c]) * n;
+#pragma unroll 4
+      for (int j = lane; j < n; j += 64) {
+        const double2 a = row[j], z = cc_rhs<B>(M, p, M.off[c] + j, r);
+        re = fma(a.x, z.x, fma(-a.y, z.y, re));
+        im = fma(a.x, z.y, fma(a.y, z.x, im));
+      }
+      const double2* g = M.G[p] + (int64_t)e * M.n_p;
+#pragma unroll 4
+      for (int m = lane; m < M.n_p; m += 64) {
+        const double2 a = g[m], z = M.pw[p * M.n_p + m];
+        re = fma(a.x, z.x, fma(-a.y, z.y, re));
+        im = fma(a.x, z.y, fma(a.y, z.x, im));
+      }
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) {
+        re += __shfl_xor(re, off, 64);
+        im += __shfl_xor(im, off, 64);
+      }
+    } else {
+      const double2 v = M.pw[p * M.n_p + e - M.n_v];
+      re = v.x;
+      im = v.y;
+    }
+    const int f = M.first[p];
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      out[i] = fma(M.V[i * B + f], re, out[i]);
+      if (M.sz[p] == 2) out[i] = fma(M.V[i * B + f + 1], im, out[i]);
+    }
+  }
+  if (lane < B) {
+    double v = out[0];
+#pragma unroll
+    for (int i = 1; i < B; ++i) v = lane == i ? out[i] : v;
+    d[(int64_t)(M.row_off + M.order[e]) * B + lane] = v;
+  }
+}
+
+hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
+  k_cc_fill<<<dim3(D.n, D.blk * kCcMax, D.cnt), 64, 0, s>>>(cc);
+  return hipGetLastError();
+}
+
+// After the V chain: V^-1, Z, G and the Schur blocks.
+hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
+  const unsigned lds = sizeof(double2) * D.n;
+  k_cc_collect_v<<<dim3(D.n, D.blk * kCcMax, D.cnt), 256, 0, s>>>(cc);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_cc_z<<<dim3(D.n_p, D.blk * kCcMax, D.cnt), 256, 0, s>>>(cc);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_cc_s<<<dim3(D.n_p, D.blk, D.cnt), 256, lds, s>>>(cc);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_cc_g<<<dim3(D.n, D.blk * kCcMax, D.cnt), 256, lds, s>>>(cc);
+  return hipGetLastError();
+}
+
+// After the Schur chain: S^-1, P and the verdicts.
+hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
+  k_cc_collect_s<<<dim3(D.n_p, D.blk, D.cnt), 256, 0, s>>>(cc);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_cc_p<<<dim3((D.n_s + 63) / 64, (D.n_p + 63) / 64, D.cnt * D.blk), 256, 0, s>>>(cc, D.blk);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_cc_verdict<<<D.cnt, 4 * (kCcMax + 1), 0, s>>>(cc);
+  return hipGetLastError();
+}
+
+hipError_t launch_cc_solve(hipStream_t s, int b, const CompCoarse* cc, const CcDims& D,
+                           const double* r, double* d) {
+  const dim3 gp(D.n_p, D.blk, D.cnt), gu((D.n_s + 3) / 4, 1, D.cnt), block(256);
+#define STV_CC(B)                                              \
+  case B:                                                      \
+    launch(k_cc_solve_p<B>, gp, block, 0, s, cc, r);           \
+    launch(k_cc_solve_u<B>, gu, block, 0, s, cc, r, d);        \
+    break;
+  switch (b) {
+    STV_CC(1) STV_CC(2) STV_CC(3) STV_CC(4)
+    default: return hipErrorInvalidValue;
+  }
+#undef STV_CC
+  return hipGetLastError();
+}
+
+}  // namespace stv

@@ -5,6 +5,7 @@
 // HIP kernels; the host only does index bookkeeping, the (k+1)-sized Givens
 // and triangular solves of GMRES, and control flow.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <complex>
 #include <cstdio>
@@ -115,14 +116,21 @@ void free_graph(stv_ctx* ctx) {
 }
 
 void free_coarse_groups(stv_ctx* ctx) {
-  for (auto& G : ctx->cgroups) {
-    dfree(G.d_desc); dfree(G.w.A); dfree(G.w.rpiv); dfree(G.w.used); dfree(G.w.B);
-    dfree(G.w.P); dfree(G.w.S); dfree(G.w.Bin); dfree(G.rinv);
-    dfree(G.w.cand); dfree(G.w.Z); dfree(G.w.counter);
-    dfree(G.d_kdesc);
+  for (auto* groups : {&ctx->cgroups, &ctx->vgroups, &ctx->sgroups}) {
+    for (auto& G : *groups) {
+      dfree(G.d_desc); dfree(G.w.A); dfree(G.w.rpiv); dfree(G.w.used); dfree(G.w.B);
+      dfree(G.w.P); dfree(G.w.S); dfree(G.w.Bin); dfree(G.rinv);
+      dfree(G.w.cand); dfree(G.w.Z); dfree(G.w.counter);
+      dfree(G.d_kdesc);
+    }
+    groups->clear();
   }
-  ctx->cgroups.clear();
+  for (void*& p : ctx->cc_bufs) dfree(p);
+  ctx->cc_bufs.clear();
   for (int g = 0; g < kMaxLevels; ++g) {
+    ctx->h_cc[g].clear();
+    dfree(ctx->d_cc[g]);
+    ctx->cc_dims[g] = CcDims{};
     ctx->h_kc[g].clear();
     dfree(ctx->d_kc[g]);
     ctx->kc_max_ns[g] = 0;
@@ -197,6 +205,7 @@ void free_hierarchy(stv_ctx* ctx) {
   ctx->inst_row.clear();
   ctx->inst_info.clear();
   ctx->max_seg = 0;
+  ctx->cc_off = 0;
   ctx->have_hier = false;
   ctx->n_levels = 0;
 }
@@ -440,9 +449,11 @@ int sweeps(stv_ctx* ctx, int g, const double* r, double* d, int n, double omega,
 // members with a whole stored inverse by a dense product, the time-decoupled
 // ones from their blocks' inverses.
 int coarse_apply(stv_ctx* ctx, int g, const double* r, double* d) {
-  const int nw = ctx->n_whole[g], nk = (int)ctx->h_kc[g].size();
-  if (nw == 0 && nk == 0) return STV_OK;
-  Timed t(ctx, KC_COARSE, g, nullptr, true);
+  const int nw = ctx->n_whole[g], nk = (int)ctx->h_kc[g].size(), nc = (int)ctx->h_cc[g].size();
+  if (nw == 0 && nk == 0 && nc == 0) return STV_OK;
+  Timed t(ctx, KC_COARSE, g, nullptr, nc == 0);
+  if (nc > 0)   // made for the forward direction only
+    STV_HIP(launch_cc_solve(ctx->stream, ctx->b, ctx->d_cc[g], ctx->cc_dims[g], r, d));
   if (nw > 0 && ctx->transposed)
     STV_HIP(launch_dense_gemv_t(ctx->stream, ctx->d_coarse[g], nw, ctx->b, ctx->coarse_max_n0[g],
                                 ctx->coarse_inv, r, d));
@@ -1197,6 +1208,271 @@ static bool time_split(const double* C, const double* tw, int b, TimeSplit& out)
   return true;
 }
 
+// Elimination plan and buffers of a group (its members' descriptors hd).
+static int alloc_group(stv_ctx* ctx, CoarseGroup& G, const std::vector<CoarseDesc>& hd, int algo) {
+  G.plan = gj_plan(G.n0, algo, G.kron);
+  G.np = (G.n0 + G.plan.pad - 1) / G.plan.pad * G.plan.pad;
+  if (G.np > G.plan.max_n)
+    return fail(ctx, STV_EINVAL, "coarse level larger than " + std::to_string(G.plan.max_n) + " unknowns");
+  const int64_t cnt = (int64_t)hd.size(), np = G.np;
+  const int64_t nbo = std::max(G.plan.nb, G.plan.no);
+  GjWork& w = G.w;
+  w = GjWork{};
+  w.sA = np * np;
+  w.sV = np;
+  w.sB = nbo * np;
+  w.sP = 2 * G.plan.nb * np;
+  w.sS = 2 * (int64_t)G.plan.no * np;
+  w.sBin = (int64_t)G.plan.nb * G.plan.no;
+  STV_TRY(upload(ctx, &G.d_desc, hd.data(), hd.size()));
+  STV_TRY(dalloc(ctx, &w.A, (size_t)(cnt * w.sA)));
+  STV_TRY(dalloc(ctx, &w.rpiv, (size_t)(cnt * w.sV)));
+  STV_TRY(dalloc(ctx, &w.used, (size_t)(cnt * w.sV)));
+  STV_TRY(dalloc(ctx, &w.B, (size_t)(cnt * w.sB)));
+  STV_TRY(dalloc(ctx, &w.P, (size_t)(cnt * w.sP)));
+  STV_TRY(dalloc(ctx, &G.rinv, (size_t)(cnt * w.sV)));
+  if (G.plan.no > 0) {
+    STV_TRY(dalloc(ctx, &w.S, (size_t)(cnt * w.sS)));
+    STV_TRY(dalloc(ctx, &w.Bin, (size_t)(cnt * w.sBin)));
+  }
+  if (G.plan.algo == 3) {
+    // the workgroups' lists and, for the merge tree, the lists and
+    // arrival counters of its nodes (fewer than a third more)
+    w.sC = 2 * ((np + 255) / 256 * G.plan.nb);
+    w.sZ = 2 * (int64_t)G.plan.nb * G.plan.no;
+    w.sK = np / 64 + 8;
+    STV_TRY(dalloc(ctx, &w.cand, (size_t)(cnt * w.sC)));
+    STV_TRY(dalloc(ctx, &w.Z, (size_t)(cnt * w.sZ)));
+    STV_TRY(dalloc(ctx, &w.counter, (size_t)(cnt * w.sK)));
+  }
+  return STV_OK;
+}
+
+// The component structure of a coarse member's rows, read off the nonzero
+// factors: rows without a diagonal entry last (the pressure), the others by
+// connected component; B's entries by pressure column.  Returns false where
+// there are not 2 .. kCcMax components and a pressure, or a component's row
+// does not fit the LDS of the kernels that stage it.
+struct CompStruct {
+  int nc = 0, n_v = 0, n_p = 0;
+  int n[kCcMax] = {}, off[kCcMax] = {};
+  std::vector<int32_t> order, where, bptr, bi, bq;
+};
+
+static bool component_structure(const int32_t* rp, const int32_t* col, const double* ma,
+                                int32_t row_off, int32_t n_s, CompStruct& S) {
+  std::vector<int32_t> up((size_t)n_s);
+  std::vector<char> vel((size_t)n_s, 0);
+  auto nonzero = [&](int64_t q) { return ma[2 * q] != 0.0 || ma[2 * q + 1] != 0.0; };
+  for (int32_t i = 0; i < n_s; ++i) {
+    up[(size_t)i] = i;
+    for (int64_t q = rp[row_off + i]; q < rp[row_off + i + 1]; ++q)
+      if (col[q] == row_off + i && nonzero(q)) vel[(size_t)i] = 1;
+  }
+  auto find = [&](int32_t i) {
+    while (up[(size_t)i] != i) i = up[(size_t)i] = up[(size_t)up[(size_t)i]];
+    return i;
+  };
+  for (int32_t i = 0; i < n_s; ++i)
+    for (int64_t q = rp[row_off + i]; vel[(size_t)i] && q < rp[row_off + i + 1]; ++q) {
+      const int32_t j = col[q] - row_off;
+      if (j < 0 || j >= n_s) return false;
+      if (!vel[(size_t)j] || !nonzero(q)) continue;
+      const int32_t a = find(i), b = find(j);
+      if (a != b) up[(size_t)std::max(a, b)] = std::min(a, b);
+    }
+  std::vector<int32_t> root;
+  for (int32_t i = 0; i < n_s; ++i)
+    if (vel[(size_t)i] && find(i) == i) root.push_back(i);
+  if (root.size() < 2 || root.size() > (size_t)kCcMax) return false;
+  S.nc = (int)root.size();
+  for (int c = 0; c < S.nc; ++c) {
+    S.off[c] = (int)S.order.size();
+    for (int32_t i = 0; i < n_s; ++i)
+      if (vel[(size_t)i] && find(i) == root[(size_t)c]) S.order.push_back(i);
+    S.n[c] = (int)S.order.size() - S.off[c];
+    if (S.n[c] > 4096) return false;
+  }
+  S.n_v = (int)S.order.size();
+  for (int32_t i = 0; i < n_s; ++i)
+    if (!vel[(size_t)i]) S.order.push_back(i);
+  S.n_p = n_s - S.n_v;
+  if (S.n_p < 1) return false;
+  S.where.assign((size_t)n_s, 0);
+  for (int32_t e = 0; e < n_s; ++e) S.where[(size_t)S.order[(size_t)e]] = e;
+  // counting sort of B's entries by (pressure column, component)
+  S.bptr.assign((size_t)S.n_p * S.nc + 1, 0);
+  for (int pass = 0; pass < 2; ++pass) {
+    std::vector<int32_t> at(S.bptr.begin(), S.bptr.end());
+    for (int c = 0; c < S.nc; ++c)
+      for (int i = 0; i < S.n[c]; ++i) {
+        const int32_t row = row_off + S.order[(size_t)(S.off[c] + i)];
+        for (int32_t q = rp[row]; q < rp[row + 1]; ++q) {
+          const int m = S.where[(size_t)(col[q] - row_off)] - S.n_v;
+          if (m < 0) continue;
+          if (pass == 0) {
+            S.bptr[(size_t)m * S.nc + c + 1]++;
+          } else {
+            const int32_t k = at[(size_t)m * S.nc + c]++;
+            S.bi[(size_t)k] = i;
+            S.bq[(size_t)k] = q;
+          }
+        }
+      }
+    if (pass == 0) {
+      for (size_t e = 1; e < S.bptr.size(); ++e) S.bptr[e] += S.bptr[e - 1];
+      S.bi.resize((size_t)S.bptr.back());
+      S.bq.resize((size_t)S.bptr.back());
+    }
+  }
+  return true;
+}
+
+// Members with a component structure: descriptors, chains and buffers.  The
+// whole-member set-up then leaves them out (inv_off = -2).
+static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& split,
+                                  const std::vector<bool>& has_split) {
+  struct Slot { size_t group, slot; };
+  struct Member { int g; CompStruct S; Slot at[4][kCcMax + 1]; };
+  std::vector<Member> mem;
+  auto slot_of = [](std::vector<CoarseGroup>& groups, int64_t order) -> Slot {
+    size_t k = 0;
+    while (k < groups.size() && groups[k].n0 != order) ++k;
+    if (k == groups.size()) {
+      groups.emplace_back();
+      groups[k].n0 = order;
+      groups[k].kron = true;
+    }
+    groups[k].lev.push_back(0);
+    return {k, groups[k].lev.size() - 1};
+  };
+  for (int g = 0; g < ctx->n_levels; ++g) {
+    if (!has_split[(size_t)g]) continue;
+    const DevLevel& L = ctx->lv[g];
+    std::vector<int32_t> rp((size_t)L.n_s + 1), col((size_t)L.nnzb);
+    std::vector<double> ma((size_t)2 * L.nnzb);
+    STV_HIP(hipMemcpy(rp.data(), L.rowptr, 4 * rp.size(), hipMemcpyDeviceToHost));
+    STV_HIP(hipMemcpy(col.data(), L.col, 4 * col.size(), hipMemcpyDeviceToHost));
+    STV_HIP(hipMemcpy(ma.data(), L.kron_ma, 8 * ma.size(), hipMemcpyDeviceToHost));
+    for (CoarseDesc& c : ctx->h_coarse[g]) {
+      Member M{};
+      if (!component_structure(rp.data(), col.data(), ma.data(), c.row_off, c.n_s, M.S)) continue;
+      M.g = g;
+      const TimeSplit& T = split[(size_t)g];
+      CompCoarse R{};
+      R.rowptr = L.rowptr; R.col = L.col; R.ma = L.kron_ma;
+      R.row_off = c.row_off;
+      R.nc = M.S.nc; R.n_v = M.S.n_v; R.n_p = M.S.n_p; R.nblk = T.nblk;
+      for (int e = 0; e < 16; ++e) { R.V[e] = T.V[e]; R.W[e] = T.W[e]; }
+      for (int k = 0; k < R.nc; ++k) { R.n[k] = M.S.n[k]; R.off[k] = M.S.off[k]; }
+      for (int p = 0; p < T.nblk; ++p) {
+        R.sz[p] = T.sz[p];
+        R.first[p] = T.first[p];
+        R.al[p] = T.t[p][0];
+        R.be[p] = T.sz[p] == 2 ? T.t[p][1] : 0.0;
+        for (int k = 0; k < R.nc; ++k) M.at[p][k] = slot_of(ctx->vgroups, 2 * (int64_t)R.n[k]);
+        M.at[p][kCcMax] = slot_of(ctx->sgroups, 2 * (int64_t)R.n_p);
+      }
+      c.inv_off = -2;
+      ctx->h_cc[g].push_back(R);
+      mem.push_back(std::move(M));
+    }
+  }
+  if (mem.empty()) return STV_OK;
+  for (auto* groups : {&ctx->vgroups, &ctx->sgroups})
+    for (CoarseGroup& G : *groups) {
+      CoarseDesc d{};
+      d.n_s = (int32_t)G.n0;
+      STV_TRY(alloc_group(ctx, G, std::vector<CoarseDesc>(G.lev.size(), d), 3));
+    }
+  auto keep = [&](auto** p, size_t n) -> int {
+    STV_TRY(dalloc(ctx, p, n));
+    ctx->cc_bufs.push_back((void*)*p);
+    return STV_OK;
+  };
+  auto keep_copy = [&](const int32_t** p, const std::vector<int32_t>& v) -> int {
+    int32_t* q = nullptr;
+    STV_TRY(upload(ctx, &q, v.data(), v.size()));
+    ctx->cc_bufs.push_back((void*)q);
+    *p = q;
+    return STV_OK;
+  };
+  std::vector<size_t> next((size_t)ctx->n_levels, 0);
+  for (const Member& M : mem) {
+    CompCoarse& R = ctx->h_cc[M.g][next[(size_t)M.g]++];
+    STV_TRY(keep_copy(&R.order, M.S.order));
+    STV_TRY(keep_copy(&R.where, M.S.where));
+    STV_TRY(keep_copy(&R.bptr, M.S.bptr));
+    STV_TRY(keep_copy(&R.bi, M.S.bi));
+    STV_TRY(keep_copy(&R.bq, M.S.bq));
+    const size_t nv = (size_t)R.n_v, np = (size_t)R.n_p;
+    unsigned long long* norm = nullptr;
+    STV_TRY(keep(&norm, 4 * (kCcMax + 1) * 2));
+    R.norm = reinterpret_cast<unsigned long long(*)[kCcMax + 1][2]>(norm);
+    STV_TRY(keep(&R.pw, (size_t)R.nblk * np));
+    for (int p = 0; p < R.nblk; ++p) {
+      for (int c = 0; c <= kCcMax; ++c) {
+        if (c < kCcMax && c >= R.nc) continue;
+        const Slot& at = M.at[p][c];
+        const CoarseGroup& G = (c == kCcMax ? ctx->sgroups : ctx->vgroups)[at.group];
+        R.A[p][c] = G.w.A + (int64_t)at.slot * G.w.sA;
+        R.rpiv[p][c] = G.w.rpiv + (int64_t)at.slot * G.w.sV;
+        R.lda[c] = G.np;
+        if (c < kCcMax) STV_TRY(keep(&R.Vi[p][c], (size_t)R.n[c] * R.n[c]));
+      }
+      STV_TRY(keep(&R.Si[p], np * np));
+      STV_TRY(keep(&R.Z[p], np * nv));
+      STV_TRY(keep(&R.G[p], nv * np));
+      STV_TRY(keep(&R.P[p], np * (nv + np)));
+    }
+    CcDims& D = ctx->cc_dims[M.g];
+    for (int c = 0; c < R.nc; ++c) D.n = std::max(D.n, (unsigned)R.n[c]);
+    D.n_p = std::max(D.n_p, (unsigned)R.n_p);
+    D.n_s = std::max(D.n_s, (unsigned)(R.n_v + R.n_p));
+    D.blk = std::max(D.blk, (unsigned)R.nblk);
+    D.cnt += 1;
+  }
+  // the slots' verdicts: consecutive in the report, v groups then s groups
+  // (assigned with the report, see assign_verdicts)
+  ctx->cc_slots.clear();
+  for (const Member& M : mem) {
+    std::array<int, 4 * (kCcMax + 1)> v;
+    v.fill(-1);
+    const int nblk = ctx->h_cc[M.g][0].nblk;
+    for (int p = 0; p < nblk; ++p)
+      for (int c = 0; c <= kCcMax; ++c) {
+        if (c < kCcMax && c >= M.S.nc) continue;
+        int base = 0;
+        if (c == kCcMax)
+          for (const CoarseGroup& G : ctx->vgroups) base += (int)G.lev.size();
+        const auto& groups = c == kCcMax ? ctx->sgroups : ctx->vgroups;
+        for (size_t k = 0; k < M.at[p][c].group; ++k) base += (int)groups[k].lev.size();
+        v[(size_t)(p * (kCcMax + 1) + c)] = base + (int)M.at[p][c].slot;
+      }
+    ctx->cc_slots.emplace_back(M.g, v);
+  }
+  return STV_OK;
+}
+
+// Device descriptors of the component members, their verdicts at `report`.
+static int upload_component_members(stv_ctx* ctx, int* report) {
+  std::vector<size_t> next((size_t)ctx->n_levels, 0);
+  for (const auto& sl : ctx->cc_slots) {
+    CompCoarse& R = ctx->h_cc[sl.first][next[(size_t)sl.first]++];
+    for (int p = 0; p < 4; ++p)
+      for (int c = 0; c <= kCcMax; ++c) {
+        const int v = sl.second[(size_t)(p * (kCcMax + 1) + c)];
+        R.verdict[p][c] = v >= 0 ? report + v : nullptr;
+      }
+  }
+  for (int g = 0; g < ctx->n_levels; ++g) {
+    dfree(ctx->d_cc[g]);
+    if (!ctx->h_cc[g].empty())
+      STV_TRY(upload(ctx, &ctx->d_cc[g], ctx->h_cc[g].data(), ctx->h_cc[g].size()));
+  }
+  return STV_OK;
+}
+
 // Coarse members grouped by order (one batched elimination per group), their
 // buffers, the coarse inverse store and the member descriptors.  A member on
 // a level with spatial factors whose time matrix splits (time_split) is
@@ -1218,6 +1494,27 @@ static int make_coarse_groups(stv_ctx* ctx) {
   for (int g = 0; g < ctx->n_levels; ++g)
     if (ctx->lv[g].kron_ma && !ctx->h_coarse[g].empty())
       has_split[(size_t)g] = time_split(ctx->lv[g].kron_C, ctx->lv[g].kron_tw, b, split[(size_t)g]);
+  // by component where that applies: the schedule is not prescribed and only
+  // forward solves are needed (transposed ones go with the all-rows layout)
+  for (int g = 0; g < ctx->n_levels; ++g)
+    for (CoarseDesc& c : ctx->h_coarse[g]) c.inv_off = 0;
+  if (ctx->coarse_algo == 0 && !ctx->inv_full && !ctx->cc_off) {
+    std::vector<TimeSplit> cs = split;
+    std::vector<bool> has = has_split;
+    for (int g = 0; b == 1 && g < ctx->n_levels; ++g) {
+      // one time component: the block itself
+      const DevLevel& L = ctx->lv[g];
+      if (!L.kron_ma || ctx->h_coarse[g].empty() || L.kron_tw[0] == 0.0) continue;
+      TimeSplit& T = cs[(size_t)g];
+      T.nblk = 1;
+      T.sz[0] = 1;
+      T.t[0][0] = L.kron_C[0] / L.kron_tw[0];
+      T.V[0] = 1.0;
+      T.W[0] = 1.0 / L.kron_tw[0];
+      has[(size_t)g] = true;
+    }
+    STV_TRY(make_component_members(ctx, cs, has));
+  }
   // whole members: one group per order; blocks of time-decoupled members:
   // one group, each block padded with the identity to the largest order
   // (the blocks then share every launch of one elimination chain)
@@ -1236,6 +1533,7 @@ static int make_coarse_groups(stv_ctx* ctx) {
   for (int g = 0; g < ctx->n_levels; ++g)
     for (size_t q = 0; q < ctx->h_coarse[g].size(); ++q) {
       CoarseDesc& c = ctx->h_coarse[g][q];
+      if (c.inv_off == -2) continue;
       const int64_t n0 = (int64_t)c.n_s * b;
       if (!has_split[(size_t)g]) {
         c.inv_off = coarse_total;
@@ -1271,20 +1569,6 @@ static int make_coarse_groups(stv_ctx* ctx) {
   // per group: plan, descriptors, buffers
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     CoarseGroup& G = groups[gi];
-    G.plan = gj_plan(G.n0, ctx->coarse_algo, G.kron);
-    G.np = (G.n0 + G.plan.pad - 1) / G.plan.pad * G.plan.pad;
-    if (G.np > G.plan.max_n)
-      return fail(ctx, STV_EINVAL, "coarse level larger than " + std::to_string(G.plan.max_n) + " unknowns");
-    const int64_t cnt = (int64_t)G.lev.size(), np = G.np;
-    const int64_t nbo = std::max(G.plan.nb, G.plan.no);
-    GjWork& w = G.w;
-    w = GjWork{};
-    w.sA = np * np;
-    w.sV = np;
-    w.sB = nbo * np;
-    w.sP = 2 * G.plan.nb * np;
-    w.sS = 2 * (int64_t)G.plan.no * np;
-    w.sBin = (int64_t)G.plan.nb * G.plan.no;
     std::vector<CoarseDesc> hd;
     if (!G.kron) {
       for (size_t m = 0; m < G.lev.size(); ++m) hd.push_back(ctx->h_coarse[G.lev[m]][(size_t)G.idx[m]]);
@@ -1316,27 +1600,7 @@ static int make_coarse_groups(stv_ctx* ctx) {
       }
       STV_TRY(upload(ctx, &G.d_kdesc, kd.data(), kd.size()));
     }
-    STV_TRY(upload(ctx, &G.d_desc, hd.data(), hd.size()));
-    STV_TRY(dalloc(ctx, &w.A, (size_t)(cnt * w.sA)));
-    STV_TRY(dalloc(ctx, &w.rpiv, (size_t)(cnt * w.sV)));
-    STV_TRY(dalloc(ctx, &w.used, (size_t)(cnt * w.sV)));
-    STV_TRY(dalloc(ctx, &w.B, (size_t)(cnt * w.sB)));
-    STV_TRY(dalloc(ctx, &w.P, (size_t)(cnt * w.sP)));
-    STV_TRY(dalloc(ctx, &G.rinv, (size_t)(cnt * w.sV)));
-    if (G.plan.no > 0) {
-      STV_TRY(dalloc(ctx, &w.S, (size_t)(cnt * w.sS)));
-      STV_TRY(dalloc(ctx, &w.Bin, (size_t)(cnt * w.sBin)));
-    }
-    if (G.plan.algo == 3) {
-      // the workgroups' lists and, for the merge tree, the lists and
-      // arrival counters of its nodes (fewer than a third more)
-      w.sC = 2 * ((np + 255) / 256 * G.plan.nb);
-      w.sZ = 2 * (int64_t)G.plan.nb * G.plan.no;
-      w.sK = np / 64 + 8;
-      STV_TRY(dalloc(ctx, &w.cand, (size_t)(cnt * w.sC)));
-      STV_TRY(dalloc(ctx, &w.Z, (size_t)(cnt * w.sZ)));
-      STV_TRY(dalloc(ctx, &w.counter, (size_t)(cnt * w.sK)));
-    }
+    STV_TRY(alloc_group(ctx, G, hd, ctx->coarse_algo));
   }
   // time-decoupled members: where their blocks' inverses and pivot records
   // are left by the elimination
@@ -1610,14 +1874,21 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
       rc = dalloc(ctx, &ctx->inv_scratch[g], (size_t)ctx->inv_slots[g] * L.n_ls * b * L.n_ls * b);
     }
   }
-  if (rc == STV_OK && ctx->cgroups_algo != ctx->coarse_algo) {
+  ctx->inv_fp32 = fp32;
+  ctx->inv_full = full;
+  const int want_groups = ctx->coarse_algo + (full ? 16 : 0);
+  bool regrouped = false;
+  if (rc == STV_OK && ctx->cgroups_algo != want_groups) {
     free_coarse_groups(ctx);
     rc = make_coarse_groups(ctx);
-    if (rc == STV_OK) ctx->cgroups_algo = ctx->coarse_algo;
-    moved = true;
+    if (rc == STV_OK) ctx->cgroups_algo = want_groups;
+    moved = regrouped = true;
   }
-  int members = 0;
+  int members = 0, parts = 0;   // verdicts: whole members, then component blocks
   for (const auto& G : ctx->cgroups) members += (int)G.lev.size();
+  for (const auto* groups : {&ctx->vgroups, &ctx->sgroups})
+    for (const auto& G : *groups) parts += (int)G.lev.size();
+  members += parts;
   const int nrep = ctx->n_levels + members;
   if (rc == STV_OK && ctx->n_report != nrep) {
     dfree(ctx->inv_report);
@@ -1632,7 +1903,10 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
       rc = fail(ctx, STV_ENOMEM, "pinned host allocation of the build report failed");
     }
     if (rc == STV_OK) ctx->n_report = nrep;
+    regrouped = true;
   }
+  if (rc == STV_OK && regrouped)
+    rc = upload_component_members(ctx, ctx->inv_report + nrep - parts);
   if (rc != STV_OK) {
     free_inverses(ctx);
     return rc;
@@ -1641,9 +1915,6 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
     ++ctx->generation;
     free_graph(ctx);
   }
-  ctx->inv_fp32 = fp32;
-  ctx->inv_full = full;
-
   // ---- launch: cell inverses on the caller's stream, coarse factorisations
   // on the internal stream (it starts after everything queued before it);
   // the report starts at 0x7f7f7f7f ("no flagged cell") per level
@@ -1659,7 +1930,7 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
   // elimination chain's latency-bound workgroups then start at once instead
   // of waiting for the inverse kernel to drain whole compute units
   int n_cu = 0;
-  if (STV_CHAIN_VGPRS > 0 && side != s && !ctx->cgroups.empty()) {
+  if (STV_CHAIN_VGPRS > 0 && side != s && !(ctx->cgroups.empty() && ctx->vgroups.empty())) {
     if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) !=
         hipSuccess)
       n_cu = 0;
@@ -1677,6 +1948,41 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
   };
   if (side != s) cell_inverses();
   int mbase = ctx->n_levels;
+  // members by component: their V blocks, the Schur complements, the factors
+  const GjAux aux{ctx->side2, ctx->ev_gj[0], ctx->ev_gj[1]};
+  if (parts > 0) {
+    Timed t(ctx, KC_COARSE_FACTOR, 0, side);
+    int vbase = nrep - parts;
+    auto clear = [&](CoarseGroup& G) {
+      const int cnt = (int)G.lev.size();
+      if (e == hipSuccess) e = launch_fill(side, G.w.A, cnt * G.w.sA, 0.0);
+      if (e == hipSuccess) e = launch_set_diag(side, G.d_desc, cnt, 1, G.w.A, G.w.sA, G.np);
+      if (e == hipSuccess) e = hipMemsetAsync(G.w.used, 0, (size_t)(cnt * G.w.sV), side);
+      if (e == hipSuccess) e = hipMemsetAsync(G.w.counter, 0, 4 * (size_t)(cnt * G.w.sK), side);
+    };
+    auto eliminate = [&](CoarseGroup& G) {
+      const int cnt = (int)G.lev.size();
+      if (e == hipSuccess) e = launch_gj(side, G.plan, G.w, G.np, cnt, ctx->coarse_lookahead ? &aux : nullptr);
+      if (e == hipSuccess)
+        e = launch_gj_invert_perm(side, G.w.rpiv, G.w.sV, G.np, G.d_desc, cnt, 1, G.rinv, rep + vbase);
+      vbase += cnt;
+    };
+    auto members_do = [&](auto&& f) {
+      for (int g = 0; g < ctx->n_levels && e == hipSuccess; ++g)
+        if (!ctx->h_cc[g].empty()) e = f(side, ctx->d_cc[g], ctx->cc_dims[g]);
+    };
+    for (auto& G : ctx->vgroups) clear(G);
+    for (auto& G : ctx->sgroups) clear(G);
+    for (int g = 0; g < ctx->n_levels && e == hipSuccess; ++g)
+      for (const CompCoarse& R : ctx->h_cc[g])
+        if (e == hipSuccess) e = hipMemsetAsync(R.norm, 0, sizeof(R.norm[0]) * 4, side);
+    members_do(launch_cc_fill);
+    for (auto& G : ctx->vgroups) eliminate(G);
+    members_do(launch_cc_schur);
+    for (auto& G : ctx->sgroups) eliminate(G);
+    members_do(launch_cc_finish);
+    t.done();
+  }
   for (auto& G : ctx->cgroups) {
     if (e != hipSuccess) break;
     const int gb = G.kron ? 1 : b;   // a block's descriptor holds its order in n_s
@@ -1693,7 +1999,6 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
     if (e == hipSuccess) e = hipMemsetAsync(G.w.used, 0, (size_t)(cnt * G.w.sV), side);
     if (e == hipSuccess && G.w.counter)
       e = hipMemsetAsync(G.w.counter, 0, sizeof(unsigned) * (size_t)(cnt * G.w.sK), side);
-    const GjAux aux{ctx->side2, ctx->ev_gj[0], ctx->ev_gj[1]};
     if (e == hipSuccess) e = launch_gj(side, G.plan, G.w, G.np, cnt, ctx->coarse_lookahead ? &aux : nullptr);
     // pivot records -> inverse permutations and verdicts, then the
     // unpermuted inverses (the blocks of time-decoupled members are applied
@@ -1735,8 +2040,13 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
       ctx->lv[g].comp_off = 1;
       again = true;
     }
+  for (int k = nrep - parts; k < nrep; ++k)
+    if (ctx->h_report[k] != 0) {
+      ctx->cc_off = 1;
+      again = true;
+    }
   if (again) {
-    ctx->inv_layout = -1;
+    ctx->inv_layout = ctx->cgroups_algo = -1;
     return stv_build_cell_inverses(ctx, storage, bad_level, bad_cell);
   }
   for (int g = 1; g < ctx->n_levels; ++g)
@@ -2696,7 +3006,7 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
     STV_HIP(hipStreamSynchronize(ctx->stream));
     dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
     L.kg = KronGroups{};
-    L.comp_off = 0;
+    L.comp_off = ctx->cc_off = 0;
     ctx->cgroups_algo = -1;   // the coarse groups may refer to the factors
     ctx->inv_layout = -1;     // and the cell-inverse layout of the level
     ++ctx->generation;
@@ -2755,7 +3065,7 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
   if (rc != STV_OK) { drop(); return rc; }
   dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
   L.kron_ma = dma;
-  L.comp_off = 0;
+  L.comp_off = ctx->cc_off = 0;
   L.kg = kg;
   L.kg_idx = kg_idx;
   L.kg_val = kg_val;

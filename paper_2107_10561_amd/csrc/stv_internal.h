@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <array>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -209,6 +210,37 @@ struct KronCoarse {
   double V[16], W[16];
 };
 
+// A coarse member whose velocity components do not couple, time-decoupled
+// (k_coarse.hip).  Its n_s spatial rows in member order (`order`: component
+// 0 .. nc - 1, then the rows without a diagonal entry; `where` the inverse),
+// the columns of B listed by pressure column and component (bptr, local row
+// bi, block bq), and per time block p: the eliminated real forms A (component
+// c, or kCcMax: the Schur complement) with pivot records and verdicts, the
+// inverses Vi, Si and the factors Z, G, P of the solve; norm: largest entry of
+// each block and of its inverse (bit patterns).
+constexpr int kCcMax = 3;
+struct CompCoarse {
+  const int32_t *rowptr, *col;
+  const double* ma;
+  const int32_t *order, *where, *bptr, *bi;
+  const int32_t* bq;
+  int32_t row_off, nc, n_v, n_p, nblk;
+  int32_t n[kCcMax], off[kCcMax];
+  int sz[4], first[4];
+  double al[4], be[4], V[16], W[16];
+  double* A[4][kCcMax + 1];
+  int64_t lda[kCcMax + 1];
+  const int* rpiv[4][kCcMax + 1];
+  int* verdict[4][kCcMax + 1];
+  unsigned long long (*norm)[kCcMax + 1][2];
+  double2* Vi[4][kCcMax];
+  double2 *Si[4], *Z[4], *G[4], *P[4];
+  double2* pw;
+};
+// launch dimensions over the members of one level: largest component,
+// pressure and whole order, time blocks, members
+struct CcDims { unsigned n = 0, n_p = 0, n_s = 0, blk = 0, cnt = 0; };
+
 // The coarse members of one order, eliminated by one batched Gauss-Jordan:
 // members (packed level, index in that level), their device descriptors,
 // the elimination buffers and the inverse pivot permutations.
@@ -293,7 +325,19 @@ struct stv_ctx {
   double* inv_scratch[stv::kMaxLevels] = {};
   int inv_slots[stv::kMaxLevels] = {};
   std::vector<stv::CoarseGroup> cgroups;
-  int cgroups_algo = -1;
+  int cgroups_algo = -1;        // the coarse algorithm, + 16 for the all-rows layout
+  // coarse members with uncoupled components, per packed level; the chains
+  // over their component blocks and over their Schur complements; their other
+  // device arrays; cc_off: a block was not trusted for these factors
+  std::vector<stv::CompCoarse> h_cc[stv::kMaxLevels];
+  stv::CompCoarse* d_cc[stv::kMaxLevels] = {};
+  stv::CcDims cc_dims[stv::kMaxLevels];
+  std::vector<stv::CoarseGroup> vgroups, sgroups;
+  std::vector<void*> cc_bufs;
+  // per component member (level, then per time block and block the index of
+  // its verdict among those of the chains)
+  std::vector<std::pair<int, std::array<int, 4 * (stv::kCcMax + 1)>>> cc_slots;
+  int cc_off = 0;
   // coarse members inverted through time decoupling, per packed level:
   // applied from their blocks' inverses (device descriptors, one per member,
   // and the largest spatial order)
@@ -431,6 +475,11 @@ hipError_t launch_kron_block_dense(hipStream_t s, const KronBlockDesc* kdesc, in
 hipError_t launch_kron_coarse_apply(hipStream_t s, int b, const KronCoarse* kc, int cnt,
                                     int max_blocks, int32_t max_ns, int transposed,
                                     const double* r, double* d);
+hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D);
+hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D);
+hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D);
+hipError_t launch_cc_solve(hipStream_t s, int b, const CompCoarse* cc, const CcDims& D,
+                           const double* r, double* d);
 // rinv = the inverse of every member's pivot record rpiv (order n, real
 // order n0 from desc); verdict[z] = 0 when member z's record is a
 // permutation whose real columns pivot on real rows, else 1.

@@ -177,3 +177,49 @@ def test_coarse_algorithm_option_rejects_unknown(stv):
         s.set_coarse_algorithm("lu")
     with pytest.raises(stv.StvError):
         s._check(stv._lib.stv_set_option(s._h, 1, 7))
+
+
+@pytest.mark.parametrize("singular", [False, True])
+@pytest.mark.parametrize("name", ["2d_16x4_dg1", "2d_32x8_dg2", "3d_8x2x2_dg1", "2d_6x2_dg0"])
+def test_coarse_solve_by_component(stv, name, singular):
+    """With spatial factors and no prescribed schedule the coarse level is
+    eliminated by velocity component and a pressure Schur complement.
+    singular: one node's second component loses its velocity couplings, so its
+    component block is singular although the coarse matrix is not; the build
+    then eliminates the whole matrix.  Bounds as for the other schedules."""
+    import scipy.sparse as sp
+    dim, n, k = {**COARSE, "2d_6x2_dg0": (2, (6, 2), 0)}[name]
+    p = make_problem(dim, n, 1, k, 0.01, 1e-3, 7)
+    _, w, C, _ = fe_time.time_matrices(k)
+    C, tw = np.asarray(C, dtype=np.float64), p.tau * np.asarray(w, dtype=np.float64)
+    L = p.levels[0]
+    m, a = (np.array(v) for v in spatial_factors(L))
+    if singular:
+        nv = 3 ** dim
+        row = int(L.cell_sdofs[-1, nv + nv // 2])
+        rows = np.repeat(np.arange(L.n_sdofs), np.diff(L.rowptr))
+        hit = ((rows == row) | (np.asarray(L.col) == row)) & (m != 0.0)
+        m[hit] = a[hit] = 0.0
+        keep = int(np.nonzero((rows == row) & (np.asarray(L.col) == row))[0][0])
+        a[keep] = 1e-300          # a stored diagonal, far below any other entry
+    val = m[:, None, None] * C[None] + a[:, None, None] * np.diag(tw)[None]
+    J = sp.bsr_matrix((val, L.col, L.rowptr), shape=(L.n_sdofs * p.b,) * 2).tocsc()
+    lu = sla.splu(J)
+    cond = sla.onenormest(J) * sla.onenormest(
+        sla.LinearOperator(J.shape, matvec=lu.solve, rmatvec=lambda v: lu.solve(v, trans="T")))
+    s = stv.Solver(0)
+    s.set_hierarchy([dict(n_sdofs=L.n_sdofs, rowptr=L.rowptr, col=L.col, val=val,
+                          cell_sdofs=L.cell_sdofs, P=None)], p.dim, p.k)
+    s.set_kron_factors(0, m, a, C, tw)
+    r = np.random.default_rng(28).standard_normal(J.shape[0])
+    ref = lu.solve(r)
+    for _ in range(2):
+        s.build_cell_inverses()
+        d = to_dev(np.zeros_like(r))
+        s.coarse_solve(to_dev(r), d)
+        d = to_host(d)
+        res = np.linalg.norm(r - J @ d) / np.linalg.norm(r)
+        fe = relerr(d, ref)
+        log(f"[coarse] {name} singular={singular} relres {res:.2e} forward {fe:.2e} cond {cond:.1e}")
+        assert res <= 1e-11 * max(1.0, 1e-8 * cond)
+        assert fe <= 1e-15 * cond * 10
