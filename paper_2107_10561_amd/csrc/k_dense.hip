@@ -2084,29 +2084,42 @@ __global__ void __launch_bounds__(256) k_dense_gemv(const CoarseDesc* __restrict
 }
 
 // y = A^T x on every member's rows (the direct solve of the transposed
-// coarse matrix, (A^T)^-1 = (A^-1)^T): thread per column, coalesced over the
-// columns of each row of the stored inverse.
-__global__ void __launch_bounds__(256) k_dense_gemv_t(const CoarseDesc* __restrict__ desc, int b,
-                                                      const double* __restrict__ inv,
-                                                      const double* __restrict__ x,
-                                                      double* __restrict__ y) {
+// coarse matrix, (A^T)^-1 = (A^-1)^T): 16 columns per workgroup, 64 row groups
+// of 16 threads each take the rows g, g + 64, ... (a 128-byte run of a row per
+// group, eight rows in flight), and the groups' sums meet in LDS in a fixed
+// order.  Bound by HBM / L2; one thread per column over all rows was bound by
+// the latency of its serial loads (order 1,572: 630 -> 9.6 us, 2.1 TB/s).
+__global__ void __launch_bounds__(1024) k_dense_gemv_t(const CoarseDesc* __restrict__ desc, int b,
+                                                       const double* __restrict__ inv,
+                                                       const double* __restrict__ x,
+                                                       double* __restrict__ y) {
+  constexpr int NC = 16, NG = 64;
+  __shared__ double red[NG][NC + 1];
   const CoarseDesc D = desc[blockIdx.z];
   const int64_t n0 = (int64_t)D.n_s * b;
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n0) return;
+  const int c = threadIdx.x % NC, g = threadIdx.x / NC;
+  const int64_t j = (int64_t)blockIdx.x * NC + c;
+  if ((int64_t)blockIdx.x * NC >= n0) return;
   const int64_t vo = (int64_t)D.row_off * b;
-  const double* A = inv + D.inv_off;
+  const double* A = inv + D.inv_off + (j < n0 ? j : n0 - 1);
   const double* xz = x + vo;
   double acc = 0.0;
-  for (int64_t i = 0; i < n0; ++i) acc = fma(A[i * n0 + j], xz[i], acc);
-  y[vo + j] = acc;
+#pragma unroll 8
+  for (int64_t i = g; i < n0; i += NG) acc = fma(A[i * n0], xz[i], acc);
+  red[g][c] = acc;
+  __syncthreads();
+  for (int h = NG / 2; h >= 1; h >>= 1) {
+    if (g < h) red[g][c] += red[g + h][c];
+    __syncthreads();
+  }
+  if (g == 0 && j < n0) y[vo + j] = red[0][c];
 }
 
 hipError_t launch_dense_gemv_t(hipStream_t s, const CoarseDesc* desc, int cnt, int b,
                                int64_t max_n0, const double* inv, const double* x, double* y) {
   if (cnt < 1) return hipSuccess;
-  dim3 grid((unsigned)((max_n0 + 255) / 256), 1, (unsigned)cnt);
-  launch(k_dense_gemv_t, dim3(grid), dim3(256), 0, s, desc, b, inv, x, y);
+  dim3 grid((unsigned)((max_n0 + 15) / 16), 1, (unsigned)cnt);
+  launch(k_dense_gemv_t, dim3(grid), dim3(1024), 0, s, desc, b, inv, x, y);
   return hipGetLastError();
 }
 
