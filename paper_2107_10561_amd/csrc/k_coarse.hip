@@ -1,16 +1,21 @@
-// The direct coarse solve of a member whose velocity components do not couple
-// (spatial factors, time-decoupled): one time block of the coarse operator is
-//   [ V  B ]   V = blockdiag(V_1 .. V_nc), one block per velocity component,
-//   [ C  D ]   and the rows without a diagonal entry (the pressure) last.
+// The direct coarse solve of a member whose spatial rows fall into uncoupled
+// blocks and a border (spatial factors, time-decoupled): one time block of the
+// coarse operator is
+//   [ V  B ]   V = blockdiag(V_1 .. V_nc): the velocity components, each cut
+//   [ C  D ]   into parts by separators; border: the separators and the rows
+//              without a diagonal entry (the pressure).
 // The V_c are eliminated as one batch by the complex-pivot chain (k_dense.hip),
-// then the Schur complement S = D - C V^-1 B by a second, smaller one, and the
-// solve is applied in factored form,
-//   p = P (f, g),  P = S^-1 [-C V^-1 | I],   u = V^-1 f + G p,  G = -V^-1 B.
-// In 3d (16x3x3 cells) that is three complex blocks of order 1,617 and one of
-// 576 instead of one of 5,427: 13 times fewer operations, 138 panels in
-// sequence instead of 340, and 220 instead of 471 MB per apply.  All matrices
-// here are complex, row-major, in the member's order (components one after
-// the other, then the pressure); entry x of a real form [[Re, -Im], [Im, Re]].
+// then the Schur complement S = D - C V^-1 B by a second chain, and the solve
+// is applied in factored form,
+//   p = S^-1 (g - Z f),  Z = C V^-1,   u = V^-1 f + G p,  G = -V^-1 B
+// (three launches), or with P = S^-1 [-Z | I] formed, p = P (f, g) (two).
+// The chains are bound by their panels in sequence, 16 complex pivots each: in
+// 3d (16x3x3 cells) 32 for nine blocks of order 506 and 55 for a border of 870
+// instead of 340 for the whole matrix of order 5,427 (138 for the components
+// uncut), with fewer operations and 178 instead of 471 MB per apply.  All
+// matrices here are complex, row-major, in the member's order (blocks one
+// after the other, then the border); entry x of a real form is
+// [[Re, -Im], [Im, Re]].
 #include "stv_internal.h"
 
 namespace stv {
@@ -21,6 +26,17 @@ typedef double stv_d4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ double2 cc_value(const CompCoarse& M, int p, int64_t q) {
   const double2 f = reinterpret_cast<const double2*>(M.ma)[q];
   return make_double2(fma(M.al[p], f.x, f.y), -M.be[p] * f.x);
+}
+
+// Entry e of an array that the solve reads (V^-1, G, P): a real number per
+// entry for a real eigenvalue's block, a complex one for a pair's.
+__device__ __forceinline__ double2 cc_get(const double2* a, int64_t e, bool pair) {
+  return pair ? a[e] : make_double2(reinterpret_cast<const double*>(a)[e], 0.0);
+}
+
+__device__ __forceinline__ void cc_put(double2* a, int64_t e, bool pair, double2 v) {
+  if (pair) a[e] = v;
+  else reinterpret_cast<double*>(a)[e] = v.x;
 }
 
 __device__ __forceinline__ void atomic_max_bits(unsigned long long* at, double v) {
@@ -37,38 +53,44 @@ __device__ __forceinline__ double wave_fmax(double v) {
   return v;
 }
 
-// The dense V_c in real form (A zeroed before): local row blockIdx.x of block
-// blockIdx.y = p * kCcMax + c, member blockIdx.z; one wavefront per row.
+// The dense V_c and D in real form (the matrices zeroed before): member row
+// blockIdx.x, time block blockIdx.y, member blockIdx.z; one wavefront per row.
+// Only couplings inside a block and inside the border are written here.
 __global__ void __launch_bounds__(64) k_cc_fill(const CompCoarse* __restrict__ cc) {
   const CompCoarse& M = cc[blockIdx.z];
-  const int p = blockIdx.y / kCcMax, c = blockIdx.y % kCcMax, i = blockIdx.x;
-  if (p >= M.nblk || c >= M.nc || i >= M.n[c]) return;
-  const int32_t row = M.row_off + M.order[M.off[c] + i];
-  double* A = M.A[p][c];
-  const int64_t ld = M.lda[c];
+  const int p = blockIdx.y, e = blockIdx.x;
+  if (p >= M.nblk || e >= M.n_v + M.n_p) return;
+  int c = 0;
+  while (c < M.nc && e >= M.off[c] + M.n[c]) ++c;
+  const bool border = c == M.nc;
+  const int o = border ? M.n_v : M.off[c], n = border ? M.n_p : M.n[c], i = e - o;
+  double* A = M.A[p][border ? kCcMax : c];
+  const int64_t ld = M.lda[border ? kCcMax : c];
+  const int32_t row = M.row_off + M.order[e];
   double mx = 0.0;
   for (int32_t q = M.rowptr[row] + (int)threadIdx.x; q < M.rowptr[row + 1]; q += 64) {
-    const int j = M.where[M.col[q] - M.row_off] - M.off[c];
-    if (j < 0 || j >= M.n[c]) continue;
+    const int j = M.where[M.col[q] - M.row_off] - o;
+    if (j < 0 || j >= n) continue;
     const double2 v = cc_value(M, p, q);
     *reinterpret_cast<double2*>(&A[2 * (int64_t)i * ld + 2 * j]) = make_double2(v.x, -v.y);
     *reinterpret_cast<double2*>(&A[(2 * (int64_t)i + 1) * ld + 2 * j]) = make_double2(v.y, v.x);
     mx = fmax(mx, fabs(v.x) + fabs(v.y));
   }
   mx = wave_fmax(mx);
-  if (threadIdx.x == 0) atomic_max_bits(&M.norm[p][c][0], mx);
+  if (threadIdx.x == 0 && !border) atomic_max_bits(&M.norm[p][c][0], mx);
 }
 
 // Inverse rows out of the eliminated real form, in natural order: row i is S's
 // row rpiv[2i], column 2t belongs to j = rpiv[2t] / 2.  Nothing is read where
 // the pivot record is not a permutation (verdict).
 __device__ __forceinline__ void cc_collect(const double* A, int64_t ld, const int* rpiv, int n,
-                                           int i, double2* out, unsigned long long* norm) {
+                                           int i, bool pair, double2* out,
+                                           unsigned long long* norm) {
   const double* row = A + (int64_t)rpiv[2 * i] * ld;
   double mx = 0.0;
   for (int t = threadIdx.x; t < n; t += 256) {
     const double2 e = *reinterpret_cast<const double2*>(row + 2 * (int64_t)t);
-    out[(int64_t)i * n + (rpiv[2 * t] >> 1)] = make_double2(e.x, -e.y);
+    cc_put(out, (int64_t)i * n + (rpiv[2 * t] >> 1), pair, make_double2(e.x, -e.y));
     const double m = fabs(e.x) + fabs(e.y);
     mx = (m != m || m > mx) ? m : mx;
   }
@@ -76,37 +98,38 @@ __device__ __forceinline__ void cc_collect(const double* A, int64_t ld, const in
   if ((threadIdx.x & 63) == 0) atomic_max_bits(norm, mx);
 }
 
-__global__ void __launch_bounds__(256) k_cc_collect_v(const CompCoarse* __restrict__ cc) {
+__global__ void __launch_bounds__(256) k_cc_collect_v(const CompCoarse* __restrict__ cc, int nc) {
   const CompCoarse& M = cc[blockIdx.z];
-  const int p = blockIdx.y / kCcMax, c = blockIdx.y % kCcMax, i = blockIdx.x;
+  const int p = blockIdx.y / nc, c = blockIdx.y % nc, i = blockIdx.x;
   if (p >= M.nblk || c >= M.nc || i >= M.n[c] || *M.verdict[p][c]) return;
-  cc_collect(M.A[p][c], M.lda[c], M.rpiv[p][c], M.n[c], i, M.Vi[p][c], &M.norm[p][c][1]);
+  cc_collect(M.A[p][c], M.lda[c], M.rpiv[p][c], M.n[c], i, M.sz[p] == 2, M.Vi[p][c],
+             &M.norm[p][c][1]);
 }
 
 __global__ void __launch_bounds__(256) k_cc_collect_s(const CompCoarse* __restrict__ cc) {
   const CompCoarse& M = cc[blockIdx.z];
   const int p = blockIdx.y, m = blockIdx.x;
   if (p >= M.nblk || m >= M.n_p || *M.verdict[p][kCcMax]) return;
-  cc_collect(M.A[p][kCcMax], M.lda[kCcMax], M.rpiv[p][kCcMax], M.n_p, m, M.Si[p],
-             &M.norm[p][kCcMax][1]);
+  cc_collect(M.A[p][kCcMax], M.lda[kCcMax], M.rpiv[p][kCcMax], M.n_p, m, true,
+             M.Si[p], &M.norm[p][kCcMax][1]);
 }
 
-// Z = C V^-1, row m: the pressure row's entries of each component times the
-// rows of V_c^-1 (coalesced over the columns).
-__global__ void __launch_bounds__(256) k_cc_z(const CompCoarse* __restrict__ cc) {
+// Z = C V^-1, row m: the border row's entries in block c (listed at cptr) times
+// the rows of V_c^-1 (coalesced over the columns).
+__global__ void __launch_bounds__(256) k_cc_z(const CompCoarse* __restrict__ cc, int nc) {
   const CompCoarse& M = cc[blockIdx.z];
-  const int p = blockIdx.y / kCcMax, c = blockIdx.y % kCcMax, m = blockIdx.x;
+  const int p = blockIdx.y / nc, c = blockIdx.y % nc, m = blockIdx.x;
   if (p >= M.nblk || c >= M.nc || m >= M.n_p) return;
-  const int32_t row = M.row_off + M.order[M.n_v + m];
   const int n = M.n[c];
+  const bool pair = M.sz[p] == 2;
   const double2* Vi = M.Vi[p][c];
+  const int32_t e0 = M.cptr[m * M.nc + c], e1 = M.cptr[m * M.nc + c + 1];
   double2* out = M.Z[p] + (int64_t)m * M.n_v + M.off[c];
   for (int j = threadIdx.x; j < n; j += 256) {
     double re = 0.0, im = 0.0;
-    for (int32_t q = M.rowptr[row]; q < M.rowptr[row + 1]; ++q) {
-      const int i = M.where[M.col[q] - M.row_off] - M.off[c];
-      if (i < 0 || i >= n) continue;
-      const double2 a = cc_value(M, p, q), v = Vi[(int64_t)i * n + j];
+#pragma unroll 4
+    for (int32_t e = e0; e < e1; ++e) {
+      const double2 a = cc_value(M, p, M.cq[e]), v = cc_get(Vi, (int64_t)M.ci[e] * n + j, pair);
       re = fma(a.x, v.x, fma(-a.y, v.y, re));
       im = fma(a.x, v.y, fma(a.y, v.x, im));
     }
@@ -114,66 +137,73 @@ __global__ void __launch_bounds__(256) k_cc_z(const CompCoarse* __restrict__ cc)
   }
 }
 
-// One row x (length n, in LDS) times the columns of B_c: column m's entries are
-// listed at bptr[m nc + c].
-__device__ __forceinline__ double2 cc_times_b(const CompCoarse& M, int p, int c, int m,
-                                              const double2* x, double2 acc) {
-  for (int32_t e = M.bptr[m * M.nc + c]; e < M.bptr[m * M.nc + c + 1]; ++e) {
-    const double2 a = cc_value(M, p, M.bq[e]), v = x[M.bi[e]];
-    acc.x = fma(a.x, v.x, fma(-a.y, v.y, acc.x));
-    acc.y = fma(a.x, v.y, fma(a.y, v.x, acc.y));
-  }
-  return acc;
-}
-
-// G = -V^-1 B, row (c, i): the row of V_c^-1 staged in LDS, a pressure column
-// per thread.
-__global__ void __launch_bounds__(256) k_cc_g(const CompCoarse* __restrict__ cc) {
-  extern __shared__ double2 x[];
-  const CompCoarse& M = cc[blockIdx.z];
-  const int p = blockIdx.y / kCcMax, c = blockIdx.y % kCcMax, i = blockIdx.x;
-  if (p >= M.nblk || c >= M.nc || i >= M.n[c]) return;
-  const int n = M.n[c];
-  for (int j = threadIdx.x; j < n; j += 256) x[j] = M.Vi[p][c][(int64_t)i * n + j];
-  __syncthreads();
-  for (int m = threadIdx.x; m < M.n_p; m += 256) {
-    const double2 v = cc_times_b(M, p, c, m, x, make_double2(0.0, 0.0));
-    M.G[p][(int64_t)(M.off[c] + i) * M.n_p + m] = make_double2(-v.x, -v.y);
+// acc[k] = sum over the listed entries e of B(., m) times x at row k of a
+// kRows-row slice of a row-major matrix (column bi[e] - o): the entries' values
+// are read once for the slice's rows.
+constexpr int kRows = 8;
+template <typename X>
+__device__ __forceinline__ void cc_times_b(const CompCoarse& M, int p, int32_t e0, int32_t e1,
+                                           X&& x, double2 (&acc)[kRows]) {
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) acc[k] = make_double2(0.0, 0.0);
+#pragma unroll 2
+  for (int32_t e = e0; e < e1; ++e) {
+    const double2 a = cc_value(M, p, M.bq[e]);
+    const int j = M.bi[e];
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+      const double2 v = x(k, j);
+      acc[k].x = fma(a.x, v.x, fma(-a.y, v.y, acc[k].x));
+      acc[k].y = fma(a.x, v.y, fma(a.y, v.x, acc[k].y));
+    }
   }
 }
 
-// S = D - Z B, row m, in real form into the Schur block's matrix (zeroed before).
+// G = -V^-1 B: rows i0 .. of block c, a border column per thread.
+__global__ void __launch_bounds__(256) k_cc_g(const CompCoarse* __restrict__ cc, int nc, int blk) {
+  const CompCoarse& M = cc[blockIdx.z / (nc * blk)];
+  const int pc = blockIdx.z % (nc * blk), p = pc / nc, c = pc % nc;
+  const int i0 = blockIdx.x * kRows, m = blockIdx.y * 256 + (int)threadIdx.x;
+  if (p >= M.nblk || c >= M.nc || i0 >= M.n[c] || m >= M.n_p) return;
+  const int n = M.n[c], o = M.off[c];
+  const bool pair = M.sz[p] == 2;
+  const double2* Vi = M.Vi[p][c];
+  double2 acc[kRows];
+  cc_times_b(M, p, M.bptr[m * M.nc + c], M.bptr[m * M.nc + c + 1],
+             [&](int k, int j) { return cc_get(Vi, (int64_t)min(i0 + k, n - 1) * n + j - o, pair); },
+             acc);
+#pragma unroll
+  for (int k = 0; k < kRows; ++k)
+    if (i0 + k < n)
+      cc_put(M.G[p], (int64_t)(o + i0 + k) * M.n_p + m, pair, make_double2(-acc[k].x, -acc[k].y));
+}
+
+// S = D - Z B, rows m0 .., a column per thread, onto D in the Schur block's
+// matrix (real form).
 __global__ void __launch_bounds__(256) k_cc_s(const CompCoarse* __restrict__ cc) {
-  extern __shared__ double2 x[];
-  const CompCoarse& M = cc[blockIdx.z];
-  const int p = blockIdx.y, m = blockIdx.x;
-  if (p >= M.nblk || m >= M.n_p) return;
+  const CompCoarse& M = cc[blockIdx.z / 4];
+  const int p = blockIdx.z % 4, m0 = blockIdx.x * kRows, col = blockIdx.y * 256 + (int)threadIdx.x;
+  if (p >= M.nblk || m0 >= M.n_p) return;
   double* A = M.A[p][kCcMax];
   const int64_t ld = M.lda[kCcMax];
-  const int32_t row = M.row_off + M.order[M.n_v + m];
   double mx = 0.0;
-  for (int k0 = 0; k0 < M.n_p; k0 += 256) {
-    const int k = k0 + (int)threadIdx.x;
-    double2 acc = make_double2(0.0, 0.0);
-    for (int c = 0; c < M.nc; ++c) {
-      __syncthreads();
-      for (int j = threadIdx.x; j < M.n[c]; j += 256)
-        x[j] = M.Z[p][(int64_t)m * M.n_v + M.off[c] + j];
-      __syncthreads();
-      if (k < M.n_p) acc = cc_times_b(M, p, c, k, x, acc);
+  if (col < M.n_p) {
+    const double2* Z = M.Z[p];
+    double2 acc[kRows];
+    cc_times_b(M, p, M.bptr[col * M.nc], M.bptr[(col + 1) * M.nc],
+               [&](int k, int j) { return Z[(int64_t)min(m0 + k, M.n_p - 1) * M.n_v + j]; }, acc);
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+      if (m0 + k >= M.n_p) continue;
+      double2* even = reinterpret_cast<double2*>(&A[2 * (int64_t)(m0 + k) * ld + 2 * col]);
+      const double2 d = *even;
+      const double re = d.x - acc[k].x, im = -d.y - acc[k].y;
+      *even = make_double2(re, -im);
+      *reinterpret_cast<double2*>(&A[(2 * (int64_t)(m0 + k) + 1) * ld + 2 * col]) =
+          make_double2(im, re);
+      const double t = fabs(re) + fabs(im);
+      mx = (t != t || t > mx) ? t : mx;
     }
-    if (k >= M.n_p) continue;
-    double2 d = make_double2(-acc.x, -acc.y);
-    for (int32_t q = M.rowptr[row]; q < M.rowptr[row + 1]; ++q)
-      if (M.where[M.col[q] - M.row_off] - M.n_v == k) {
-        const double2 v = cc_value(M, p, q);
-        d.x += v.x;
-        d.y += v.y;
-      }
-    *reinterpret_cast<double2*>(&A[2 * (int64_t)m * ld + 2 * k]) = make_double2(d.x, -d.y);
-    *reinterpret_cast<double2*>(&A[(2 * (int64_t)m + 1) * ld + 2 * k]) = make_double2(d.y, d.x);
-    const double t = fabs(d.x) + fabs(d.y);
-    mx = (t != t || t > mx) ? t : mx;
   }
   mx = wave_fmax(mx);
   if ((threadIdx.x & 63) == 0) atomic_max_bits(&M.norm[p][kCcMax][0], mx);
@@ -181,13 +211,15 @@ __global__ void __launch_bounds__(256) k_cc_s(const CompCoarse* __restrict__ cc)
 
 // P = S^-1 [-Z | I]: a complex matrix product on FP64 matrix cores, 64 x 64
 // tiles, four wavefronts of 2 x 2 instruction tiles each, 16 columns of S^-1
-// per step staged in LDS.  3d: 12.9 GFLOP.
+// per step staged in LDS.  Only where the product is small (CcDims::form_p): it
+// saves one launch per solve.
 __global__ void __launch_bounds__(256) k_cc_p(const CompCoarse* __restrict__ cc, int blocks) {
   constexpr int KC = 16;
   __shared__ double2 As[64][KC + 1], Bs[KC][64 + 1];
   const CompCoarse& M = cc[blockIdx.z / blocks];
   const int p = blockIdx.z % blocks;
   if (p >= M.nblk) return;
+  if (!M.P[p]) return;
   const int n_p = M.n_p, n_v = M.n_v, n_s = n_v + n_p;
   const int m0 = blockIdx.y * 64, e0 = blockIdx.x * 64;
   if (m0 >= n_p || e0 >= n_s) return;
@@ -236,8 +268,8 @@ __global__ void __launch_bounds__(256) k_cc_p(const CompCoarse* __restrict__ cc,
       for (int v = 0; v < 4; ++v) {
         const int m = m0 + wr + 16 * i + 4 * v + lr, e = e0 + wc + 16 * j + lc;
         if (m >= n_p || e >= n_s) continue;
-        M.P[p][(int64_t)m * n_s + e] =
-            e < n_v ? make_double2(-re[i][j][v], -im[i][j][v]) : Si[(int64_t)m * n_p + e - n_v];
+        cc_put(M.P[p], (int64_t)m * n_s + e, M.sz[p] == 2,
+               e < n_v ? make_double2(-re[i][j][v], -im[i][j][v]) : Si[(int64_t)m * n_p + e - n_v]);
       }
 }
 
@@ -269,23 +301,8 @@ __device__ __forceinline__ double2 cc_rhs(const CompCoarse& M, int p, int e,
   return make_double2(z0, z1);
 }
 
-// First half of the solve: p = P z, one workgroup per pressure row and block.
-template <int B>
-__global__ void __launch_bounds__(256) k_cc_solve_p(const CompCoarse* __restrict__ cc,
-                                                    const double* __restrict__ r) {
-  __shared__ double2 red[4];
-  const CompCoarse& M = cc[blockIdx.z];
-  const int p = blockIdx.y, m = blockIdx.x;
-  if (p >= M.nblk || m >= M.n_p) return;
-  const int n_s = M.n_v + M.n_p;
-  const double2* row = M.P[p] + (int64_t)m * n_s;
-  double re = 0.0, im = 0.0;
-#pragma unroll 4
-  for (int e = threadIdx.x; e < n_s; e += 256) {
-    const double2 a = row[e], z = cc_rhs<B>(M, p, e, r);
-    re = fma(a.x, z.x, fma(-a.y, z.y, re));
-    im = fma(a.x, z.y, fma(a.y, z.x, im));
-  }
+// Sum over a workgroup of 256 threads, in thread 0.
+__device__ __forceinline__ double2 cc_block_sum(double re, double im, double2 (&red)[4]) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     re += __shfl_xor(re, off, 64);
@@ -293,13 +310,67 @@ __global__ void __launch_bounds__(256) k_cc_solve_p(const CompCoarse* __restrict
   }
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_double2(re, im);
   __syncthreads();
-  if (threadIdx.x == 0)
-    M.pw[p * M.n_p + m] = make_double2((red[0].x + red[1].x) + (red[2].x + red[3].x),
-                                       (red[0].y + red[1].y) + (red[2].y + red[3].y));
+  return make_double2((red[0].x + red[1].x) + (red[2].x + red[3].x),
+                      (red[0].y + red[1].y) + (red[2].y + red[3].y));
+}
+
+// First half of the solve: p = P z, one workgroup per border row and time
+// block; without P, q = z_border - Z z instead (k_cc_solve_s then forms
+// p = S^-1 q).
+template <int B>
+__global__ void __launch_bounds__(256) k_cc_solve_p(const CompCoarse* __restrict__ cc,
+                                                    const double* __restrict__ r) {
+  __shared__ double2 red[4];
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y, m = blockIdx.x;
+  if (p >= M.nblk || m >= M.n_p) return;
+  const bool form = M.P[p] != nullptr;
+  const int len = form ? M.n_v + M.n_p : M.n_v;
+  double re = 0.0, im = 0.0;
+  if (form && M.sz[p] == 1) {
+    const double* row = reinterpret_cast<const double*>(M.P[p]) + (int64_t)m * len;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < len; e += 256) re = fma(row[e], cc_rhs<B>(M, p, e, r).x, re);
+  } else {
+    const double2* row = (form ? M.P[p] : M.Z[p]) + (int64_t)m * len;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < len; e += 256) {
+      const double2 a = row[e], z = cc_rhs<B>(M, p, e, r);
+      re = fma(a.x, z.x, fma(-a.y, z.y, re));
+      im = fma(a.x, z.y, fma(a.y, z.x, im));
+    }
+  }
+  const double2 v = cc_block_sum(re, im, red);
+  if (threadIdx.x != 0) return;
+  if (form) {
+    M.pw[p * M.n_p + m] = v;
+  } else {
+    const double2 z = cc_rhs<B>(M, p, M.n_v + m, r);
+    M.pw[(M.nblk + p) * M.n_p + m] = make_double2(z.x - v.x, z.y - v.y);
+  }
+}
+
+// p = S^-1 q, one workgroup per border row and time block.
+__global__ void __launch_bounds__(256) k_cc_solve_s(const CompCoarse* __restrict__ cc) {
+  __shared__ double2 red[4];
+  const CompCoarse& M = cc[blockIdx.z];
+  const int p = blockIdx.y, m = blockIdx.x;
+  if (p >= M.nblk || m >= M.n_p || M.P[p]) return;
+  const double2* row = M.Si[p] + (int64_t)m * M.n_p;
+  const double2* q = M.pw + (M.nblk + p) * M.n_p;
+  double re = 0.0, im = 0.0;
+#pragma unroll 4
+  for (int e = threadIdx.x; e < M.n_p; e += 256) {
+    const double2 a = row[e], z = q[e];
+    re = fma(a.x, z.x, fma(-a.y, z.y, re));
+    im = fma(a.x, z.y, fma(a.y, z.x, im));
+  }
+  const double2 v = cc_block_sum(re, im, red);
+  if (threadIdx.x == 0) M.pw[p * M.n_p + m] = v;
 }
 
 // Second half: u = V^-1 z + G p and the time recombination, one wavefront per
-// spatial row (a pressure row only copies its p).
+// spatial row (a border row only copies its p).
 template <int B>
 __global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict__ cc,
                                                     const double* __restrict__ r,
@@ -315,7 +386,17 @@ __global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict
   for (int i = 0; i < B; ++i) out[i] = 0.0;
   for (int p = 0; p < M.nblk; ++p) {
     double re = 0.0, im = 0.0;
-    if (c < M.nc) {
+    if (c < M.nc && M.sz[p] == 1) {
+      const int n = M.n[c];
+      const double* row = reinterpret_cast<const double*>(M.Vi[p][c]) + (int64_t)(e - M.off[c]) * n;
+#pragma unroll 4
+      for (int j = lane; j < n; j += 64) re = fma(row[j], cc_rhs<B>(M, p, M.off[c] + j, r).x, re);
+      const double* g = reinterpret_cast<const double*>(M.G[p]) + (int64_t)e * M.n_p;
+#pragma unroll 4
+      for (int m = lane; m < M.n_p; m += 64) re = fma(g[m], M.pw[p * M.n_p + m].x, re);
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) re += __shfl_xor(re, off, 64);
+    } else if (c < M.nc) {
       const int n = M.n[c];
       const double2* row = M.Vi[p][c] + (int64_t)(e - M.off[c]) * n;
 #pragma unroll 4
@@ -357,42 +438,47 @@ __global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict
 }
 
 hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
-  k_cc_fill<<<dim3(D.n, D.blk * kCcMax, D.cnt), 64, 0, s>>>(cc);
+  k_cc_fill<<<dim3(D.n_s, D.blk, D.cnt), 64, 0, s>>>(cc);
   return hipGetLastError();
 }
 
 // After the V chain: V^-1, Z, G and the Schur blocks.
 hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
-  const unsigned lds = sizeof(double2) * D.n;
-  k_cc_collect_v<<<dim3(D.n, D.blk * kCcMax, D.cnt), 256, 0, s>>>(cc);
+  const unsigned cols = (D.n_p + 255) / 256;
+  k_cc_collect_v<<<dim3(D.n, D.blk * D.nc, D.cnt), 256, 0, s>>>(cc, D.nc);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_cc_z<<<dim3(D.n_p, D.blk * kCcMax, D.cnt), 256, 0, s>>>(cc);
+  k_cc_z<<<dim3(D.n_p, D.blk * D.nc, D.cnt), 256, 0, s>>>(cc, D.nc);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_cc_s<<<dim3(D.n_p, D.blk, D.cnt), 256, lds, s>>>(cc);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_cc_g<<<dim3(D.n, D.blk * kCcMax, D.cnt), 256, lds, s>>>(cc);
+  k_cc_s<<<dim3((D.n_p + kRows - 1) / kRows, cols, 4 * D.cnt), 256, 0, s>>>(cc);
   return hipGetLastError();
 }
 
-// After the Schur chain: S^-1, P and the verdicts.
+// After the Schur chain: S^-1, P, G and the verdicts.
 hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
-  k_cc_collect_s<<<dim3(D.n_p, D.blk, D.cnt), 256, 0, s>>>(cc);
+  const unsigned cols = (D.n_p + 255) / 256;
+  k_cc_g<<<dim3((D.n + kRows - 1) / kRows, cols, D.cnt * D.blk * D.nc), 256, 0, s>>>(cc, D.nc,
+                                                                                   D.blk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_cc_p<<<dim3((D.n_s + 63) / 64, (D.n_p + 63) / 64, D.cnt * D.blk), 256, 0, s>>>(cc, D.blk);
+  k_cc_collect_s<<<dim3(D.n_p, D.blk, D.cnt), 256, 0, s>>>(cc);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_cc_verdict<<<D.cnt, 4 * (kCcMax + 1), 0, s>>>(cc);
+  if (D.form_p) {
+    k_cc_p<<<dim3((D.n_s + 63) / 64, (D.n_p + 63) / 64, D.cnt * D.blk), 256, 0, s>>>(cc, D.blk);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  k_cc_verdict<<<D.cnt, 4 * (kCcMax + 1), 0, s>>>(cc);   // one wavefront
   return hipGetLastError();
 }
 
 hipError_t launch_cc_solve(hipStream_t s, int b, const CompCoarse* cc, const CcDims& D,
                            const double* r, double* d) {
   const dim3 gp(D.n_p, D.blk, D.cnt), gu((D.n_s + 3) / 4, 1, D.cnt), block(256);
-#define STV_CC(B)                                              \
-  case B:                                                      \
-    launch(k_cc_solve_p<B>, gp, block, 0, s, cc, r);           \
-    launch(k_cc_solve_u<B>, gu, block, 0, s, cc, r, d);        \
+#define STV_CC(B)                                                       \
+  case B:                                                               \
+    launch(k_cc_solve_p<B>, gp, block, 0, s, cc, r);                    \
+    if (!D.form_p) launch(k_cc_solve_s, gp, block, 0, s, cc);           \
+    launch(k_cc_solve_u<B>, gu, block, 0, s, cc, r, d);                 \
     break;
   switch (b) {
     STV_CC(1) STV_CC(2) STV_CC(3) STV_CC(4)

@@ -1248,59 +1248,144 @@ static int alloc_group(stv_ctx* ctx, CoarseGroup& G, const std::vector<CoarseDes
   return STV_OK;
 }
 
-// The component structure of a coarse member's rows, read off the nonzero
-// factors: rows without a diagonal entry last (the pressure), the others by
-// connected component; B's entries by pressure column.  Returns false where
-// there are not 2 .. kCcMax components and a pressure, or a component's row
-// does not fit the LDS of the kernels that stage it.
+// The block structure of a coarse member's rows, read off the nonzero factors:
+// uncoupled blocks first, then the border.  The border takes the rows without
+// a diagonal entry (the pressure); what remains falls into connected
+// components (the velocity components), and each is cut into up to four parts
+// of about equal size by separators that join the border (from the level sets
+// of a breadth-first search; the nodes of a level that touch the next).  The
+// number of parts is the one with the least order of the largest block plus
+// order of the border, which is the number of pivots in sequence of the two
+// elimination chains.  Returns false where there is no border or fewer than
+// two blocks.  B's entries are listed by border column and block, C's by border
+// row and block.
 struct CompStruct {
   int nc = 0, n_v = 0, n_p = 0;
   int n[kCcMax] = {}, off[kCcMax] = {};
-  std::vector<int32_t> order, where, bptr, bi, bq;
+  std::vector<int32_t> order, where, bptr, bi, bq, cptr, ci, cq;
 };
 
 static bool component_structure(const int32_t* rp, const int32_t* col, const double* ma,
                                 int32_t row_off, int32_t n_s, CompStruct& S) {
-  std::vector<int32_t> up((size_t)n_s);
-  std::vector<char> vel((size_t)n_s, 0);
-  auto nonzero = [&](int64_t q) { return ma[2 * q] != 0.0 || ma[2 * q + 1] != 0.0; };
-  for (int32_t i = 0; i < n_s; ++i) {
-    up[(size_t)i] = i;
-    for (int64_t q = rp[row_off + i]; q < rp[row_off + i + 1]; ++q)
-      if (col[q] == row_off + i && nonzero(q)) vel[(size_t)i] = 1;
-  }
-  auto find = [&](int32_t i) {
-    while (up[(size_t)i] != i) i = up[(size_t)i] = up[(size_t)up[(size_t)i]];
-    return i;
-  };
-  for (int32_t i = 0; i < n_s; ++i)
-    for (int64_t q = rp[row_off + i]; vel[(size_t)i] && q < rp[row_off + i + 1]; ++q) {
-      const int32_t j = col[q] - row_off;
-      if (j < 0 || j >= n_s) return false;
-      if (!vel[(size_t)j] || !nonzero(q)) continue;
-      const int32_t a = find(i), b = find(j);
-      if (a != b) up[(size_t)std::max(a, b)] = std::min(a, b);
+  // symmetric adjacency of the nonzero off-diagonal entries
+  std::vector<char> diag((size_t)n_s, 0);
+  std::vector<int32_t> ptr((size_t)n_s + 1, 0), adj;
+  for (int pass = 0; pass < 2; ++pass) {
+    std::vector<int32_t> at(ptr.begin(), ptr.end());
+    for (int32_t i = 0; i < n_s; ++i)
+      for (int64_t q = rp[row_off + i]; q < rp[row_off + i + 1]; ++q) {
+        const int32_t j = col[q] - row_off;
+        if (j < 0 || j >= n_s) return false;
+        if (ma[2 * q] == 0.0 && ma[2 * q + 1] == 0.0) continue;
+        if (j == i) { diag[(size_t)i] = 1; continue; }
+        if (pass == 0) {
+          ++ptr[(size_t)i + 1];
+          ++ptr[(size_t)j + 1];
+        } else {
+          adj[(size_t)at[(size_t)i]++] = j;
+          adj[(size_t)at[(size_t)j]++] = i;
+        }
+      }
+    if (pass == 0) {
+      for (int32_t i = 0; i < n_s; ++i) ptr[(size_t)i + 1] += ptr[(size_t)i];
+      adj.resize((size_t)ptr[(size_t)n_s]);
     }
-  std::vector<int32_t> root;
-  for (int32_t i = 0; i < n_s; ++i)
-    if (vel[(size_t)i] && find(i) == i) root.push_back(i);
-  if (root.size() < 2 || root.size() > (size_t)kCcMax) return false;
-  S.nc = (int)root.size();
+  }
+  // breadth-first levels from i among the rows with in[] = tag; the visit order
+  std::vector<int32_t> lev((size_t)n_s, -1);
+  auto bfs = [&](int32_t i, const std::vector<char>& in, std::vector<int32_t>& out) {
+    out.assign(1, i);
+    lev[(size_t)i] = 0;
+    for (size_t k = 0; k < out.size(); ++k)
+      for (int32_t e = ptr[(size_t)out[k]]; e < ptr[(size_t)out[k] + 1]; ++e) {
+        const int32_t j = adj[(size_t)e];
+        if (!in[(size_t)j] || lev[(size_t)j] >= 0) continue;
+        lev[(size_t)j] = lev[(size_t)out[k]] + 1;
+        out.push_back(j);
+      }
+  };
+  // the components' visit orders from a far end, with their level sets
+  std::vector<std::vector<int32_t>> comp, depth;
+  std::vector<char> todo(diag);
+  for (int32_t i = 0; i < n_s; ++i) {
+    if (!todo[(size_t)i]) continue;
+    std::vector<int32_t> v;
+    bfs(i, diag, v);
+    const int32_t far = v.back();
+    for (int32_t j : v) lev[(size_t)j] = -1;
+    bfs(far, diag, v);
+    std::vector<int32_t> d;
+    for (int32_t j : v) { d.push_back(lev[(size_t)j]); todo[(size_t)j] = 0; }
+    comp.push_back(std::move(v));
+    depth.push_back(std::move(d));
+  }
+  if (comp.empty() || comp.size() > 3) return false;
+  // cut every component into `parts`; label: block of each row (-1: border)
+  auto cut = [&](int parts, std::vector<int32_t>& label, std::vector<int>& sizes) {
+    label.assign((size_t)n_s, -1);
+    sizes.clear();
+    std::vector<char> in(diag);
+    for (size_t c = 0; c < comp.size(); ++c) {
+      const auto &v = comp[c], &d = depth[c];
+      for (int k = 1; k < parts; ++k) {
+        // the level that holds the k-th quantile; its nodes next to the level after
+        const int L = d[v.size() * (size_t)k / (size_t)parts];
+        for (size_t t = 0; t < v.size(); ++t) {
+          if (d[t] != L) continue;
+          for (int32_t e = ptr[(size_t)v[t]]; e < ptr[(size_t)v[t] + 1]; ++e)
+            if (diag[(size_t)adj[(size_t)e]] && lev[(size_t)adj[(size_t)e]] == L + 1) {
+              in[(size_t)v[t]] = 0;
+              break;
+            }
+        }
+      }
+    }
+    for (const auto& v : comp)
+      for (int32_t i : v) {
+        if (!in[(size_t)i] || label[(size_t)i] >= 0) continue;
+        std::vector<int32_t> q(1, i);
+        const int32_t id = (int32_t)sizes.size();
+        label[(size_t)i] = id;
+        for (size_t k = 0; k < q.size(); ++k)
+          for (int32_t e = ptr[(size_t)q[k]]; e < ptr[(size_t)q[k] + 1]; ++e) {
+            const int32_t j = adj[(size_t)e];
+            if (!in[(size_t)j] || label[(size_t)j] >= 0) continue;
+            label[(size_t)j] = id;
+            q.push_back(j);
+          }
+        sizes.push_back((int)q.size());
+      }
+  };
+  std::vector<int32_t> label, best_label;
+  std::vector<int> sizes, best_sizes;
+  int64_t best = INT64_MAX;
+  for (int parts = 1; parts <= 4; ++parts) {
+    cut(parts, label, sizes);
+    if (sizes.empty() || sizes.size() > (size_t)kCcMax) continue;
+    int64_t nv = 0, mx = 0;
+    for (int n : sizes) { nv += n; mx = std::max<int64_t>(mx, n); }
+    if (mx + n_s - nv < best) {
+      best = mx + n_s - nv;
+      best_label = label;
+      best_sizes = sizes;
+    }
+  }
+  if (best_sizes.size() < 2) return false;
+  S.nc = (int)best_sizes.size();
   for (int c = 0; c < S.nc; ++c) {
     S.off[c] = (int)S.order.size();
     for (int32_t i = 0; i < n_s; ++i)
-      if (vel[(size_t)i] && find(i) == root[(size_t)c]) S.order.push_back(i);
+      if (best_label[(size_t)i] == c) S.order.push_back(i);
     S.n[c] = (int)S.order.size() - S.off[c];
-    if (S.n[c] > 4096) return false;
   }
   S.n_v = (int)S.order.size();
   for (int32_t i = 0; i < n_s; ++i)
-    if (!vel[(size_t)i]) S.order.push_back(i);
+    if (best_label[(size_t)i] < 0) S.order.push_back(i);
   S.n_p = n_s - S.n_v;
   if (S.n_p < 1) return false;
   S.where.assign((size_t)n_s, 0);
   for (int32_t e = 0; e < n_s; ++e) S.where[(size_t)S.order[(size_t)e]] = e;
-  // counting sort of B's entries by (pressure column, component)
+  // counting sort of B's entries by (border column, block)
   S.bptr.assign((size_t)S.n_p * S.nc + 1, 0);
   for (int pass = 0; pass < 2; ++pass) {
     std::vector<int32_t> at(S.bptr.begin(), S.bptr.end());
@@ -1314,7 +1399,7 @@ static bool component_structure(const int32_t* rp, const int32_t* col, const dou
             S.bptr[(size_t)m * S.nc + c + 1]++;
           } else {
             const int32_t k = at[(size_t)m * S.nc + c]++;
-            S.bi[(size_t)k] = i;
+            S.bi[(size_t)k] = S.off[c] + i;
             S.bq[(size_t)k] = q;
           }
         }
@@ -1325,6 +1410,20 @@ static bool component_structure(const int32_t* rp, const int32_t* col, const dou
       S.bq.resize((size_t)S.bptr.back());
     }
   }
+  // C's entries by (border row, block)
+  S.cptr.assign(1, 0);
+  for (int m = 0; m < S.n_p; ++m) {
+    const int32_t row = row_off + S.order[(size_t)(S.n_v + m)];
+    for (int c = 0; c < S.nc; ++c) {
+      for (int32_t q = rp[row]; q < rp[row + 1]; ++q) {
+        const int i = S.where[(size_t)(col[q] - row_off)] - S.off[c];
+        if (i < 0 || i >= S.n[c]) continue;
+        S.ci.push_back(i);
+        S.cq.push_back(q);
+      }
+      S.cptr.push_back((int32_t)S.ci.size());
+    }
+  }
   return true;
 }
 
@@ -1332,19 +1431,17 @@ static bool component_structure(const int32_t* rp, const int32_t* col, const dou
 // whole-member set-up then leaves them out (inv_off = -2).
 static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& split,
                                   const std::vector<bool>& has_split) {
-  struct Slot { size_t group, slot; };
-  struct Member { int g; CompStruct S; Slot at[4][kCcMax + 1]; };
+  struct Member { int g; CompStruct S; int at[4][kCcMax + 1]; };
   std::vector<Member> mem;
-  auto slot_of = [](std::vector<CoarseGroup>& groups, int64_t order) -> Slot {
-    size_t k = 0;
-    while (k < groups.size() && groups[k].n0 != order) ++k;
-    if (k == groups.size()) {
-      groups.emplace_back();
-      groups[k].n0 = order;
-      groups[k].kron = true;
-    }
-    groups[k].lev.push_back(0);
-    return {k, groups[k].lev.size() - 1};
+  // one group for all the blocks, one for all the Schur complements, each
+  // padded with the identity to the largest order: the chains are bound by
+  // their sequence of launches, which all blocks then share
+  std::vector<CoarseDesc> desc[2];
+  auto slot_of = [&](int kind, int64_t order) {
+    CoarseDesc d{};
+    d.n_s = (int32_t)order;
+    desc[kind].push_back(d);
+    return (int)desc[kind].size() - 1;
   };
   for (int g = 0; g < ctx->n_levels; ++g) {
     if (!has_split[(size_t)g]) continue;
@@ -1370,8 +1467,8 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
         R.first[p] = T.first[p];
         R.al[p] = T.t[p][0];
         R.be[p] = T.sz[p] == 2 ? T.t[p][1] : 0.0;
-        for (int k = 0; k < R.nc; ++k) M.at[p][k] = slot_of(ctx->vgroups, 2 * (int64_t)R.n[k]);
-        M.at[p][kCcMax] = slot_of(ctx->sgroups, 2 * (int64_t)R.n_p);
+        for (int k = 0; k < R.nc; ++k) M.at[p][k] = slot_of(0, 2 * (int64_t)R.n[k]);
+        M.at[p][kCcMax] = slot_of(1, 2 * (int64_t)R.n_p);
       }
       c.inv_off = -2;
       ctx->h_cc[g].push_back(R);
@@ -1379,12 +1476,15 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     }
   }
   if (mem.empty()) return STV_OK;
-  for (auto* groups : {&ctx->vgroups, &ctx->sgroups})
-    for (CoarseGroup& G : *groups) {
-      CoarseDesc d{};
-      d.n_s = (int32_t)G.n0;
-      STV_TRY(alloc_group(ctx, G, std::vector<CoarseDesc>(G.lev.size(), d), 3));
-    }
+  for (int kind = 0; kind < 2; ++kind) {
+    auto& groups = kind ? ctx->sgroups : ctx->vgroups;
+    groups.emplace_back();
+    CoarseGroup& G = groups.back();
+    G.kron = true;
+    G.lev.assign(desc[kind].size(), 0);
+    for (const CoarseDesc& d : desc[kind]) G.n0 = std::max<int64_t>(G.n0, d.n_s);
+    STV_TRY(alloc_group(ctx, G, desc[kind], 3));
+  }
   auto keep = [&](auto** p, size_t n) -> int {
     STV_TRY(dalloc(ctx, p, n));
     ctx->cc_bufs.push_back((void*)*p);
@@ -1397,6 +1497,11 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     *p = q;
     return STV_OK;
   };
+  for (int g = 0; g < ctx->n_levels; ++g) {
+    double flops = 0.0;   // of forming P on this level
+    for (const CompCoarse& R : ctx->h_cc[g]) flops += 8.0 * R.nblk * R.n_p * R.n_p * R.n_v;
+    ctx->cc_dims[g].form_p = flops <= 2e9;
+  }
   std::vector<size_t> next((size_t)ctx->n_levels, 0);
   for (const Member& M : mem) {
     CompCoarse& R = ctx->h_cc[M.g][next[(size_t)M.g]++];
@@ -1405,28 +1510,31 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     STV_TRY(keep_copy(&R.bptr, M.S.bptr));
     STV_TRY(keep_copy(&R.bi, M.S.bi));
     STV_TRY(keep_copy(&R.bq, M.S.bq));
+    STV_TRY(keep_copy(&R.cptr, M.S.cptr));
+    STV_TRY(keep_copy(&R.ci, M.S.ci));
+    STV_TRY(keep_copy(&R.cq, M.S.cq));
     const size_t nv = (size_t)R.n_v, np = (size_t)R.n_p;
     unsigned long long* norm = nullptr;
     STV_TRY(keep(&norm, 4 * (kCcMax + 1) * 2));
     R.norm = reinterpret_cast<unsigned long long(*)[kCcMax + 1][2]>(norm);
-    STV_TRY(keep(&R.pw, (size_t)R.nblk * np));
+    STV_TRY(keep(&R.pw, (size_t)2 * R.nblk * np));
     for (int p = 0; p < R.nblk; ++p) {
       for (int c = 0; c <= kCcMax; ++c) {
         if (c < kCcMax && c >= R.nc) continue;
-        const Slot& at = M.at[p][c];
-        const CoarseGroup& G = (c == kCcMax ? ctx->sgroups : ctx->vgroups)[at.group];
-        R.A[p][c] = G.w.A + (int64_t)at.slot * G.w.sA;
-        R.rpiv[p][c] = G.w.rpiv + (int64_t)at.slot * G.w.sV;
+        const CoarseGroup& G = (c == kCcMax ? ctx->sgroups : ctx->vgroups)[0];
+        R.A[p][c] = G.w.A + (int64_t)M.at[p][c] * G.w.sA;
+        R.rpiv[p][c] = G.w.rpiv + (int64_t)M.at[p][c] * G.w.sV;
         R.lda[c] = G.np;
         if (c < kCcMax) STV_TRY(keep(&R.Vi[p][c], (size_t)R.n[c] * R.n[c]));
       }
       STV_TRY(keep(&R.Si[p], np * np));
       STV_TRY(keep(&R.Z[p], np * nv));
       STV_TRY(keep(&R.G[p], nv * np));
-      STV_TRY(keep(&R.P[p], np * (nv + np)));
+      if (ctx->cc_dims[M.g].form_p) STV_TRY(keep(&R.P[p], np * (nv + np)));
     }
     CcDims& D = ctx->cc_dims[M.g];
     for (int c = 0; c < R.nc; ++c) D.n = std::max(D.n, (unsigned)R.n[c]);
+    D.nc = std::max(D.nc, (unsigned)R.nc);
     D.n_p = std::max(D.n_p, (unsigned)R.n_p);
     D.n_s = std::max(D.n_s, (unsigned)(R.n_v + R.n_p));
     D.blk = std::max(D.blk, (unsigned)R.nblk);
@@ -1442,12 +1550,8 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     for (int p = 0; p < nblk; ++p)
       for (int c = 0; c <= kCcMax; ++c) {
         if (c < kCcMax && c >= M.S.nc) continue;
-        int base = 0;
-        if (c == kCcMax)
-          for (const CoarseGroup& G : ctx->vgroups) base += (int)G.lev.size();
-        const auto& groups = c == kCcMax ? ctx->sgroups : ctx->vgroups;
-        for (size_t k = 0; k < M.at[p][c].group; ++k) base += (int)groups[k].lev.size();
-        v[(size_t)(p * (kCcMax + 1) + c)] = base + (int)M.at[p][c].slot;
+        const int base = c == kCcMax ? (int)ctx->vgroups[0].lev.size() : 0;
+        v[(size_t)(p * (kCcMax + 1) + c)] = base + M.at[p][c];
       }
     ctx->cc_slots.emplace_back(M.g, v);
   }

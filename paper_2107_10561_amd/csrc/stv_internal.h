@@ -210,20 +210,20 @@ struct KronCoarse {
   double V[16], W[16];
 };
 
-// A coarse member whose velocity components do not couple, time-decoupled
-// (k_coarse.hip).  Its n_s spatial rows in member order (`order`: component
-// 0 .. nc - 1, then the rows without a diagonal entry; `where` the inverse),
-// the columns of B listed by pressure column and component (bptr, local row
-// bi, block bq), and per time block p: the eliminated real forms A (component
-// c, or kCcMax: the Schur complement) with pivot records and verdicts, the
+// A coarse member of uncoupled blocks and a border, time-decoupled
+// (k_coarse.hip).  Its n_s spatial rows in member order (`order`: block
+// 0 .. nc - 1, then the border; `where` the inverse), the columns of B listed
+// by border column and block (bptr, member row bi, entry bq), the rows of C by
+// border row and block (cptr, local column ci, entry cq), and per time
+// block p: the eliminated real forms A (block c, or kCcMax: the Schur
+// complement) with pivot records and verdicts, the
 // inverses Vi, Si and the factors Z, G, P of the solve; norm: largest entry of
 // each block and of its inverse (bit patterns).
-constexpr int kCcMax = 3;
+constexpr int kCcMax = 12;
 struct CompCoarse {
   const int32_t *rowptr, *col;
   const double* ma;
-  const int32_t *order, *where, *bptr, *bi;
-  const int32_t* bq;
+  const int32_t *order, *where, *bptr, *bi, *bq, *cptr, *ci, *cq;
   int32_t row_off, nc, n_v, n_p, nblk;
   int32_t n[kCcMax], off[kCcMax];
   int sz[4], first[4];
@@ -237,9 +237,16 @@ struct CompCoarse {
   double2 *Si[4], *Z[4], *G[4], *P[4];
   double2* pw;
 };
-// launch dimensions over the members of one level: largest component,
-// pressure and whole order, time blocks, members
-struct CcDims { unsigned n = 0, n_p = 0, n_s = 0, blk = 0, cnt = 0; };
+// launch dimensions over the members of one level: largest block, border and
+// whole order, blocks, time blocks, members
+// form_p: P is formed, not applied in two launches.  A solve of some 10 to 20
+// cycles pays 4 to 5 us per cycle for the third launch; forming P runs at
+// about 20 TFLOP/s beside the build, so the line is at 2 GFLOP (2d 16x4 coarse
+// cells: 23 us formed; 3d 12x3x3: 550 us formed, 45 us of launches).
+struct CcDims {
+  unsigned n = 0, n_p = 0, n_s = 0, nc = 0, blk = 0, cnt = 0;
+  bool form_p = false;
+};
 
 // The coarse members of one order, eliminated by one batched Gauss-Jordan:
 // members (packed level, index in that level), their device descriptors,
