@@ -137,7 +137,10 @@ __device__ __forceinline__ void gj_rows(double (&re)[NC], double (&im)[CX ? NC :
   }
 }
 
-// Inverses of one time block of every cell, one wavefront per cell: X_c =
+// Inverses of one time block of every cell, one wavefront per cell (four
+// independent ones per workgroup, so that a workgroup that ends leaves a whole
+// slot on every SIMD of its compute unit for the coarse chain's workgroups that
+// run beside; single wavefronts left the chain waiting and needed a cap): X_c =
 // (t00 M + A) + i t10 M (real blocks: t00 M + A) of component c, bordered by
 // the B columns and C rows of the components that share it (all of them where
 // V_c is the same, else its own): lane = row (n velocity rows, D m border
@@ -148,7 +151,7 @@ __device__ __forceinline__ void gj_rows(double (&re)[NC], double (&im)[CX ? NC :
 // COMP (3d): written as the component store of k_vanka_comp; else as the
 // time-decoupled rows of k_vanka_dec.
 template <int D, bool CX, bool COMP>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ ma,
                const uint8_t* __restrict__ flags, const int32_t* __restrict__ own_ptr,
                const uint8_t* __restrict__ own_loc, const int64_t* __restrict__ inv_off, int ld,
@@ -158,19 +161,31 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
   constexpr int NV = D == 2 ? 9 : 27, NM = D + 1, NLS = D * NV + NM;
   constexpr int NB = D * NM, NC = NV + NB;
   static_assert(NC <= 64, "one row per lane");
-  __shared__ double2 zb[NB][NV];          // border rows: -C_c V_c^-1
-  __shared__ double2 corner[NB][NM];      // -C_c V_c^-1 B_c
-  __shared__ double2 sinv[NM][NM];
-  __shared__ int rowof[NV];               // stored node row of each node (COMP)
-  __shared__ double2 vinv[COMP ? 1 : D][COMP ? 1 : NV][COMP ? 1 : NV];
-  __shared__ double2 gneg[COMP ? 1 : NV][COMP ? 1 : NB];
-  __shared__ double2 prow[COMP ? 1 : NM][COMP ? 1 : NLS];
-  const int lane = threadIdx.x;
+  struct Wave {
+    double2 zb[NB][NV];          // border rows: -C_c V_c^-1
+    double2 corner[NB][NM];      // -C_c V_c^-1 B_c
+    double2 sinv[NM][NM];
+    int rowof[NV];               // stored node row of each node (COMP)
+    double2 vinv[COMP ? 1 : D][COMP ? 1 : NV][COMP ? 1 : NV];
+    double2 gneg[COMP ? 1 : NV][COMP ? 1 : NB];
+    double2 prow[COMP ? 1 : NM][COMP ? 1 : NLS];
+  };
+  __shared__ Wave waves[4];
+  const int lane = threadIdx.x & 63;
+  Wave& sh = waves[threadIdx.x >> 6];
+  auto& zb = sh.zb;
+  auto& corner = sh.corner;
+  auto& sinv = sh.sinv;
+  auto& rowof = sh.rowof;
+  auto& vinv = sh.vinv;
+  auto& gneg = sh.gneg;
+  auto& prow = sh.prow;
   auto put = [&](int64_t e, double v) {
     if (fp32) ((float*)store)[e] = (float)v;
     else ((double*)store)[e] = v;
   };
-  for (int T = blockIdx.x; T < n_cells; T += gridDim.x) {
+  const int T0 = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  for (int T = T0; T < n_cells; T += gridDim.x * 4) {
     const int32_t* pos = posmap + (int64_t)T * (NLS * NLS);
     const bool same = flags[T] & 1;
     bool sing = false;
@@ -192,21 +207,48 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
       const int bb = lane - NV, bc = bb / NM, bm = bb - bc * NM;
       const bool vel = lane < NV, bor = lane >= NV && lane < NC && (same || bc == c0);
       double re[NC], im[CX ? NC : 1];
+      // the row's entries, a sixth of them in flight at a time: the block
+      // positions (those of no entry of this row replaced by the first), then
+      // the values, chosen afterwards (the empty asm statements keep the
+      // compiler from turning each choice into a branch around its load)
+      constexpr int NG = 6, GC = (NC + NG - 1) / NG;
 #pragma unroll
-      for (int j = 0; j < NC; ++j) {
-        int at = -1;
-        if (j < NV) {
-          if (vel) at = (c0 * NV + lane) * NLS + c0 * NV + j;
-          else if (bor) at = (D * NV + bm) * NLS + bc * NV + j;
-        } else {
-          constexpr int nm = NM;
-          const int jc = (j - NV) / nm, jm = (j - NV) - jc * nm;
-          if (vel && (same || jc == c0)) at = (jc * NV + lane) * NLS + D * NV + jm;
+      for (int g = 0; g < NG; ++g) {
+        int32_t q[GC];
+        unsigned hv = 0;
+#pragma unroll
+        for (int k = 0; k < GC; ++k) {
+          const int j = g * GC + k;
+          if (j >= NC) continue;
+          int at;
+          bool have;
+          if (j < NV) {
+            at = vel ? (c0 * NV + lane) * NLS + c0 * NV + j : (D * NV + bm) * NLS + bc * NV + j;
+            have = vel || bor;
+          } else {
+            const int jc = (j - NV) / NM, jm = (j - NV) - jc * NM;
+            at = (jc * NV + lane) * NLS + D * NV + jm;
+            have = vel && (same || jc == c0);
+          }
+          q[k] = pos[have ? at : 0];
+          hv |= have ? 1u << k : 0u;
         }
-        const int32_t q = at >= 0 ? pos[at] : -1;
-        const double2 f = q >= 0 ? ma[q] : make_double2(0.0, 0.0);
-        re[j] = fma(t00, f.x, f.y);
-        if constexpr (CX) im[j] = t10 * f.x;
+        double2 f[GC];
+#pragma unroll
+        for (int k = 0; k < GC; ++k) {
+          if (g * GC + k >= NC) continue;
+          asm volatile("" : "+v"(q[k]));
+          if (!((hv >> k) & 1u)) q[k] = -1;
+          f[k] = ma[max(q[k], 0)];
+        }
+#pragma unroll
+        for (int k = 0; k < GC; ++k) {
+          const int j = g * GC + k;
+          if (j >= NC) continue;
+          asm volatile("" : "+v"(f[k].x), "+v"(f[k].y));
+          re[j] = q[k] >= 0 ? fma(t00, f[k].x, f[k].y) : 0.0;
+          if constexpr (CX) im[j] = q[k] >= 0 ? t10 * f[k].x : 0.0;
+        }
       }
       double big = 0.0;
 #pragma unroll
@@ -346,23 +388,11 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
   }
 }
 
-template <typename K>
-static int grid_leaving(K f, int n_cells, int n_cu, int reserve) {
-  if (n_cu <= 0 || reserve <= 0) return n_cells;
-  hipFuncAttributes a{};
-  if (hipFuncGetAttributes(&a, reinterpret_cast<const void*>(f)) != hipSuccess) return n_cells;
-  const int regs = (a.numRegs + 7) / 8 * 8;
-  if (regs <= 0 || regs > 512 - reserve) return n_cells;
-  return std::min(n_cells, n_cu * 4 * std::min(8, (512 - reserve) / regs));
-}
-
-hipError_t launch_inverse_comp(hipStream_t s, const DevLevel& L, int fp32, uint8_t* status,
-                               int n_cu, int reserve) {
+hipError_t launch_inverse_comp(hipStream_t s, const DevLevel& L, int fp32, uint8_t* status) {
   const double2* ma = (const double2*)L.kron_ma;
 #define STV_COMP(DD, CXX, ST, t0, t1, off, acc)                                               \
   {                                                                                          \
-    const int g = grid_leaving(k_inverse_comp<DD, CXX, ST>, L.n_cells, n_cu, reserve);       \
-    k_inverse_comp<DD, CXX, ST><<<g, 64, 0, s>>>(                                            \
+    k_inverse_comp<DD, CXX, ST><<<(L.n_cells + 3) / 4, 256, 0, s>>>(                         \
         L.posmap, ma, L.comp_flags, L.own_ptr, L.own_loc, L.inv_off, L.inv_ld, L.comp_cell,  \
         L.comp_node, L.inv_store, fp32, status, L.n_cells, t0, t1, off, acc);                \
   }

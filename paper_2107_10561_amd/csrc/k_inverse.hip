@@ -1067,7 +1067,7 @@ static hipError_t inv_mfma(hipStream_t s, const DevLevel& L, int fp32, int full,
 hipError_t launch_cell_inverses(hipStream_t s, int b, const DevLevel& L, int fp32, int full,
                                 uint8_t* status, double* gscratch, int n_slots, int n_cu,
                                 int reserve, int cu_cap) {
-  if (L.comp) return launch_inverse_comp(s, L, fp32, status, n_cu, reserve);
+  if (L.comp) return launch_inverse_comp(s, L, fp32, status);
   if (L.cx) {
     // the complex decoupled build of a 3d dG(1) level: four wavefronts of
     // up to 512 registers per cell, one cell per compute unit at a time;
