@@ -382,6 +382,9 @@ struct stv_ctx {
   double* scal = nullptr;       // device scalars
   double* hscal = nullptr;      // pinned host mirror
   double* hstep = nullptr;      // pinned: the coefficients of the next Arnoldi step (look-ahead)
+  char* slab = nullptr;         // the levels' lists and vectors
+  char* ring = nullptr;         // pinned: staging of large uploads
+  hipEvent_t ring_ev[8] = {};
   int ws_restart = 0;
   int64_t ws_n = 0;
   // timing
