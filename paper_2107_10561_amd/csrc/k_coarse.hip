@@ -1,6 +1,6 @@
 // The direct coarse solve of a member whose spatial rows fall into uncoupled
-// blocks and a border (spatial factors, time-decoupled): one time block of the
-// coarse operator is
+// blocks and a border.  With spatial factors (time-decoupled) one time block of
+// the coarse operator, without them the whole matrix of scalar rows, is
 //   [ V  B ]   V = blockdiag(V_1 .. V_nc): the velocity components, each cut
 //   [ C  D ]   into parts by separators; border: the separators and the rows
 //              without a diagonal entry (the pressure).
@@ -12,7 +12,8 @@
 // The chains are bound by their panels in sequence, 16 complex pivots each: in
 // 3d (16x3x3 cells) 32 for nine blocks of order 506 and 55 for a border of 870
 // instead of 340 for the whole matrix of order 5,427 (138 for the components
-// uncut), with fewer operations and 178 instead of 471 MB per apply.  All
+// uncut), with fewer operations and 178 instead of 471 MB per apply; in 3d
+// without factors (8x2x2 cells, order 2806) 55 instead of 176.  All
 // matrices here are complex, row-major, in the member's order (blocks one
 // after the other, then the border); entry x of a real form is
 // [[Re, -Im], [Im, Re]].
@@ -437,6 +438,48 @@ __global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict
   }
 }
 
+__global__ void __launch_bounds__(256) k_block_nonzero(const double* __restrict__ val, int b2,
+                                                       int64_t nnzb, uint8_t* __restrict__ nz) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (q >= nnzb) return;
+  bool any = false;
+  for (int e = 0; e < b2; ++e) any |= val[q * b2 + e] != 0.0;   // a NaN counts
+  nz[q] = any;
+}
+
+hipError_t launch_block_nonzero(hipStream_t s, int b, const double* val, int64_t nnzb, uint8_t* nz) {
+  k_block_nonzero<<<(unsigned)((nnzb + 255) / 256), 256, 0, s>>>(val, b * b, nnzb, nz);
+  return hipGetLastError();
+}
+
+__global__ void __launch_bounds__(64) k_expand_blocks(int b, int32_t n_s,
+                                                      const int32_t* __restrict__ ptr,
+                                                      const int32_t* __restrict__ bcol,
+                                                      const int32_t* __restrict__ src,
+                                                      const double* __restrict__ val,
+                                                      int32_t* __restrict__ rowptr,
+                                                      int32_t* __restrict__ col,
+                                                      double2* __restrict__ ma) {
+  const int32_t r = blockIdx.x, first = ptr[r];
+  const int len = (ptr[r + 1] - first) * b;
+  const int64_t base = (int64_t)first * b * b;
+  for (int t = threadIdx.x; t < len * b; t += 64) {
+    const int l = t / len, k = (t % len) / b, j = t % len % b;
+    col[base + t] = bcol[first + k] * b + j;
+    ma[base + t] = make_double2(0.0, val[(int64_t)src[first + k] * b * b + l * b + j]);
+  }
+  if ((int)threadIdx.x < b) rowptr[r * b + threadIdx.x] = (int32_t)(base + threadIdx.x * len);
+  if (r == n_s - 1 && threadIdx.x == 0) rowptr[n_s * b] = (int32_t)(base + b * len);
+}
+
+hipError_t launch_expand_blocks(hipStream_t s, int b, int32_t n_s, const int32_t* ptr,
+                                const int32_t* bcol, const int32_t* src, const double* val,
+                                int32_t* rowptr, int32_t* col, double* ma) {
+  k_expand_blocks<<<(unsigned)n_s, 64, 0, s>>>(b, n_s, ptr, bcol, src, val, rowptr, col,
+                                               reinterpret_cast<double2*>(ma));
+  return hipGetLastError();
+}
+
 hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
   k_cc_fill<<<dim3(D.n_s, D.blk, D.cnt), 64, 0, s>>>(cc);
   return hipGetLastError();
@@ -471,7 +514,7 @@ hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
   return hipGetLastError();
 }
 
-hipError_t launch_cc_solve(hipStream_t s, int b, const CompCoarse* cc, const CcDims& D,
+hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D,
                            const double* r, double* d) {
   const dim3 gp(D.n_p, D.blk, D.cnt), gu((D.n_s + 3) / 4, 1, D.cnt), block(256);
 #define STV_CC(B)                                                       \
@@ -480,7 +523,7 @@ hipError_t launch_cc_solve(hipStream_t s, int b, const CompCoarse* cc, const CcD
     if (!D.form_p) launch(k_cc_solve_s, gp, block, 0, s, cc);           \
     launch(k_cc_solve_u<B>, gu, block, 0, s, cc, r, d);                 \
     break;
-  switch (b) {
+  switch (D.b) {
     STV_CC(1) STV_CC(2) STV_CC(3) STV_CC(4)
     default: return hipErrorInvalidValue;
   }

@@ -586,7 +586,7 @@ int coarse_apply(stv_ctx* ctx, int g, const double* r, double* d) {
   if (nw == 0 && nk == 0 && nc == 0) return STV_OK;
   Timed t(ctx, KC_COARSE, g, nullptr, nc == 0);
   if (nc > 0)   // made for the forward direction only
-    STV_HIP(launch_cc_solve(ctx->stream, ctx->b, ctx->d_cc[g], ctx->cc_dims[g], r, d));
+    STV_HIP(launch_cc_solve(ctx->stream, ctx->d_cc[g], ctx->cc_dims[g], r, d));
   if (nw > 0 && ctx->transposed)
     STV_HIP(launch_dense_gemv_t(ctx->stream, ctx->d_coarse[g], nw, ctx->b, ctx->coarse_max_n0[g],
                                 ctx->coarse_inv, r, d));
@@ -1448,7 +1448,8 @@ static int alloc_group(stv_ctx* ctx, CoarseGroup& G, const std::vector<CoarseDes
   return STV_OK;
 }
 
-// The block structure of a coarse member's rows, read off the nonzero factors:
+// The block structure of a coarse member's rows, read off the nonzero factors
+// (ma; null: every listed block counts):
 // uncoupled blocks first, then the border.  The border takes the rows without
 // a diagonal entry (the pressure); what remains falls into connected
 // components (the velocity components), and each is cut into up to four parts
@@ -1460,7 +1461,7 @@ static int alloc_group(stv_ctx* ctx, CoarseGroup& G, const std::vector<CoarseDes
 // two blocks.  B's entries are listed by border column and block, C's by border
 // row and block.
 struct CompStruct {
-  int nc = 0, n_v = 0, n_p = 0;
+  int nc = 0, n_v = 0, n_p = 0, n_bare = 0;   // n_bare: rows without a diagonal entry
   int n[kCcMax] = {}, off[kCcMax] = {};
   std::vector<int32_t> order, where, bptr, bi, bq, cptr, ci, cq;
 };
@@ -1476,7 +1477,7 @@ static bool component_structure(const int32_t* rp, const int32_t* col, const dou
       for (int64_t q = rp[row_off + i]; q < rp[row_off + i + 1]; ++q) {
         const int32_t j = col[q] - row_off;
         if (j < 0 || j >= n_s) return false;
-        if (ma[2 * q] == 0.0 && ma[2 * q + 1] == 0.0) continue;
+        if (ma && ma[2 * q] == 0.0 && ma[2 * q + 1] == 0.0) continue;
         if (j == i) { diag[(size_t)i] = 1; continue; }
         if (pass == 0) {
           ++ptr[(size_t)i + 1];
@@ -1583,6 +1584,7 @@ static bool component_structure(const int32_t* rp, const int32_t* col, const dou
     if (best_label[(size_t)i] < 0) S.order.push_back(i);
   S.n_p = n_s - S.n_v;
   if (S.n_p < 1) return false;
+  S.n_bare = (int)std::count(diag.begin(), diag.end(), char(0));
   S.where.assign((size_t)n_s, 0);
   for (int32_t e = 0; e < n_s; ++e) S.where[(size_t)S.order[(size_t)e]] = e;
   // counting sort of B's entries by (border column, block)
@@ -1627,6 +1629,104 @@ static bool component_structure(const int32_t* rp, const int32_t* col, const dou
   return true;
 }
 
+// The nonzero blocks of a level's coarse members: rows [ptr[s], ptr[s+1]) of
+// all the level's rows (those of other members stay empty), their columns and
+// where they stand among the level's blocks.
+struct NzBlocks { std::vector<int32_t> ptr, col, src; };
+
+static int nonzero_blocks(stv_ctx* ctx, int g, NzBlocks& Z) {
+  const DevLevel& L = ctx->lv[g];
+  std::vector<int32_t> rp((size_t)L.n_s + 1), col((size_t)L.nnzb);
+  std::vector<uint8_t> nz((size_t)L.nnzb);
+  uint8_t* dev = nullptr;
+  STV_TRY(dalloc(ctx, &dev, nz.size()));
+  hipError_t e = launch_block_nonzero(ctx->stream, ctx->b, L.val, L.nnzb, dev);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e == hipSuccess) e = hipMemcpy(nz.data(), dev, nz.size(), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemcpy(rp.data(), L.rowptr, 4 * rp.size(), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemcpy(col.data(), L.col, 4 * col.size(), hipMemcpyDeviceToHost);
+  dfree(dev);
+  STV_HIP(e);
+  Z.ptr.assign((size_t)L.n_s + 1, 0);
+  std::vector<char> in((size_t)L.n_s, 0);
+  for (const CoarseDesc& c : ctx->h_coarse[g])
+    std::fill(in.begin() + c.row_off, in.begin() + c.row_off + c.n_s, 1);
+  for (int32_t r = 0; r < L.n_s; ++r) {
+    for (int32_t q = rp[(size_t)r]; in[(size_t)r] && q < rp[(size_t)r + 1]; ++q)
+      if (nz[(size_t)q]) {
+        Z.col.push_back(col[(size_t)q]);
+        Z.src.push_back(q);
+      }
+    Z.ptr[(size_t)r + 1] = (int32_t)Z.col.size();
+  }
+  return STV_OK;
+}
+
+// The same structure for b x b blocks taken as scalars: row r of the blocks
+// becomes rows r b + l, whose entries are those of launch_expand_blocks.
+static void expand_structure(CompStruct& S, int b, int32_t row_off, const NzBlocks& Z) {
+  CompStruct E;
+  E.nc = S.nc;
+  E.n_v = S.n_v * b;
+  E.n_p = S.n_p * b;
+  for (int c = 0; c < S.nc; ++c) { E.n[c] = S.n[c] * b; E.off[c] = S.off[c] * b; }
+  const size_t ns = S.order.size();
+  E.order.resize(ns * b);
+  E.where.resize(ns * b);
+  for (size_t e = 0; e < ns; ++e)
+    for (int l = 0; l < b; ++l) {
+      E.order[e * b + l] = S.order[e] * b + l;
+      E.where[e * b + l] = S.where[e] * b + l;
+    }
+  // entry (l, j) of the q-th nonzero block, in the row of order index e
+  auto entry = [&](int32_t e, int32_t q, int l, int j) {
+    const size_t r = (size_t)row_off + (size_t)S.order[(size_t)e];
+    const int32_t first = Z.ptr[r], len = (Z.ptr[r + 1] - first) * b;
+    return first * b * b + l * len + (q - first) * b + j;
+  };
+  E.bptr.assign(1, 0);
+  for (int m = 0; m < S.n_p; ++m)
+    for (int j = 0; j < b; ++j)
+      for (int c = 0; c < S.nc; ++c) {
+        const size_t k = (size_t)m * S.nc + c;
+        for (int32_t t = S.bptr[k]; t < S.bptr[k + 1]; ++t)
+          for (int l = 0; l < b; ++l) {
+            E.bi.push_back(S.bi[(size_t)t] * b + l);
+            E.bq.push_back(entry(S.bi[(size_t)t], S.bq[(size_t)t], l, j));
+          }
+        E.bptr.push_back((int32_t)E.bi.size());
+      }
+  E.cptr.assign(1, 0);
+  for (int m = 0; m < S.n_p; ++m)
+    for (int l = 0; l < b; ++l)
+      for (int c = 0; c < S.nc; ++c) {
+        const size_t k = (size_t)m * S.nc + c;
+        for (int32_t t = S.cptr[k]; t < S.cptr[k + 1]; ++t)
+          for (int j = 0; j < b; ++j) {
+            E.ci.push_back(S.ci[(size_t)t] * b + j);
+            E.cq.push_back(entry(S.n_v + m, S.cq[(size_t)t], l, j));
+          }
+        E.cptr.push_back((int32_t)E.ci.size());
+      }
+  S = std::move(E);
+}
+
+// Whether a member without factors is cut.  Some rows have no diagonal entry (a
+// block of a matrix with pressure-pressure entries can be singular up to a
+// constant, and the build would find that out late), and the real forms fit
+// the elimination.  The pivots left in sequence decide the rest, a chain of
+// these being slower per pivot than the whole matrix's (32 real columns for 16
+// pivots): at 0.29 of the order 8.9 -> 3.1 ms (2806), at 0.48 4.5 -> 2.2 ms
+// (1572), at 0.51 2.15 -> 1.70 ms (892), at 0.60 none (0.34 -> 0.46 ms at 124).
+// Below order 512 the 0.15 ms won are spent by the 3 us per apply of the
+// second launch within 50 cycles.
+static bool worth_cutting(const CompStruct& S, int32_t n_s, int b) {
+  int mx = 0;
+  for (int c = 0; c < S.nc; ++c) mx = std::max(mx, S.n[c]);
+  return S.n_bare > 0 && (int64_t)n_s * b > 512 && 20 * ((int64_t)mx + S.n_p) <= 11 * (int64_t)n_s &&
+         2 * (int64_t)std::max(mx, S.n_p) * b <= gj_plan(2, 3, true).max_n;
+}
+
 // Members with a component structure: descriptors, chains and buffers.  The
 // whole-member set-up then leaves them out (inv_off = -2).
 static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& split,
@@ -1643,22 +1743,67 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     desc[kind].push_back(d);
     return (int)desc[kind].size() - 1;
   };
+  auto keep = [&](auto** p, size_t n) -> int {
+    STV_TRY(dalloc(ctx, p, n));
+    ctx->cc_bufs.push_back((void*)*p);
+    return STV_OK;
+  };
   for (int g = 0; g < ctx->n_levels; ++g) {
     if (!has_split[(size_t)g]) continue;
     const DevLevel& L = ctx->lv[g];
-    std::vector<int32_t> rp((size_t)L.n_s + 1), col((size_t)L.nnzb);
-    std::vector<double> ma((size_t)2 * L.nnzb);
-    STV_HIP(hipMemcpy(rp.data(), L.rowptr, 4 * rp.size(), hipMemcpyDeviceToHost));
-    STV_HIP(hipMemcpy(col.data(), L.col, 4 * col.size(), hipMemcpyDeviceToHost));
-    STV_HIP(hipMemcpy(ma.data(), L.kron_ma, 8 * ma.size(), hipMemcpyDeviceToHost));
+    // with spatial factors each time block is a matrix over the spatial rows;
+    // without, the blocks' entries are one real matrix of n_s b scalar rows
+    const int b = L.kron_ma ? ctx->b : 1, sb = L.kron_ma ? 1 : ctx->b;
+    const int32_t *d_rp = L.rowptr, *d_col = L.col;
+    const double* d_ma = L.kron_ma;
+    NzBlocks Z;
+    std::vector<double> ma;
+    if (L.kron_ma) {
+      Z.ptr.resize((size_t)L.n_s + 1);
+      Z.col.resize((size_t)L.nnzb);
+      ma.resize((size_t)2 * L.nnzb);
+      STV_HIP(hipMemcpy(Z.ptr.data(), L.rowptr, 4 * Z.ptr.size(), hipMemcpyDeviceToHost));
+      STV_HIP(hipMemcpy(Z.col.data(), L.col, 4 * Z.col.size(), hipMemcpyDeviceToHost));
+      STV_HIP(hipMemcpy(ma.data(), L.kron_ma, 8 * ma.size(), hipMemcpyDeviceToHost));
+    } else {
+      STV_TRY(nonzero_blocks(ctx, g, Z));
+      if ((int64_t)Z.col.size() * sb * sb >= INT32_MAX) continue;
+    }
+    ctx->cc_dims[g].b = b;
     for (CoarseDesc& c : ctx->h_coarse[g]) {
       Member M{};
-      if (!component_structure(rp.data(), col.data(), ma.data(), c.row_off, c.n_s, M.S)) continue;
+      if (!component_structure(Z.ptr.data(), Z.col.data(), L.kron_ma ? ma.data() : nullptr,
+                               c.row_off, c.n_s, M.S))
+        continue;
+      if (!L.kron_ma) {
+        if (!worth_cutting(M.S, c.n_s, sb)) continue;
+        expand_structure(M.S, sb, c.row_off, Z);
+        if (d_ma == nullptr) {
+          int32_t *rp2 = nullptr, *col2 = nullptr, *src = nullptr;
+          double* ma2 = nullptr;
+          const size_t n = Z.col.size() * sb * sb;
+          STV_TRY(keep(&rp2, (size_t)L.n_s * sb + 1));
+          STV_TRY(keep(&col2, n));
+          STV_TRY(keep(&ma2, 2 * n));
+          int32_t *ptr = nullptr, *zcol = nullptr;
+          int rc = upload(ctx, &ptr, Z.ptr.data(), Z.ptr.size());
+          if (rc == STV_OK) rc = upload(ctx, &zcol, Z.col.data(), Z.col.size());
+          if (rc == STV_OK) rc = upload(ctx, &src, Z.src.data(), Z.src.size());
+          hipError_t e = hipSuccess;
+          if (rc == STV_OK)
+            e = launch_expand_blocks(ctx->stream, sb, L.n_s, ptr, zcol, src, L.val, rp2, col2, ma2);
+          if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+          dfree(ptr); dfree(zcol); dfree(src);
+          STV_TRY(rc);
+          STV_HIP(e);
+          d_rp = rp2; d_col = col2; d_ma = ma2;
+        }
+      }
       M.g = g;
       const TimeSplit& T = split[(size_t)g];
       CompCoarse R{};
-      R.rowptr = L.rowptr; R.col = L.col; R.ma = L.kron_ma;
-      R.row_off = c.row_off;
+      R.rowptr = d_rp; R.col = d_col; R.ma = d_ma;
+      R.row_off = c.row_off * sb;
       R.nc = M.S.nc; R.n_v = M.S.n_v; R.n_p = M.S.n_p; R.nblk = T.nblk;
       for (int e = 0; e < 16; ++e) { R.V[e] = T.V[e]; R.W[e] = T.W[e]; }
       for (int k = 0; k < R.nc; ++k) { R.n[k] = M.S.n[k]; R.off[k] = M.S.off[k]; }
@@ -1685,11 +1830,6 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     for (const CoarseDesc& d : desc[kind]) G.n0 = std::max<int64_t>(G.n0, d.n_s);
     STV_TRY(alloc_group(ctx, G, desc[kind], 3));
   }
-  auto keep = [&](auto** p, size_t n) -> int {
-    STV_TRY(dalloc(ctx, p, n));
-    ctx->cc_bufs.push_back((void*)*p);
-    return STV_OK;
-  };
   auto keep_copy = [&](const int32_t** p, const std::vector<int32_t>& v) -> int {
     int32_t* q = nullptr;
     STV_TRY(upload(ctx, &q, v.data(), v.size()));
@@ -1805,16 +1945,16 @@ static int make_coarse_groups(stv_ctx* ctx) {
   if (ctx->coarse_algo == 0 && !ctx->inv_full && !ctx->cc_off) {
     std::vector<TimeSplit> cs = split;
     std::vector<bool> has = has_split;
-    for (int g = 0; b == 1 && g < ctx->n_levels; ++g) {
-      // one time component: the block itself
+    for (int g = 0; g < ctx->n_levels; ++g) {
+      // no factors, or one time component: one real block
       const DevLevel& L = ctx->lv[g];
-      if (!L.kron_ma || ctx->h_coarse[g].empty() || L.kron_tw[0] == 0.0) continue;
+      if (ctx->h_coarse[g].empty() || (L.kron_ma && (b > 1 || L.kron_tw[0] == 0.0))) continue;
       TimeSplit& T = cs[(size_t)g];
       T.nblk = 1;
       T.sz[0] = 1;
-      T.t[0][0] = L.kron_C[0] / L.kron_tw[0];
+      T.t[0][0] = L.kron_ma ? L.kron_C[0] / L.kron_tw[0] : 0.0;
       T.V[0] = 1.0;
-      T.W[0] = 1.0 / L.kron_tw[0];
+      T.W[0] = L.kron_ma ? 1.0 / L.kron_tw[0] : 1.0;
       has[(size_t)g] = true;
     }
     STV_TRY(make_component_members(ctx, cs, has));

@@ -245,6 +245,7 @@ struct CompCoarse {
 // cells: 23 us formed; 3d 12x3x3: 550 us formed, 45 us of launches).
 struct CcDims {
   unsigned n = 0, n_p = 0, n_s = 0, nc = 0, blk = 0, cnt = 0;
+  int b = 0;   // time components of the rows
   bool form_p = false;
 };
 
@@ -484,10 +485,17 @@ hipError_t launch_kron_block_dense(hipStream_t s, const KronBlockDesc* kdesc, in
 hipError_t launch_kron_coarse_apply(hipStream_t s, int b, const KronCoarse* kc, int cnt,
                                     int max_blocks, int32_t max_ns, int transposed,
                                     const double* r, double* d);
+// nz[q] = 1 where block q has a nonzero entry
+hipError_t launch_block_nonzero(hipStream_t s, int b, const double* val, int64_t nnzb, uint8_t* nz);
+// The nonzero blocks (ptr, bcol; src: their place in val) as scalar rows: row
+// r b + l lists entry (l, j) of its blocks in order, j fastest, as (0, value).
+hipError_t launch_expand_blocks(hipStream_t s, int b, int32_t n_s, const int32_t* ptr,
+                                const int32_t* bcol, const int32_t* src, const double* val,
+                                int32_t* rowptr, int32_t* col, double* ma);
 hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D);
-hipError_t launch_cc_solve(hipStream_t s, int b, const CompCoarse* cc, const CcDims& D,
+hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D,
                            const double* r, double* d);
 // rinv = the inverse of every member's pivot record rpiv (order n, real
 // order n0 from desc); verdict[z] = 0 when member z's record is a

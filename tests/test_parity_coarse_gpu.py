@@ -223,3 +223,63 @@ def test_coarse_solve_by_component(stv, name, singular):
         log(f"[coarse] {name} singular={singular} relres {res:.2e} forward {fe:.2e} cond {cond:.1e}")
         assert res <= 1e-11 * max(1.0, 1e-8 * cond)
         assert fe <= 1e-15 * cond * 10
+
+
+# kinds of coarse matrices given as blocks only: the velocity components apart,
+# coupled (as in a Newton iteration), one node's velocity block singular, and a
+# pressure block on the diagonal (eliminated as a whole)
+@pytest.mark.parametrize("kind", ["apart", "coupled", "singular", "pressure"])
+@pytest.mark.parametrize("case", [(2, [(16, 4)], 1), (3, [(8, 2, 2)], 1), (2, [(18, 2)], 0),
+                                  (2, [(15, 3)], 2), (2, [(16, 4), (20, 2), (5, 3)], 1)])
+def test_coarse_solve_of_blocks_by_separators(stv, case, kind):
+    """Without spatial factors the coarse blocks are one real matrix, cut by
+    separators and reduced to the border.  Bounds as for the other schedules."""
+    import scipy.sparse as sp
+    dim, shapes, k = case
+    rng = np.random.default_rng(31)
+    hier, mats = [], []
+    for n in shapes:
+        p = make_problem(dim, n, 1, k, 0.01, 1e-3, 7)
+        L = p.levels[0]
+        val = np.array(L.val)
+        rows = np.repeat(np.arange(L.n_sdofs), np.diff(L.rowptr))
+        col = np.asarray(L.col)
+        nv = 3 ** dim
+        comp = np.full(L.n_sdofs, dim)
+        for d in range(dim):
+            comp[np.asarray(L.cell_sdofs)[:, d * nv:(d + 1) * nv]] = d
+        if kind == "coupled":
+            hit = (comp[rows] < dim) & (comp[col] < dim) & (comp[rows] != comp[col])
+            scale = 1e-2 * np.median(np.abs(val[(rows == col) & (comp[rows] == 0)]).max(axis=(1, 2)))
+            val[hit] = scale * rng.uniform(-1, 1, (int(hit.sum()), p.b, p.b))
+        elif kind == "singular":
+            row = int(L.cell_sdofs[-1, nv + nv // 2])
+            hit = ((rows == row) | (col == row)) & (comp[rows] < dim) & (comp[col] < dim)
+            val[hit] = 0.0
+            val[(rows == row) & (col == row)] = 1e-300 * np.eye(p.b)
+        elif kind == "pressure":
+            hit = (rows == col) & (comp[rows] == dim)
+            val[hit] = 1e-3 * np.abs(val).max() * np.eye(p.b)
+        hier.append([dict(n_sdofs=L.n_sdofs, rowptr=L.rowptr, col=L.col, val=val,
+                          cell_sdofs=L.cell_sdofs, P=None)])
+        mats.append(sp.bsr_matrix((val, L.col, L.rowptr), shape=(L.n_sdofs * p.b,) * 2).tocsc())
+    s = stv.Solver(0)
+    s.set_batch(hier, dim, k) if len(hier) > 1 else s.set_hierarchy(hier[0], dim, k)
+    r = rng.standard_normal(sum(J.shape[0] for J in mats))
+    for _ in range(2):
+        s.build_cell_inverses()
+        dd = to_dev(np.zeros_like(r))
+        s.coarse_solve(to_dev(r), dd)
+        d, at = to_host(dd), 0
+        for n, J in zip(shapes, mats):
+            sl = slice(at, at + J.shape[0])
+            at += J.shape[0]
+            lu = sla.splu(J)
+            cond = sla.onenormest(J) * sla.onenormest(
+                sla.LinearOperator(J.shape, matvec=lu.solve, rmatvec=lambda v: lu.solve(v, trans="T")))
+            res = np.linalg.norm(r[sl] - J @ d[sl]) / np.linalg.norm(r[sl])
+            fe = relerr(d[sl], lu.solve(r[sl]))
+            log(f"[coarse] blocks {dim}d {n} k={k} {kind} relres {res:.2e} forward {fe:.2e} cond {cond:.1e}")
+            assert res <= 1e-11 * max(1.0, 1e-8 * cond)
+            assert fe <= 1e-15 * cond * 10
+    s.close()
