@@ -64,12 +64,18 @@ typedef double stv_d4 __attribute__((ext_vector_type(4)));
 // and B = the pivot rows before the panel, one MFMA per 16x16 tile.  At the
 // end element (rho, q) of the in-place result belongs to row rinv[rho] and
 // column rpiv[q] of the inverse.
+// Bound by the serial pivots (43 panels of 4 at order 170, where a workgroup
+// has a compute unit to itself): the panel is held in wave 0's registers, not
+// in LDS, for its four pivots (3d dG(1) without factors, 1,024 cells twice:
+// 2.31 -> 1.93 ms; dG(0) 0.54 -> 0.48, dG(2) 2.81 -> 2.47, 2d dG(3) 0.81 ->
+// 0.70).  Three workgroups of six wavefronts need 96 registers.
 template <int B, int NLS>
 __global__ void __launch_bounds__(((B * NLS + 15) / 16) * 64)
-__attribute__((amdgpu_waves_per_eu((((B * NLS + 15) / 16) + 3) / 4, 8))) k_inverse_mfma(
+__attribute__((amdgpu_waves_per_eu((B * NLS + 15) / 16 <= 6 ? 5 : (((B * NLS + 15) / 16) + 3) / 4, 8))) k_inverse_mfma(
     const int32_t* __restrict__ posmap, const double* __restrict__ val,
     const int32_t* __restrict__ own_ptr, const uint8_t* __restrict__ own_loc, int full,
-    const int64_t* __restrict__ inv_off, int ld, void* store, int fp32, uint8_t* status) {
+    const int64_t* __restrict__ inv_off, int ld, void* store, int fp32, uint8_t* status,
+    int first) {
   constexpr int N = B * NLS;
   constexpr int NT = (N + 15) / 16;
   constexpr int NP = 16 * NT;
@@ -78,7 +84,6 @@ __attribute__((amdgpu_waves_per_eu((((B * NLS + 15) / 16) + 3) / 4, 8))) k_inver
   __shared__ double brow[4][NP];
   __shared__ int rpiv[NP];
   __shared__ int rinv[NP];
-  __shared__ uint8_t used[NP];
   __shared__ int rowmap[N];
   __shared__ int sing;
   const int tid = threadIdx.x;
@@ -86,11 +91,10 @@ __attribute__((amdgpu_waves_per_eu((((B * NLS + 15) / 16) + 3) / 4, 8))) k_inver
   const int w = tid >> 6;
   const int lr = lane >> 4;   // row offset inside a 4-row group
   const int lc = lane & 15;   // column inside a tile
-  const int T = blockIdx.x;
+  const int T = first + blockIdx.x;
   const int32_t* pos = posmap + (int64_t)T * (NLS * NLS);
 
   if (tid == 0) sing = 0;
-  for (int i = tid; i < NP; i += NT * 64) used[i] = 0;
   for (int i = tid; i < N; i += NT * 64) rowmap[i] = full ? i : -1;
   __syncthreads();
   if (!full) {
@@ -120,10 +124,16 @@ __attribute__((amdgpu_waves_per_eu((((B * NLS + 15) / 16) + 3) / 4, 8))) k_inver
     }
   }
 
+  // rows of this lane (wave 0) used as pivots, or beyond the block
+  int done = 0;
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) done |= (lane + 64 * ch < NP ? 0 : 1) << ch;
+
   // tile column tc is a run-time index: the accumulator tiles are selected
   // by compile-time comparisons so that they stay in registers
 #pragma unroll 1
   for (int tc = 0; tc < NT; ++tc) {
+#pragma unroll 1
     for (int q4 = 0; q4 < 4; ++q4) {
       const int c0 = 4 * q4;          // first panel column inside tile column tc
       const int p0 = 16 * tc + c0;
@@ -137,19 +147,25 @@ __attribute__((amdgpu_waves_per_eu((((B * NLS + 15) / 16) + 3) / 4, 8))) k_inver
           }
       }
       __syncthreads();
-      // (b) wave 0 eliminates the panel (partial pivoting over unused rows)
+      // (b) wave 0 eliminates the panel (partial pivoting over unused rows),
+      // rows lane, lane + 64, .. in registers
       if (w == 0) {
+        double x[NCH][4];
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+          const int rho = lane + 64 * ch < NP ? lane + 64 * ch : NP - 1;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) x[ch][c] = panel[rho][c];
+        }
+#pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int p = p0 + t;
           double best = -1.0;
           int bi = 0x7fffffff;
 #pragma unroll
           for (int ch = 0; ch < NCH; ++ch) {
-            const int rho = lane + 64 * ch;
-            if (rho < NP && !used[rho]) {
-              const double v = fabs(panel[rho][t]);
-              if (v > best) { best = v; bi = rho; }
-            }
+            const double v = fabs(x[ch][t]);
+            if (!(done >> ch & 1) && v > best) { best = v; bi = lane + 64 * ch; }
           }
           // the largest magnitude (DPP max), then the lowest row holding it:
           // read from the single lane that has it, or a DPP min over ties
@@ -166,39 +182,50 @@ __attribute__((amdgpu_waves_per_eu((((B * NLS + 15) / 16) + 3) / 4, 8))) k_inver
           if (r >= NP) {   // no finite candidate (NaN column): lowest unused row
             int u = 0x7fffffff;
 #pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
-              const int rho = lane + 64 * ch;
-              if (rho < NP && !used[rho]) u = min(u, rho);
-            }
+            for (int ch = NCH - 1; ch >= 0; --ch)
+              if (!(done >> ch & 1)) u = lane + 64 * ch;
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) u = min(u, __shfl_xor(u, off, 64));
-            r = u;
+            r = __builtin_amdgcn_readfirstlane(u);
             if (lane == 0) sing = 1;
           }
-          const double piv = panel[r][t];
+          const int rl = r & 63, rc = r >> 6;
+          double pr[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            double v = x[0][c];
+#pragma unroll
+            for (int ch = 1; ch < NCH; ++ch) {
+              const double o = x[ch][c];
+              v = rc == ch ? o : v;
+            }
+            pr[c] = readlane_f64(v, rl);
+          }
+          const double piv = pr[t];
           if (lane == 0) {
             if (!(m > 0.0) || !(piv != 0.0)) sing = 1;
             rpiv[p] = r;
-            used[r] = 1;
           }
           const double ipiv = (piv != 0.0) ? 1.0 / piv : 0.0;
-          double pr[4];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) pr[c] = panel[r][c];
 #pragma unroll
           for (int ch = 0; ch < NCH; ++ch) {
-            const int rho = lane + 64 * ch;
-            if (rho < NP) {
-              if (rho == r) {
+            const bool is = lane == rl && rc == ch;
+            if (is) done |= 1 << ch;
+            const double f = x[ch][t] * ipiv;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) panel[rho][c] = (c == t) ? ipiv : pr[c] * ipiv;
-              } else {
-                const double f = panel[rho][t] * ipiv;
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                  panel[rho][c] = (c == t) ? -f : fma(-f, pr[c], panel[rho][c]);
-              }
+            for (int c = 0; c < 4; ++c) {
+              const double e = c == t ? -f : fma(-f, pr[c], x[ch][c]);
+              const double g = c == t ? ipiv : pr[c] * ipiv;
+              x[ch][c] = is ? g : e;
             }
+          }
+        }
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+          const int rho = lane + 64 * ch;
+          if (rho < NP) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) panel[rho][c] = x[ch][c];
           }
         }
       }
@@ -1057,10 +1084,21 @@ static hipError_t inv_mfma(hipStream_t s, const DevLevel& L, int fp32, int full,
                                                       status, L.n_cells, CellSplit{}, 0);
     return hipGetLastError();
   } else {
-    k_inverse_mfma<B, NLS><<<L.n_cells, NT * 64, 0, s>>>(L.posmap, L.val, L.own_ptr, L.own_loc,
-                                                       full, L.inv_off, L.inv_ld, L.inv_store, fp32,
-                                                         status);
-    return hipGetLastError();
+    // From 9 wavefronts on a workgroup fills its compute unit, and all of a
+    // launch start and end together: a coarse chain beside it (n_cu > 0) waits
+    // for a whole cell at each of its launches.  Launches of 7/8 of the units
+    // leave the rest to the chain (3d 32x8x8, build with chunks of 256, 240,
+    // 224, 208, 192, 160 cells: 6.0, 5.9, 3.9, 4.0, 4.1, 4.8 ms).
+    int step = L.n_cells;
+    if (NT > 8 && n_cu > 0) step = std::max(1, n_cu * 7 / 8);
+    for (int first = 0; first < L.n_cells; first += step) {
+      k_inverse_mfma<B, NLS><<<std::min(step, L.n_cells - first), NT * 64, 0, s>>>(
+          L.posmap, L.val, L.own_ptr, L.own_loc, full, L.inv_off, L.inv_ld, L.inv_store, fp32,
+          status, first);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
 }
 

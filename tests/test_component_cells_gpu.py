@@ -85,3 +85,26 @@ def test_component_cells(stv, name, singular):
             s.vanka_sweep(g, to_dev(r), d, 2, 0.7)
             # FP32 store: 2^-24 per value, times the inverse's condition at most
             assert relerr(to_host(d), ref) <= (max(1e-5, 2.0 ** -24 * cond) if fp32 else tol), wgs
+
+
+@pytest.mark.parametrize("cells", [(56, 2, 2), (38, 6, 2), (56, 4, 2), (30, 4, 4)])
+@pytest.mark.parametrize("k", [1, 2])
+def test_block_cells_in_chunks(stv, cells, k):
+    """3d cells without factors, built beside the coarse chain in launches of
+    7/8 of the compute units (224 of 256): 224, 456, 448 and 480 cells; first,
+    last and the cells on both sides of every cut, against the oracle."""
+    p = make_problem(3, cells, 2, k, 0.01, 1e-3, 17)
+    L = p.levels[-1]
+    own = oracle.owner_cells(L.cell_sdofs, L.n_sdofs)
+    nls, n = L.cell_sdofs.shape[1], L.cell_sdofs.shape[0]
+    s = stv.Solver(0)
+    s.set_hierarchy(p.levels, 3, k)
+    s.build_cell_inverses()
+    for T in sorted({0, 223, 224 % n, 447 % n, 448 % n, n - 1}):
+        JT = oracle.extract_cell_matrix_blocks(L.rowptr, L.col, L.val, p.b, L.cell_sdofs[T])
+        O, G = oracle.cell_inverse(JT), s.get_cell_inverse(1, T)
+        rows = [l * nls + a for l in range(p.b) for a in range(nls)
+                if own[L.cell_sdofs[T, a]] == T]
+        tol = max(1e-12, 64 * 2.0 ** -53 * np.linalg.norm(JT, 2) * np.linalg.norm(O, 2))
+        assert np.abs(G[rows] - O[rows]).max() <= tol * np.abs(O).max(), T
+    s.close()
