@@ -8,7 +8,9 @@
 // then the Schur complement S = D - C V^-1 B by a second chain, and the solve
 // is applied in factored form,
 //   p = S^-1 (g - Z f),  Z = C V^-1,   u = V^-1 f + G p,  G = -V^-1 B
-// (three launches), or with P = S^-1 [-Z | I] formed, p = P (f, g) (two).
+// (three launches), or with P = S^-1 [-Z | I] formed, p = P (f, g) (two), or,
+// small or needed in both directions, as the whole inverse
+//   [ V^-1 0 ; 0 0 ] + [ G ; I ] P   (one).
 // The chains are bound by their panels in sequence, 16 complex pivots each: in
 // 3d (16x3x3 cells) 32 for nine blocks of order 506 and 55 for a border of 870
 // instead of 340 for the whole matrix of order 5,427 (138 for the components
@@ -210,68 +212,176 @@ __global__ void __launch_bounds__(256) k_cc_s(const CompCoarse* __restrict__ cc)
   if ((threadIdx.x & 63) == 0) atomic_max_bits(&M.norm[p][kCcMax][0], mx);
 }
 
-// P = S^-1 [-Z | I]: a complex matrix product on FP64 matrix cores, 64 x 64
-// tiles, four wavefronts of 2 x 2 instruction tiles each, 16 columns of S^-1
-// per step staged in LDS.  Only where the product is small (CcDims::form_p): it
+// A 32 x 32 tile of a complex (real: pair false) matrix product on FP64 matrix
+// cores: one instruction tile for each of four wavefronts, 16 columns of the
+// left factor per step staged in LDS.  left(r, k) and right(k, c) read the
+// factors (zero outside); element v of the result is row wr + 4 v + (lane >> 4),
+// column wc + (lane & 15) of the tile.  Bound by the number of tiles: of 64 x 64
+// there are 65 for P and 169 for X at order 786 (dG(1), 16x4 cells), for 256
+// compute units (that build 1.25 -> 1.20 ms).
+constexpr int kCcTile = 32, kCcK = 16;
+struct CcLds { double2 a[kCcTile][kCcK + 1], b[kCcK][kCcTile + 1]; };
+template <typename L, typename R>
+__device__ __forceinline__ void cc_tile(CcLds& lds, int len, bool pair, L&& left, R&& right,
+                                        stv_d4& re, stv_d4& im) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int lr = lane >> 4, lc = lane & 15, wr = 16 * (w >> 1), wc = 16 * (w & 1);
+  for (int k0 = 0; k0 < len; k0 += kCcK) {
+    double2 a[2], b[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = tid + 256 * u;
+      a[u] = left(e / kCcK, k0 + e % kCcK);
+      b[u] = right(k0 + e / kCcTile, e % kCcTile);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = tid + 256 * u;
+      lds.a[e / kCcK][e % kCcK] = a[u];
+      lds.b[e / kCcTile][e % kCcTile] = b[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kCcK; k += 4) {
+      const double2 x = lds.a[wr + lc][k + lr], y = lds.b[k + lr][wc + lc];
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.x, re, 0, 0, 0);
+      if (!pair) continue;
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.y, y.y, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.y, im, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.x, im, 0, 0, 0);
+    }
+  }
+}
+
+// P = S^-1 [-Z | I].  Only where the product is small (CcDims::form_p): it
 // saves one launch per solve.
 __global__ void __launch_bounds__(256) k_cc_p(const CompCoarse* __restrict__ cc, int blocks) {
-  constexpr int KC = 16;
-  __shared__ double2 As[64][KC + 1], Bs[KC][64 + 1];
+  __shared__ CcLds lds;
   const CompCoarse& M = cc[blockIdx.z / blocks];
   const int p = blockIdx.z % blocks;
   if (p >= M.nblk) return;
   if (!M.P[p]) return;
   const int n_p = M.n_p, n_v = M.n_v, n_s = n_v + n_p;
-  const int m0 = blockIdx.y * 64, e0 = blockIdx.x * 64;
+  const int m0 = blockIdx.y * kCcTile, e0 = blockIdx.x * kCcTile;
   if (m0 >= n_p || e0 >= n_s) return;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int lr = lane >> 4, lc = lane & 15, wr = 32 * (w >> 1), wc = 32 * (w & 1);
-  const double2 *Si = M.Si[p], *Z = M.Z[p];
-  stv_d4 re[2][2] = {}, im[2][2] = {};
-  if (e0 < n_v) {
-    for (int k0 = 0; k0 < n_p; k0 += KC) {
-      __syncthreads();
+  const bool pair = M.sz[p] == 2;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lr = lane >> 4, lc = lane & 15, wr = 16 * (w >> 1), wc = 16 * (w & 1);
+  const double2 *Si = M.Si[p], *Z = M.Z[p], zero = make_double2(0.0, 0.0);
+  stv_d4 re = {}, im = {};
+  if (e0 < n_v)
+    cc_tile(lds, n_p, pair,
+            [&](int r, int k) {
+              return m0 + r < n_p && k < n_p ? Si[(int64_t)(m0 + r) * n_p + k] : zero;
+            },
+            [&](int k, int c) {
+              return k < n_p && e0 + c < n_v ? Z[(int64_t)k * n_v + e0 + c] : zero;
+            },
+            re, im);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = tid + 256 * u, r = e / KC, k = e % KC;
-        As[r][k] = (m0 + r < n_p && k0 + k < n_p) ? Si[(int64_t)(m0 + r) * n_p + k0 + k]
-                                                  : make_double2(0.0, 0.0);
-        const int kb = e / 64, cb = e % 64;
-        Bs[kb][cb] = (k0 + kb < n_p && e0 + cb < n_v) ? Z[(int64_t)(k0 + kb) * n_v + e0 + cb]
-                                                      : make_double2(0.0, 0.0);
-      }
-      __syncthreads();
+  for (int v = 0; v < 4; ++v) {
+    const int m = m0 + wr + 4 * v + lr, e = e0 + wc + lc;
+    if (m >= n_p || e >= n_s) continue;
+    cc_put(M.P[p], (int64_t)m * n_s + e, pair,
+           e < n_v ? make_double2(-re[v], -im[v]) : Si[(int64_t)m * n_p + e - n_v]);
+  }
+}
+
+// The whole inverse, real and in the level's order (CcDims::form_x): block rows
+// G P + V^-1, border rows P, the time blocks recombined, X = sum_p V_p x_p W_p.
+// It is then applied like any whole inverse, in one launch and both directions.
+template <int B>
+__global__ void __launch_bounds__(256) k_cc_x(const CompCoarse* __restrict__ cc) {
+  __shared__ CcLds lds;
+  const CompCoarse& M = cc[blockIdx.z];
+  const int n_p = M.n_p, n_v = M.n_v, n_s = n_v + n_p;
+  const int e0 = blockIdx.y * kCcTile, f0 = blockIdx.x * kCcTile;
+  if (e0 >= n_s || f0 >= n_s) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lr = lane >> 4, lc = lane & 15, wr = 16 * (w >> 1), wc = 16 * (w & 1);
+  const double2 zero = make_double2(0.0, 0.0);
+  // the tile's rows: place in the level, block (kCcMax: border), its range;
+  // columns: place in the level
+  __shared__ int row_at[kCcTile], row_c[kCcTile], row_o[kCcTile], row_n[kCcTile], col_at[kCcTile];
+  if (threadIdx.x < kCcTile) {
+    const int e = min(e0 + (int)threadIdx.x, n_s - 1), f = min(f0 + (int)threadIdx.x, n_s - 1);
+    int c = kCcMax, o = 0, n = 0;
+    for (int t = 0; t < M.nc; ++t)
+      if (e >= M.off[t] && e < M.off[t] + M.n[t]) { c = t; o = M.off[t]; n = M.n[t]; }
+    row_at[threadIdx.x] = M.order[e];
+    row_c[threadIdx.x] = c;
+    row_o[threadIdx.x] = o;
+    row_n[threadIdx.x] = n;
+    col_at[threadIdx.x] = M.order[f];
+  }
+  __syncthreads();
+  const int f = min(f0 + wc + lc, n_s - 1);
+  for (int p = 0; p < M.nblk; ++p) {
+    const bool pair = M.sz[p] == 2;
+    const double2 *G = M.G[p], *P = M.P[p];
+    stv_d4 re = {}, im = {};
+    if (e0 < n_v)
+      cc_tile(lds, n_p, pair,
+              [&](int r, int k) {
+                return e0 + r < n_v && k < n_p ? cc_get(G, (int64_t)(e0 + r) * n_p + k, pair) : zero;
+              },
+              [&](int k, int c) {
+                return k < n_p && f0 + c < n_s ? cc_get(P, (int64_t)k * n_s + f0 + c, pair) : zero;
+              },
+              re, im);
+    // the rows' own entries; all reads stand before the writes, which they
+    // could not pass
+    double2 x[4];
 #pragma unroll
-      for (int k = 0; k < KC; k += 4) {
-        double2 a[2], b[2];
+    for (int v = 0; v < 4; ++v) {
+      const int er = wr + 4 * v + lr, e = min(e0 + er, n_s - 1);
+      const int c = row_c[er], o = row_o[er], n = row_n[er];
+      const bool border = c == kCcMax, in = f >= o && f < o + n;
+      const double2* from = border ? P : M.Vi[p][in ? c : 0];
+      const int64_t at = border ? (int64_t)(e - n_v) * n_s + f
+                                : in ? (int64_t)(e - o) * n + f - o : 0;
+      const double2 q = cc_get(from, at, pair);
+      x[v].x = (border ? 0.0 : re[v]) + (border || in ? q.x : 0.0);
+      x[v].y = (border ? 0.0 : im[v]) + (border || in ? q.y : 0.0);
+    }
+    const int t = M.first[p];
+    double old[4][B][B];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          a[t] = As[wr + 16 * t + lc][k + lr];
-          b[t] = Bs[k + lr][wc + 16 * t + lc];
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+#pragma unroll
+        for (int l = 0; l < B; ++l)
+          old[v][q][l] = p > 0 ? M.X[((int64_t)row_at[wr + 4 * v + lr] * B + q) * n_s * B +
+                                     (int64_t)col_at[wc + lc] * B + l]
+                               : 0.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int l = 0; l < B; ++l) {
+        const double w0 = M.W[t * B + l], w1 = pair ? M.W[(t + 1) * B + l] : 0.0;
+        const double zr = x[v].x * w0 - x[v].y * w1, zi = x[v].x * w1 + x[v].y * w0;
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+          double y = fma(M.V[q * B + t], zr, old[v][q][l]);
+          if (pair) y = fma(M.V[q * B + t + 1], zi, y);
+          old[v][q][l] = y;
         }
+      }
+    if (f0 + wc + lc < n_s) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int v = 0; v < 4; ++v) {
+        if (e0 + wr + 4 * v + lr >= n_s) continue;
 #pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, re[i][j], 0, 0, 0);
-            re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[i].y, b[j].y, re[i][j], 0, 0, 0);
-            im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, im[i][j], 0, 0, 0);
-            im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].x, im[i][j], 0, 0, 0);
-          }
+        for (int q = 0; q < B; ++q)
+#pragma unroll
+          for (int l = 0; l < B; ++l)
+            M.X[((int64_t)row_at[wr + 4 * v + lr] * B + q) * n_s * B +
+                (int64_t)col_at[wc + lc] * B + l] = old[v][q][l];
       }
     }
   }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int m = m0 + wr + 16 * i + 4 * v + lr, e = e0 + wc + 16 * j + lc;
-        if (m >= n_p || e >= n_s) continue;
-        cc_put(M.P[p], (int64_t)m * n_s + e, M.sz[p] == 2,
-               e < n_v ? make_double2(-re[i][j][v], -im[i][j][v]) : Si[(int64_t)m * n_p + e - n_v]);
-      }
 }
 
 // A block whose largest entry times its inverse's largest is above 1e10 (or
@@ -507,7 +617,20 @@ hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
   k_cc_collect_s<<<dim3(D.n_p, D.blk, D.cnt), 256, 0, s>>>(cc);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (D.form_p) {
-    k_cc_p<<<dim3((D.n_s + 63) / 64, (D.n_p + 63) / 64, D.cnt * D.blk), 256, 0, s>>>(cc, D.blk);
+    k_cc_p<<<dim3((D.n_s + kCcTile - 1) / kCcTile, (D.n_p + kCcTile - 1) / kCcTile, D.cnt * D.blk),
+             256, 0, s>>>(cc, D.blk);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (D.form_x) {
+    const unsigned tiles = (D.n_s + kCcTile - 1) / kCcTile;
+    const dim3 grid(tiles, tiles, D.cnt);
+    switch (D.b) {
+      case 1: k_cc_x<1><<<grid, 256, 0, s>>>(cc); break;
+      case 2: k_cc_x<2><<<grid, 256, 0, s>>>(cc); break;
+      case 3: k_cc_x<3><<<grid, 256, 0, s>>>(cc); break;
+      case 4: k_cc_x<4><<<grid, 256, 0, s>>>(cc); break;
+      default: return hipErrorInvalidValue;
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   k_cc_verdict<<<D.cnt, 4 * (kCcMax + 1), 0, s>>>(cc);   // one wavefront

@@ -2063,7 +2063,9 @@ hipError_t launch_gj_unpermute(hipStream_t s, const double* S, int64_t sA, int64
 }
 
 // y = A x on every member's rows: one wavefront per row of a member's
-// row-major dense inverse (member z in blockIdx.z).
+// row-major dense inverse (member z in blockIdx.z).  Bound by the latency of a
+// row's loads below some 2,000 rows (1.5 wavefronts per SIMD at 1,572): eight
+// are in flight (order 1,572: 8.8 -> 6.4 us, 3.1 TB/s).
 __global__ void __launch_bounds__(256) k_dense_gemv(const CoarseDesc* __restrict__ desc, int b,
                                                     const double* __restrict__ inv,
                                                     const double* __restrict__ x,
@@ -2076,8 +2078,31 @@ __global__ void __launch_bounds__(256) k_dense_gemv(const CoarseDesc* __restrict
   const int64_t vo = (int64_t)D.row_off * b;
   const double* Ar = inv + D.inv_off + row * n0;
   const double* xz = x + vo;
-  double acc = 0.0;
-  for (int64_t j = lane; j < n0; j += 64) acc = fma(Ar[j], xz[j], acc);
+  constexpr int U = 8;
+  double part[U] = {};
+  int64_t j = lane;
+  for (; j + 64 * (U - 1) < n0; j += 64 * U) {
+    double a[U], v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { a[u] = Ar[j + 64 * u]; v[u] = xz[j + 64 * u]; }
+#pragma unroll
+    for (int u = 0; u < U; ++u) part[u] = fma(a[u], v[u], part[u]);
+  }
+  // the rest, clamped: all its loads at once too
+  double a[U], v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t q = j + 64 * u < n0 ? j + 64 * u : n0 - 1;
+    a[u] = Ar[q];
+    v[u] = xz[q];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const double s = fma(a[u], v[u], part[u]);
+    part[u] = j + 64 * u < n0 ? s : part[u];
+  }
+  double acc = ((part[0] + part[1]) + (part[2] + part[3])) +
+               ((part[4] + part[5]) + (part[6] + part[7]));
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
   if (lane == 0) y[vo + row] = acc;
@@ -2088,7 +2113,7 @@ __global__ void __launch_bounds__(256) k_dense_gemv(const CoarseDesc* __restrict
 // of 16 threads each take the rows g, g + 64, ... (a 128-byte run of a row per
 // group, eight rows in flight), and the groups' sums meet in LDS in a fixed
 // order.  Bound by HBM / L2; one thread per column over all rows was bound by
-// the latency of its serial loads (order 1,572: 630 -> 9.6 us, 2.1 TB/s).
+// the latency of its serial loads (order 1,572: 630 -> 11.8 us, 1.7 TB/s).
 __global__ void __launch_bounds__(1024) k_dense_gemv_t(const CoarseDesc* __restrict__ desc, int b,
                                                        const double* __restrict__ inv,
                                                        const double* __restrict__ x,

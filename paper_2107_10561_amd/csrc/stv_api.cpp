@@ -582,7 +582,8 @@ int sweeps(stv_ctx* ctx, int g, const double* r, double* d, int n, double omega,
 // members with a whole stored inverse by a dense product, the time-decoupled
 // ones from their blocks' inverses.
 int coarse_apply(stv_ctx* ctx, int g, const double* r, double* d) {
-  const int nw = ctx->n_whole[g], nk = (int)ctx->h_kc[g].size(), nc = (int)ctx->h_cc[g].size();
+  const int nw = ctx->n_whole[g], nk = (int)ctx->h_kc[g].size();
+  const int nc = ctx->cc_dims[g].form_x ? 0 : (int)ctx->h_cc[g].size();
   if (nw == 0 && nk == 0 && nc == 0) return STV_OK;
   Timed t(ctx, KC_COARSE, g, nullptr, nc == 0);
   if (nc > 0)   // made for the forward direction only
@@ -1728,9 +1729,11 @@ static bool worth_cutting(const CompStruct& S, int32_t n_s, int b) {
 }
 
 // Members with a component structure: descriptors, chains and buffers.  The
-// whole-member set-up then leaves them out (inv_off = -2).
+// whole-member set-up then leaves them out (inv_off = -2) or, where their whole
+// inverse is formed, only gives them their place in the store (-3).
 static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& split,
                                   const std::vector<bool>& has_split) {
+  const bool full = ctx->inv_full != 0;
   struct Member { int g; CompStruct S; int at[4][kCcMax + 1]; };
   std::vector<Member> mem;
   // one group for all the blocks, one for all the Schur complements, each
@@ -1819,6 +1822,28 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
       ctx->h_cc[g].push_back(R);
       mem.push_back(std::move(M));
     }
+    // what is formed of them
+    double fp = 0.0, fx = 0.0;
+    int64_t rows = 0;
+    for (const CompCoarse& R : ctx->h_cc[g]) {
+      for (int p = 0; p < R.nblk; ++p) {
+        const double c = R.sz[p] == 2 ? 8.0 : 2.0;
+        fp += c * R.n_p * R.n_p * R.n_v;
+        fx += c * R.n_p * R.n_v * (R.n_v + R.n_p);
+      }
+      rows = std::max<int64_t>(rows, (int64_t)(R.n_v + R.n_p) * b);
+    }
+    CcDims& D = ctx->cc_dims[g];
+    // The whole inverse: always with the all-rows layout, whose transposed
+    // solves need it (a second set of factored kernels otherwise); else where
+    // a solve of some 10 cycles wins it back.  Forming it and an apply then
+    // and without: order 132 26 us, 3.9 and 6.5 us; 786 23 us, 4.0 and 8.1;
+    // 1572 40 to 90 us, 6.4 and 9.1; from 2055 the applies are equal.
+    D.form_x = full || (rows <= 1024 && fp + fx <= 1e9);
+    D.form_p = D.form_x || fp <= 2e9;
+    if (D.form_x)
+      for (CoarseDesc& c : ctx->h_coarse[g])
+        if (c.inv_off == -2) c.inv_off = -3;
   }
   if (mem.empty()) return STV_OK;
   for (int kind = 0; kind < 2; ++kind) {
@@ -1837,11 +1862,6 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     *p = q;
     return STV_OK;
   };
-  for (int g = 0; g < ctx->n_levels; ++g) {
-    double flops = 0.0;   // of forming P on this level
-    for (const CompCoarse& R : ctx->h_cc[g]) flops += 8.0 * R.nblk * R.n_p * R.n_p * R.n_v;
-    ctx->cc_dims[g].form_p = flops <= 2e9;
-  }
   std::vector<size_t> next((size_t)ctx->n_levels, 0);
   for (const Member& M : mem) {
     CompCoarse& R = ctx->h_cc[M.g][next[(size_t)M.g]++];
@@ -1903,6 +1923,7 @@ static int upload_component_members(stv_ctx* ctx, int* report) {
   std::vector<size_t> next((size_t)ctx->n_levels, 0);
   for (const auto& sl : ctx->cc_slots) {
     CompCoarse& R = ctx->h_cc[sl.first][next[(size_t)sl.first]++];
+    R.X = ctx->cc_dims[sl.first].form_x ? ctx->coarse_inv + R.X_off : nullptr;
     for (int p = 0; p < 4; ++p)
       for (int c = 0; c <= kCcMax; ++c) {
         const int v = sl.second[(size_t)(p * (kCcMax + 1) + c)];
@@ -1938,11 +1959,10 @@ static int make_coarse_groups(stv_ctx* ctx) {
   for (int g = 0; g < ctx->n_levels; ++g)
     if (ctx->lv[g].kron_ma && !ctx->h_coarse[g].empty())
       has_split[(size_t)g] = time_split(ctx->lv[g].kron_C, ctx->lv[g].kron_tw, b, split[(size_t)g]);
-  // by component where that applies: the schedule is not prescribed and only
-  // forward solves are needed (transposed ones go with the all-rows layout)
+  // by component where that applies and the schedule is not prescribed
   for (int g = 0; g < ctx->n_levels; ++g)
     for (CoarseDesc& c : ctx->h_coarse[g]) c.inv_off = 0;
-  if (ctx->coarse_algo == 0 && !ctx->inv_full && !ctx->cc_off) {
+  if (ctx->coarse_algo == 0 && !ctx->cc_off) {
     std::vector<TimeSplit> cs = split;
     std::vector<bool> has = has_split;
     for (int g = 0; g < ctx->n_levels; ++g) {
@@ -1974,11 +1994,18 @@ static int make_coarse_groups(stv_ctx* ctx) {
   struct BlockRef { size_t gi; size_t slot; };
   std::vector<std::vector<BlockRef>> mblocks;
   int64_t coarse_total = 0;
+  std::vector<size_t> formed((size_t)ctx->n_levels, 0);   // members of h_cc placed
   for (int g = 0; g < ctx->n_levels; ++g)
     for (size_t q = 0; q < ctx->h_coarse[g].size(); ++q) {
       CoarseDesc& c = ctx->h_coarse[g][q];
       if (c.inv_off == -2) continue;
       const int64_t n0 = (int64_t)c.n_s * b;
+      if (c.inv_off == -3) {
+        c.inv_off = coarse_total;
+        ctx->h_cc[g][formed[(size_t)g]++].X_off = coarse_total;
+        coarse_total += n0 * n0;
+        continue;
+      }
       if (!has_split[(size_t)g]) {
         c.inv_off = coarse_total;
         coarse_total += n0 * n0;

@@ -236,6 +236,8 @@ struct CompCoarse {
   double2* Vi[4][kCcMax];
   double2 *Si[4], *Z[4], *G[4], *P[4];
   double2* pw;
+  double* X;       // the whole inverse, where it is formed: X_off in the coarse store
+  int64_t X_off;
 };
 // launch dimensions over the members of one level: largest block, border and
 // whole order, blocks, time blocks, members
@@ -247,6 +249,8 @@ struct CcDims {
   unsigned n = 0, n_p = 0, n_s = 0, nc = 0, blk = 0, cnt = 0;
   int b = 0;   // time components of the rows
   bool form_p = false;
+  // form_x: and the whole inverse from the factors, applied as one
+  bool form_x = false;
 };
 
 // The coarse members of one order, eliminated by one batched Gauss-Jordan:

@@ -283,3 +283,39 @@ def test_coarse_solve_of_blocks_by_separators(stv, case, kind):
             assert res <= 1e-11 * max(1.0, 1e-8 * cond)
             assert fe <= 1e-15 * cond * 10
     s.close()
+
+
+@pytest.mark.parametrize("factors", [False, True])
+@pytest.mark.parametrize("case", [(2, (4, 1), 1), (2, (16, 4), 0), (2, (16, 4), 1), (2, (9, 3), 2),
+                                  (2, (8, 3), 3), (3, (4, 2, 2), 1)])
+@pytest.mark.parametrize("full", [False, True])
+def test_whole_inverse_from_parts(stv, case, factors, full):
+    """The whole coarse inverse made of the parts' inverses and the border's
+    (all time blocks recombined): forward, and transposed with the all-rows
+    layout.  Bounds as for the other schedules."""
+    dim, n, k = case
+    p = make_problem(dim, n, 1, k, 0.01, 1e-3, 7)
+    J = oracle.prepare_levels(p.levels, p.b)[0].J.tocsc()
+    lu = sla.splu(J)
+    cond = sla.onenormest(J) * sla.onenormest(
+        sla.LinearOperator(J.shape, matvec=lu.solve, rmatvec=lambda v: lu.solve(v, trans="T")))
+    s = stv.Solver(0)
+    s.set_hierarchy(p.levels, dim, k)
+    if factors:
+        _, w, C, _ = fe_time.time_matrices(k)
+        m, a = spatial_factors(p.levels[0])
+        s.set_kron_factors(0, m, a, np.asarray(C, dtype=np.float64),
+                           p.tau * np.asarray(w, dtype=np.float64))
+    s.build_cell_inverses(full=full)
+    r = np.random.default_rng(37).standard_normal(J.shape[0])
+    for trans in ((False, True) if full else (False,)):
+        dd = to_dev(np.zeros_like(r))
+        s.vcycle_transposed(to_dev(r), dd) if trans else s.coarse_solve(to_dev(r), dd)
+        d, A = to_host(dd), J.T if trans else J
+        res = np.linalg.norm(r - A @ d) / np.linalg.norm(r)
+        fe = relerr(d, lu.solve(r, trans="T" if trans else "N"))
+        log(f"[coarse] whole {case} factors={factors} full={full} transposed={trans} "
+            f"relres {res:.2e} forward {fe:.2e} cond {cond:.1e}")
+        assert res <= 1e-11 * max(1.0, 1e-8 * cond)
+        assert fe <= 1e-15 * cond * 10
+    s.close()
