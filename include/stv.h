@@ -407,12 +407,14 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
                          const double* C, const double* tw);
 
 /* Launch shapes of the level kernels of one level: spmv_rows = shape of the
- * residual (1..12, default 2): with the blocks, block rows per wavefront (5
- * to 12 act as 4); with spatial factors, (lanes per block row, blocks per
- * lane and round) = (4,4), (8,3), (8,4), (16,2), (16,4), (32,2) over one
- * list of (m, a) pairs per row (1..6), or the same six over two lists per
- * row, the blocks with a mass entry as (m, a) pairs and the others as a
- * alone (7..12: fewer bytes, more rounds); sweep_wgs = workgroups
+ * residual (1..12, default 2): with the blocks, (lanes per block row, blocks
+ * per lane and round) = (32,2), (16,2), (32,1), (8,4), the first two exchanged
+ * on levels of over 48 blocks per row and order > 1 (shapes 1 to 4, more act
+ * as 4; blocks of order 4 are read by two or four lanes each); with spatial
+ * factors, (4,4), (8,3), (8,4), (16,2), (16,4), (32,2) over one list of (m, a)
+ * pairs per row (1..6), or the same six over groups of rows that repeat each
+ * other, the velocity rows of a node and the pressure rows of a cell (7..12:
+ * fewer bytes); sweep_wgs = workgroups
  * of the Vanka sweep, 0 (default) for one wavefront per cell, otherwise a
  * persistent launch of that many workgroups whose wavefronts stride over the
  * cells.  The residual's summation order depends on spmv_rows (results

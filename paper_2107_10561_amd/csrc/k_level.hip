@@ -74,39 +74,15 @@ __device__ __forceinline__ void swap_halves(float& x, float& y) {
   y = __uint_as_float(yw);
 }
 
-// Transpose-reduce: NV (a power of two, 2..64) per-lane partial sums are
-// summed over the wavefront; afterwards the lanes L with L / (64 / NV) == v
-// hold the total of value v.  Each halving step exchanges half of the values
-// with the partner lane, so the cost is about NV + log2(64 / NV) shuffles.
-template <int CNT, int M, int NV>
-__device__ __forceinline__ void fold_level(double (&p)[NV], int lane) {
-  if constexpr (CNT > 1) {
-    const bool hi = lane & M;
-#pragma unroll
-    for (int t = 0; t < CNT / 2; ++t) {
-      const double keep = hi ? p[t + CNT / 2] : p[t];
-      const double send = hi ? p[t] : p[t + CNT / 2];
-      p[t] = keep + __shfl_xor(send, M, 64);
-    }
-    fold_level<CNT / 2, M / 2, NV>(p, lane);
-  }
-}
-
-template <int NV>
-__device__ __forceinline__ double fold(double (&p)[NV], int lane) {
-  fold_level<NV, 32, NV>(p, lane);
-  double u = p[0];
-#pragma unroll
-  for (int m = 32 / NV; m >= 1; m >>= 1) u += __shfl_xor(u, m, 64);
-  return u;
-}
-
-// The same transpose-reduce (FP64 or FP32 values) with the exchanges done
-// without LDS: across rows by lane-half swaps, inside a row by DPP and
-// swizzle.  Every sum takes the same two operands as in fold, so the FP64
-// results are identical.  LIVE marks the values that can be nonzero (bit v
-// for value v): a pair of slots that are both known to be zero is not
-// exchanged, which saves the padding of outputs per row up to a power of two.
+// Transpose-reduce (FP64 or FP32 values): NV (a power of two, 4..64) per-lane
+// partial sums are summed over the wavefront; afterwards the lanes L with
+// L / (64 / NV) == v hold the total of value v.  Each halving step exchanges
+// half of the values with the partner lane, so the cost is about
+// NV + log2(64 / NV) exchanges, done without LDS: across rows by lane-half
+// swaps, inside a row by DPP and swizzle.  LIVE marks the values that can be
+// nonzero (bit v for value v): a pair of slots that are both known to be zero
+// is not exchanged, which saves the padding of outputs per row up to a power
+// of two.
 template <int M, unsigned long long NEXT, int T, int H, int NV, typename V>
 __device__ __forceinline__ void fold_swap_pairs(V (&p)[NV], int lane) {
   if constexpr (T < H) {
@@ -157,96 +133,6 @@ constexpr unsigned long long live_slots(int G, int P, int U) {
   return m;
 }
 
-// ---------------------------------------------------------------------------
-// Level residual y = r + sx J x  (sx = -1: r - J x; r == nullptr: sx J x).
-// RPW consecutive block rows per 64-lane wavefront: the rows' blocks are
-// contiguous, so lane (q_off, j) streams block column j of every (64/B)-th
-// block of the whole range (consecutive lanes read consecutive doubles),
-// keeping RPW*B partial sums that one transpose-reduce folds at the end.
-// The rows per wavefront (1-4) are a per-level launch parameter: few rows
-// leave lanes idle at the end of the range, many cost registers.
-template <int B, int RPW>
-__global__ void __launch_bounds__(256) k_spmv_rows(const int32_t* __restrict__ rowptr,
-                                                   const int32_t* __restrict__ col,
-                                                   const double* __restrict__ val,
-                                                   const double* __restrict__ r,
-                                                   const double* __restrict__ x,
-                                                   double* __restrict__ y, int32_t n_rows,
-                                                   double sx) {
-  constexpr int NQ = 64 / B;
-  constexpr int NV = RPW * B;
-  constexpr int NVP = NV <= 2 ? 2 : NV <= 4 ? 4 : NV <= 8 ? 8 : NV <= 16 ? 16 : 32;
-  const int lane = threadIdx.x & 63;
-  const int row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW;
-  if (row0 >= n_rows) return;  // uniform per wavefront
-  const int qo = lane / B;
-  const int j = lane - qo * B;
-  int32_t rp[RPW + 1];
-#pragma unroll
-  for (int t = 0; t <= RPW; ++t) rp[t] = rowptr[min(row0 + t, n_rows)];
-  double acc[NVP];
-#pragma unroll
-  for (int v = 0; v < NVP; ++v) acc[v] = 0.0;
-  if (qo < NQ) {
-#pragma unroll 4
-    for (int32_t q = rp[0] + qo; q < rp[RPW]; q += NQ) {
-      const int32_t c = col[q];
-      const double xv = x[(int64_t)c * B + j];
-      const double* vb = val + (int64_t)q * (B * B) + j;
-      int rr = 0;
-#pragma unroll
-      for (int t = 1; t < RPW; ++t) rr += (q >= rp[t]) ? 1 : 0;
-#pragma unroll
-      for (int i = 0; i < B; ++i) {
-        const double pv = vb[i * B] * xv;
-#pragma unroll
-        for (int t = 0; t < RPW; ++t) acc[t * B + i] += (rr == t) ? pv : 0.0;
-      }
-    }
-  }
-  const double sum = fold<NVP>(acc, lane);
-  constexpr int SPAN = 64 / NVP;
-  const int v = lane / SPAN;
-  if ((lane % SPAN) == 0 && v < NV) {
-    const int t = v / B, i = v - (v / B) * B;
-    const int row = row0 + t;
-    if (row < n_rows) {
-      const int64_t o = (int64_t)row * B + i;
-      y[o] = r ? fma(sx, sum, r[o]) : sx * sum;
-    }
-  }
-}
-
-template <int B>
-static hipError_t spmv_b(hipStream_t s, const DevLevel& L, bool tr, const double* r,
-                         const double* x, double* y, double sx) {
-  const int rpw = L.spmv_rpw < 4 ? L.spmv_rpw : 4;
-  const int32_t* rp = tr ? L.rowptr_t : L.rowptr;
-  const int32_t* cl = tr ? L.col_t : L.col;
-  const double* vl = tr ? L.val_t : L.val;
-  if (!rp || !cl || !vl) return hipErrorInvalidValue;
-  dim3 grid((L.n_s + 4 * rpw - 1) / (4 * rpw)), block(256);
-  switch (rpw) {
-    case 1: launch(k_spmv_rows<B, 1>, dim3(grid), dim3(block), 0, s, rp, cl, vl, r, x, y, L.n_s, sx); break;
-    case 2: launch(k_spmv_rows<B, 2>, dim3(grid), dim3(block), 0, s, rp, cl, vl, r, x, y, L.n_s, sx); break;
-    case 3: launch(k_spmv_rows<B, 3>, dim3(grid), dim3(block), 0, s, rp, cl, vl, r, x, y, L.n_s, sx); break;
-    case 4: launch(k_spmv_rows<B, 4>, dim3(grid), dim3(block), 0, s, rp, cl, vl, r, x, y, L.n_s, sx); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_spmv(hipStream_t s, int b, const DevLevel& L, const double* r, const double* x,
-                       double* y, double sx, bool transposed) {
-  switch (b) {
-    case 1: return spmv_b<1>(s, L, transposed, r, x, y, sx);
-    case 2: return spmv_b<2>(s, L, transposed, r, x, y, sx);
-    case 3: return spmv_b<3>(s, L, transposed, r, x, y, sx);
-    case 4: return spmv_b<4>(s, L, transposed, r, x, y, sx);
-  }
-  return hipErrorInvalidValue;
-}
-
 // Level residual from the spatial factors of an operator whose blocks are
 // C[i][l] M + delta_il tw[i] A (time-independent coefficients): per block only
 // the two scalars m = M(s, s') and a = A(s, s') are streamed.  LPR lanes per
@@ -287,6 +173,121 @@ __device__ __forceinline__ void row_store(const double (&acc)[NV], int nv, int s
     y[o] = r ? fma(sx, s, r[o]) : sx * s;
   }
   if constexpr (E0 + LPR < NV) row_store<LPR, NV, E0 + LPR>(acc, nv, sub, o0, r, y, sx);
+}
+
+// Level residual y = r + sx J x  (sx = -1: r - J x; r == nullptr: sx J x) from
+// the blocks.  LPR lanes per block row, a block per H lanes (B / H of its rows
+// each), U blocks per lane and round, every load of a round issued before the
+// first is used (as in k_spmv_kron).  Bound by HBM, given that: the rows of a
+// 2d operator have 12 to 62 blocks, and a loop over them with a block column
+// per lane spent two dependent latencies per round of 64 / B blocks (untuned
+// shapes: 2d 256x64 dG(1), 148 MB, 41.7 -> 24.3 us, partly from the last-level
+// cache; 2d 128x64 dG(2), 154 MB, 30.8 -> 24.6; 3d 32x8x8 dG(1), 168 MB, 28.9
+// -> 26.7; 3d 32x16x8 dG(0), 112 MB, 30.6 -> 22.6).
+template <int B, int H, int LPR, int U>
+__global__ void __launch_bounds__(256) k_spmv_rows(const int32_t* __restrict__ rowptr,
+                                                   const int32_t* __restrict__ col,
+                                                   const double* __restrict__ val,
+                                                   const double* __restrict__ r,
+                                                   const double* __restrict__ x,
+                                                   double* __restrict__ y, int32_t n_rows,
+                                                   double sx) {
+  constexpr int RPWV = 64 / LPR, BH = B / H, NQ = LPR / H;
+  static_assert(B % H == 0 && (H & (H - 1)) == 0 && NQ >= BH);
+  const int lane = threadIdx.x & 63, sub = lane % LPR, part = sub % H, slot = sub / H;
+  const int row = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPWV + lane / LPR;
+  const bool live = row < n_rows;
+  const int rr = live ? row : n_rows - 1;
+  double acc[BH];
+#pragma unroll
+  for (int i = 0; i < BH; ++i) acc[i] = 0.0;
+  const int32_t q1 = rowptr[rr + 1];
+  for (int32_t q0 = rowptr[rr]; q0 < q1; q0 += U * NQ) {
+    int64_t c[U];
+    double f[U][BH * B];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t q = min(q0 + slot + u * NQ, q1 - 1);
+      c[u] = col[q];
+      const double* vb = val + (int64_t)q * (B * B) + part * (BH * B);
+#pragma unroll
+      for (int e = 0; e < BH * B; ++e) f[u][e] = vb[e];
+    }
+    double xl[U][B];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int l = 0; l < B; ++l) xl[u][l] = x[c[u] * B + l];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < BH; ++i) {
+        double s = acc[i];
+#pragma unroll
+        for (int l = 0; l < B; ++l) s = fma(f[u][i * B + l], xl[u][l], s);
+        acc[i] = q0 + slot + u * NQ < q1 ? s : acc[i];
+      }
+  }
+#pragma unroll
+  for (int off = LPR / 2; off >= H; off >>= 1)
+#pragma unroll
+    for (int i = 0; i < BH; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
+  // entry part * BH + slot from the lane of that part and slot
+  double s = acc[0];
+#pragma unroll
+  for (int i = 1; i < BH; ++i) s = slot == i ? acc[i] : s;
+  if (live && slot < BH) {
+    const int64_t o = (int64_t)row * B + part * BH + slot;
+    y[o] = r ? fma(sx, s, r[o]) : sx * s;
+  }
+}
+
+template <int B>
+static hipError_t spmv_b(hipStream_t s, const DevLevel& L, bool tr, const double* r,
+                         const double* x, double* y, double sx) {
+  const int32_t* rp = tr ? L.rowptr_t : L.rowptr;
+  const int32_t* cl = tr ? L.col_t : L.col;
+  const double* vl = tr ? L.val_t : L.val;
+  if (!rp || !cl || !vl) return hipErrorInvalidValue;
+#define STV_SPMV(H, LPR, U)                                                                       \
+  launch(k_spmv_rows<B, H, LPR, U>, dim3((L.n_s + 256 / LPR - 1) / (256 / LPR)), dim3(256), 0, s, \
+         rp, cl, vl, r, x, y, L.n_s, sx)
+  // shapes 1 to 4 (more act as 4).  A block of order 4 is two lines, which four
+  // lanes read together (2d 128x32 dG(3): 21 us, one lane per block 28 us).
+  // Shape 2 is what is used without tuning: two rounds of 16 lanes take most 2d
+  // rows at once; rows of over 48 blocks on average (3d) have 32 lanes
+  // (168 MB of dG(1) 27.6 -> 26.7 us, 177 MB of dG(2) 31.6 -> 29.9 us; dG(0),
+  // of an eighth of the bytes per block, 22.6 -> 27.4 us and so does not).
+  int shape = L.spmv_rpw;
+  if (B > 1 && shape <= 2 && L.nnzb > 48 * (int64_t)L.n_s) shape = 3 - shape;
+  if constexpr (B == 4) {
+    switch (shape) {
+      case 1: STV_SPMV(4, 64, 2); break;
+      case 2: STV_SPMV(4, 32, 2); break;
+      case 3: STV_SPMV(2, 32, 1); break;
+      default: STV_SPMV(2, 16, 2); break;
+    }
+  } else {
+    switch (shape) {
+      case 1: STV_SPMV(1, 32, 2); break;
+      case 2: STV_SPMV(1, 16, 2); break;
+      case 3: STV_SPMV(1, 32, 1); break;
+      default: STV_SPMV(1, 8, 4); break;
+    }
+  }
+#undef STV_SPMV
+  return hipGetLastError();
+}
+
+hipError_t launch_spmv(hipStream_t s, int b, const DevLevel& L, const double* r, const double* x,
+                       double* y, double sx, bool transposed) {
+  switch (b) {
+    case 1: return spmv_b<1>(s, L, transposed, r, x, y, sx);
+    case 2: return spmv_b<2>(s, L, transposed, r, x, y, sx);
+    case 3: return spmv_b<3>(s, L, transposed, r, x, y, sx);
+    case 4: return spmv_b<4>(s, L, transposed, r, x, y, sx);
+  }
+  return hipErrorInvalidValue;
 }
 
 // acc += the (m, a) blocks [q0, q1) of one row (list position in ma and col).

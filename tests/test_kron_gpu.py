@@ -290,3 +290,41 @@ def test_residual_row_groups(stv, name, change):
         out = to_dev(np.zeros(n * p.b))
         s.residual(len(levels) - 1, to_dev(r), to_dev(d), out)
         assert (np.abs(to_host(out) - ref) <= 360 * 2.0 ** -53 * scale).all()
+
+
+@pytest.mark.parametrize("k", [0, 1, 2, 3])
+@pytest.mark.parametrize("long_rows", [False, True])
+def test_block_residual_row_lengths(stv, k, long_rows):
+    """The block residual on rows of no, one and many blocks, around every
+    multiple of a round, in every shape, with and without r; long_rows: over
+    48 blocks per row on average (the default shape changes there)."""
+    p = make_problem(2, (9, 5), 1, k, 0.01, 1e-3, 7)
+    L, b = p.levels[0], p.b
+    n = L.n_sdofs
+    rng = np.random.default_rng(41)
+    lens = rng.choice([0, 1, 7, 8, 15, 16, 17, 31, 32, 33, 63, 64, 65, 200, 300, 300], n)
+    if not long_rows:
+        lens = np.minimum(lens, 33)
+    lens[0], lens[-1] = 0, 0
+    cols = [np.sort(rng.choice(n, m, replace=False)) for m in lens]
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = np.concatenate(cols).astype(np.int32)
+    assert (len(col) > 48 * n) == long_rows
+    val = rng.standard_normal((len(col), b, b))
+    s = stv.Solver(0)
+    s.set_hierarchy([dict(n_sdofs=n, rowptr=rowptr, col=col, val=val, cell_sdofs=L.cell_sdofs,
+                          P=None)], 2, k)
+    r, d = rng.standard_normal((n, b)), rng.standard_normal((n, b))
+    rows = np.repeat(np.arange(n), lens)
+    Jd, scale = np.zeros((n, b)), np.abs(r)
+    np.add.at(Jd, rows, np.matmul(val, d[col][:, :, None])[:, :, 0])
+    np.add.at(scale, rows, np.matmul(np.abs(val), np.abs(d[col])[:, :, None])[:, :, 0])
+    for shape in (1, 2, 3, 4, 9):
+        s.set_launch(0, shape, 0)
+        for rhs in (r, None):
+            out = to_dev(np.full(n * b, np.nan))
+            s.residual(0, None if rhs is None else to_dev(rhs.reshape(-1)), to_dev(d.reshape(-1)), out)
+            # a sum of at most 1200 products in two orders
+            err = np.abs(to_host(out).reshape(n, b) - ((0.0 if rhs is None else rhs) - Jd))
+            assert (err <= 2400 * np.finfo(float).eps * scale).all(), shape
+    s.close()
