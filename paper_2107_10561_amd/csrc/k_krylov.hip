@@ -9,6 +9,7 @@
 namespace stv {
 
 constexpr int kGroup = 8;
+constexpr int kStepCols = 256;
 
 int seg_blocks(const Segs& g) {
   // kDotBlocks shared among the instances, at least 4 each; for a batch also
@@ -265,6 +266,132 @@ hipError_t launch_scale_by_norm(hipStream_t s, const double* w, const double* nr
                                 int64_t nstride, double* v, const Segs& g) {
   dim3 grid((unsigned)((g.max_seg + 255) / 256), (unsigned)g.nseg);
   k_scale_by_norm<<<grid, 256, 0, s>>>(w, nrm2, nstride, v, g.seg);
+  return hipGetLastError();
+}
+
+// One Arnoldi step's Gram-Schmidt on short segments, a workgroup per segment
+// with its part of w in registers (E entries per thread):
+//   h1 = V'w, w -= V h1, h2 = V'w, w -= V h2, nrm = w.w, v = w / ||w||
+// (0 where the norm is 0), V's columns in groups of kGroup.  Bound by latency
+// either way: the separate kernels are 7 launches up to 8 columns and 20 at 30.
+constexpr int kStepThreads = 1024;   // 16 wavefronts (step_sums)
+
+// Sum over the workgroup of acc[lane & 7], in every lane.
+__device__ __forceinline__ double step_sums(double (&acc)[kGroup], double (*red)[kGroup]) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  // eight sums over 64 lanes by exchange: lane l ends with sum l >> 3
+#pragma unroll
+  for (int half = 4, off = 32; half >= 1; half >>= 1, off >>= 1) {
+    const bool hi = lane & off;
+#pragma unroll
+    for (int k = 0; k < half; ++k) {
+      const double a = acc[k], b = acc[k + half];
+      acc[k] = (hi ? b : a) + __shfl_xor(hi ? a : b, off, 64);
+    }
+  }
+  double t = acc[0];
+#pragma unroll
+  for (int off = 4; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
+  __syncthreads();   // the last sums have been read
+  if ((lane & 7) == 0) red[wv][lane >> 3] = t;
+  __syncthreads();
+  // 16 wavefronts' sums: two per lane, then over the lanes of equal lane & 7
+  double u = red[lane >> 3][lane & 7] + red[8 + (lane >> 3)][lane & 7];
+#pragma unroll
+  for (int off = 8; off <= 32; off <<= 1) u += __shfl_xor(u, off, 64);
+  return u;
+}
+
+template <int E>
+__global__ void __launch_bounds__(kStepThreads) k_cgs2_step(const double* __restrict__ V, int m,
+                                                            int64_t n,
+                                                            const double* __restrict__ w,
+                                                            const int64_t* __restrict__ seg,
+                                                            double* __restrict__ h1,
+                                                            double* __restrict__ h2,
+                                                            int64_t hstride,
+                                                            double* __restrict__ nrm,
+                                                            double* __restrict__ v) {
+  __shared__ double red[kStepThreads / 64][kGroup];
+  __shared__ double coef[kStepCols];
+  const int z = blockIdx.x, tid = threadIdx.x;
+  const int64_t lo = seg[z], hi = seg[z + 1];
+  // entries past the segment's end: its last one, weighted by zero
+  int64_t at[E];
+  double x[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int64_t i = lo + tid + (int64_t)e * kStepThreads;
+    at[e] = i < hi ? i : hi - 1;
+    x[e] = i < hi ? w[at[e]] : 0.0;
+  }
+  for (int pass = 0; pass < 2; ++pass) {
+    double* h = (pass ? h2 : h1) + z * hstride;
+    for (int k0 = 0; k0 < m; k0 += kGroup) {
+      double acc[kGroup];
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        const double* col = V + (int64_t)min(k0 + k, m - 1) * n;
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) s = fma(col[at[e]], x[e], s);
+        acc[k] = s;
+      }
+      const double sum = step_sums(acc, red);
+      if (tid < kGroup && k0 + tid < m) {
+        coef[k0 + tid] = sum;
+        h[k0 + tid] = sum;
+      }
+    }
+    __syncthreads();
+    double s[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) s[e] = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < m; ++k) {
+      const double c = coef[k];
+#pragma unroll
+      for (int e = 0; e < E; ++e) s[e] = fma(c, V[(int64_t)k * n + at[e]], s[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      x[e] = lo + tid + (int64_t)e * kStepThreads < hi ? x[e] - s[e] : 0.0;
+    __syncthreads();   // coef has been read
+  }
+  double acc[kGroup] = {};
+#pragma unroll
+  for (int e = 0; e < E; ++e) acc[0] = fma(x[e], x[e], acc[0]);
+  const double nr2 = __shfl(step_sums(acc, red), 0, 64);
+  const double nr = sqrt(nr2);
+  if (tid == 0) nrm[z] = nr2;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int64_t i = lo + tid + (int64_t)e * kStepThreads;
+    if (i < hi) v[i] = nr > 0.0 ? x[e] / nr : 0.0;
+  }
+}
+
+// Four entries per thread: one compute unit reads V's columns four times, which
+// at 7,332 entries costs more than the launches (10 and 30 steps of FGMRES on
+// 2d operators, separate kernels -> one: 402 entries 0.85 -> 0.65 and 3.44 ->
+// 2.06 ms, 1,540 0.91 -> 0.73 and 3.65 -> 2.38, 3,012 0.93 -> 0.81 and 3.64 ->
+// 2.77, 7,332 0.98 -> 1.07 and 3.81 -> 4.41).
+bool cgs2_step_fits(int m, const Segs& g) {
+  return m <= kStepCols && g.max_seg <= 4 * kStepThreads;
+}
+
+hipError_t launch_cgs2_step(hipStream_t s, const double* V, int m, const double* w, int64_t n,
+                            const Segs& g, double* h1, double* h2, int64_t hstride, double* nrm,
+                            double* v) {
+  if (m < 1 || !cgs2_step_fits(m, g)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)g.nseg);
+  const int64_t e = (g.max_seg + kStepThreads - 1) / kStepThreads;
+#define STV_STEP(E) \
+  k_cgs2_step<E><<<grid, kStepThreads, 0, s>>>(V, m, n, w, g.seg, h1, h2, hstride, nrm, v)
+  if (e <= 1) STV_STEP(1);
+  else if (e <= 2) STV_STEP(2);
+  else STV_STEP(4);
+#undef STV_STEP
   return hipGetLastError();
 }
 

@@ -2797,17 +2797,24 @@ int stv_gmres_solve(stv_ctx* ctx, const double* bvec, double* x, const stv_gmres
         // is fused with the products that follow it (one pass over V and w
         // fewer each; the same blocks and order of operations as the separate
         // kernels), the first while V has at most kKrylovFuse columns.
-        STV_HIP(launch_multidot(s, ctx->V, j + 1, ctx->w, n, sg, ctx->partial, ctx->scal + lay.h1(0), kScalR));
-        if (j + 1 <= kKrylovFuse) {
-          STV_HIP(launch_multiaxpy_dot(s, ctx->V, j + 1, ctx->scal + lay.h1(0), kScalR, -1.0, ctx->w, n, sg,
-                                       ctx->partial, ctx->scal + lay.h2(0), kScalR));
+        // On short segments all of it is one launch.
+        if (cgs2_step_fits(j + 1, sg)) {
+          STV_HIP(launch_cgs2_step(s, ctx->V, j + 1, ctx->w, n, sg, ctx->scal + lay.h1(0),
+                                   ctx->scal + lay.h2(0), kScalR, ctx->scal + lay.nrm(),
+                                   ctx->V + (int64_t)(j + 1) * n));
         } else {
-          STV_HIP(launch_multiaxpy(s, ctx->V, j + 1, ctx->scal + lay.h1(0), kScalR, -1.0, ctx->w, n, sg));
-          STV_HIP(launch_multidot(s, ctx->V, j + 1, ctx->w, n, sg, ctx->partial, ctx->scal + lay.h2(0), kScalR));
+          STV_HIP(launch_multidot(s, ctx->V, j + 1, ctx->w, n, sg, ctx->partial, ctx->scal + lay.h1(0), kScalR));
+          if (j + 1 <= kKrylovFuse) {
+            STV_HIP(launch_multiaxpy_dot(s, ctx->V, j + 1, ctx->scal + lay.h1(0), kScalR, -1.0, ctx->w, n, sg,
+                                         ctx->partial, ctx->scal + lay.h2(0), kScalR));
+          } else {
+            STV_HIP(launch_multiaxpy(s, ctx->V, j + 1, ctx->scal + lay.h1(0), kScalR, -1.0, ctx->w, n, sg));
+            STV_HIP(launch_multidot(s, ctx->V, j + 1, ctx->w, n, sg, ctx->partial, ctx->scal + lay.h2(0), kScalR));
+          }
+          STV_HIP(launch_multiaxpy_nrm(s, ctx->V, j + 1, ctx->scal + lay.h2(0), kScalR, -1.0, ctx->w, n, sg,
+                                       ctx->partial, ctx->scal + lay.nrm(), 1));
+          STV_HIP(launch_scale_by_norm(s, ctx->w, ctx->scal + lay.nrm(), 1, ctx->V + (int64_t)(j + 1) * n, sg));
         }
-        STV_HIP(launch_multiaxpy_nrm(s, ctx->V, j + 1, ctx->scal + lay.h2(0), kScalR, -1.0, ctx->w, n, sg,
-                                     ctx->partial, ctx->scal + lay.nrm(), 1));
-        STV_HIP(launch_scale_by_norm(s, ctx->w, ctx->scal + lay.nrm(), 1, ctx->V + (int64_t)(j + 1) * n, sg));
         t.done();
       }
       STV_HIP(hipMemcpyAsync(hbuf[j & 1], ctx->scal, sizeof(double) * (lay.nrm() + S),

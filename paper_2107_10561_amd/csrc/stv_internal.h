@@ -531,6 +531,11 @@ hipError_t launch_multiaxpy_nrm(hipStream_t s, const double* V, int m, const dou
                                 const Segs& g, double* partial, double* out, int64_t ostride);
 hipError_t launch_multiaxpy(hipStream_t s, const double* V, int m, const double* coef,
                             int64_t cstride, double sign, double* w, int64_t n, const Segs& g);
+// a whole Gram-Schmidt step in one launch, for short segments
+bool cgs2_step_fits(int m, const Segs& g);
+hipError_t launch_cgs2_step(hipStream_t s, const double* V, int m, const double* w, int64_t n,
+                            const Segs& g, double* h1, double* h2, int64_t hstride, double* nrm,
+                            double* v);
 hipError_t launch_scale_by_norm(hipStream_t s, const double* w, const double* nrm2,
                                 int64_t nstride, double* v, const Segs& g);
 
