@@ -1835,11 +1835,12 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     }
     CcDims& D = ctx->cc_dims[g];
     // The whole inverse: always with the all-rows layout, whose transposed
-    // solves need it (a second set of factored kernels otherwise); else where
-    // a solve of some 10 cycles wins it back.  Forming it and an apply then
-    // and without: order 132 26 us, 3.9 and 6.5 us; 786 23 us, 4.0 and 8.1;
-    // 1572 40 to 90 us, 6.4 and 9.1; from 2055 the applies are equal.
-    D.form_x = full || (rows <= 1024 && fp + fx <= 1e9);
+    // solves need it (a second set of factored kernels otherwise); else while
+    // one launch is faster than two.  Forming it and an apply then and
+    // without: order 132 26 us, 3.9 and 6.5 us; 786 23 us, 4.0 and 8.1; 1188
+    // 4.8 and 7.8; 1572 40 to 90 us, 6.4 and 9.1; from 2055 the applies are
+    // equal.
+    D.form_x = full || (rows <= 1600 && fp + fx <= 4e9);
     D.form_p = D.form_x || fp <= 2e9;
     if (D.form_x)
       for (CoarseDesc& c : ctx->h_coarse[g])
