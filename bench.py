@@ -150,11 +150,14 @@ def sweep_bytes(L, b, inv_bytes, zero_init_fraction):
     return inv_bytes + idx + vec
 
 
-def residual_bytes(L, b, kron=False, n_mass=None):
-    """Algorithmic bytes of one level residual: blocks (or the spatial factor
-    values of each block: (m, a) where the mass entry m is nonzero, a alone
-    elsewhere; n_mass = number of blocks with m != 0), columns, row
-    pointers, x, r and y once each."""
+def residual_bytes(L, b, kron=False, n_mass=None, dim=2):
+    """Algorithmic bytes of one level residual: blocks, or the spatial factors;
+    columns, row pointers, x, r and y once each.  With factors either one list
+    of (m, a) pairs, or (n_mass = number of blocks with m != 0) rows read in
+    groups: the dim velocity rows of a node share their (m, a) pairs and
+    columns, a coupling to the pressure has a column per dim values, and the
+    dim + 1 pressure rows of a cell a column per node and dim (dim + 1) values.
+    Rows on a wall that do not group cost more than is counted here."""
     nnzb = int(L.col.shape[0])
     n_st = L.n_sdofs * b
     vec = 3 * n_st * 8
@@ -162,8 +165,11 @@ def residual_bytes(L, b, kron=False, n_mass=None):
         return nnzb * (b * b * 8 + 4) + (L.n_sdofs + 1) * 4 + vec
     if n_mass is None:     # one list of (m, a) pairs
         return nnzb * (16 + 4) + (L.n_sdofs + 1) * 4 + vec
-    n1 = int(n_mass)
-    return n1 * (16 + 4) + (nnzb - n1) * (8 + 4) + 2 * (L.n_sdofs + 1) * 4 + vec
+    pairs = int(n_mass) / dim
+    half = (nnzb - int(n_mass)) / 2      # couplings of velocity rows, of pressure rows
+    nodes = (L.n_sdofs - (dim + 1) * L.n_cells) / dim
+    return int(pairs * (16 + 4) + 2 * half * 8 + 4 * (half / dim + half / (dim * (dim + 1))) +
+               4 * (3 * nodes + 2 * L.n_cells)) + vec
 
 
 def cpu_baseline(workload, nu1, nu2, omega):
@@ -506,37 +512,21 @@ def newton_bench(args):
 FP64_PEAK_TFLOPS = 78.6
 
 
-def inverse_flops_per_cell(dim, k, n_ls, dec, cx=False):
-    """Flops of the Gauss-Jordan inversion(s) one cell's build runs: 2 n^3 for
-    an explicit inverse of order n.  The time-decoupled build (2d levels with
-    spatial factors) inverts one block of order n_ls per real eigenvalue of the
-    time matrix and the real form (order 2 n_ls) of one block per complex
-    pair instead of the whole J_T of order (k+1) n_ls; the complex build (3d
-    dG(1) levels with spatial factors) inverts the complex block of order n_ls
-    in complex arithmetic, 8 n_ls^3 real flops."""
+def inverse_flops_per_cell(dim, k, n_ls, comp):
+    """Flops of one cell's inversion: 2 n^3 for an explicit inverse of order n.
+    With spatial factors each time block (real, or complex at four times the
+    flops for a pair) is eliminated by velocity component: one block of order
+    3^dim, shared by the components away from the walls, its products with the
+    couplings of every component to the dim + 1 pressure rows, both ways, and
+    in 2d, where the owned rows are stored whole, the border's product."""
     b = k + 1
-    if cx:
-        return 8 * n_ls ** 3
-    if dec:
-        n_pairs = b // 2
-        n_real = b - 2 * n_pairs
-        return n_real * 2 * n_ls ** 3 + n_pairs * 2 * (2 * n_ls) ** 3
-    return 2 * (b * n_ls) ** 3
-
-
-def coarse_flops(k, n_s, kron):
-    """Flops of the coarse Gauss-Jordan inverse: 2 N^3 for the whole matrix of
-    order N = (k+1) n_s; with spatial factors the eliminated matrices are the
-    real forms (order 2 n_s) of the pair blocks, and of the real eigenvalues'
-    blocks padded into the same launches (one real-form block per two real
-    eigenvalues, rounded up)."""
-    b = k + 1
-    if not kron:
-        return 2 * (b * n_s) ** 3
+    if not comp:
+        return 2 * (b * n_ls) ** 3
     n_pairs = b // 2
     n_real = b - 2 * n_pairs
-    blocks = n_pairs + (n_real + 1) // 2
-    return blocks * 2 * (2 * n_s) ** 3
+    nv, q = 3 ** dim, dim + 1
+    one = 2 * nv ** 3 + 4 * dim * nv * nv * q + (2 * (dim * nv) ** 2 * q if dim == 2 else 0)
+    return (n_real + 4 * n_pairs) * one
 
 
 def measured_peaks():
@@ -690,11 +680,11 @@ def run_workload(args, name, legs=True):
         return inv_b[g] + sum(sweep_bytes(L, b, 0, zi) for L, sm in members[g] if sm)
 
     def residual_bytes_packed(g):
-        # the split lists (shapes 7..12) stream a alone where m = 0
-        split = kron and shapes is not None and shapes.get(str(g), [0])[0] >= 7
-        nm = n_mass.get(g) if split else None
+        # shapes 7..12 read the rows in groups
+        groups = kron and shapes is not None and shapes.get(str(g), [0])[0] >= 7
+        nm = n_mass.get(g) if groups else None
         nm = nm or [None] * len(members[g])
-        return sum(residual_bytes(L, b, kron, q) for (L, _), q in zip(members[g], nm))
+        return sum(residual_bytes(L, b, kron, q, dim) for (L, _), q in zip(members[g], nm))
 
     def roofline(cls, bytes_of, kernel, traffic_key):
         """The finest level's launches of the kernel in the timed region: the
@@ -728,7 +718,7 @@ def run_workload(args, name, legs=True):
     # with spatial factors the library stores the owned rows of 2d cell
     # problems (n_loc = 21, B <= 3) time-decoupled and sweeps with k_vanka_dec
     # (one row per owned spatial DoF), and those of 3d dG(1) levels (one complex
-    # pair: k_inverse_cx) as complex rows swept by k_vanka_cx
+    # pair) by velocity component, swept by k_vanka_comp
     dec = kron and dim == 2 and 2 <= b <= 3
     cx = kron and dim == 3 and b == 2
     if dec:
@@ -737,15 +727,15 @@ def run_workload(args, name, legs=True):
                               "k_vanka_dec")
     elif cx:
         roof_sweep = roofline("sweep", sweep_bytes_packed,
-                              "Vanka cell sweep on complex time-decoupled inverses (k_vanka_cx)",
-                              "k_vanka_cx")
+                              "Vanka cell sweep on inverses by velocity component (k_vanka_comp)",
+                              "k_vanka_comp")
     else:
         roof_sweep = roofline("sweep", sweep_bytes_packed, "Vanka cell sweep (k_vanka)", "k_vanka")
-    split_top = kron and shapes is not None and shapes.get(str(top), [0])[0] >= 7
-    if split_top:
-        kname_res = "level residual from spatial factors, split lists (k_spmv_kron)"
+    groups_top = kron and shapes is not None and shapes.get(str(top), [0])[0] >= 7
+    if groups_top:
+        kname_res = "level residual from spatial factors, row groups (k_spmv_group)"
     roof_res = roofline("residual", residual_bytes_packed, kname_res,
-                        ("k_spmv_kron_split" if split_top else "k_spmv_kron") if kron
+                        ("k_spmv_group" if groups_top else "k_spmv_kron") if kron
                         else "k_spmv")
     # time per kernel class (and both kernels over every level) from one more
     # step with every class and level timed, outside the timed region: the
@@ -764,9 +754,7 @@ def run_workload(args, name, legs=True):
     for g in range(1, G):
         for L, sm in members[g]:
             if sm:
-                inv_flops += L.n_cells * inverse_flops_per_cell(dim, k, L.cell_sdofs.shape[1], dec,
-                                                                cx=cx)
-    crs_flops = sum(coarse_flops(k, p.levels[0].n_sdofs, kron) for p in probs)
+                inv_flops += L.n_cells * inverse_flops_per_cell(dim, k, L.cell_sdofs.shape[1], dec or cx)
     n_inv, ms_inv = s.kernel_stats("inverse")
     n_crs, ms_crs = s.kernel_stats("coarse_factor")
 
@@ -777,10 +765,12 @@ def run_workload(args, name, legs=True):
                     ms_per_build=round(ms, 3), launches=launches, kernel=kernel)
     inv_roof = dict(
         cell_inverses=flop_roof(inv_flops, ms_inv, "cell inverses, every smoothed level "
-                                "(k_inverse_cx)" if cx else "cell inverses, every smoothed level "
-                                "(k_inverse_wave / k_inverse_mfma)", n_inv),
-        coarse=flop_roof(crs_flops, ms_crs, "coarse Gauss-Jordan inverse chain "
-                         "(k_gj_tour_cx / k_gj_slab_update and helpers)", n_crs),
+                                "(k_inverse_comp)" if dec or cx else "cell inverses, every "
+                                "smoothed level (k_inverse_wave / k_inverse_mfma)", n_inv),
+        # the blocks the separators cut are the library's choice: no flops here
+        coarse=dict(bound="latency", ms_per_build=round(ms_crs, 3), launches=n_crs,
+                    kernel="coarse blocks, border and factors (k_gj_tour_cx, "
+                           "k_gj_slab_update_cx, k_cc_*)"),
         concurrent="the coarse chain runs on a second stream beside the cell inverses; "
                    "each class's time includes the contention")
     s.set_timing(False)
@@ -893,8 +883,6 @@ def main():
         peaks["sweep_frac_of_copy"] = round(main_res["roofline"]["achieved"] / peaks["copy_GBps"], 4)
         peaks["cell_inverses_frac_of_dgemm"] = round(
             main_res["inverse_roofline"]["cell_inverses"]["achieved"] / peaks["dgemm_TFLOPs"], 4)
-        peaks["coarse_frac_of_dgemm"] = round(
-            main_res["inverse_roofline"]["coarse"]["achieved"] / peaks["dgemm_TFLOPs"], 4)
     cpu = None
     if not args.no_cpu_baseline:
         print("[bench] cpu baseline (oracle) ...", file=sys.stderr, flush=True)
