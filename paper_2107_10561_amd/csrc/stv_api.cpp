@@ -129,6 +129,7 @@ void free_coarse_groups(stv_ctx* ctx) {
   }
   for (void*& p : ctx->cc_bufs) dfree(p);
   ctx->cc_bufs.clear();
+  ctx->cc_slots.clear();   // they index the members in h_cc
   for (int g = 0; g < kMaxLevels; ++g) {
     ctx->h_cc[g].clear();
     dfree(ctx->d_cc[g]);
@@ -1902,8 +1903,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     D.cnt += 1;
   }
   // the slots' verdicts: consecutive in the report, v groups then s groups
-  // (assigned with the report, see assign_verdicts)
-  ctx->cc_slots.clear();
+  // (assigned with the report, see upload_component_members)
   for (const Member& M : mem) {
     std::array<int, 4 * (kCcMax + 1)> v;
     v.fill(-1);
@@ -1923,6 +1923,8 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
 static int upload_component_members(stv_ctx* ctx, int* report) {
   std::vector<size_t> next((size_t)ctx->n_levels, 0);
   for (const auto& sl : ctx->cc_slots) {
+    if (sl.first >= ctx->n_levels || next[(size_t)sl.first] >= ctx->h_cc[sl.first].size())
+      return fail(ctx, STV_ESTATE, "coarse verdicts without their members");
     CompCoarse& R = ctx->h_cc[sl.first][next[(size_t)sl.first]++];
     R.X = ctx->cc_dims[sl.first].form_x ? ctx->coarse_inv + R.X_off : nullptr;
     for (int p = 0; p < 4; ++p)
