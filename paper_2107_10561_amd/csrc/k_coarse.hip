@@ -47,15 +47,6 @@ __device__ __forceinline__ void atomic_max_bits(unsigned long long* at, double v
   atomicMax(at, __builtin_bit_cast(unsigned long long, v));
 }
 
-__device__ __forceinline__ double wave_fmax(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double o = __shfl_xor(v, off, 64);
-    v = (v != v || v > o) ? v : o;   // a NaN wins
-  }
-  return v;
-}
-
 // The dense V_c and D in real form (the matrices zeroed before): member row
 // blockIdx.x, time block blockIdx.y, member blockIdx.z; one wavefront per row.
 // Only couplings inside a block and inside the border are written here.
@@ -70,51 +61,39 @@ __global__ void __launch_bounds__(64) k_cc_fill(const CompCoarse* __restrict__ c
   double* A = M.A[p][border ? kCcMax : c];
   const int64_t ld = M.lda[border ? kCcMax : c];
   const int32_t row = M.row_off + M.order[e];
-  double mx = 0.0;
   for (int32_t q = M.rowptr[row] + (int)threadIdx.x; q < M.rowptr[row + 1]; q += 64) {
     const int j = M.where[M.col[q] - M.row_off] - o;
     if (j < 0 || j >= n) continue;
     const double2 v = cc_value(M, p, q);
     *reinterpret_cast<double2*>(&A[2 * (int64_t)i * ld + 2 * j]) = make_double2(v.x, -v.y);
     *reinterpret_cast<double2*>(&A[(2 * (int64_t)i + 1) * ld + 2 * j]) = make_double2(v.y, v.x);
-    mx = fmax(mx, fabs(v.x) + fabs(v.y));
   }
-  mx = wave_fmax(mx);
-  if (threadIdx.x == 0 && !border) atomic_max_bits(&M.norm[p][c][0], mx);
 }
 
 // Inverse rows out of the eliminated real form, in natural order: row i is S's
 // row rpiv[2i], column 2t belongs to j = rpiv[2t] / 2.  Nothing is read where
 // the pivot record is not a permutation (verdict).
 __device__ __forceinline__ void cc_collect(const double* A, int64_t ld, const int* rpiv, int n,
-                                           int i, bool pair, double2* out,
-                                           unsigned long long* norm) {
+                                           int i, bool pair, double2* out) {
   const double* row = A + (int64_t)rpiv[2 * i] * ld;
-  double mx = 0.0;
   for (int t = threadIdx.x; t < n; t += 256) {
     const double2 e = *reinterpret_cast<const double2*>(row + 2 * (int64_t)t);
     cc_put(out, (int64_t)i * n + (rpiv[2 * t] >> 1), pair, make_double2(e.x, -e.y));
-    const double m = fabs(e.x) + fabs(e.y);
-    mx = (m != m || m > mx) ? m : mx;
   }
-  mx = wave_fmax(mx);
-  if ((threadIdx.x & 63) == 0) atomic_max_bits(norm, mx);
 }
 
 __global__ void __launch_bounds__(256) k_cc_collect_v(const CompCoarse* __restrict__ cc, int nc) {
   const CompCoarse& M = cc[blockIdx.z];
   const int p = blockIdx.y / nc, c = blockIdx.y % nc, i = blockIdx.x;
   if (p >= M.nblk || c >= M.nc || i >= M.n[c] || *M.verdict[p][c]) return;
-  cc_collect(M.A[p][c], M.lda[c], M.rpiv[p][c], M.n[c], i, M.sz[p] == 2, M.Vi[p][c],
-             &M.norm[p][c][1]);
+  cc_collect(M.A[p][c], M.lda[c], M.rpiv[p][c], M.n[c], i, M.sz[p] == 2, M.Vi[p][c]);
 }
 
 __global__ void __launch_bounds__(256) k_cc_collect_s(const CompCoarse* __restrict__ cc) {
   const CompCoarse& M = cc[blockIdx.z];
   const int p = blockIdx.y, m = blockIdx.x;
   if (p >= M.nblk || m >= M.n_p || *M.verdict[p][kCcMax]) return;
-  cc_collect(M.A[p][kCcMax], M.lda[kCcMax], M.rpiv[p][kCcMax], M.n_p, m, true,
-             M.Si[p], &M.norm[p][kCcMax][1]);
+  cc_collect(M.A[p][kCcMax], M.lda[kCcMax], M.rpiv[p][kCcMax], M.n_p, m, true, M.Si[p]);
 }
 
 // Z = C V^-1, row m: the border row's entries in block c (listed at cptr) times
@@ -187,29 +166,23 @@ __global__ void __launch_bounds__(256) k_cc_s(const CompCoarse* __restrict__ cc)
   const CompCoarse& M = cc[blockIdx.z / 4];
   const int p = blockIdx.z % 4, m0 = blockIdx.x * kRows, col = blockIdx.y * 256 + (int)threadIdx.x;
   if (p >= M.nblk || m0 >= M.n_p) return;
+  if (col >= M.n_p) return;
   double* A = M.A[p][kCcMax];
   const int64_t ld = M.lda[kCcMax];
-  double mx = 0.0;
-  if (col < M.n_p) {
-    const double2* Z = M.Z[p];
-    double2 acc[kRows];
-    cc_times_b(M, p, M.bptr[col * M.nc], M.bptr[(col + 1) * M.nc],
-               [&](int k, int j) { return Z[(int64_t)min(m0 + k, M.n_p - 1) * M.n_v + j]; }, acc);
+  const double2* Z = M.Z[p];
+  double2 acc[kRows];
+  cc_times_b(M, p, M.bptr[col * M.nc], M.bptr[(col + 1) * M.nc],
+             [&](int k, int j) { return Z[(int64_t)min(m0 + k, M.n_p - 1) * M.n_v + j]; }, acc);
 #pragma unroll
-    for (int k = 0; k < kRows; ++k) {
-      if (m0 + k >= M.n_p) continue;
-      double2* even = reinterpret_cast<double2*>(&A[2 * (int64_t)(m0 + k) * ld + 2 * col]);
-      const double2 d = *even;
-      const double re = d.x - acc[k].x, im = -d.y - acc[k].y;
-      *even = make_double2(re, -im);
-      *reinterpret_cast<double2*>(&A[(2 * (int64_t)(m0 + k) + 1) * ld + 2 * col]) =
-          make_double2(im, re);
-      const double t = fabs(re) + fabs(im);
-      mx = (t != t || t > mx) ? t : mx;
-    }
+  for (int k = 0; k < kRows; ++k) {
+    if (m0 + k >= M.n_p) continue;
+    double2* even = reinterpret_cast<double2*>(&A[2 * (int64_t)(m0 + k) * ld + 2 * col]);
+    const double2 d = *even;
+    const double re = d.x - acc[k].x, im = -d.y - acc[k].y;
+    *even = make_double2(re, -im);
+    *reinterpret_cast<double2*>(&A[(2 * (int64_t)(m0 + k) + 1) * ld + 2 * col]) =
+        make_double2(im, re);
   }
-  mx = wave_fmax(mx);
-  if ((threadIdx.x & 63) == 0) atomic_max_bits(&M.norm[p][kCcMax][0], mx);
 }
 
 // A 32 x 32 tile of a complex (real: pair false) matrix product on FP64 matrix
@@ -384,16 +357,178 @@ __global__ void __launch_bounds__(256) k_cc_x(const CompCoarse* __restrict__ cc)
   }
 }
 
-// A block whose largest entry times its inverse's largest is above 1e10 (or
-// not finite) is not trusted: its verdict is set, and the build then
-// eliminates the whole coarse matrix.
+// ---------------------------------------------------------------------------
+// Whether the parts give an inverse.  Each V_c takes its pivots in itself, so a
+// velocity block that is nearly singular inside a well-conditioned matrix leaves
+// V^-1 and S with entries that cancel in V^-1 + G P, and no bound on the blocks'
+// own condition sees that (max |V| max |V^-1| of 3e7 and 1e6 for S with an error
+// of 5e-9; 2e5 and 1e3 on a channel operator without any).  So the factors are
+// tried: y = A^-1 z by them for kProbe pseudo-random right-hand sides, and a
+// time block counts as inverted when, over the rows with a diagonal entry and
+// over those without (of another scale: the pressure) separately,
+//   max_i |z - A y|_i <= 2^-53 (4096 + 2 n) max_i (|A| |y| + |z|)_i.
+// Measured over channel operators of order 218 to 1,706 (nu 1e-6 to 1e-1, tau
+// 1e-4 to 10): 2 to 60 and 20 to 800 units of 2^-53 for these factors, growing
+// with the order, 5 to 300 and 20 to 400 for a pivoted inverse of the whole
+// matrix; errors beyond the pivoted inverse's came with 1e4 units and more.
+// Otherwise the build eliminates the whole coarse matrix.  Four launches of a
+// few us; the right-hand sides share every load.
+constexpr int kProbe = kCcProbe;
+
+// entry e of right-hand side j: parts in [-1, 1) from a multiplicative hash
+__device__ __forceinline__ double2 cc_probe(int e, int j, bool pair) {
+  auto part = [&](uint32_t k) {
+    uint32_t h = ((uint32_t)e * kProbe * 2 + (uint32_t)j * 2 + k + 1u) * 2654435769u;
+    h = (h ^ (h >> 15)) * 2246822519u;
+    h = (h ^ (h >> 13)) * 3266489917u;
+    return (double)(int32_t)(h ^ (h >> 16)) * 0x1p-31;
+  };
+  return make_double2(part(0), pair ? part(1) : 0.0);
+}
+
+__device__ __forceinline__ void cc_mad(double2& s, double2 a, double2 b) {
+  s.x = fma(a.x, b.x, fma(-a.y, b.y, s.x));
+  s.y = fma(a.x, b.y, fma(a.y, b.x, s.y));
+}
+
+__device__ __forceinline__ void cc_wave_sum(double2 (&s)[kProbe]) {
+#pragma unroll
+  for (int j = 0; j < kProbe; ++j)
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      s[j].x += __shfl_xor(s[j].x, off, 64);
+      s[j].y += __shfl_xor(s[j].y, off, 64);
+    }
+}
+
+// Border part, a wavefront per border row: y = P z, or without P first
+// q = z_border - Z z (last false), then y = S^-1 q (last true).
+__global__ void __launch_bounds__(256) k_cc_probe_p(const CompCoarse* __restrict__ cc, bool last) {
+  const CompCoarse& M = cc[blockIdx.z];
+  const int lane = threadIdx.x & 63;
+  const int p = blockIdx.y, m = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (p >= M.nblk || m >= M.n_p) return;
+  const bool pair = M.sz[p] == 2, form = M.P[p] != nullptr;
+  const int n_s = M.n_v + M.n_p;
+  double2* q = M.probe_q + (int64_t)p * kProbe * M.n_p;
+  double2 s[kProbe] = {};
+  if (last) {
+    const double2* row = M.Si[p] + (int64_t)m * M.n_p;
+    for (int e = lane; e < M.n_p; e += 64) {
+      const double2 a = row[e];
+#pragma unroll
+      for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, q[(int64_t)j * M.n_p + e]);
+    }
+  } else {
+    const int len = form ? n_s : M.n_v;
+    for (int e = lane; e < len; e += 64) {
+      const double2 a = form ? cc_get(M.P[p], (int64_t)m * len + e, pair)
+                             : M.Z[p][(int64_t)m * len + e];
+#pragma unroll
+      for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, cc_probe(e, j, pair));
+    }
+  }
+  cc_wave_sum(s);
+  if (lane != 0) return;
+  double2* y = M.probe_y + (int64_t)p * kProbe * n_s + M.n_v + m;
+#pragma unroll
+  for (int j = 0; j < kProbe; ++j) {
+    if (last || form) {
+      y[(int64_t)j * n_s] = s[j];
+    } else {
+      const double2 z = cc_probe(M.n_v + m, j, pair);
+      q[(int64_t)j * M.n_p + m] = make_double2(z.x - s[j].x, z.y - s[j].y);
+    }
+  }
+}
+
+// Block part, a wavefront per row: y = V^-1 z + G y_border.
+__global__ void __launch_bounds__(256) k_cc_probe_u(const CompCoarse* __restrict__ cc) {
+  const CompCoarse& M = cc[blockIdx.z];
+  const int lane = threadIdx.x & 63;
+  const int p = blockIdx.y, e = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (p >= M.nblk || e >= M.n_v) return;
+  const bool pair = M.sz[p] == 2;
+  int c = 0;
+  while (c + 1 < M.nc && e >= M.off[c] + M.n[c]) ++c;
+  const int n = M.n[c], o = M.off[c], n_s = M.n_v + M.n_p;
+  double2* y = M.probe_y + (int64_t)p * kProbe * n_s;
+  double2 s[kProbe] = {};
+  for (int k = lane; k < n; k += 64) {
+    const double2 a = cc_get(M.Vi[p][c], (int64_t)(e - o) * n + k, pair);
+#pragma unroll
+    for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, cc_probe(o + k, j, pair));
+  }
+  for (int m = lane; m < M.n_p; m += 64) {
+    const double2 a = cc_get(M.G[p], (int64_t)e * M.n_p + m, pair);
+#pragma unroll
+    for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, y[(int64_t)j * n_s + M.n_v + m]);
+  }
+  cc_wave_sum(s);
+  if (lane != 0) return;
+#pragma unroll
+  for (int j = 0; j < kProbe; ++j) y[(int64_t)j * n_s + e] = s[j];
+}
+
+// Residuals and their scale, a wavefront per row.
+__global__ void __launch_bounds__(256) k_cc_probe_r(const CompCoarse* __restrict__ cc) {
+  __shared__ double red[4][4];   // per wavefront: residual, scale; without a diagonal the last two
+  const CompCoarse& M = cc[blockIdx.z];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int n_s = M.n_v + M.n_p;
+  const int p = blockIdx.y, e = min((int)blockIdx.x * 4 + wv, n_s - 1);   // the last row twice
+  if (p >= M.nblk || (int)blockIdx.x * 4 >= n_s) return;
+  const bool pair = M.sz[p] == 2;
+  const double2* y = M.probe_y + (int64_t)p * kProbe * n_s;
+  const int32_t row = M.row_off + M.order[e];
+  double2 s[kProbe] = {}, w[kProbe] = {};
+  bool diag = false;
+  for (int32_t q = M.rowptr[row] + lane; q < M.rowptr[row + 1]; q += 64) {
+    const double2 a = cc_value(M, p, q);
+    const int at = M.where[M.col[q] - M.row_off];
+    diag = diag || (at == e && (a.x != 0.0 || a.y != 0.0));
+#pragma unroll
+    for (int j = 0; j < kProbe; ++j) {
+      const double2 v = y[(int64_t)j * n_s + at];
+      cc_mad(s[j], a, v);
+      w[j].x = fma(fabs(a.x) + fabs(a.y), fabs(v.x) + fabs(v.y), w[j].x);
+    }
+  }
+  cc_wave_sum(s);
+  cc_wave_sum(w);
+  auto larger = [](double a, double b) { return (a != a || a > b) ? a : b; };   // a NaN stays
+  double r = 0.0, t = 0.0;
+#pragma unroll
+  for (int j = 0; j < kProbe; ++j) {
+    const double2 z = cc_probe(e, j, pair);
+    r = larger(fabs(z.x - s[j].x) + fabs(z.y - s[j].y), r);
+    t = larger(w[j].x + fabs(z.x) + fabs(z.y), t);
+  }
+  diag = __any(diag);
+  if (lane == 0) {
+    red[wv][0] = diag ? r : 0.0;
+    red[wv][1] = diag ? t : 0.0;
+    red[wv][2] = diag ? 0.0 : r;
+    red[wv][3] = diag ? 0.0 : t;
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    double v = red[0][threadIdx.x];
+    for (int k = 1; k < 4; ++k) v = larger(red[k][threadIdx.x], v);
+    atomic_max_bits(&M.probe_max[4 * p + threadIdx.x], v);
+  }
+}
+
 __global__ void k_cc_verdict(const CompCoarse* __restrict__ cc) {
   const CompCoarse& M = cc[blockIdx.x];
-  const int p = threadIdx.x / (kCcMax + 1), c = threadIdx.x % (kCcMax + 1);
-  if (p >= M.nblk || (c < kCcMax && c >= M.nc)) return;
-  const double a = __builtin_bit_cast(double, M.norm[p][c][0]);
-  const double i = __builtin_bit_cast(double, M.norm[p][c][1]);
-  if (!(a * i <= 1e10)) *M.verdict[p][c] = 1;
+  const int p = threadIdx.x;
+  if (p >= M.nblk) return;
+  for (int k = 0; k < 2; ++k) {
+    const double r = __builtin_bit_cast(double, M.probe_max[4 * p + 2 * k]);
+    const double s = __builtin_bit_cast(double, M.probe_max[4 * p + 2 * k + 1]);
+    if (!(r <= 0x1p-53 * (4096.0 + 2.0 * (M.n_v + M.n_p)) * s && s < INFINITY))
+      *M.verdict[p][kCcMax] = 1;
+  }
 }
 
 // z_e = (W r)_e of time block p at member position e (its complex pair)
@@ -633,7 +768,18 @@ hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  k_cc_verdict<<<D.cnt, 4 * (kCcMax + 1), 0, s>>>(cc);   // one wavefront
+  const dim3 gb((D.n_p + 3) / 4, D.blk, D.cnt), gs((D.n_s + 3) / 4, D.blk, D.cnt);
+  k_cc_probe_p<<<gb, 256, 0, s>>>(cc, false);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (!D.form_p) {
+    k_cc_probe_p<<<gb, 256, 0, s>>>(cc, true);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  k_cc_probe_u<<<gs, 256, 0, s>>>(cc);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_cc_probe_r<<<gs, 256, 0, s>>>(cc);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_cc_verdict<<<D.cnt, 64, 0, s>>>(cc);
   return hipGetLastError();
 }
 

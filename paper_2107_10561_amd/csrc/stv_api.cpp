@@ -129,6 +129,7 @@ void free_coarse_groups(stv_ctx* ctx) {
   }
   for (void*& p : ctx->cc_bufs) dfree(p);
   ctx->cc_bufs.clear();
+  dfree(ctx->cc_probe_max);
   ctx->cc_slots.clear();   // they index the members in h_cc
   for (int g = 0; g < kMaxLevels; ++g) {
     ctx->h_cc[g].clear();
@@ -1864,6 +1865,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     *p = q;
     return STV_OK;
   };
+  STV_TRY(dalloc(ctx, &ctx->cc_probe_max, 16 * mem.size()));
   std::vector<size_t> next((size_t)ctx->n_levels, 0);
   for (const Member& M : mem) {
     CompCoarse& R = ctx->h_cc[M.g][next[(size_t)M.g]++];
@@ -1876,9 +1878,9 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     STV_TRY(keep_copy(&R.ci, M.S.ci));
     STV_TRY(keep_copy(&R.cq, M.S.cq));
     const size_t nv = (size_t)R.n_v, np = (size_t)R.n_p;
-    unsigned long long* norm = nullptr;
-    STV_TRY(keep(&norm, 4 * (kCcMax + 1) * 2));
-    R.norm = reinterpret_cast<unsigned long long(*)[kCcMax + 1][2]>(norm);
+    R.probe_max = ctx->cc_probe_max + 16 * (&M - mem.data());
+    STV_TRY(keep(&R.probe_y, (size_t)R.nblk * kCcProbe * (nv + np)));
+    STV_TRY(keep(&R.probe_q, (size_t)R.nblk * kCcProbe * np));
     STV_TRY(keep(&R.pw, (size_t)2 * R.nblk * np));
     for (int p = 0; p < R.nblk; ++p) {
       for (int c = 0; c <= kCcMax; ++c) {
@@ -2447,9 +2449,8 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
     };
     for (auto& G : ctx->vgroups) clear(G);
     for (auto& G : ctx->sgroups) clear(G);
-    for (int g = 0; g < ctx->n_levels && e == hipSuccess; ++g)
-      for (const CompCoarse& R : ctx->h_cc[g])
-        if (e == hipSuccess) e = hipMemsetAsync(R.norm, 0, sizeof(R.norm[0]) * 4, side);
+    if (e == hipSuccess)   // zero bits
+      e = launch_fill(side, reinterpret_cast<double*>(ctx->cc_probe_max), 16 * (int64_t)ctx->cc_slots.size(), 0.0);
     members_do(launch_cc_fill);
     for (auto& G : ctx->vgroups) eliminate(G);
     members_do(launch_cc_schur);

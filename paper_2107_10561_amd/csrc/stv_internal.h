@@ -217,9 +217,11 @@ struct KronCoarse {
 // border row and block (cptr, local column ci, entry cq), and per time
 // block p: the eliminated real forms A (block c, or kCcMax: the Schur
 // complement) with pivot records and verdicts, the
-// inverses Vi, Si and the factors Z, G, P of the solve; norm: largest entry of
-// each block and of its inverse (bit patterns).
+// inverses Vi, Si and the factors Z, G, P of the solve.  probe_*: the trial of
+// the factors: solutions, border right-hand sides, and per time block the
+// largest residual and its scale, twice (bit patterns).
 constexpr int kCcMax = 12;
+constexpr int kCcProbe = 4;   // right-hand sides of the trial
 struct CompCoarse {
   const int32_t *rowptr, *col;
   const double* ma;
@@ -232,7 +234,8 @@ struct CompCoarse {
   int64_t lda[kCcMax + 1];
   const int* rpiv[4][kCcMax + 1];
   int* verdict[4][kCcMax + 1];
-  unsigned long long (*norm)[kCcMax + 1][2];
+  unsigned long long* probe_max;
+  double2 *probe_y, *probe_q;
   double2* Vi[4][kCcMax];
   double2 *Si[4], *Z[4], *G[4], *P[4];
   double2* pw;
@@ -346,6 +349,7 @@ struct stv_ctx {
   stv::CcDims cc_dims[stv::kMaxLevels];
   std::vector<stv::CoarseGroup> vgroups, sgroups;
   std::vector<void*> cc_bufs;
+  unsigned long long* cc_probe_max = nullptr;   // probe_max of all of them, in cc_slots' order
   // per component member (level, then per time block and block the index of
   // its verdict among those of the chains)
   std::vector<std::pair<int, std::array<int, 4 * (stv::kCcMax + 1)>>> cc_slots;
