@@ -11,7 +11,17 @@
 // 85), and 31 instead of 85 values per velocity row in the store.
 // Block elimination takes its pivots inside V_c first, then in S; a cell with a
 // pivot below kPivotTol of its block's largest entry is flagged, and the build
-// then eliminates the whole cell matrices of the level instead.
+// then eliminates the whole cell matrices of the level instead.  So is a cell
+// where V^-1 is nearly singular although the cell's matrix is not: V^-1 and G P
+// then cancel.  With
+//   g = max_c max |V_c^-1| / max_i |(V_c^-1 + G_c P)_i . s|  (signs s), and
+//   kappa = m max(|S|, |C V^-1 B|) max |S^-1|,
+// the error of the velocity rows is below 2^-53 g kappa apart from V^-1's own
+// (cell matrices of channel operators with one to four velocity directions
+// scaled down to 1e-1 .. 1e-7: errors of 1e-5 to 0.5 of that), so g kappa is held to
+// kCancelTol.  Channel operators, nu 1e-6 to 1e-1, tau 1e-4 to 10, have 9 to
+// 470; errors at the limit are 2e-14 of the largest entry and less.  The check
+// costs 3d 6,912 cells 0.72 -> 0.78 ms, 2d nothing measurable.
 #include "stv_internal.h"
 #include "wave.h"
 
@@ -20,6 +30,8 @@
 namespace stv {
 
 static constexpr double kPivotTol = 1e-7;
+static constexpr double kCancelTol = 4096.0;
+static constexpr unsigned kSigns = 0x59a7c36;   // s of the check, bit j: the sign of node j
 
 typedef double stv_d4 __attribute__((ext_vector_type(4)));
 
@@ -166,8 +178,10 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
     double2 corner[NB][NM];      // -C_c V_c^-1 B_c
     double2 sinv[NM][NM];
     int rowof[NV];               // stored node row of each node (COMP)
+    double2 vs[D][NV];           // (V_c^-1 s)_i
+    double2 ps[NB];              // C_c's rows of -C V^-1 s, then (P s_c)_m
+    double2 gneg[NV][NB];        // G
     double2 vinv[COMP ? 1 : D][COMP ? 1 : NV][COMP ? 1 : NV];
-    double2 gneg[COMP ? 1 : NV][COMP ? 1 : NB];
     double2 prow[COMP ? 1 : NM][COMP ? 1 : NLS];
   };
   __shared__ Wave waves[4];
@@ -202,6 +216,9 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
       wave_lds_sync();
     }
     const int nvb = same ? 1 : D;
+    double vmax[D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) vmax[c] = 0.0;
     for (int c0 = 0; c0 < nvb; ++c0) {
       // border row (bc, bm) of lanes NV ..
       const int bb = lane - NV, bc = bb / NM, bm = bb - bc * NM;
@@ -269,6 +286,8 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
             for (int m = 0; m < NM; ++m) corner[bb][m] = val(jc * NM + m);
           }
       }
+      double2 rs = make_double2(0.0, 0.0);   // the row times s
+      double rmax = 0.0;
 #pragma unroll
       for (int q = 0; q < NV; ++q) {
         const int j = __builtin_amdgcn_readlane(piv, q);
@@ -276,6 +295,27 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
         if constexpr (!COMP) {
           if (vel) vinv[c0][var][j] = val(NB + q);
         }
+        const double2 e = val(NB + q);
+        const double sj = (kSigns >> j) & 1u ? -1.0 : 1.0;
+        rs.x = fma(sj, e.x, rs.x);
+        rs.y = fma(sj, e.y, rs.y);
+        rmax = fmax(rmax, fabs(e.x) + fabs(e.y));
+      }
+      rmax = wave_max_f64(vel ? rmax : 0.0);
+#pragma unroll
+      for (int c = 0; c < D; ++c)
+        if (same || c == c0) vmax[c] = rmax;
+      if (bor) sh.ps[bb] = rs;
+      if (vel) {
+#pragma unroll
+        for (int c = 0; c < D; ++c)
+          if (same || c == c0) sh.vs[c][var] = rs;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          if (same || b / NM == c0) {
+            const double2 v = val(b);
+            gneg[var][b] = make_double2(-v.x, -v.y);
+          }
       }
       if constexpr (COMP) {
         // V part k-major: entry ((2 j + s) R + row), one block per distinct V_c
@@ -296,20 +336,19 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
               put(gb + (int64_t)(2 * b + 1) * R, CX ? -im[CX ? b : 0] : 0.0);
             }
         }
-      } else if (vel) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          if (same || b / NM == c0) {
-            const double2 v = val(b);
-            gneg[var][b] = make_double2(-v.x, -v.y);
-          }
       }
     }
     wave_lds_sync();
     // S^-1, one row per lane
+    double kappa;
     {
       double re[NM], im[CX ? NM : 1];
-      double big = 0.0;
+      double big = 0.0, part = 0.0;
+      if (lane < NB) {
+#pragma unroll
+        for (int j = 0; j < NM; ++j)
+          part = fmax(part, fabs(corner[lane][j].x) + fabs(corner[lane][j].y));
+      }
 #pragma unroll
       for (int j = 0; j < NM; ++j) {
         double2 f = make_double2(0.0, 0.0);
@@ -326,14 +365,52 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
         big = fmax(big, fabs(f.x) + fabs(f.y));
       }
       int var, piv;
-      gj_rows<NM, NM, CX>(re, im, lane, kPivotTol * wave_max_f64(big), var, piv, sing);
+      const double bigs = wave_max_f64(big);
+      gj_rows<NM, NM, CX>(re, im, lane, kPivotTol * bigs, var, piv, sing);
+      double imax = 0.0;
 #pragma unroll
       for (int q = 0; q < NM; ++q) {
         const int j = __builtin_amdgcn_readlane(piv, q);
-        if (lane < NM) sinv[var][j] = make_double2(re[q], CX ? im[CX ? q : 0] : 0.0);
+        const double2 e = make_double2(re[q], CX ? im[CX ? q : 0] : 0.0);
+        if (lane < NM) {
+          sinv[var][j] = e;
+          imax = fmax(imax, fabs(e.x) + fabs(e.y));
+        }
       }
+      kappa = NM * fmax(bigs, wave_max_f64(part)) * wave_max_f64(imax);
     }
     wave_lds_sync();
+    // cancellation between V^-1 and G P
+    {
+      double2 ps = make_double2(0.0, 0.0);
+      if (lane < NB) {
+        const int c = lane / NM, m = lane - c * NM;
+#pragma unroll
+        for (int k = 0; k < NM; ++k) {
+          const double2 a = sinv[m][k], b = sh.ps[c * NM + k];
+          ps.x += a.x * b.x - a.y * b.y;
+          ps.y += a.x * b.y + a.y * b.x;
+        }
+      }
+      wave_lds_sync();
+      if (lane < NB) sh.ps[lane] = ps;
+      wave_lds_sync();
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        double x = 0.0;
+        if (lane < NV) {
+          double2 v = sh.vs[c][lane];
+#pragma unroll
+          for (int m = 0; m < NM; ++m) {
+            const double2 g = gneg[lane][c * NM + m], q = sh.ps[c * NM + m];
+            v.x += g.x * q.x - g.y * q.y;
+            v.y += g.x * q.y + g.y * q.x;
+          }
+          x = fabs(v.x) + fabs(v.y);
+        }
+        if (!(kappa * vmax[c] <= kCancelTol * wave_max_f64(x))) sing = true;
+      }
+    }
     // pressure rows P = S^-1 [-C V^-1 | I], column e per lane
     for (int e = lane; e < (COMP ? 88 : NLS); e += 64) {
       const int c = e / NV, j = e - c * NV;
