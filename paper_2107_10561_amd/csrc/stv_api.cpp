@@ -1736,18 +1736,8 @@ static bool worth_cutting(const CompStruct& S, int32_t n_s, int b) {
 static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& split,
                                   const std::vector<bool>& has_split) {
   const bool full = ctx->inv_full != 0;
-  struct Member { int g; CompStruct S; int at[4][kCcMax + 1]; };
+  struct Member { int g; CompStruct S; int group[2]; int at[4][kCcMax + 1]; };
   std::vector<Member> mem;
-  // one group for all the blocks, one for all the Schur complements, each
-  // padded with the identity to the largest order: the chains are bound by
-  // their sequence of launches, which all blocks then share
-  std::vector<CoarseDesc> desc[2];
-  auto slot_of = [&](int kind, int64_t order) {
-    CoarseDesc d{};
-    d.n_s = (int32_t)order;
-    desc[kind].push_back(d);
-    return (int)desc[kind].size() - 1;
-  };
   auto keep = [&](auto** p, size_t n) -> int {
     STV_TRY(dalloc(ctx, p, n));
     ctx->cc_bufs.push_back((void*)*p);
@@ -1817,8 +1807,6 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
         R.first[p] = T.first[p];
         R.al[p] = T.t[p][0];
         R.be[p] = T.sz[p] == 2 ? T.t[p][1] : 0.0;
-        for (int k = 0; k < R.nc; ++k) M.at[p][k] = slot_of(0, 2 * (int64_t)R.n[k]);
-        M.at[p][kCcMax] = slot_of(1, 2 * (int64_t)R.n_p);
       }
       c.inv_off = -2;
       ctx->h_cc[g].push_back(R);
@@ -1849,14 +1837,58 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
         if (c.inv_off == -2) c.inv_off = -3;
   }
   if (mem.empty()) return STV_OK;
+  // The blocks of all members in few groups, and the Schur complements, each
+  // padded with the identity to its group's largest order: the chains are bound
+  // by their sequence of launches, which a group's blocks share.  From the
+  // largest order down a group takes the next member while its matrices then
+  // hold at most twice what they need, or 64 MB more (a batch of 8x2 and 12x3
+  // coarse cells: one chain of each kind; 32 members of 16x4 cells beside one of
+  // 96x24 without this bound: every small matrix at the large one's order).
+  int verdicts = 0;
+  std::vector<int> first[2];   // of each group, among the verdicts
   for (int kind = 0; kind < 2; ++kind) {
     auto& groups = kind ? ctx->sgroups : ctx->vgroups;
-    groups.emplace_back();
-    CoarseGroup& G = groups.back();
-    G.kron = true;
-    G.lev.assign(desc[kind].size(), 0);
-    for (const CoarseDesc& d : desc[kind]) G.n0 = std::max<int64_t>(G.n0, d.n_s);
-    STV_TRY(alloc_group(ctx, G, desc[kind], 3));
+    auto order_of = [&](const Member& M) {
+      return 2 * (int64_t)(kind ? M.S.n_p : *std::max_element(M.S.n, M.S.n + M.S.nc));
+    };
+    std::vector<size_t> by(mem.size());
+    for (size_t i = 0; i < by.size(); ++i) by[i] = i;
+    std::stable_sort(by.begin(), by.end(),
+                     [&](size_t a, size_t b) { return order_of(mem[a]) > order_of(mem[b]); });
+    std::vector<std::vector<CoarseDesc>> desc;
+    double need = 0.0, held = 0.0;
+    for (size_t i : by) {
+      Member& M = mem[i];
+      const int nblk = split[(size_t)M.g].nblk, slots = nblk * (kind ? 1 : M.S.nc);
+      const double n = (double)order_of(M);
+      const double top = groups.empty() ? 0.0 : (double)groups.back().n0;
+      need += slots * n * n;
+      held += slots * top * top;
+      if (groups.empty() || held > std::max(2.0 * need, need + 64e6 / 8)) {
+        groups.emplace_back();
+        groups.back().kron = true;
+        groups.back().n0 = order_of(M);
+        desc.emplace_back();
+        need = held = slots * n * n;
+      }
+      M.group[kind] = (int)groups.size() - 1;
+      auto slot = [&](int64_t order) {
+        CoarseDesc d{};
+        d.n_s = (int32_t)order;
+        desc.back().push_back(d);
+        return (int)desc.back().size() - 1;
+      };
+      for (int p = 0; p < nblk; ++p) {
+        if (kind) M.at[p][kCcMax] = slot(2 * (int64_t)M.S.n_p);
+        for (int k = 0; !kind && k < M.S.nc; ++k) M.at[p][k] = slot(2 * (int64_t)M.S.n[k]);
+      }
+    }
+    for (size_t k = 0; k < groups.size(); ++k) {
+      groups[k].lev.assign(desc[k].size(), 0);
+      first[kind].push_back(verdicts);
+      verdicts += (int)desc[k].size();
+      STV_TRY(alloc_group(ctx, groups[k], desc[k], 3));
+    }
   }
   auto keep_copy = [&](const int32_t** p, const std::vector<int32_t>& v) -> int {
     int32_t* q = nullptr;
@@ -1885,7 +1917,8 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     for (int p = 0; p < R.nblk; ++p) {
       for (int c = 0; c <= kCcMax; ++c) {
         if (c < kCcMax && c >= R.nc) continue;
-        const CoarseGroup& G = (c == kCcMax ? ctx->sgroups : ctx->vgroups)[0];
+        const int kind = c == kCcMax;
+        const CoarseGroup& G = (kind ? ctx->sgroups : ctx->vgroups)[(size_t)M.group[kind]];
         R.A[p][c] = G.w.A + (int64_t)M.at[p][c] * G.w.sA;
         R.rpiv[p][c] = G.w.rpiv + (int64_t)M.at[p][c] * G.w.sV;
         R.lda[c] = G.np;
@@ -1913,8 +1946,8 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     for (int p = 0; p < nblk; ++p)
       for (int c = 0; c <= kCcMax; ++c) {
         if (c < kCcMax && c >= M.S.nc) continue;
-        const int base = c == kCcMax ? (int)ctx->vgroups[0].lev.size() : 0;
-        v[(size_t)(p * (kCcMax + 1) + c)] = base + M.at[p][c];
+        const int kind = c == kCcMax;
+        v[(size_t)(p * (kCcMax + 1) + c)] = first[kind][(size_t)M.group[kind]] + M.at[p][c];
       }
     ctx->cc_slots.emplace_back(M.g, v);
   }

@@ -152,3 +152,45 @@ def test_weak_velocity_block(stv, case, kind, delta):
         log(f"[coarse] backward {back:.1e} units")
         assert back <= 4 * (4096 + 2 * J.shape[0])
     s.close()
+
+
+@pytest.mark.parametrize("factors", [True, False])
+def test_batch_of_members_far_apart(stv, factors):
+    """Eight members of 16x4 coarse cells and one of 48x12: every member's
+    solve, and device memory near what the members take alone (each matrix at
+    most doubled, as the large one's order for all would not be)."""
+    import torch
+    small, large = mesh_problem(2, (16, 4), 1, 1), mesh_problem(2, (48, 12), 1, 1)
+
+    def build(ps):
+        s = stv.Solver(0)
+        s.set_batch([p.levels for p in ps], 2, 1)
+        if factors:
+            _, w, C, _ = fe_time.time_matrices(1)
+            ma = [spatial_factors(p.levels[0]) for p in ps]
+            s.set_kron_factors(0, np.concatenate([m for m, _ in ma]), np.concatenate([a for _, a in ma]),
+                               np.asarray(C, dtype=np.float64), ps[0].tau * np.asarray(w, dtype=np.float64))
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        s.build_cell_inverses()
+        return s, free - torch.cuda.mem_get_info()[0]
+
+    alone = 0
+    for p, n in ((small, 8), (large, 1)):
+        s, used = build([p])
+        alone += n * used
+        s.close()
+    ps = [small] * 4 + [large] + [small] * 4
+    s, used = build(ps)
+    log(f"[coarse] far apart: {used / 1e6:.0f} MB, alone {alone / 1e6:.0f} MB")
+    assert used <= 2 * alone + 64e6
+    mats = {id(p): matrix(p.levels[0], p.levels[0].val, p.b) for p in (small, large)}
+    r = np.random.default_rng(41).standard_normal(sum(mats[id(p)].shape[0] for p in ps))
+    d, at = coarse_solve(s, r), 0
+    for i, p in enumerate(ps):
+        J = mats[id(p)]
+        sl = slice(at, at + J.shape[0])
+        at += J.shape[0]
+        if i in (0, 4, 8):
+            check_solve(J, r[sl], d[sl], f"far apart {i} factors={factors}")
+    s.close()
