@@ -11,6 +11,7 @@
 #include <complex>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -320,15 +321,21 @@ class HostJobs {
 
 // f(t, lo, hi), t < 16, over [0, n) cut into one range per thread; inline
 // where that gives each less than `grain` (a thread costs some 30 us).
-// The ranges ascend with t.
+// The ranges ascend with t.  False where a range ended by an exception (memory).
 template <typename F>
-void host_ranges(int64_t n, int64_t grain, F&& f) {
+bool host_ranges(int64_t n, int64_t grain, F&& f) {
   const int64_t most = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
   const int64_t nth = std::max<int64_t>(1, std::min(most, n / grain));
   HostJobs jobs;
   for (int64_t t = 1; t < nth; ++t)
     jobs.run([&f, t, n, nth]() { f((int)t, n * t / nth, n * (t + 1) / nth); });
-  f(0, int64_t(0), n / nth);
+  bool ok = true;
+  try {
+    f(0, int64_t(0), n / nth);
+  } catch (...) {
+    ok = false;
+  }
+  return jobs.join() && ok;
 }
 
 // ---------------------------------------------------------------- uploads
@@ -1632,42 +1639,72 @@ static bool component_structure(const int32_t* rp, const int32_t* col, const dou
   return true;
 }
 
-// The nonzero blocks of a level's coarse members: rows [ptr[s], ptr[s+1]) of
-// all the level's rows (those of other members stay empty), their columns and
-// where they stand among the level's blocks.
-struct NzBlocks { std::vector<int32_t> ptr, col, src; };
+// The pattern of a level's coarse members on the host: rows [ptr[s], ptr[s+1])
+// of all the level's rows.  With spatial factors ptr and col stand as on the
+// device, with the factors ma beside them (entries of other members are not
+// set); without, the nonzero blocks only (rows of other members stay empty),
+// src saying where they stand among the level's blocks.
+struct CoarsePattern {
+  std::vector<int32_t> ptr, nz_col, src;
+  std::unique_ptr<int32_t[]> col;   // without a first touch of what is not copied
+  std::unique_ptr<double[]> ma;
+  const int32_t* cols() const { return col ? col.get() : nz_col.data(); }
+};
 
-static int nonzero_blocks(stv_ctx* ctx, int g, NzBlocks& Z) {
+static int coarse_pattern(stv_ctx* ctx, int g, CoarsePattern& Z) {
   const DevLevel& L = ctx->lv[g];
-  std::vector<int32_t> rp((size_t)L.n_s + 1), col((size_t)L.nnzb);
-  std::vector<uint8_t> nz((size_t)L.nnzb);
+  Z.ptr.resize((size_t)L.n_s + 1);
+  STV_HIP(hipMemcpy(Z.ptr.data(), L.rowptr, 4 * Z.ptr.size(), hipMemcpyDeviceToHost));
+  // runs of coarse members' rows
+  std::vector<std::pair<int32_t, int32_t>> runs;
+  for (const CoarseDesc& c : ctx->h_coarse[g]) {
+    if (!runs.empty() && runs.back().second == c.row_off) runs.back().second += c.n_s;
+    else runs.emplace_back(c.row_off, c.row_off + c.n_s);
+  }
+  std::unique_ptr<int32_t[]> col(new int32_t[(size_t)L.nnzb]);
+  std::unique_ptr<uint8_t[]> nz;
   uint8_t* dev = nullptr;
-  STV_TRY(dalloc(ctx, &dev, nz.size()));
-  hipError_t e = launch_block_nonzero(ctx->stream, ctx->b, L.val, L.nnzb, dev);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  if (e == hipSuccess) e = hipMemcpy(nz.data(), dev, nz.size(), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipMemcpy(rp.data(), L.rowptr, 4 * rp.size(), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipMemcpy(col.data(), L.col, 4 * col.size(), hipMemcpyDeviceToHost);
+  hipError_t e = hipSuccess;
+  if (L.kron_ma) {
+    Z.ma.reset(new double[(size_t)2 * L.nnzb]);
+  } else {
+    nz.reset(new uint8_t[(size_t)L.nnzb]);
+    STV_TRY(dalloc(ctx, &dev, (size_t)L.nnzb));
+    e = launch_block_nonzero(ctx->stream, ctx->b, L.val, L.nnzb, dev);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  }
+  for (const auto& r : runs) {
+    const size_t q = (size_t)Z.ptr[(size_t)r.first], n = (size_t)Z.ptr[(size_t)r.second] - q;
+    if (e == hipSuccess) e = hipMemcpy(col.get() + q, L.col + q, 4 * n, hipMemcpyDeviceToHost);
+    if (e == hipSuccess)
+      e = dev ? hipMemcpy(nz.get() + q, dev + q, n, hipMemcpyDeviceToHost)
+              : hipMemcpy(Z.ma.get() + 2 * q, L.kron_ma + 2 * q, 16 * n, hipMemcpyDeviceToHost);
+  }
   dfree(dev);
   STV_HIP(e);
-  Z.ptr.assign((size_t)L.n_s + 1, 0);
-  std::vector<char> in((size_t)L.n_s, 0);
-  for (const CoarseDesc& c : ctx->h_coarse[g])
-    std::fill(in.begin() + c.row_off, in.begin() + c.row_off + c.n_s, 1);
-  for (int32_t r = 0; r < L.n_s; ++r) {
-    for (int32_t q = rp[(size_t)r]; in[(size_t)r] && q < rp[(size_t)r + 1]; ++q)
-      if (nz[(size_t)q]) {
-        Z.col.push_back(col[(size_t)q]);
-        Z.src.push_back(q);
-      }
-    Z.ptr[(size_t)r + 1] = (int32_t)Z.col.size();
+  if (L.kron_ma) {
+    Z.col = std::move(col);
+    return STV_OK;
   }
+  std::vector<int32_t> ptr((size_t)L.n_s + 1, 0);
+  size_t k = 0;
+  for (int32_t r = 0; r < L.n_s; ++r) {
+    while (k < runs.size() && r >= runs[k].second) ++k;
+    if (k < runs.size() && r >= runs[k].first)
+      for (int32_t q = Z.ptr[(size_t)r]; q < Z.ptr[(size_t)r + 1]; ++q)
+        if (nz[(size_t)q]) {
+          Z.nz_col.push_back(col[(size_t)q]);
+          Z.src.push_back(q);
+        }
+    ptr[(size_t)r + 1] = (int32_t)Z.nz_col.size();
+  }
+  Z.ptr = std::move(ptr);
   return STV_OK;
 }
 
 // The same structure for b x b blocks taken as scalars: row r of the blocks
 // becomes rows r b + l, whose entries are those of launch_expand_blocks.
-static void expand_structure(CompStruct& S, int b, int32_t row_off, const NzBlocks& Z) {
+static void expand_structure(CompStruct& S, int b, int32_t row_off, const CoarsePattern& Z) {
   CompStruct E;
   E.nc = S.nc;
   E.n_v = S.n_v * b;
@@ -1723,10 +1760,11 @@ static void expand_structure(CompStruct& S, int b, int32_t row_off, const NzBloc
 // (1572), at 0.51 2.15 -> 1.70 ms (892), at 0.60 none (0.34 -> 0.46 ms at 124).
 // Below order 512 the 0.15 ms won are spent by the 3 us per apply of the
 // second launch within 50 cycles.
+constexpr int64_t kCutAbove = 512;
 static bool worth_cutting(const CompStruct& S, int32_t n_s, int b) {
   int mx = 0;
   for (int c = 0; c < S.nc; ++c) mx = std::max(mx, S.n[c]);
-  return S.n_bare > 0 && (int64_t)n_s * b > 512 && 20 * ((int64_t)mx + S.n_p) <= 11 * (int64_t)n_s &&
+  return S.n_bare > 0 && (int64_t)n_s * b > kCutAbove && 20 * ((int64_t)mx + S.n_p) <= 11 * (int64_t)n_s &&
          2 * (int64_t)std::max(mx, S.n_p) * b <= gj_plan(2, 3, true).max_n;
 }
 
@@ -1749,51 +1787,60 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     // with spatial factors each time block is a matrix over the spatial rows;
     // without, the blocks' entries are one real matrix of n_s b scalar rows
     const int b = L.kron_ma ? ctx->b : 1, sb = L.kron_ma ? 1 : ctx->b;
+    std::vector<CoarseDesc>& all = ctx->h_coarse[g];
+    if (!L.kron_ma && std::none_of(all.begin(), all.end(), [&](const CoarseDesc& c) {
+          return (int64_t)c.n_s * sb > kCutAbove;
+        }))
+      continue;
+    CoarsePattern Z;
+    STV_TRY(coarse_pattern(ctx, g, Z));
+    if (!L.kron_ma && (int64_t)Z.nz_col.size() * sb * sb >= INT32_MAX) continue;
+    // the members' structures, by threads (some 0.2 ms per thousand rows)
+    std::vector<CompStruct> found(all.size());   // nc = 0: not cut
+    const bool ok = host_ranges((int64_t)all.size(), 2, [&](int, int64_t lo, int64_t hi) {
+      for (int64_t i = lo; i < hi; ++i) {
+        const CoarseDesc& c = all[(size_t)i];
+        CompStruct S;
+        if (!L.kron_ma && (int64_t)c.n_s * sb <= kCutAbove) continue;
+        if (!component_structure(Z.ptr.data(), Z.cols(), Z.ma.get(), c.row_off, c.n_s, S)) continue;
+        if (!L.kron_ma) {
+          if (!worth_cutting(S, c.n_s, sb)) continue;
+          expand_structure(S, sb, c.row_off, Z);
+        }
+        found[(size_t)i] = std::move(S);
+      }
+    });
+    if (!ok) return fail(ctx, STV_ENOMEM, "out of host memory for the coarse structure");
+    const bool any = std::any_of(found.begin(), found.end(), [](const CompStruct& S) { return S.nc > 0; });
+    if (!any) continue;
     const int32_t *d_rp = L.rowptr, *d_col = L.col;
     const double* d_ma = L.kron_ma;
-    NzBlocks Z;
-    std::vector<double> ma;
-    if (L.kron_ma) {
-      Z.ptr.resize((size_t)L.n_s + 1);
-      Z.col.resize((size_t)L.nnzb);
-      ma.resize((size_t)2 * L.nnzb);
-      STV_HIP(hipMemcpy(Z.ptr.data(), L.rowptr, 4 * Z.ptr.size(), hipMemcpyDeviceToHost));
-      STV_HIP(hipMemcpy(Z.col.data(), L.col, 4 * Z.col.size(), hipMemcpyDeviceToHost));
-      STV_HIP(hipMemcpy(ma.data(), L.kron_ma, 8 * ma.size(), hipMemcpyDeviceToHost));
-    } else {
-      STV_TRY(nonzero_blocks(ctx, g, Z));
-      if ((int64_t)Z.col.size() * sb * sb >= INT32_MAX) continue;
+    if (!L.kron_ma) {
+      int32_t *rp2 = nullptr, *col2 = nullptr, *src = nullptr;
+      double* ma2 = nullptr;
+      const size_t n = Z.nz_col.size() * sb * sb;
+      STV_TRY(keep(&rp2, (size_t)L.n_s * sb + 1));
+      STV_TRY(keep(&col2, n));
+      STV_TRY(keep(&ma2, 2 * n));
+      int32_t *ptr = nullptr, *zcol = nullptr;
+      int rc = upload(ctx, &ptr, Z.ptr.data(), Z.ptr.size());
+      if (rc == STV_OK) rc = upload(ctx, &zcol, Z.nz_col.data(), Z.nz_col.size());
+      if (rc == STV_OK) rc = upload(ctx, &src, Z.src.data(), Z.src.size());
+      hipError_t e = hipSuccess;
+      if (rc == STV_OK)
+        e = launch_expand_blocks(ctx->stream, sb, L.n_s, ptr, zcol, src, L.val, rp2, col2, ma2);
+      if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+      dfree(ptr); dfree(zcol); dfree(src);
+      STV_TRY(rc);
+      STV_HIP(e);
+      d_rp = rp2; d_col = col2; d_ma = ma2;
     }
     ctx->cc_dims[g].b = b;
-    for (CoarseDesc& c : ctx->h_coarse[g]) {
+    for (size_t i = 0; i < all.size(); ++i) {
+      if (found[i].nc == 0) continue;
+      CoarseDesc& c = all[i];
       Member M{};
-      if (!component_structure(Z.ptr.data(), Z.col.data(), L.kron_ma ? ma.data() : nullptr,
-                               c.row_off, c.n_s, M.S))
-        continue;
-      if (!L.kron_ma) {
-        if (!worth_cutting(M.S, c.n_s, sb)) continue;
-        expand_structure(M.S, sb, c.row_off, Z);
-        if (d_ma == nullptr) {
-          int32_t *rp2 = nullptr, *col2 = nullptr, *src = nullptr;
-          double* ma2 = nullptr;
-          const size_t n = Z.col.size() * sb * sb;
-          STV_TRY(keep(&rp2, (size_t)L.n_s * sb + 1));
-          STV_TRY(keep(&col2, n));
-          STV_TRY(keep(&ma2, 2 * n));
-          int32_t *ptr = nullptr, *zcol = nullptr;
-          int rc = upload(ctx, &ptr, Z.ptr.data(), Z.ptr.size());
-          if (rc == STV_OK) rc = upload(ctx, &zcol, Z.col.data(), Z.col.size());
-          if (rc == STV_OK) rc = upload(ctx, &src, Z.src.data(), Z.src.size());
-          hipError_t e = hipSuccess;
-          if (rc == STV_OK)
-            e = launch_expand_blocks(ctx->stream, sb, L.n_s, ptr, zcol, src, L.val, rp2, col2, ma2);
-          if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-          dfree(ptr); dfree(zcol); dfree(src);
-          STV_TRY(rc);
-          STV_HIP(e);
-          d_rp = rp2; d_col = col2; d_ma = ma2;
-        }
-      }
+      M.S = std::move(found[i]);
       M.g = g;
       const TimeSplit& T = split[(size_t)g];
       CompCoarse R{};
@@ -1890,30 +1937,42 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
       STV_TRY(alloc_group(ctx, groups[k], desc[k], 3));
     }
   }
-  auto keep_copy = [&](const int32_t** p, const std::vector<int32_t>& v) -> int {
-    int32_t* q = nullptr;
-    STV_TRY(upload(ctx, &q, v.data(), v.size()));
-    ctx->cc_bufs.push_back((void*)q);
-    *p = q;
-    return STV_OK;
+  // The members' lists in one array, sent at once, and their matrices in
+  // another (some twenty allocations and eight copies per member otherwise:
+  // 256 members of 8x2 coarse cells 49 ms for a first build).
+  std::vector<int32_t> lists;
+  std::vector<std::pair<const int32_t**, size_t>> list_at;
+  auto list = [&](const int32_t*& p, const std::vector<int32_t>& v) {
+    list_at.emplace_back(&p, lists.size());
+    lists.insert(lists.end(), v.begin(), v.end());
+  };
+  size_t list_entries = 0;
+  for (const Member& M : mem)
+    list_entries += 2 * M.S.order.size() + M.S.bptr.size() + M.S.cptr.size() + 2 * (M.S.bi.size() + M.S.ci.size());
+  lists.reserve(list_entries);
+  size_t entries = 0;
+  std::vector<std::pair<double2**, size_t>> array_at;
+  auto array = [&](double2*& p, size_t n) {
+    array_at.emplace_back(&p, entries);
+    entries += (n + 15) & ~size_t(15);   // 256 bytes
   };
   STV_TRY(dalloc(ctx, &ctx->cc_probe_max, 16 * mem.size()));
   std::vector<size_t> next((size_t)ctx->n_levels, 0);
-  for (const Member& M : mem) {
+  for (Member& M : mem) {
     CompCoarse& R = ctx->h_cc[M.g][next[(size_t)M.g]++];
-    STV_TRY(keep_copy(&R.order, M.S.order));
-    STV_TRY(keep_copy(&R.where, M.S.where));
-    STV_TRY(keep_copy(&R.bptr, M.S.bptr));
-    STV_TRY(keep_copy(&R.bi, M.S.bi));
-    STV_TRY(keep_copy(&R.bq, M.S.bq));
-    STV_TRY(keep_copy(&R.cptr, M.S.cptr));
-    STV_TRY(keep_copy(&R.ci, M.S.ci));
-    STV_TRY(keep_copy(&R.cq, M.S.cq));
+    list(R.order, M.S.order);
+    list(R.where, M.S.where);
+    list(R.bptr, M.S.bptr);
+    list(R.bi, M.S.bi);
+    list(R.bq, M.S.bq);
+    list(R.cptr, M.S.cptr);
+    list(R.ci, M.S.ci);
+    list(R.cq, M.S.cq);
     const size_t nv = (size_t)R.n_v, np = (size_t)R.n_p;
     R.probe_max = ctx->cc_probe_max + 16 * (&M - mem.data());
-    STV_TRY(keep(&R.probe_y, (size_t)R.nblk * kCcProbe * (nv + np)));
-    STV_TRY(keep(&R.probe_q, (size_t)R.nblk * kCcProbe * np));
-    STV_TRY(keep(&R.pw, (size_t)2 * R.nblk * np));
+    array(R.probe_y, (size_t)R.nblk * kCcProbe * (nv + np));
+    array(R.probe_q, (size_t)R.nblk * kCcProbe * np);
+    array(R.pw, (size_t)2 * R.nblk * np);
     for (int p = 0; p < R.nblk; ++p) {
       for (int c = 0; c <= kCcMax; ++c) {
         if (c < kCcMax && c >= R.nc) continue;
@@ -1922,12 +1981,12 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
         R.A[p][c] = G.w.A + (int64_t)M.at[p][c] * G.w.sA;
         R.rpiv[p][c] = G.w.rpiv + (int64_t)M.at[p][c] * G.w.sV;
         R.lda[c] = G.np;
-        if (c < kCcMax) STV_TRY(keep(&R.Vi[p][c], (size_t)R.n[c] * R.n[c]));
+        if (c < kCcMax) array(R.Vi[p][c], (size_t)R.n[c] * R.n[c]);
       }
-      STV_TRY(keep(&R.Si[p], np * np));
-      STV_TRY(keep(&R.Z[p], np * nv));
-      STV_TRY(keep(&R.G[p], nv * np));
-      if (ctx->cc_dims[M.g].form_p) STV_TRY(keep(&R.P[p], np * (nv + np)));
+      array(R.Si[p], np * np);
+      array(R.Z[p], np * nv);
+      array(R.G[p], nv * np);
+      if (ctx->cc_dims[M.g].form_p) array(R.P[p], np * (nv + np));
     }
     CcDims& D = ctx->cc_dims[M.g];
     for (int c = 0; c < R.nc; ++c) D.n = std::max(D.n, (unsigned)R.n[c]);
@@ -1937,6 +1996,13 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     D.blk = std::max(D.blk, (unsigned)R.nblk);
     D.cnt += 1;
   }
+  int32_t* d_lists = nullptr;
+  double2* d_arrays = nullptr;
+  STV_TRY(keep(&d_lists, lists.size()));
+  STV_TRY(keep(&d_arrays, entries));
+  for (const auto& l : list_at) *l.first = d_lists + l.second;
+  for (const auto& a : array_at) *a.first = d_arrays + a.second;
+  STV_TRY(send_pieces(ctx, {{d_lists, lists.data(), 4 * lists.size()}}));
   // the slots' verdicts: consecutive in the report, v groups then s groups
   // (assigned with the report, see upload_component_members)
   for (const Member& M : mem) {

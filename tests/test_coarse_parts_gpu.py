@@ -194,3 +194,37 @@ def test_batch_of_members_far_apart(stv, factors):
         if i in (0, 4, 8):
             check_solve(J, r[sl], d[sl], f"far apart {i} factors={factors}")
     s.close()
+
+
+@pytest.mark.parametrize("factors", [True, False])
+def test_coarse_members_between_others(stv, factors):
+    """Members of two levels before, between and after members of three: the
+    coarse ones stand in several runs of rows on a level that others smooth.
+    A cycle of the batch against each member's own (sums in other orders, the
+    cycle's condition some 1e4)."""
+    two, three = mesh_problem(2, (32, 8), 2, 1), mesh_problem(2, (32, 8), 3, 1)
+    order = [two, three, two, two, three, three, two]
+    _, w, C, _ = fe_time.time_matrices(1)
+    C, tw = np.asarray(C, dtype=np.float64), two.tau * np.asarray(w, dtype=np.float64)
+
+    def cycle(ps, r):
+        s = stv.Solver(0)
+        s.set_batch([p.levels for p in ps], 2, 1)
+        D = max(len(p.levels) for p in ps)
+        for g in range(D) if factors else ():
+            ma = [spatial_factors(p.levels[g - D + len(p.levels)]) for p in ps if g - D + len(p.levels) >= 0]
+            s.set_kron_factors(g, np.concatenate([m for m, _ in ma]),
+                               np.concatenate([a for _, a in ma]), C, tw)
+        s.build_cell_inverses()
+        d = to_dev(np.zeros_like(r))
+        s.vcycle(to_dev(r), d)
+        out = to_host(d)
+        s.close()
+        return out
+
+    n = two.levels[-1].n_sdofs * two.b
+    r = np.random.default_rng(43).standard_normal(len(order) * n)
+    d = cycle(order, r)
+    for i, p in enumerate(order):
+        own = cycle([p], r[i * n:(i + 1) * n])
+        assert relerr(d[i * n:(i + 1) * n], own) <= 1e-11, i
