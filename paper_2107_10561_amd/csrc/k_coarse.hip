@@ -725,13 +725,28 @@ hipError_t launch_expand_blocks(hipStream_t s, int b, int32_t n_s, const int32_t
   return hipGetLastError();
 }
 
+// The members in slices whose grids stay within 65,535 in z (a batch has up to
+// 65,535 members, and up to 48 blocks each).
+template <typename F>
+static hipError_t cc_slices(const CompCoarse* cc, const CcDims& D, F&& f) {
+  constexpr unsigned kSlice = 1024;
+  static_assert(kSlice * 4 * kCcMax <= 65535);
+  for (unsigned at = 0; at < D.cnt; at += kSlice) {
+    CcDims S = D;
+    S.cnt = D.cnt - at < kSlice ? D.cnt - at : kSlice;
+    const hipError_t e = f(cc + at, S);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
   k_cc_fill<<<dim3(D.n_s, D.blk, D.cnt), 64, 0, s>>>(cc);
   return hipGetLastError();
 }
 
 // After the V chain: V^-1, Z, G and the Schur blocks.
-hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
+static hipError_t cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
   const unsigned cols = (D.n_p + 255) / 256;
   k_cc_collect_v<<<dim3(D.n, D.blk * D.nc, D.cnt), 256, 0, s>>>(cc, D.nc);
   hipError_t e = hipGetLastError();
@@ -742,8 +757,12 @@ hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D)
   return hipGetLastError();
 }
 
+hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
+  return cc_slices(cc, D, [&](const CompCoarse* c, const CcDims& S) { return cc_schur(s, c, S); });
+}
+
 // After the Schur chain: S^-1, P, G and the verdicts.
-hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
+static hipError_t cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
   const unsigned cols = (D.n_p + 255) / 256;
   k_cc_g<<<dim3((D.n + kRows - 1) / kRows, cols, D.cnt * D.blk * D.nc), 256, 0, s>>>(cc, D.nc,
                                                                                    D.blk);
@@ -781,6 +800,10 @@ hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
   if ((e = hipGetLastError()) != hipSuccess) return e;
   k_cc_verdict<<<D.cnt, 64, 0, s>>>(cc);
   return hipGetLastError();
+}
+
+hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
+  return cc_slices(cc, D, [&](const CompCoarse* c, const CcDims& S) { return cc_finish(s, c, S); });
 }
 
 hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D,

@@ -1890,7 +1890,9 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
   // largest order down a group takes the next member while its matrices then
   // hold at most twice what they need, or 64 MB more (a batch of 8x2 and 12x3
   // coarse cells: one chain of each kind; 32 members of 16x4 cells beside one of
-  // 96x24 without this bound: every small matrix at the large one's order).
+  // 96x24 without this bound: every small matrix at the large one's order).  Nor
+  // does it grow past the grid of its kernels.
+  constexpr size_t kMaxGrid = 65535;
   int verdicts = 0;
   std::vector<int> first[2];   // of each group, among the verdicts
   for (int kind = 0; kind < 2; ++kind) {
@@ -1911,7 +1913,8 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
       const double top = groups.empty() ? 0.0 : (double)groups.back().n0;
       need += slots * n * n;
       held += slots * top * top;
-      if (groups.empty() || held > std::max(2.0 * need, need + 64e6 / 8)) {
+      if (groups.empty() || held > std::max(2.0 * need, need + 64e6 / 8) ||
+          desc.back().size() + (size_t)slots > kMaxGrid) {
         groups.emplace_back();
         groups.back().kron = true;
         groups.back().n0 = order_of(M);

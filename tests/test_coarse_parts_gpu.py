@@ -228,3 +228,28 @@ def test_coarse_members_between_others(stv, factors):
     for i, p in enumerate(order):
         own = cycle([p], r[i * n:(i + 1) * n])
         assert relerr(d[i * n:(i + 1) * n], own) <= 1e-11, i
+
+
+def test_many_members(stv):
+    """17,000 members of two cells: more blocks, and four times more members,
+    than a grid has layers.  Every member's solve against the dense inverse:
+    order 72, both of them to some tens of roundings per unit of condition."""
+    p, n = mesh_problem(2, (2, 1), 1, 1), 17000
+    L = p.levels[0]
+    _, w, C, _ = fe_time.time_matrices(1)
+    m, a = spatial_factors(L)
+    s = stv.Solver(0)
+    s.set_batch([p.levels] * n, 2, 1)
+    s.set_kron_factors(0, np.tile(m, n), np.tile(a, n), np.asarray(C, dtype=np.float64),
+                       p.tau * np.asarray(w, dtype=np.float64))
+    s.build_cell_inverses()
+    J = matrix(L, L.val, p.b).toarray()
+    inv = np.linalg.inv(J)
+    r = np.random.default_rng(47).standard_normal((n, J.shape[0]))
+    d = coarse_solve(s, r.reshape(-1)).reshape(n, -1)
+    ref = r @ inv.T
+    cond = np.linalg.norm(J, 2) * np.linalg.norm(inv, 2)
+    err = np.linalg.norm(d - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    log(f"[coarse] many members: worst {err.max():.2e}, cond {cond:.1e}")
+    assert err.max() <= 64 * 2.0 ** -53 * cond
+    s.close()
