@@ -547,6 +547,11 @@ __device__ __forceinline__ double2 cc_rhs(const CompCoarse& M, int p, int e,
   return make_double2(z0, z1);
 }
 
+// The border vectors of one of the two sets.
+__device__ __forceinline__ double2* cc_pw(const CompCoarse& M, int set) {
+  return M.pw + (int64_t)set * 2 * M.nblk * M.n_p;
+}
+
 // Sum over a workgroup of 256 threads, in thread 0.
 __device__ __forceinline__ double2 cc_block_sum(double re, double im, double2 (&red)[4]) {
 #pragma unroll
@@ -564,7 +569,7 @@ __device__ __forceinline__ double2 cc_block_sum(double re, double im, double2 (&
 // block; without P, q = z_border - Z z instead (k_cc_solve_s then forms
 // p = S^-1 q).
 template <int B>
-__global__ void __launch_bounds__(256) k_cc_solve_p(const CompCoarse* __restrict__ cc,
+__global__ void __launch_bounds__(256) k_cc_solve_p(const CompCoarse* __restrict__ cc, int set,
                                                     const double* __restrict__ r) {
   __shared__ double2 red[4];
   const CompCoarse& M = cc[blockIdx.z];
@@ -588,22 +593,24 @@ __global__ void __launch_bounds__(256) k_cc_solve_p(const CompCoarse* __restrict
   }
   const double2 v = cc_block_sum(re, im, red);
   if (threadIdx.x != 0) return;
+  double2* pw = cc_pw(M, set);
   if (form) {
-    M.pw[p * M.n_p + m] = v;
+    pw[p * M.n_p + m] = v;
   } else {
     const double2 z = cc_rhs<B>(M, p, M.n_v + m, r);
-    M.pw[(M.nblk + p) * M.n_p + m] = make_double2(z.x - v.x, z.y - v.y);
+    pw[(M.nblk + p) * M.n_p + m] = make_double2(z.x - v.x, z.y - v.y);
   }
 }
 
 // p = S^-1 q, one workgroup per border row and time block.
-__global__ void __launch_bounds__(256) k_cc_solve_s(const CompCoarse* __restrict__ cc) {
+__global__ void __launch_bounds__(256) k_cc_solve_s(const CompCoarse* __restrict__ cc, int set) {
   __shared__ double2 red[4];
   const CompCoarse& M = cc[blockIdx.z];
   const int p = blockIdx.y, m = blockIdx.x;
   if (p >= M.nblk || m >= M.n_p || M.P[p]) return;
   const double2* row = M.Si[p] + (int64_t)m * M.n_p;
-  const double2* q = M.pw + (M.nblk + p) * M.n_p;
+  double2* pw = cc_pw(M, set);
+  const double2* q = pw + (M.nblk + p) * M.n_p;
   double re = 0.0, im = 0.0;
 #pragma unroll 4
   for (int e = threadIdx.x; e < M.n_p; e += 256) {
@@ -612,19 +619,20 @@ __global__ void __launch_bounds__(256) k_cc_solve_s(const CompCoarse* __restrict
     im = fma(a.x, z.y, fma(a.y, z.x, im));
   }
   const double2 v = cc_block_sum(re, im, red);
-  if (threadIdx.x == 0) M.pw[p * M.n_p + m] = v;
+  if (threadIdx.x == 0) pw[p * M.n_p + m] = v;
 }
 
 // Second half: u = V^-1 z + G p and the time recombination, one wavefront per
 // spatial row (a border row only copies its p).
 template <int B>
-__global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict__ cc,
+__global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict__ cc, int set,
                                                     const double* __restrict__ r,
                                                     double* __restrict__ d) {
   const CompCoarse& M = cc[blockIdx.z];
   const int lane = threadIdx.x & 63;
   const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (e >= M.n_v + M.n_p) return;
+  const double2* pw = cc_pw(M, set);
   int c = 0;
   while (c < M.nc && e >= M.off[c] + M.n[c]) ++c;
   double out[B];
@@ -639,7 +647,7 @@ __global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict
       for (int j = lane; j < n; j += 64) re = fma(row[j], cc_rhs<B>(M, p, M.off[c] + j, r).x, re);
       const double* g = reinterpret_cast<const double*>(M.G[p]) + (int64_t)e * M.n_p;
 #pragma unroll 4
-      for (int m = lane; m < M.n_p; m += 64) re = fma(g[m], M.pw[p * M.n_p + m].x, re);
+      for (int m = lane; m < M.n_p; m += 64) re = fma(g[m], pw[p * M.n_p + m].x, re);
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) re += __shfl_xor(re, off, 64);
     } else if (c < M.nc) {
@@ -654,7 +662,7 @@ __global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict
       const double2* g = M.G[p] + (int64_t)e * M.n_p;
 #pragma unroll 4
       for (int m = lane; m < M.n_p; m += 64) {
-        const double2 a = g[m], z = M.pw[p * M.n_p + m];
+        const double2 a = g[m], z = pw[p * M.n_p + m];
         re = fma(a.x, z.x, fma(-a.y, z.y, re));
         im = fma(a.x, z.y, fma(a.y, z.x, im));
       }
@@ -664,7 +672,7 @@ __global__ void __launch_bounds__(256) k_cc_solve_u(const CompCoarse* __restrict
         im += __shfl_xor(im, off, 64);
       }
     } else {
-      const double2 v = M.pw[p * M.n_p + e - M.n_v];
+      const double2 v = pw[p * M.n_p + e - M.n_v];
       re = v.x;
       im = v.y;
     }
@@ -806,14 +814,14 @@ hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
   return cc_slices(cc, D, [&](const CompCoarse* c, const CcDims& S) { return cc_finish(s, c, S); });
 }
 
-hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D,
+hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D, int set,
                            const double* r, double* d) {
   const dim3 gp(D.n_p, D.blk, D.cnt), gu((D.n_s + 3) / 4, 1, D.cnt), block(256);
 #define STV_CC(B)                                                       \
   case B:                                                               \
-    launch(k_cc_solve_p<B>, gp, block, 0, s, cc, r);                    \
-    if (!D.form_p) launch(k_cc_solve_s, gp, block, 0, s, cc);           \
-    launch(k_cc_solve_u<B>, gu, block, 0, s, cc, r, d);                 \
+    launch(k_cc_solve_p<B>, gp, block, 0, s, cc, set, r);                    \
+    if (!D.form_p) launch(k_cc_solve_s, gp, block, 0, s, cc, set);           \
+    launch(k_cc_solve_u<B>, gu, block, 0, s, cc, set, r, d);                 \
     break;
   switch (D.b) {
     STV_CC(1) STV_CC(2) STV_CC(3) STV_CC(4)

@@ -596,7 +596,7 @@ int coarse_apply(stv_ctx* ctx, int g, const double* r, double* d) {
   if (nw == 0 && nk == 0 && nc == 0) return STV_OK;
   Timed t(ctx, KC_COARSE, g, nullptr, nc == 0);
   if (nc > 0)   // made for the forward direction only
-    STV_HIP(launch_cc_solve(ctx->stream, ctx->d_cc[g], ctx->cc_dims[g], r, d));
+    STV_HIP(launch_cc_solve(ctx->stream, ctx->d_cc[g], ctx->cc_dims[g], ctx->cc_set, r, d));
   if (nw > 0 && ctx->transposed)
     STV_HIP(launch_dense_gemv_t(ctx->stream, ctx->d_coarse[g], nw, ctx->b, ctx->coarse_max_n0[g],
                                 ctx->coarse_inv, r, d));
@@ -1975,7 +1975,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     R.probe_max = ctx->cc_probe_max + 16 * (&M - mem.data());
     array(R.probe_y, (size_t)R.nblk * kCcProbe * (nv + np));
     array(R.probe_q, (size_t)R.nblk * kCcProbe * np);
-    array(R.pw, (size_t)2 * R.nblk * np);
+    array(R.pw, (size_t)4 * R.nblk * np);
     for (int p = 0; p < R.nblk; ++p) {
       for (int c = 0; c <= kCcMax; ++c) {
         if (c < kCcMax && c >= R.nc) continue;
@@ -2742,7 +2742,9 @@ int stv_vcycle_noalloc(stv_ctx* ctx, const double* r, double* d, const stv_mg_pa
   // event pool may allocate), no graph
   const bool timing = ctx->timing;
   ctx->timing = false;
+  ctx->cc_set = 1;   // the border vectors of the cut coarse solves, too, are not the context's cycle's
   const int rc = vcycle_level(ctx, ctx->n_levels - 1, r, d, *p);
+  ctx->cc_set = 0;
   ctx->timing = timing;
   for (int g = 0; g < ctx->n_levels; ++g) {
     DevLevel& L = ctx->lv[g];

@@ -238,7 +238,7 @@ struct CompCoarse {
   double2 *probe_y, *probe_q;
   double2* Vi[4][kCcMax];
   double2 *Si[4], *Z[4], *G[4], *P[4];
-  double2* pw;
+  double2* pw;     // border vectors of the solve, two sets (launch_cc_solve)
   double* X;       // the whole inverse, where it is formed: X_off in the coarse store
   int64_t X_off;
 };
@@ -354,6 +354,7 @@ struct stv_ctx {
   // its verdict among those of the chains)
   std::vector<std::pair<int, std::array<int, 4 * (stv::kCcMax + 1)>>> cc_slots;
   int cc_off = 0;
+  int cc_set = 0;               // border vectors of the cut coarse solves in use
   // coarse members inverted through time decoupling, per packed level:
   // applied from their blocks' inverses (device descriptors, one per member,
   // and the largest spatial order)
@@ -503,7 +504,8 @@ hipError_t launch_expand_blocks(hipStream_t s, int b, int32_t n_s, const int32_t
 hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D);
-hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D,
+// set: which border vectors it works with (0: the context's, 1: stv_vcycle_noalloc's)
+hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D, int set,
                            const double* r, double* d);
 // rinv = the inverse of every member's pivot record rpiv (order n, real
 // order n0 from desc); verdict[z] = 0 when member z's record is a

@@ -253,3 +253,41 @@ def test_many_members(stv):
     log(f"[coarse] many members: worst {err.max():.2e}, cond {cond:.1e}")
     assert err.max() <= 64 * 2.0 ** -53 * cond
     s.close()
+
+
+def test_noalloc_beside_the_contexts_cycle(stv):
+    """A captured stv_vcycle_noalloc replayed on another stream beside the
+    context's own V-cycle, on a coarse level solved from its parts in several
+    launches: neither sees the other's vectors (bitwise, every repetition)."""
+    import torch
+    p = mesh_problem(2, (64, 16), 2, 1)
+    _, w, C, _ = fe_time.time_matrices(1)
+    C, tw = np.asarray(C, dtype=np.float64), p.tau * np.asarray(w, dtype=np.float64)
+    own, other = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(own):
+        s = stv.Solver(0, own)
+        s.set_hierarchy(p.levels, 2, 1)
+        for g, L in enumerate(p.levels):
+            s.set_kron_factors(g, *spatial_factors(L), C, tw)
+        s.build_cell_inverses()
+        rng = np.random.default_rng(53)
+        r1, r2 = (to_dev(rng.standard_normal(p.levels[-1].n_sdofs * p.b)) for _ in range(2))
+        d1, d2, ref1, ref2 = (torch.zeros_like(r1) for _ in range(4))
+        s.vcycle(r1, ref1)
+        s.vcycle(r2, ref2)
+        s.vcycle_noalloc(r1, d1)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=own):
+        s.vcycle_noalloc(r1, d1)
+    for i in range(50):
+        d1.zero_()
+        d2.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(other):
+            g.replay()
+        with torch.cuda.stream(own):
+            s.vcycle(r2, d2)
+        torch.cuda.synchronize()
+        assert torch.equal(d1, ref1) and torch.equal(d2, ref2), i
+    s.close()
