@@ -208,7 +208,7 @@ void free_hierarchy(stv_ctx* ctx) {
   ctx->inst_row.clear();
   ctx->inst_info.clear();
   ctx->max_seg = 0;
-  ctx->cc_off = 0;
+  for (auto& o : ctx->cc_off) o.clear();
   ctx->have_hier = false;
   ctx->n_levels = 0;
 }
@@ -1774,7 +1774,7 @@ static bool worth_cutting(const CompStruct& S, int32_t n_s, int b) {
 static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& split,
                                   const std::vector<bool>& has_split) {
   const bool full = ctx->inv_full != 0;
-  struct Member { int g; CompStruct S; int group[2]; int at[4][kCcMax + 1]; };
+  struct Member { int g, q; CompStruct S; int group[2]; int at[4][kCcMax + 1]; };
   std::vector<Member> mem;
   auto keep = [&](auto** p, size_t n) -> int {
     STV_TRY(dalloc(ctx, p, n));
@@ -1801,6 +1801,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
       for (int64_t i = lo; i < hi; ++i) {
         const CoarseDesc& c = all[(size_t)i];
         CompStruct S;
+        if (!ctx->cc_off[g].empty() && ctx->cc_off[g][(size_t)i]) continue;
         if (!L.kron_ma && (int64_t)c.n_s * sb <= kCutAbove) continue;
         if (!component_structure(Z.ptr.data(), Z.cols(), Z.ma.get(), c.row_off, c.n_s, S)) continue;
         if (!L.kron_ma) {
@@ -1842,6 +1843,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
       Member M{};
       M.S = std::move(found[i]);
       M.g = g;
+      M.q = (int)i;
       const TimeSplit& T = split[(size_t)g];
       CompCoarse R{};
       R.rowptr = d_rp; R.col = d_col; R.ma = d_ma;
@@ -2009,7 +2011,8 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
   // the slots' verdicts: consecutive in the report, v groups then s groups
   // (assigned with the report, see upload_component_members)
   for (const Member& M : mem) {
-    std::array<int, 4 * (kCcMax + 1)> v;
+    CcSlot sl{M.g, M.q, {}};
+    auto& v = sl.verdict;
     v.fill(-1);
     const int nblk = ctx->h_cc[M.g][0].nblk;
     for (int p = 0; p < nblk; ++p)
@@ -2018,7 +2021,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
         const int kind = c == kCcMax;
         v[(size_t)(p * (kCcMax + 1) + c)] = first[kind][(size_t)M.group[kind]] + M.at[p][c];
       }
-    ctx->cc_slots.emplace_back(M.g, v);
+    ctx->cc_slots.push_back(sl);
   }
   return STV_OK;
 }
@@ -2026,14 +2029,14 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
 // Device descriptors of the component members, their verdicts at `report`.
 static int upload_component_members(stv_ctx* ctx, int* report) {
   std::vector<size_t> next((size_t)ctx->n_levels, 0);
-  for (const auto& sl : ctx->cc_slots) {
-    if (sl.first >= ctx->n_levels || next[(size_t)sl.first] >= ctx->h_cc[sl.first].size())
+  for (const CcSlot& sl : ctx->cc_slots) {
+    if (sl.level >= ctx->n_levels || next[(size_t)sl.level] >= ctx->h_cc[sl.level].size())
       return fail(ctx, STV_ESTATE, "coarse verdicts without their members");
-    CompCoarse& R = ctx->h_cc[sl.first][next[(size_t)sl.first]++];
-    R.X = ctx->cc_dims[sl.first].form_x ? ctx->coarse_inv + R.X_off : nullptr;
+    CompCoarse& R = ctx->h_cc[sl.level][next[(size_t)sl.level]++];
+    R.X = ctx->cc_dims[sl.level].form_x ? ctx->coarse_inv + R.X_off : nullptr;
     for (int p = 0; p < 4; ++p)
       for (int c = 0; c <= kCcMax; ++c) {
-        const int v = sl.second[(size_t)(p * (kCcMax + 1) + c)];
+        const int v = sl.verdict[(size_t)(p * (kCcMax + 1) + c)];
         R.verdict[p][c] = v >= 0 ? report + v : nullptr;
       }
   }
@@ -2069,7 +2072,7 @@ static int make_coarse_groups(stv_ctx* ctx) {
   // by component where that applies and the schedule is not prescribed
   for (int g = 0; g < ctx->n_levels; ++g)
     for (CoarseDesc& c : ctx->h_coarse[g]) c.inv_off = 0;
-  if (ctx->coarse_algo == 0 && !ctx->cc_off) {
+  if (ctx->coarse_algo == 0) {
     std::vector<TimeSplit> cs = split;
     std::vector<bool> has = has_split;
     for (int g = 0; g < ctx->n_levels; ++g) {
@@ -2609,23 +2612,25 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
     return fail(ctx, STV_EHIP, std::string("inverse build failed: ") + hipGetErrorString(e));
   }
   const int none = 0x7f7f7f7f;
-  // a component-wise elimination met a small pivot: these levels eliminate
-  // the whole cell matrices instead (with these factors, from now on)
+  // a component-wise elimination was not trusted: these levels eliminate the
+  // whole cell matrices, these members the whole coarse matrix instead (with
+  // these factors, from now on)
   bool again = false;
   for (int g = 1; g < ctx->n_levels; ++g)
     if (ctx->lv[g].n_cells > 0 && ctx->lv[g].comp && ctx->h_report[g] != none) {
       ctx->lv[g].comp_off = 1;
+      ctx->inv_layout = -1;
       again = true;
     }
-  for (int k = nrep - parts; k < nrep; ++k)
-    if (ctx->h_report[k] != 0) {
-      ctx->cc_off = 1;
+  for (const CcSlot& sl : ctx->cc_slots)
+    if (std::any_of(sl.verdict.begin(), sl.verdict.end(),
+                    [&](int v) { return v >= 0 && ctx->h_report[nrep - parts + v] != 0; })) {
+      ctx->cc_off[sl.level].resize(ctx->h_coarse[sl.level].size(), 0);
+      ctx->cc_off[sl.level][(size_t)sl.member] = 1;
+      ctx->cgroups_algo = -1;
       again = true;
     }
-  if (again) {
-    ctx->inv_layout = ctx->cgroups_algo = -1;
-    return stv_build_cell_inverses(ctx, storage, bad_level, bad_cell);
-  }
+  if (again) return stv_build_cell_inverses(ctx, storage, bad_level, bad_cell);
   for (int g = 1; g < ctx->n_levels; ++g)
     if (ctx->lv[g].n_cells > 0 && ctx->h_report[g] != none) {
       if (bad_level) *bad_level = g;
@@ -3592,7 +3597,8 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
     STV_HIP(hipStreamSynchronize(ctx->stream));
     dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
     L.kg = KronGroups{};
-    L.comp_off = ctx->cc_off = 0;
+    L.comp_off = 0;
+    for (auto& o : ctx->cc_off) o.clear();
     ctx->cgroups_algo = -1;   // the coarse groups may refer to the factors
     ctx->inv_layout = -1;     // and the cell-inverse layout of the level
     ++ctx->generation;
@@ -3651,7 +3657,8 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
   if (rc != STV_OK) { drop(); return rc; }
   dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
   L.kron_ma = dma;
-  L.comp_off = ctx->cc_off = 0;
+  L.comp_off = 0;
+  for (auto& o : ctx->cc_off) o.clear();
   L.kg = kg;
   L.kg_idx = kg_idx;
   L.kg_val = kg_val;

@@ -256,6 +256,14 @@ struct CcDims {
   bool form_x = false;
 };
 
+// A cut member: its level, its place among the level's coarse members, and per
+// time block and block the index of its verdict among those of the chains (-1:
+// none).
+struct CcSlot {
+  int level, member;
+  std::array<int, 4 * (kCcMax + 1)> verdict;
+};
+
 // The coarse members of one order, eliminated by one batched Gauss-Jordan:
 // members (packed level, index in that level), their device descriptors,
 // the elimination buffers and the inverse pivot permutations.
@@ -343,17 +351,17 @@ struct stv_ctx {
   int cgroups_algo = -1;        // the coarse algorithm, + 16 for the all-rows layout
   // coarse members with uncoupled components, per packed level; the chains
   // over their component blocks and over their Schur complements; their other
-  // device arrays; cc_off: a block was not trusted for these factors
+  // device arrays
   std::vector<stv::CompCoarse> h_cc[stv::kMaxLevels];
   stv::CompCoarse* d_cc[stv::kMaxLevels] = {};
   stv::CcDims cc_dims[stv::kMaxLevels];
   std::vector<stv::CoarseGroup> vgroups, sgroups;
   std::vector<void*> cc_bufs;
   unsigned long long* cc_probe_max = nullptr;   // probe_max of all of them, in cc_slots' order
-  // per component member (level, then per time block and block the index of
-  // its verdict among those of the chains)
-  std::vector<std::pair<int, std::array<int, 4 * (stv::kCcMax + 1)>>> cc_slots;
-  int cc_off = 0;
+  std::vector<stv::CcSlot> cc_slots;
+  // coarse members (per level, as in h_coarse) whose parts were not trusted,
+  // for these factors: eliminated as a whole
+  std::vector<char> cc_off[stv::kMaxLevels];
   int cc_set = 0;               // border vectors of the cut coarse solves in use
   // coarse members inverted through time decoupling, per packed level:
   // applied from their blocks' inverses (device descriptors, one per member,

@@ -291,3 +291,32 @@ def test_noalloc_beside_the_contexts_cycle(stv):
         torch.cuda.synchronize()
         assert torch.equal(d1, ref1) and torch.equal(d2, ref2), i
     s.close()
+
+
+@pytest.mark.parametrize("factors", [True, False])
+def test_untrusted_member_of_a_batch(stv, factors):
+    """One member's parts cannot be trusted: it is eliminated as a whole, the
+    others stay cut (bitwise the solves of a batch without it)."""
+    p, L, m, a, C, tw, val, J = weakened(2, (16, 4), 1, "rows", 1e-8)
+    good = mesh_problem(2, (16, 4), 1, 1)
+    gm, ga = spatial_factors(good.levels[0])
+    weak = [dict(n_sdofs=L.n_sdofs, rowptr=L.rowptr, col=L.col, val=val, cell_sdofs=L.cell_sdofs, P=None)]
+    r = np.random.default_rng(59).standard_normal(3 * J.shape[0])
+
+    def solve(kinds):
+        s = stv.Solver(0)
+        s.set_batch([weak if k else good.levels for k in kinds], 2, 1)
+        if factors:
+            s.set_kron_factors(0, np.concatenate([m if k else gm for k in kinds]),
+                               np.concatenate([a if k else ga for k in kinds]), C, tw)
+        out = []
+        for _ in range(2):
+            s.build_cell_inverses()
+            out.append(coarse_solve(s, r).reshape(3, -1))
+        s.close()
+        return out
+
+    ref = solve([False, False, False])[0]
+    for d in solve([False, True, False]):
+        check_solve(J, r.reshape(3, -1)[1], d[1], f"untrusted member factors={factors}")
+        assert np.array_equal(d[0], ref[0]) and np.array_equal(d[2], ref[2])
