@@ -9,7 +9,7 @@
 // is applied in factored form,
 //   p = S^-1 (g - Z f),  Z = C V^-1,   u = V^-1 f + G p,  G = -V^-1 B
 // (three launches), or with P = S^-1 [-Z | I] formed, p = P (f, g) (two), or,
-// small or needed in both directions, as the whole inverse
+// small or transposed, as the whole inverse of each time block,
 //   [ V^-1 0 ; 0 0 ] + [ G ; I ] P   (one).
 // The chains are bound by their panels in sequence, 16 complex pivots each: in
 // 3d (16x3x3 cells) 32 for nine blocks of order 506 and 55 for a border of 870
@@ -261,16 +261,18 @@ __global__ void __launch_bounds__(256) k_cc_p(const CompCoarse* __restrict__ cc,
   }
 }
 
-// The whole inverse, real and in the level's order (CcDims::form_x): block rows
-// G P + V^-1, border rows P, the time blocks recombined, X = sum_p V_p x_p W_p.
-// It is then applied like any whole inverse, in one launch and both directions.
-template <int B>
-__global__ void __launch_bounds__(256) k_cc_x(const CompCoarse* __restrict__ cc) {
+// A time block's whole inverse in the level's row order: block rows G P + V^-1,
+// border rows P.  One time component (CcDims::form_x): real, into the coarse
+// store, scaled by the block's V and W.  More (form_c): Xp, a complex or real
+// entry per spatial pair, for k_cc_apply: 16 n^2 instead of the 32 n^2 bytes of
+// the recombined inverse for a pair, 24 instead of 72 with a real block beside.
+__global__ void __launch_bounds__(256) k_cc_x(const CompCoarse* __restrict__ cc, int blocks) {
   __shared__ CcLds lds;
-  const CompCoarse& M = cc[blockIdx.z];
+  const CompCoarse& M = cc[blockIdx.z / blocks];
+  const int p = blockIdx.z % blocks;
   const int n_p = M.n_p, n_v = M.n_v, n_s = n_v + n_p;
   const int e0 = blockIdx.y * kCcTile, f0 = blockIdx.x * kCcTile;
-  if (e0 >= n_s || f0 >= n_s) return;
+  if (p >= M.nblk || e0 >= n_s || f0 >= n_s) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int lr = lane >> 4, lc = lane & 15, wr = 16 * (w >> 1), wc = 16 * (w & 1);
   const double2 zero = make_double2(0.0, 0.0);
@@ -290,71 +292,183 @@ __global__ void __launch_bounds__(256) k_cc_x(const CompCoarse* __restrict__ cc)
   }
   __syncthreads();
   const int f = min(f0 + wc + lc, n_s - 1);
-  for (int p = 0; p < M.nblk; ++p) {
+  const bool pair = M.sz[p] == 2;
+  const double2 *G = M.G[p], *P = M.P[p];
+  stv_d4 re = {}, im = {};
+  if (e0 < n_v)
+    cc_tile(lds, n_p, pair,
+            [&](int r, int k) {
+              return e0 + r < n_v && k < n_p ? cc_get(G, (int64_t)(e0 + r) * n_p + k, pair) : zero;
+            },
+            [&](int k, int c) {
+              return k < n_p && f0 + c < n_s ? cc_get(P, (int64_t)k * n_s + f0 + c, pair) : zero;
+            },
+            re, im);
+  // the rows' own entries; all reads stand before the writes, which they
+  // could not pass
+  double2 x[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int er = wr + 4 * v + lr, e = min(e0 + er, n_s - 1);
+    const int c = row_c[er], o = row_o[er], n = row_n[er];
+    const bool border = c == kCcMax, in = f >= o && f < o + n;
+    const double2* from = border ? P : M.Vi[p][in ? c : 0];
+    const int64_t at = border ? (int64_t)(e - n_v) * n_s + f
+                              : in ? (int64_t)(e - o) * n + f - o : 0;
+    const double2 q = cc_get(from, at, pair);
+    x[v].x = (border ? 0.0 : re[v]) + (border || in ? q.x : 0.0);
+    x[v].y = (border ? 0.0 : im[v]) + (border || in ? q.y : 0.0);
+  }
+  if (f0 + wc + lc >= n_s) return;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    if (e0 + wr + 4 * v + lr >= n_s) continue;
+    const int64_t at = (int64_t)row_at[wr + 4 * v + lr] * n_s + col_at[wc + lc];
+    if (M.X) M.X[at] = M.V[0] * (x[v].x * M.W[0]);
+    else cc_put(M.Xp[p], at, pair, x[v]);
+  }
+}
+
+// d = J^-1 r from the time blocks' whole inverses, a workgroup per spatial row:
+// z = W r on the fly, y_p = x_p z_p, d = V y.  Bound by the latency of a row's
+// loads: four are in flight per thread.
+template <int B>
+__global__ void __launch_bounds__(256) k_cc_apply(const CompCoarse* __restrict__ cc,
+                                                  const double* __restrict__ r,
+                                                  double* __restrict__ d) {
+  __shared__ double2 red[4][B];
+  const CompCoarse& M = cc[blockIdx.z];
+  const int n = M.n_v + M.n_p, s = blockIdx.x;
+  if (s >= n) return;
+  const double* rz = r + (int64_t)M.row_off * B;
+  double2 acc[B];
+#pragma unroll
+  for (int p = 0; p < B; ++p) {
+    acc[p] = make_double2(0.0, 0.0);
+    if (p >= M.nblk) continue;
+    const int f = M.first[p];
     const bool pair = M.sz[p] == 2;
-    const double2 *G = M.G[p], *P = M.P[p];
-    stv_d4 re = {}, im = {};
-    if (e0 < n_v)
-      cc_tile(lds, n_p, pair,
-              [&](int r, int k) {
-                return e0 + r < n_v && k < n_p ? cc_get(G, (int64_t)(e0 + r) * n_p + k, pair) : zero;
-              },
-              [&](int k, int c) {
-                return k < n_p && f0 + c < n_s ? cc_get(P, (int64_t)k * n_s + f0 + c, pair) : zero;
-              },
-              re, im);
-    // the rows' own entries; all reads stand before the writes, which they
-    // could not pass
-    double2 x[4];
+    double w0[B], w1[B];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int er = wr + 4 * v + lr, e = min(e0 + er, n_s - 1);
-      const int c = row_c[er], o = row_o[er], n = row_n[er];
-      const bool border = c == kCcMax, in = f >= o && f < o + n;
-      const double2* from = border ? P : M.Vi[p][in ? c : 0];
-      const int64_t at = border ? (int64_t)(e - n_v) * n_s + f
-                                : in ? (int64_t)(e - o) * n + f - o : 0;
-      const double2 q = cc_get(from, at, pair);
-      x[v].x = (border ? 0.0 : re[v]) + (border || in ? q.x : 0.0);
-      x[v].y = (border ? 0.0 : im[v]) + (border || in ? q.y : 0.0);
+    for (int l = 0; l < B; ++l) {
+      w0[l] = M.W[f * B + l];
+      w1[l] = pair ? M.W[(f + 1) * B + l] : 0.0;
     }
-    const int t = M.first[p];
-    double old[4][B][B];
+    constexpr int U = 4;
+    for (int c0 = threadIdx.x; c0 < n; c0 += 256 * U) {
+      double2 x[U];
+      double v[U][B];
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+      for (int u = 0; u < U; ++u) {
+        const int c = min(c0 + 256 * u, n - 1);
+        x[u] = cc_get(M.Xp[p], (int64_t)s * n + c, pair);
 #pragma unroll
-      for (int q = 0; q < B; ++q)
-#pragma unroll
-        for (int l = 0; l < B; ++l)
-          old[v][q][l] = p > 0 ? M.X[((int64_t)row_at[wr + 4 * v + lr] * B + q) * n_s * B +
-                                     (int64_t)col_at[wc + lc] * B + l]
-                               : 0.0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int l = 0; l < B; ++l) {
-        const double w0 = M.W[t * B + l], w1 = pair ? M.W[(t + 1) * B + l] : 0.0;
-        const double zr = x[v].x * w0 - x[v].y * w1, zi = x[v].x * w1 + x[v].y * w0;
-#pragma unroll
-        for (int q = 0; q < B; ++q) {
-          double y = fma(M.V[q * B + t], zr, old[v][q][l]);
-          if (pair) y = fma(M.V[q * B + t + 1], zi, y);
-          old[v][q][l] = y;
-        }
+        for (int l = 0; l < B; ++l) v[u][l] = rz[(int64_t)c * B + l];
       }
-    if (f0 + wc + lc < n_s) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        if (e0 + wr + 4 * v + lr >= n_s) continue;
+      for (int u = 0; u < U; ++u) {
+        double z0 = 0.0, z1 = 0.0;
 #pragma unroll
-        for (int q = 0; q < B; ++q)
-#pragma unroll
-          for (int l = 0; l < B; ++l)
-            M.X[((int64_t)row_at[wr + 4 * v + lr] * B + q) * n_s * B +
-                (int64_t)col_at[wc + lc] * B + l] = old[v][q][l];
+        for (int l = 0; l < B; ++l) {
+          z0 = fma(w0[l], v[u][l], z0);
+          z1 = fma(w1[l], v[u][l], z1);
+        }
+        const double re = fma(x[u].x, z0, fma(-x[u].y, z1, acc[p].x));
+        const double im = fma(x[u].x, z1, fma(x[u].y, z0, acc[p].y));
+        const bool in = c0 + 256 * u < n;
+        acc[p].x = in ? re : acc[p].x;
+        acc[p].y = in ? im : acc[p].y;
       }
     }
   }
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int p = 0; p < B; ++p) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      acc[p].x += __shfl_xor(acc[p].x, off, 64);
+      acc[p].y += __shfl_xor(acc[p].y, off, 64);
+    }
+    if (lane == 0) red[wv][p] = acc[p];
+  }
+  __syncthreads();
+  if (threadIdx.x >= B) return;
+  const int i = threadIdx.x;
+  double out = 0.0;
+#pragma unroll
+  for (int p = 0; p < B; ++p) {
+    if (p >= M.nblk) continue;
+    const double re = (red[0][p].x + red[1][p].x) + (red[2][p].x + red[3][p].x);
+    const double im = (red[0][p].y + red[1][p].y) + (red[2][p].y + red[3][p].y);
+    const int f = M.first[p];
+    out = fma(M.V[i * B + f], re, out);
+    if (M.sz[p] == 2) out = fma(M.V[i * B + f + 1], im, out);
+  }
+  d[((int64_t)M.row_off + s) * B + i] = out;
+}
+
+// d = J^-T r: per time block t = sum_s conj(u_s) x_p[s, .] with u = (V^T r) (its
+// pair of columns), d_l = Re(t w_l).  16 columns per workgroup, 64 row groups of
+// 16 threads each take the rows g, g + 64, ... and meet in LDS in a fixed order
+// (as k_dense_gemv_t).
+template <int B>
+__global__ void __launch_bounds__(1024) k_cc_apply_t(const CompCoarse* __restrict__ cc,
+                                                     const double* __restrict__ r,
+                                                     double* __restrict__ d) {
+  constexpr int NC = 16, NG = 64;
+  __shared__ double2 red[NG][NC + 1];
+  const CompCoarse& M = cc[blockIdx.z];
+  const int n = M.n_v + M.n_p;
+  if ((int)blockIdx.x * NC >= n) return;
+  const int c = threadIdx.x % NC, g = threadIdx.x / NC;
+  const int j = min((int)blockIdx.x * NC + c, n - 1);
+  const double* rz = r + (int64_t)M.row_off * B;
+  double out[B];
+#pragma unroll
+  for (int l = 0; l < B; ++l) out[l] = 0.0;
+  for (int p = 0; p < M.nblk; ++p) {
+    const int f = M.first[p];
+    const bool pair = M.sz[p] == 2;
+    double v0[B], v1[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      v0[i] = M.V[i * B + f];
+      v1[i] = pair ? M.V[i * B + f + 1] : 0.0;
+    }
+    double2 t = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (int s = g; s < n; s += NG) {
+      const double2 x = cc_get(M.Xp[p], (int64_t)s * n + j, pair);
+      double u0 = 0.0, u1 = 0.0;
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        const double v = rz[(int64_t)s * B + i];
+        u0 = fma(v0[i], v, u0);
+        u1 = fma(v1[i], v, u1);
+      }
+      t.x = fma(x.x, u0, fma(x.y, u1, t.x));
+      t.y = fma(x.y, u0, fma(-x.x, u1, t.y));
+    }
+    __syncthreads();   // the last block's sums have been read
+    red[g][c] = t;
+    __syncthreads();
+    for (int h = NG / 2; h >= 1; h >>= 1) {
+      if (g < h) {
+        red[g][c].x += red[g + h][c].x;
+        red[g][c].y += red[g + h][c].y;
+      }
+      __syncthreads();
+    }
+    t = red[0][c];
+#pragma unroll
+    for (int l = 0; l < B; ++l) {
+      out[l] = fma(M.W[f * B + l], t.x, out[l]);
+      if (pair) out[l] = fma(-M.W[(f + 1) * B + l], t.y, out[l]);
+    }
+  }
+  if (g != 0 || (int)blockIdx.x * NC + c >= n) return;
+#pragma unroll
+  for (int l = 0; l < B; ++l) d[((int64_t)M.row_off + j) * B + l] = out[l];
 }
 
 // ---------------------------------------------------------------------------
@@ -783,16 +897,9 @@ static hipError_t cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
              256, 0, s>>>(cc, D.blk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (D.form_x) {
+  if (D.form_x || D.form_c) {
     const unsigned tiles = (D.n_s + kCcTile - 1) / kCcTile;
-    const dim3 grid(tiles, tiles, D.cnt);
-    switch (D.b) {
-      case 1: k_cc_x<1><<<grid, 256, 0, s>>>(cc); break;
-      case 2: k_cc_x<2><<<grid, 256, 0, s>>>(cc); break;
-      case 3: k_cc_x<3><<<grid, 256, 0, s>>>(cc); break;
-      case 4: k_cc_x<4><<<grid, 256, 0, s>>>(cc); break;
-      default: return hipErrorInvalidValue;
-    }
+    k_cc_x<<<dim3(tiles, tiles, D.cnt * D.blk), 256, 0, s>>>(cc, D.blk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const dim3 gb((D.n_p + 3) / 4, D.blk, D.cnt), gs((D.n_s + 3) / 4, D.blk, D.cnt);
@@ -812,6 +919,23 @@ static hipError_t cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
 
 hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
   return cc_slices(cc, D, [&](const CompCoarse* c, const CcDims& S) { return cc_finish(s, c, S); });
+}
+
+hipError_t launch_cc_apply(hipStream_t s, const CompCoarse* cc, const CcDims& D, bool transposed,
+                           const double* r, double* d) {
+  if (!D.form_c) return hipErrorInvalidValue;
+  const dim3 row(D.n_s, 1, D.cnt), col((D.n_s + 15) / 16, 1, D.cnt);
+#define STV_CC(B)                                                               \
+  case B:                                                                       \
+    if (transposed) launch(k_cc_apply_t<B>, col, dim3(1024), 0, s, cc, r, d);   \
+    else launch(k_cc_apply<B>, row, dim3(256), 0, s, cc, r, d);                 \
+    break;
+  switch (D.b) {
+    STV_CC(2) STV_CC(3) STV_CC(4)
+    default: return hipErrorInvalidValue;
+  }
+#undef STV_CC
+  return hipGetLastError();
 }
 
 hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D, int set,

@@ -595,7 +595,9 @@ int coarse_apply(stv_ctx* ctx, int g, const double* r, double* d) {
   const int nc = ctx->cc_dims[g].form_x ? 0 : (int)ctx->h_cc[g].size();
   if (nw == 0 && nk == 0 && nc == 0) return STV_OK;
   Timed t(ctx, KC_COARSE, g, nullptr, nc == 0);
-  if (nc > 0)   // made for the forward direction only
+  if (nc > 0 && (ctx->transposed || ctx->cc_dims[g].use_c))
+    STV_HIP(launch_cc_apply(ctx->stream, ctx->d_cc[g], ctx->cc_dims[g], ctx->transposed, r, d));
+  else if (nc > 0)   // the factors: the forward direction only
     STV_HIP(launch_cc_solve(ctx->stream, ctx->d_cc[g], ctx->cc_dims[g], ctx->cc_set, r, d));
   if (nw > 0 && ctx->transposed)
     STV_HIP(launch_dense_gemv_t(ctx->stream, ctx->d_coarse[g], nw, ctx->b, ctx->coarse_max_n0[g],
@@ -1861,26 +1863,40 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
       ctx->h_cc[g].push_back(R);
       mem.push_back(std::move(M));
     }
-    // what is formed of them
-    double fp = 0.0, fx = 0.0;
+    // What is formed of them.  A solve reads the parts (part_bytes) in two or
+    // three launches, or the whole inverse (bytes) in one.  Always formed with
+    // the all-rows layout, whose transposed solves need it.  Else, several time
+    // components (a complex entry per spatial pair), where one launch is the
+    // faster by enough to pay for the forming within some 60 cycles, whole and
+    // parts: 436 rows (0.8 MB) 4.0 and 6.6 us, 1572 (9.9) 5.2 and 9.0, 2404 (23)
+    // 7.4 and 8.8, 3348 (45) 10.9 and 15.6, 3d 2142 (18) 6.2 and 8.7, 2806 (32)
+    // 9.1 and 10.9; 4484 (80) 16.4 and 20.2, but 0.6 ms of forming; 3d 8214 (270)
+    // 44 and 31.  One component (real entries, larger borders): small, or while
+    // the whole inverse stays in the last-level cache and the parts are more than
+    // half of it: 1572 rows (20 MB) 6.3 and 10.2 us, 2404 (46) 10.7 and 13.2, 3412
+    // (93) 17.8 and 24.8, 4484 (161) 27.1 and 33.7; 5956 (284) 52.8 and 47.8; 3d,
+    // parts 0.4 of it, 2142 (37) 9.8 and 8.9, 2806 (63) 12.9 and 12.4.
+    double fp = 0.0, bytes = 0.0, part_bytes = 0.0;
     int64_t rows = 0;
     for (const CompCoarse& R : ctx->h_cc[g]) {
+      const double n = R.n_v + R.n_p;
+      double parts = R.n_p * (R.n_v + n);
+      for (int k = 0; k < R.nc; ++k) parts += (double)R.n[k] * R.n[k];
       for (int p = 0; p < R.nblk; ++p) {
-        const double c = R.sz[p] == 2 ? 8.0 : 2.0;
-        fp += c * R.n_p * R.n_p * R.n_v;
-        fx += c * R.n_p * R.n_v * (R.n_v + R.n_p);
+        fp += (R.sz[p] == 2 ? 8.0 : 2.0) * R.n_p * R.n_p * R.n_v;
+        bytes += 8.0 * R.sz[p] * n * n;
+        part_bytes += 8.0 * R.sz[p] * parts;
       }
       rows = std::max<int64_t>(rows, (int64_t)(R.n_v + R.n_p) * b);
     }
     CcDims& D = ctx->cc_dims[g];
-    // The whole inverse: always with the all-rows layout, whose transposed
-    // solves need it (a second set of factored kernels otherwise); else while
-    // one launch is faster than two.  Forming it and an apply then and
-    // without: order 132 26 us, 3.9 and 6.5 us; 786 23 us, 4.0 and 8.1; 1188
-    // 4.8 and 7.8; 1572 40 to 90 us, 6.4 and 9.1; from 2055 the applies are
-    // equal.
-    D.form_x = full || (rows <= 1600 && fp + fx <= 4e9);
-    D.form_p = D.form_x || fp <= 2e9;
+    if (b == 1) {
+      D.form_x = full || (bytes <= 170e6 && (rows <= 1600 || 2.0 * part_bytes > bytes));
+    } else {
+      D.use_c = bytes <= 48e6;
+      D.form_c = full || D.use_c;
+    }
+    D.form_p = D.form_x || D.form_c || fp <= 2e9;
     if (D.form_x)
       for (CoarseDesc& c : ctx->h_coarse[g])
         if (c.inv_off == -2) c.inv_off = -3;
@@ -1992,6 +2008,8 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
       array(R.Z[p], np * nv);
       array(R.G[p], nv * np);
       if (ctx->cc_dims[M.g].form_p) array(R.P[p], np * (nv + np));
+      if (ctx->cc_dims[M.g].form_c)
+        array(R.Xp[p], R.sz[p] == 2 ? (nv + np) * (nv + np) : ((nv + np) * (nv + np) + 1) / 2);
     }
     CcDims& D = ctx->cc_dims[M.g];
     for (int c = 0; c < R.nc; ++c) D.n = std::max(D.n, (unsigned)R.n[c]);

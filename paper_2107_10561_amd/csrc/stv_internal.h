@@ -237,9 +237,9 @@ struct CompCoarse {
   unsigned long long* probe_max;
   double2 *probe_y, *probe_q;
   double2* Vi[4][kCcMax];
-  double2 *Si[4], *Z[4], *G[4], *P[4];
+  double2 *Si[4], *Z[4], *G[4], *P[4], *Xp[4];   // Xp: the block's whole inverse, where formed
   double2* pw;     // border vectors of the solve, two sets (launch_cc_solve)
-  double* X;       // the whole inverse, where it is formed: X_off in the coarse store
+  double* X;       // one time component: Xp in its place is X_off of the coarse store
   int64_t X_off;
 };
 // launch dimensions over the members of one level: largest block, border and
@@ -252,8 +252,10 @@ struct CcDims {
   unsigned n = 0, n_p = 0, n_s = 0, nc = 0, blk = 0, cnt = 0;
   int b = 0;   // time components of the rows
   bool form_p = false;
-  // form_x: and the whole inverse from the factors, applied as one
-  bool form_x = false;
+  // the whole inverses of the time blocks from the factors: form_x of the only
+  // one, in the coarse store; form_c as Xp, which use_c says the forward solve
+  // applies (the transposed one always does)
+  bool form_x = false, form_c = false, use_c = false;
 };
 
 // A cut member: its level, its place among the level's coarse members, and per
@@ -512,6 +514,8 @@ hipError_t launch_expand_blocks(hipStream_t s, int b, int32_t n_s, const int32_t
 hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D);
+hipError_t launch_cc_apply(hipStream_t s, const CompCoarse* cc, const CcDims& D, bool transposed,
+                           const double* r, double* d);
 // set: which border vectors it works with (0: the context's, 1: stv_vcycle_noalloc's)
 hipError_t launch_cc_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D, int set,
                            const double* r, double* d);

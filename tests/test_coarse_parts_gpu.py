@@ -320,3 +320,37 @@ def test_untrusted_member_of_a_batch(stv, factors):
     for d in solve([False, True, False]):
         check_solve(J, r.reshape(3, -1)[1], d[1], f"untrusted member factors={factors}")
         assert np.array_equal(d[0], ref[0]) and np.array_equal(d[2], ref[2])
+
+
+# spatial rows on both sides of a workgroup's round and of a column group, two
+# time blocks, a real one and a pair, two pairs; whole inverses and parts
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("case", [(2, (4, 1), 1), (2, (20, 5), 1), (2, (24, 8), 1), (2, (9, 3), 2),
+                                  (2, (16, 4), 3), (3, (3, 2, 2), 1)])
+def test_whole_inverse_per_time_block(stv, case, full):
+    """The time blocks' whole inverses, forward and transposed; and of two
+    members at once the same bits as of each alone."""
+    dim, n, k = case
+    p = mesh_problem(dim, n, 1, k)
+    L = p.levels[0]
+    J = matrix(L, L.val, p.b)
+    _, w, C, _ = fe_time.time_matrices(k)
+    m, a = spatial_factors(L)
+    r = np.random.default_rng(61).standard_normal(2 * J.shape[0])
+    got = {}
+    for members in (1, 2):
+        s = stv.Solver(0)
+        s.set_batch([p.levels] * members, dim, k)
+        s.set_kron_factors(0, np.tile(m, members), np.tile(a, members), np.asarray(C, dtype=np.float64),
+                           p.tau * np.asarray(w, dtype=np.float64))
+        s.build_cell_inverses(full=full)
+        rr = r[:members * J.shape[0]]
+        got[members] = coarse_solve(s, rr)
+        check_solve(J, r[:J.shape[0]], got[members][:J.shape[0]], f"{case} full={full}")
+        if full:
+            dd = to_dev(np.zeros_like(rr))
+            s.vcycle_transposed(to_dev(rr), dd)
+            check_solve(J.T.tocsc(), r[:J.shape[0]], to_host(dd)[:J.shape[0]], f"{case} transposed")
+        s.close()
+    if 16 * L.n_sdofs ** 2 * k < 24e6:   # both members' inverses are applied whole
+        assert np.array_equal(got[1], got[2][:J.shape[0]])
