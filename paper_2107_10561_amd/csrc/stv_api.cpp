@@ -1755,8 +1755,7 @@ static void expand_structure(CompStruct& S, int b, int32_t row_off, const Coarse
 
 // Whether a member without factors is cut.  Some rows have no diagonal entry (a
 // block of a matrix with pressure-pressure entries can be singular up to a
-// constant, and the build would find that out late), and the real forms fit
-// the elimination.  The pivots left in sequence decide the rest, a chain of
+// constant, and the build would find that out late).  The pivots left in sequence decide the rest, a chain of
 // these being slower per pivot than the whole matrix's (32 real columns for 16
 // pivots): at 0.29 of the order 8.9 -> 3.1 ms (2806), at 0.48 4.5 -> 2.2 ms
 // (1572), at 0.51 2.15 -> 1.70 ms (892), at 0.60 none (0.34 -> 0.46 ms at 124).
@@ -1766,8 +1765,7 @@ constexpr int64_t kCutAbove = 512;
 static bool worth_cutting(const CompStruct& S, int32_t n_s, int b) {
   int mx = 0;
   for (int c = 0; c < S.nc; ++c) mx = std::max(mx, S.n[c]);
-  return S.n_bare > 0 && (int64_t)n_s * b > kCutAbove && 20 * ((int64_t)mx + S.n_p) <= 11 * (int64_t)n_s &&
-         2 * (int64_t)std::max(mx, S.n_p) * b <= gj_plan(2, 3, true).max_n;
+  return S.n_bare > 0 && (int64_t)n_s * b > kCutAbove && 20 * ((int64_t)mx + S.n_p) <= 11 * (int64_t)n_s;
 }
 
 // Members with a component structure: descriptors, chains and buffers.  The
@@ -1806,6 +1804,9 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
         if (!ctx->cc_off[g].empty() && ctx->cc_off[g][(size_t)i]) continue;
         if (!L.kron_ma && (int64_t)c.n_s * sb <= kCutAbove) continue;
         if (!component_structure(Z.ptr.data(), Z.cols(), Z.ma.get(), c.row_off, c.n_s, S)) continue;
+        // the real forms have to fit the elimination
+        const int64_t most = std::max<int64_t>(S.n_p, *std::max_element(S.n, S.n + S.nc));
+        if (2 * most * sb > gj_plan(2, 3, true).max_n) continue;
         if (!L.kron_ma) {
           if (!worth_cutting(S, c.n_s, sb)) continue;
           expand_structure(S, sb, c.row_off, Z);
@@ -2480,6 +2481,15 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
   if (rc == STV_OK && ctx->cgroups_algo != want_groups) {
     free_coarse_groups(ctx);
     rc = make_coarse_groups(ctx);
+    // the parts can take more memory than the whole matrices: these then
+    bool cut = false;
+    for (const auto& h : ctx->h_cc) cut |= !h.empty();
+    if (rc == STV_ENOMEM && cut) {
+      (void)hipGetLastError();
+      free_coarse_groups(ctx);
+      for (int g = 0; g < ctx->n_levels; ++g) ctx->cc_off[g].assign(ctx->h_coarse[g].size(), 1);
+      rc = make_coarse_groups(ctx);
+    }
     if (rc == STV_OK) ctx->cgroups_algo = want_groups;
     moved = regrouped = true;
   }

@@ -1,0 +1,82 @@
+"""Host paths of the library that a device cannot be asked for, on a fake HIP
+runtime (fake_hip.cpp) in a process of their own: memory that is not there,
+exceptions of the host allocator at the C entries, grids at their limits."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, sys
+import numpy as np
+sys.path.insert(0, {root!r})
+fake = ctypes.CDLL({lib!r}, mode=ctypes.RTLD_GLOBAL)
+fake.fake_limit.argtypes = [ctypes.c_size_t]
+fake.fake_used.restype = fake.fake_peak.restype = ctypes.c_size_t
+fake.fake_fail_new.argtypes = [ctypes.c_long]
+fake.fake_new_left.restype = ctypes.c_long
+import paper_2107_10561_amd as stv
+from stgen import fe
+from stgen.problem import make_problem, spatial_factors
+
+def solver():
+    s = stv.Solver.__new__(stv.Solver)
+    h = ctypes.c_void_p()
+    assert stv._lib.stv_create(ctypes.byref(h), 0, None) == 0
+    s._h, s._torch, s.device, s.stream, s.n_st = h, None, 0, None, []
+    return s
+
+def factors(s, ps, g=0):
+    _, w, C, _ = fe.time_matrices(ps[0].k)
+    ma = [spatial_factors(p.levels[g]) for p in ps]
+    s.set_kron_factors(g, np.concatenate([m for m, _ in ma]), np.concatenate([a for _, a in ma]),
+                       np.asarray(C, dtype=np.float64), ps[0].tau * np.asarray(w, dtype=np.float64))
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", os.path.join(HERE, "fake_hip.cpp"), "-o", lib], check=True)
+
+    def go(body):
+        r = subprocess.run([sys.executable, "-c", PRELUDE.format(root=ROOT, lib=lib) + body],
+                           capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, (r.returncode, r.stdout[-2000:], r.stderr[-3000:])
+        return r.stdout
+
+    return go
+
+
+@pytest.mark.parametrize("kron", [True, False])
+def test_parts_that_do_not_fit(run, kron):
+    """A device that holds the whole elimination's buffers but not the parts':
+    the build succeeds, with the whole elimination."""
+    run(f"""
+p = make_problem(2, (16, 4), 1, 1, 0.01, 1e-3, 7)
+s = solver()
+s.set_coarse_algorithm("tournament")
+s.set_hierarchy(p.levels, 2, 1)
+if {kron}: factors(s, [p])
+fake.fake_peak(1)
+before = fake.fake_used()
+s.build_cell_inverses(full=True)
+whole = fake.fake_peak(0)
+s.set_coarse_algorithm("auto")
+s.set_hierarchy(p.levels, 2, 1)
+if {kron}: factors(s, [p])
+assert fake.fake_used() <= before + (1 << 20), (fake.fake_used(), before)
+fake.fake_peak(1)
+s.build_cell_inverses(full=True)
+assert fake.fake_peak(0) > whole, "the parts take more here"
+s.set_hierarchy(p.levels, 2, 1)
+if {kron}: factors(s, [p])
+fake.fake_limit(whole + (64 << 10))
+s.build_cell_inverses(full=True)
+s.build_cell_inverses(full=True)
+""")
