@@ -109,6 +109,33 @@ void dfree(T*& p) {
   p = nullptr;
 }
 
+// Device memory of a call, freed on every path out of it.
+template <typename T>
+struct Temp {
+  T* p = nullptr;
+  Temp() = default;
+  Temp(const Temp&) = delete;
+  Temp& operator=(const Temp&) = delete;
+  ~Temp() { dfree(p); }
+  T* release() {
+    T* q = p;
+    p = nullptr;
+    return q;
+  }
+};
+
+// No exception leaves a C entry.  Those the library can meet are of host memory;
+// undo takes back what the call had made.
+template <typename F, typename U>
+int guarded(stv_ctx* ctx, F&& f, U&& undo) {
+  try {
+    return f();
+  } catch (...) {
+  }
+  undo();
+  return fail(ctx, STV_ENOMEM, "no host memory");   // short enough to need none
+}
+
 void free_graph(stv_ctx* ctx) {
   if (ctx->graph_exec) (void)hipGraphExecDestroy(ctx->graph_exec);
   if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
@@ -1201,17 +1228,22 @@ const char* stv_last_error(const stv_ctx* ctx) {
 
 int stv_validate_hierarchy(int n_levels, int dim, int k, const stv_level* lv, char* err,
                            size_t errlen) {
-  std::string msg;
-  const bool ok = validate_impl(n_levels, dim, k, lv, msg);
-  if (err && errlen) {
-    std::snprintf(err, errlen, "%s", msg.c_str());
-  }
-  return ok ? STV_OK : STV_EINVAL;
+  return guarded(
+      nullptr,
+      [&]() {
+        std::string msg;
+        const bool ok = validate_impl(n_levels, dim, k, lv, msg);
+        if (err && errlen) std::snprintf(err, errlen, "%s", msg.c_str());
+        return ok ? STV_OK : STV_EINVAL;
+      },
+      [&]() { if (err && errlen) std::snprintf(err, errlen, "no host memory"); });
 }
 
 int stv_set_hierarchy(stv_ctx* ctx, int n_levels, int dim, int k, const stv_level* lv) {
   if (!ctx) return STV_EINVAL;
-  return setup_packed(ctx, 1, dim, k, &n_levels, &lv);
+  return guarded(
+      ctx, [&]() { return setup_packed(ctx, 1, dim, k, &n_levels, &lv); },
+      [&]() { free_hierarchy(ctx); });
 }
 
 int stv_set_batch(stv_ctx* ctx, int n_inst, int dim, int k, const int* n_levels,
@@ -1219,7 +1251,9 @@ int stv_set_batch(stv_ctx* ctx, int n_inst, int dim, int k, const int* n_levels,
   if (!ctx) return STV_EINVAL;
   if (n_inst < 1 || n_inst > 65535) return fail(ctx, STV_EINVAL, "n_inst must be in [1, 65535]");
   if (!n_levels || !levels) return fail(ctx, STV_EINVAL, "n_levels and levels must not be NULL");
-  return setup_packed(ctx, n_inst, dim, k, n_levels, levels);
+  return guarded(
+      ctx, [&]() { return setup_packed(ctx, n_inst, dim, k, n_levels, levels); },
+      [&]() { free_hierarchy(ctx); });
 }
 
 // Real block diagonalisation of the time matrix K = D^-1 C (D = diag(tw),
@@ -1665,24 +1699,23 @@ static int coarse_pattern(stv_ctx* ctx, int g, CoarsePattern& Z) {
   }
   std::unique_ptr<int32_t[]> col(new int32_t[(size_t)L.nnzb]);
   std::unique_ptr<uint8_t[]> nz;
-  uint8_t* dev = nullptr;
+  Temp<uint8_t> dev;
   hipError_t e = hipSuccess;
   if (L.kron_ma) {
     Z.ma.reset(new double[(size_t)2 * L.nnzb]);
   } else {
     nz.reset(new uint8_t[(size_t)L.nnzb]);
-    STV_TRY(dalloc(ctx, &dev, (size_t)L.nnzb));
-    e = launch_block_nonzero(ctx->stream, ctx->b, L.val, L.nnzb, dev);
+    STV_TRY(dalloc(ctx, &dev.p, (size_t)L.nnzb));
+    e = launch_block_nonzero(ctx->stream, ctx->b, L.val, L.nnzb, dev.p);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   }
   for (const auto& r : runs) {
     const size_t q = (size_t)Z.ptr[(size_t)r.first], n = (size_t)Z.ptr[(size_t)r.second] - q;
     if (e == hipSuccess) e = hipMemcpy(col.get() + q, L.col + q, 4 * n, hipMemcpyDeviceToHost);
     if (e == hipSuccess)
-      e = dev ? hipMemcpy(nz.get() + q, dev + q, n, hipMemcpyDeviceToHost)
-              : hipMemcpy(Z.ma.get() + 2 * q, L.kron_ma + 2 * q, 16 * n, hipMemcpyDeviceToHost);
+      e = dev.p ? hipMemcpy(nz.get() + q, dev.p + q, n, hipMemcpyDeviceToHost)
+                : hipMemcpy(Z.ma.get() + 2 * q, L.kron_ma + 2 * q, 16 * n, hipMemcpyDeviceToHost);
   }
-  dfree(dev);
   STV_HIP(e);
   if (L.kron_ma) {
     Z.col = std::move(col);
@@ -1777,8 +1810,9 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
   struct Member { int g, q; CompStruct S; int group[2]; int at[4][kCcMax + 1]; };
   std::vector<Member> mem;
   auto keep = [&](auto** p, size_t n) -> int {
+    ctx->cc_bufs.push_back(nullptr);
     STV_TRY(dalloc(ctx, p, n));
-    ctx->cc_bufs.push_back((void*)*p);
+    ctx->cc_bufs.back() = (void*)*p;
     return STV_OK;
   };
   for (int g = 0; g < ctx->n_levels; ++g) {
@@ -1820,23 +1854,18 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     const int32_t *d_rp = L.rowptr, *d_col = L.col;
     const double* d_ma = L.kron_ma;
     if (!L.kron_ma) {
-      int32_t *rp2 = nullptr, *col2 = nullptr, *src = nullptr;
+      int32_t *rp2 = nullptr, *col2 = nullptr;
       double* ma2 = nullptr;
       const size_t n = Z.nz_col.size() * sb * sb;
       STV_TRY(keep(&rp2, (size_t)L.n_s * sb + 1));
       STV_TRY(keep(&col2, n));
       STV_TRY(keep(&ma2, 2 * n));
-      int32_t *ptr = nullptr, *zcol = nullptr;
-      int rc = upload(ctx, &ptr, Z.ptr.data(), Z.ptr.size());
-      if (rc == STV_OK) rc = upload(ctx, &zcol, Z.nz_col.data(), Z.nz_col.size());
-      if (rc == STV_OK) rc = upload(ctx, &src, Z.src.data(), Z.src.size());
-      hipError_t e = hipSuccess;
-      if (rc == STV_OK)
-        e = launch_expand_blocks(ctx->stream, sb, L.n_s, ptr, zcol, src, L.val, rp2, col2, ma2);
-      if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-      dfree(ptr); dfree(zcol); dfree(src);
-      STV_TRY(rc);
-      STV_HIP(e);
+      Temp<int32_t> ptr, zcol, src;
+      STV_TRY(upload(ctx, &ptr.p, Z.ptr.data(), Z.ptr.size()));
+      STV_TRY(upload(ctx, &zcol.p, Z.nz_col.data(), Z.nz_col.size()));
+      STV_TRY(upload(ctx, &src.p, Z.src.data(), Z.src.size()));
+      STV_HIP(launch_expand_blocks(ctx->stream, sb, L.n_s, ptr.p, zcol.p, src.p, L.val, rp2, col2, ma2));
+      STV_HIP(hipStreamSynchronize(ctx->stream));
       d_rp = rp2; d_col = col2; d_ma = ma2;
     }
     ctx->cc_dims[g].b = b;
@@ -2434,7 +2463,7 @@ static int make_inverse_stores(stv_ctx* ctx, int fp32, int full) {
   return STV_OK;
 }
 
-int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_cell) {
+static int build_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_cell) {
   STV_TRY(check_ctx(ctx, true, false));
   if (bad_level) *bad_level = -1;
   if (bad_cell) *bad_cell = -1;
@@ -2658,7 +2687,7 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
       ctx->cgroups_algo = -1;
       again = true;
     }
-  if (again) return stv_build_cell_inverses(ctx, storage, bad_level, bad_cell);
+  if (again) return build_inverses(ctx, storage, bad_level, bad_cell);
   for (int g = 1; g < ctx->n_levels; ++g)
     if (ctx->lv[g].n_cells > 0 && ctx->h_report[g] != none) {
       if (bad_level) *bad_level = g;
@@ -2679,6 +2708,17 @@ int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_
   }
   ctx->have_inv = true;
   return STV_OK;
+}
+
+int stv_build_cell_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_cell) {
+  return guarded(
+      ctx, [&]() { return build_inverses(ctx, storage, bad_level, bad_cell); },
+      [&]() {   // what was launched ends first
+        if (ctx->side) (void)hipStreamSynchronize(ctx->side);
+        if (ctx->side2) (void)hipStreamSynchronize(ctx->side2);
+        (void)hipStreamSynchronize(ctx->stream);
+        free_inverses(ctx);
+      });
 }
 
 int stv_residual(stv_ctx* ctx, int level, const double* r, const double* d, double* out) {
@@ -3541,23 +3581,17 @@ static int make_groups(stv_ctx* ctx, const DevLevel& L, const double* ma, KronGr
                        int32_t** idx, double** val) {
   const int D = ctx->dim;
   const size_t ns = (size_t)L.n_s;
-  uint8_t* dkind = nullptr;
-  int32_t* dn1 = nullptr;
+  Temp<uint8_t> dkind;
+  Temp<int32_t> dn1;
   std::vector<uint8_t> kind(ns);
   std::vector<int32_t> n1(ns), rp(ns + 1);
-  int rc = dalloc(ctx, &dkind, ns);
-  if (rc == STV_OK) rc = dalloc(ctx, &dn1, ns);
-  hipError_t e = hipSuccess;
-  if (rc == STV_OK) {
-    e = launch_group_classify(ctx->stream, L, ma, dkind, dn1);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e == hipSuccess) e = hipMemcpy(kind.data(), dkind, ns, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(n1.data(), dn1, 4 * ns, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(rp.data(), L.rowptr, 4 * (ns + 1), hipMemcpyDeviceToHost);
-  }
-  dfree(dkind);
-  dfree(dn1);
-  if (rc != STV_OK) return rc;
+  STV_TRY(dalloc(ctx, &dkind.p, ns));
+  STV_TRY(dalloc(ctx, &dn1.p, ns));
+  hipError_t e = launch_group_classify(ctx->stream, L, ma, dkind.p, dn1.p);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e == hipSuccess) e = hipMemcpy(kind.data(), dkind.p, ns, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemcpy(n1.data(), dn1.p, 4 * ns, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemcpy(rp.data(), L.rowptr, 4 * (ns + 1), hipMemcpyDeviceToHost);
   if (e != hipSuccess)
     return fail(ctx, STV_EHIP, std::string("row grouping failed: ") + hipGetErrorString(e));
   std::vector<int32_t> vrow, vp1(1, 0), vp2(1, 0), prow, pp(1, 0), srow, sp1(1, 0), sp2(1, 0);
@@ -3584,40 +3618,35 @@ static int make_groups(stv_ctx* ctx, const DevLevel& L, const double* ma, KronGr
   std::vector<int32_t> h;
   auto put = [&](const std::vector<int32_t>& a) { h.insert(h.end(), a.begin(), a.end()); };
   put(vrow); put(vp1); put(vp2); put(prow); put(pp); put(srow); put(sp1); put(sp2);
-  rc = dalloc(ctx, idx, h.size() + (size_t)(nv1 + nv2 + np + n_s1 + n_s2));
-  if (rc == STV_OK)
-    rc = dalloc(ctx, val, (size_t)(2 * (nv1 + n_s1) + D * nv2 + (D + 1) * D * np + n_s2));
-  if (rc == STV_OK) {
-    KronGroups G{};
-    G.n_v = (int32_t)vrow.size();
-    G.n_p = (int32_t)prow.size();
-    G.n_s = (int32_t)srow.size();
-    const int32_t* q = *idx;
-    auto take = [&](size_t n) { const int32_t* p = q; q += n; return p; };
-    G.vrow = take(vrow.size()); G.vp1 = take(vp1.size()); G.vp2 = take(vp2.size());
-    G.prow = take(prow.size()); G.pp = take(pp.size());
-    G.srow = take(srow.size()); G.sp1 = take(sp1.size()); G.sp2 = take(sp2.size());
-    G.vc1 = take((size_t)nv1); G.vc2 = take((size_t)nv2); G.pc = take((size_t)np);
-    G.sc1 = take((size_t)n_s1); G.sc2 = take((size_t)n_s2);
-    G.vma = (const double2*)*val;
-    G.sma = G.vma + nv1;
-    G.va2 = (const double*)(G.sma + n_s1);
-    G.pa = G.va2 + D * nv2;
-    G.sa2 = G.pa + (D + 1) * D * np;
-    e = hipMemcpy(*idx, h.data(), 4 * h.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = launch_group_fill(ctx->stream, L, ma, G);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess)
-      rc = fail(ctx, STV_EHIP, std::string("row grouping failed: ") + hipGetErrorString(e));
-    else
-      *out = G;
-  }
-  if (rc != STV_OK) { dfree(*idx); dfree(*val); }
-  return rc;
+  STV_TRY(dalloc(ctx, idx, h.size() + (size_t)(nv1 + nv2 + np + n_s1 + n_s2)));
+  STV_TRY(dalloc(ctx, val, (size_t)(2 * (nv1 + n_s1) + D * nv2 + (D + 1) * D * np + n_s2)));
+  KronGroups G{};
+  G.n_v = (int32_t)vrow.size();
+  G.n_p = (int32_t)prow.size();
+  G.n_s = (int32_t)srow.size();
+  const int32_t* q = *idx;
+  auto take = [&](size_t n) { const int32_t* p = q; q += n; return p; };
+  G.vrow = take(vrow.size()); G.vp1 = take(vp1.size()); G.vp2 = take(vp2.size());
+  G.prow = take(prow.size()); G.pp = take(pp.size());
+  G.srow = take(srow.size()); G.sp1 = take(sp1.size()); G.sp2 = take(sp2.size());
+  G.vc1 = take((size_t)nv1); G.vc2 = take((size_t)nv2); G.pc = take((size_t)np);
+  G.sc1 = take((size_t)n_s1); G.sc2 = take((size_t)n_s2);
+  G.vma = (const double2*)*val;
+  G.sma = G.vma + nv1;
+  G.va2 = (const double*)(G.sma + n_s1);
+  G.pa = G.va2 + D * nv2;
+  G.sa2 = G.pa + (D + 1) * D * np;
+  e = hipMemcpy(*idx, h.data(), 4 * h.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = launch_group_fill(ctx->stream, L, ma, G);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e != hipSuccess)
+    return fail(ctx, STV_EHIP, std::string("row grouping failed: ") + hipGetErrorString(e));
+  *out = G;
+  return STV_OK;   // idx and val are the caller's on every path
 }
 
-int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const double* aval,
-                         const double* C, const double* tw) {
+static int set_factors(stv_ctx* ctx, int level, const double* mval, const double* aval,
+                       const double* C, const double* tw) {
   STV_TRY(check_ctx(ctx, true, false));
   if (level < 0 || level >= ctx->n_levels) return fail(ctx, STV_EINVAL, "level out of range");
   DevLevel& L = ctx->lv[level];
@@ -3640,56 +3669,47 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
   for (int e = 0; e < b; ++e)
     if (!std::isfinite(tw[e])) return fail(ctx, STV_EINVAL, "tw must be finite");
   STV_HIP(hipStreamSynchronize(ctx->stream));
-  double *dma = nullptr, *part = nullptr, *dm = nullptr, *da = nullptr;
+  Temp<double> dma, part;
   const int nblk = 1024;
-  auto drop = [&]() { dfree(dma); dfree(part); };
-  int rc = upload(ctx, &dm, mval, (size_t)L.nnzb);
-  if (rc == STV_OK) rc = upload(ctx, &da, aval, (size_t)L.nnzb);
-  if (rc == STV_OK) rc = dalloc(ctx, &dma, (size_t)2 * L.nnzb);
-  if (rc == STV_OK) rc = dalloc(ctx, &part, (size_t)2 * nblk);
+  STV_TRY(dalloc(ctx, &dma.p, (size_t)2 * L.nnzb));
+  STV_TRY(dalloc(ctx, &part.p, (size_t)2 * nblk));
   hipError_t e = hipSuccess;
-  if (rc == STV_OK) {
-    e = launch_interleave(ctx->stream, dm, da, dma, L.nnzb);
+  {
+    Temp<double> dm, da;
+    STV_TRY(upload(ctx, &dm.p, mval, (size_t)L.nnzb));
+    STV_TRY(upload(ctx, &da.p, aval, (size_t)L.nnzb));
+    e = launch_interleave(ctx->stream, dm.p, da.p, dma.p, L.nnzb);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess)
-      rc = fail(ctx, STV_EHIP, std::string("factor upload failed: ") + hipGetErrorString(e));
+      return fail(ctx, STV_EHIP, std::string("factor upload failed: ") + hipGetErrorString(e));
   }
-  dfree(dm);
-  dfree(da);
-  if (rc != STV_OK) { drop(); return rc; }
   // the factors must reproduce the stored blocks
   std::vector<double> hp((size_t)2 * nblk);
-  e = launch_kron_check(ctx->stream, b, L, dma, C, tw, part, nblk);
-  if (e == hipSuccess) e = hipMemcpyAsync(hp.data(), part, sizeof(double) * hp.size(),
+  e = launch_kron_check(ctx->stream, b, L, dma.p, C, tw, part.p, nblk);
+  if (e == hipSuccess) e = hipMemcpyAsync(hp.data(), part.p, sizeof(double) * hp.size(),
                                           hipMemcpyDeviceToHost, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  dfree(part);
-  if (e != hipSuccess) {
-    drop();
+  if (e != hipSuccess)
     return fail(ctx, STV_EHIP, std::string("factor check failed: ") + hipGetErrorString(e));
-  }
   double dev = 0.0, mag = 0.0;
   for (int i = 0; i < nblk; ++i) {
     dev = std::max(dev, hp[(size_t)2 * i]);
     mag = std::max(mag, hp[(size_t)2 * i + 1]);
   }
-  if (!(dev <= 1e-12 * mag)) {
-    drop();
+  if (!(dev <= 1e-12 * mag))
     return fail(ctx, STV_EINVAL, "the factors do not reproduce the level's blocks (max deviation " +
                                      std::to_string(dev) + " of " + std::to_string(mag) + ")");
-  }
   KronGroups kg{};
-  int32_t* kg_idx = nullptr;
-  double* kg_val = nullptr;
-  rc = make_groups(ctx, L, dma, &kg, &kg_idx, &kg_val);
-  if (rc != STV_OK) { drop(); return rc; }
+  Temp<int32_t> kg_idx;
+  Temp<double> kg_val;
+  STV_TRY(make_groups(ctx, L, dma.p, &kg, &kg_idx.p, &kg_val.p));
   dfree(L.kron_ma); dfree(L.kg_idx); dfree(L.kg_val);
-  L.kron_ma = dma;
+  L.kron_ma = dma.release();
   L.comp_off = 0;
   for (auto& o : ctx->cc_off) o.clear();
   L.kg = kg;
-  L.kg_idx = kg_idx;
-  L.kg_val = kg_val;
+  L.kg_idx = kg_idx.release();
+  L.kg_val = kg_val.release();
   ctx->cgroups_algo = -1;   // the coarse groups are regrouped at the next build
   ctx->inv_layout = -1;     // the cell inverses may be stored time-decoupled
   for (int i = 0; i < 16; ++i) L.kron_C[i] = i < b * b ? C[i] : 0.0;
@@ -3697,6 +3717,12 @@ int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const doub
   ++ctx->generation;
   free_graph(ctx);
   return STV_OK;
+}
+
+int stv_set_kron_factors(stv_ctx* ctx, int level, const double* mval, const double* aval,
+                         const double* C, const double* tw) {
+  return guarded(
+      ctx, [&]() { return set_factors(ctx, level, mval, aval, C, tw); }, []() {});
 }
 
 int stv_set_option(stv_ctx* ctx, int option, int64_t value) {

@@ -80,3 +80,56 @@ fake.fake_limit(whole + (64 << 10))
 s.build_cell_inverses(full=True)
 s.build_cell_inverses(full=True)
 """)
+
+
+@pytest.mark.parametrize("kron", [True, False])
+def test_host_allocations_that_fail(run, kron):
+    """Every allocation of the host in turn fails once in set_hierarchy, in
+    set_kron_factors and in the build: the call returns (with STV_ENOMEM, or
+    done where a thread's job then ran in the caller), leaves no device memory
+    behind, and the same call succeeds afterwards."""
+    out = run(f"""
+p = make_problem(2, (32, 8), 2, 1, 0.01, 1e-3, 7)
+arr, keep = stv._marshal_levels(p.levels)
+s = solver()
+lib = stv._lib
+_, w, C, _ = fe.time_matrices(1)
+C = np.ascontiguousarray(C, dtype=np.float64)
+tw = np.ascontiguousarray(p.tau * np.asarray(w, dtype=np.float64))
+ma = [tuple(np.ascontiguousarray(v, dtype=np.float64) for v in spatial_factors(L)) for L in p.levels]
+hier = lambda: lib.stv_set_hierarchy(s._h, 2, 2, 1, arr)
+fact = lambda: lib.stv_set_kron_factors(s._h, 0, ma[0][0].ctypes.data, ma[0][1].ctypes.data,
+                                        C.ctypes.data, tw.ctypes.data)
+build = lambda: lib.stv_build_cell_inverses(s._h, 0, None, None)
+calls = [("hier", lambda: None, hier), ("build", hier, build)]
+if {kron}:
+    calls = [("fact", hier, fact), ("build", lambda: (hier(), fact()), build)]
+for name, before, call in calls:
+    n, failed = 0, 0
+    while True:
+        if name != "hier":
+            before()
+        base = fake.fake_used()
+        fake.fake_fail_new(n)
+        rc = call()
+        left = fake.fake_new_left()
+        fake.fake_fail_new(-1)
+        if left >= 0:           # fewer allocations than that: the last one
+            assert rc == 0, (name, n, rc)
+            break
+        assert rc in (0, stv.STV_ENOMEM), (name, n, rc)
+        failed += rc != 0
+        if rc != 0:
+            if name == "hier":
+                assert fake.fake_used() <= (1 << 20), (name, n, fake.fake_used())
+            else:
+                assert fake.fake_used() <= base + (1 << 16), (name, n, fake.fake_used(), base)
+            if n % 16 == 0:
+                if name == "build":
+                    before()
+                assert call() == 0, (name, n)
+        n += 1 if n < 200 else 7
+    print(name, n, failed)
+    assert failed > 5
+""")
+    print(out)
