@@ -465,11 +465,15 @@ k_inverse_comp(const int32_t* __restrict__ posmap, const double2* __restrict__ m
   }
 }
 
-hipError_t launch_inverse_comp(hipStream_t s, const DevLevel& L, int fp32, uint8_t* status) {
+// cap > 0: at most that many resident workgroups in 3d, striding over the cells
+// (the caller leaves the other compute units to the coarse chain beside).
+hipError_t launch_inverse_comp(hipStream_t s, const DevLevel& L, int fp32, uint8_t* status, int cap) {
   const double2* ma = (const double2*)L.kron_ma;
+  int grid = (L.n_cells + 3) / 4;
+  if (L.n_ls == 85 && cap > 0) grid = std::min(grid, cap);
 #define STV_COMP(DD, CXX, ST, t0, t1, off, acc)                                               \
   {                                                                                          \
-    k_inverse_comp<DD, CXX, ST><<<(L.n_cells + 3) / 4, 256, 0, s>>>(                         \
+    k_inverse_comp<DD, CXX, ST><<<grid, 256, 0, s>>>(                                        \
         L.posmap, ma, L.comp_flags, L.own_ptr, L.own_loc, L.inv_off, L.inv_ld, L.comp_cell,  \
         L.comp_node, L.inv_store, fp32, status, L.n_cells, t0, t1, off, acc);                \
   }

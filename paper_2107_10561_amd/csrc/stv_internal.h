@@ -467,7 +467,7 @@ hipError_t launch_cell_inverses(hipStream_t s, int b, const DevLevel& L, int fp3
                                 int reserve, int cu_cap = 0);
 // cell problems with uncoupled velocity components (k_comp.hip)
 hipError_t launch_comp_flags(hipStream_t s, const DevLevel& L, uint8_t* flags);
-hipError_t launch_inverse_comp(hipStream_t s, const DevLevel& L, int fp32, uint8_t* status);
+hipError_t launch_inverse_comp(hipStream_t s, const DevLevel& L, int fp32, uint8_t* status, int cap);
 hipError_t launch_vanka_comp(hipStream_t s, const DevLevel& L, const double* rho, double* d,
                              double omega, int zero_init, int fp32, unsigned grid);
 // transfers: shapes 1..kTransferShapes take 1, 2, 4, 8, 16 lanes per row;

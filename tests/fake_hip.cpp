@@ -18,6 +18,7 @@ namespace {
 std::mutex mu;
 std::map<const void*, std::string>& names() { static auto* m = new std::map<const void*, std::string>; return *m; }
 std::map<void*, size_t>& blocks() { static auto* m = new std::map<void*, size_t>; return *m; }
+std::map<std::string, unsigned>& grids() { static auto* m = new std::map<std::string, unsigned>; return *m; }
 size_t used = 0, peak = 0, limit = SIZE_MAX;
 std::atomic<long> new_left{-1};   // operator new calls until one fails (-1: never)
 thread_local bool inside = false;
@@ -32,11 +33,14 @@ hipError_t run(const void* f, dim3 grid, dim3 block, void** a) {
     return hipErrorInvalidConfiguration;
   std::lock_guard<std::mutex> hold(mu);
   const std::string& n = names()[f];
+  grids()[n] = grid.x;
   auto is = [&](const char* k) { return n.find(k) != std::string::npos; };
   if (is("k_gj_invert_perm"))   // every record a permutation
     memset(*(int**)a[6], 0, 4 * (size_t)grid.x);
   else if (is("k_block_nonzero"))
     memset(*(uint8_t**)a[3], 1, (size_t)*(int64_t*)a[2]);
+  else if (is("k_comp_flags"))   // the velocity components of no cell couple
+    memset(*(uint8_t**)a[2], 3, (size_t)*(int*)a[3]);
   else if (is("k_interleave"))
     for (int64_t q = 0; q < *(int64_t*)a[3]; ++q) {
       (*(double**)a[2])[2 * q] = (*(double**)a[0])[q];
@@ -84,6 +88,13 @@ size_t fake_used() { return used; }
 size_t fake_peak(int reset) { if (reset) peak = used; return peak; }
 void fake_fail_new(long n) { new_left = n; }
 long fake_new_left() { return new_left; }
+// the last grid of the kernels whose name holds the text (0: not launched)
+unsigned fake_grid(const char* name) {
+  unsigned g = 0;
+  for (const auto& k : grids())
+    if (k.first.find(name) != std::string::npos) g = k.second;
+  return g;
+}
 
 void** __hipRegisterFatBinary(const void*) { static void* m; return &m; }
 void __hipUnregisterFatBinary(void**) {}

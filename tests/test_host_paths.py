@@ -133,3 +133,18 @@ for name, before, call in calls:
     assert failed > 5
 """)
     print(out)
+
+
+@pytest.mark.parametrize("cap,grid", [(0, 256), (7, 7), (-1, 160), (1000, 256)])
+def test_cap_of_the_cell_inverses(run, cap, grid):
+    """STV_OPT_INVERSE_CUS holds for 3d cells eliminated by component: at most
+    that many workgroups of four cells (-1: five eighths of 256)."""
+    run(f"""
+p = make_problem(3, (16, 8, 8), 2, 1, 0.01, 1e-3, 7)
+s = solver()
+s.set_hierarchy(p.levels, 3, 1)
+for g in (0, 1): factors(s, [p], g)
+s.set_inverse_cus({cap})
+s.build_cell_inverses()
+assert fake.fake_grid(b"k_inverse_comp") == {grid}, fake.fake_grid(b"k_inverse_comp")
+""")
