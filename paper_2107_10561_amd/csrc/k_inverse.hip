@@ -1029,8 +1029,8 @@ static int waves_leaving(K f, int reserve) {
 
 template <int B, int NLS>
 static hipError_t inv_mfma(hipStream_t s, const DevLevel& L, int fp32, int full, uint8_t* status,
-                           int n_cu, int reserve) {
-  constexpr int NT = (B * NLS + 15) / 16;
+                           int n_cu, int reserve, double& beside_us) {
+  constexpr int N = B * NLS, NT = (N + 15) / 16;
   if constexpr (NT <= 4) {
     int grid = L.n_cells;
     if (L.dec) {
@@ -1088,15 +1088,25 @@ static hipError_t inv_mfma(hipStream_t s, const DevLevel& L, int fp32, int full,
     // launch start and end together: a coarse chain beside it (n_cu > 0) waits
     // for a whole cell at each of its launches.  Launches of 7/8 of the units
     // leave the rest to the chain (3d 32x8x8, build with chunks of 256, 240,
-    // 224, 208, 192, 160 cells: 6.0, 5.9, 3.9, 4.0, 4.1, 4.8 ms).
-    int step = L.n_cells;
-    if (NT > 8 && n_cu > 0) step = std::max(1, n_cu * 7 / 8);
-    for (int first = 0; first < L.n_cells; first += step) {
-      k_inverse_mfma<B, NLS><<<std::min(step, L.n_cells - first), NT * 64, 0, s>>>(
-          L.posmap, L.val, L.own_ptr, L.own_loc, full, L.inv_off, L.inv_ld, L.inv_store, fp32,
-          status, first);
+    // 224, 208, 192, 160 cells: 6.0, 5.9, 3.9, 4.0, 4.1, 4.8 ms), as long as it
+    // lasts: beside_us, from which a launch takes its 260 us at order 170 (fourth
+    // power of the order: 1.3 ms at 255).  The cells after it go at once (3d
+    // 64x16x16, 16,384 cells: all in such launches 20.8 ms, none 18.3; coarse
+    // level of 518 rows 20.9 and 17.7; dG(2) 111 and 101; but a chain of 16 ms
+    // beside 7,776 cells 16.2 and 18.2).
+    const int step = std::max(1, n_cu * 7 / 8);
+    for (int first = 0; first < L.n_cells;) {
+      int cnt = L.n_cells - first;
+      if (NT > 8 && n_cu > 0 && beside_us > 0.0) {
+        cnt = std::min(cnt, step);
+        beside_us -= 260.0 * (N / 170.0) * (N / 170.0) * (N / 170.0) * (N / 170.0);
+      }
+      k_inverse_mfma<B, NLS><<<cnt, NT * 64, 0, s>>>(L.posmap, L.val, L.own_ptr, L.own_loc, full,
+                                                    L.inv_off, L.inv_ld, L.inv_store, fp32, status,
+                                                    first);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
+      first += cnt;
     }
     return hipSuccess;
   }
@@ -1104,7 +1114,7 @@ static hipError_t inv_mfma(hipStream_t s, const DevLevel& L, int fp32, int full,
 
 hipError_t launch_cell_inverses(hipStream_t s, int b, const DevLevel& L, int fp32, int full,
                                 uint8_t* status, double* gscratch, int n_slots, int n_cu,
-                                int reserve, int cu_cap) {
+                                int reserve, int cu_cap, double& beside_us) {
   // beside a concurrent coarse chain (n_cu > 0) a cap leaves the other compute
   // units to the chain; cu_cap < 0: five eighths of the compute units
   const int cap = n_cu <= 0 ? 0 : cu_cap < 0 ? (n_cu * 5) / 8 : cu_cap;
@@ -1125,16 +1135,16 @@ hipError_t launch_cell_inverses(hipStream_t s, int b, const DevLevel& L, int fp3
   }
   if (L.n_ls == 21) {
     switch (b) {
-      case 1: return inv_mfma<1, 21>(s, L, fp32, full, status, n_cu, reserve);
-      case 2: return inv_mfma<2, 21>(s, L, fp32, full, status, n_cu, reserve);
-      case 3: return inv_mfma<3, 21>(s, L, fp32, full, status, n_cu, reserve);
-      case 4: return inv_mfma<4, 21>(s, L, fp32, full, status, n_cu, reserve);
+      case 1: return inv_mfma<1, 21>(s, L, fp32, full, status, n_cu, reserve, beside_us);
+      case 2: return inv_mfma<2, 21>(s, L, fp32, full, status, n_cu, reserve, beside_us);
+      case 3: return inv_mfma<3, 21>(s, L, fp32, full, status, n_cu, reserve, beside_us);
+      case 4: return inv_mfma<4, 21>(s, L, fp32, full, status, n_cu, reserve, beside_us);
     }
   } else if (L.n_ls == 85) {
     switch (b) {
-      case 1: return inv_mfma<1, 85>(s, L, fp32, full, status, n_cu, reserve);
-      case 2: return inv_mfma<2, 85>(s, L, fp32, full, status, n_cu, reserve);
-      case 3: return inv_mfma<3, 85>(s, L, fp32, full, status, n_cu, reserve);
+      case 1: return inv_mfma<1, 85>(s, L, fp32, full, status, n_cu, reserve, beside_us);
+      case 2: return inv_mfma<2, 85>(s, L, fp32, full, status, n_cu, reserve, beside_us);
+      case 3: return inv_mfma<3, 85>(s, L, fp32, full, status, n_cu, reserve, beside_us);
       default: break;
     }
   }

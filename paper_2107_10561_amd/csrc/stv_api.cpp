@@ -2573,13 +2573,21 @@ static int build_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_ce
         hipSuccess)
       n_cu = 0;
   }
+  // the chains' expected time beside them: some 60 us per panel, 100 at order
+  // 2,600 (3d without factors, 8x2x2 coarse cells: 51 panels 3.5 ms; 12x3x3: 163
+  // panels 16 ms)
+  double beside_us = 0.0;
+  for (const auto* groups : {&ctx->cgroups, &ctx->vgroups, &ctx->sgroups})
+    for (const auto& G : *groups)
+      beside_us += 60.0 * (double)(G.np / G.plan.nb) * (1.0 + (double)G.n0 / 4000.0);
   auto cell_inverses = [&]() {
     for (int g = 1; g < ctx->n_levels && e == hipSuccess; ++g) {
       const DevLevel& L = ctx->lv[g];
       if (L.n_cells == 0) continue;
       Timed t(ctx, KC_INVERSE, g, inv);
       e = launch_cell_inverses(inv, b, L, fp32, full, ctx->inv_status[g], ctx->inv_scratch[g],
-                               ctx->inv_slots[g], n_cu, STV_CHAIN_VGPRS, ctx->inverse_cus);
+                               ctx->inv_slots[g], n_cu, STV_CHAIN_VGPRS, ctx->inverse_cus,
+                               beside_us);
       if (e == hipSuccess) e = launch_first_flag(inv, ctx->inv_status[g], L.n_cells, rep + g);
       t.done();
     }

@@ -462,9 +462,11 @@ hipError_t launch_vanka_combine(hipStream_t s, int b, const DevLevel& L, double*
 // (it strides over the cells) at the wavefronts per compute unit that leave
 // `reserve` VGPRs free on every SIMD, so that the kernels of a concurrent
 // stream find room beside it.
+// beside_us: what is left of the coarse chain's expected time, less what these
+// launches take
 hipError_t launch_cell_inverses(hipStream_t s, int b, const DevLevel& L, int fp32, int full,
                                 uint8_t* status, double* gscratch, int n_slots, int n_cu,
-                                int reserve, int cu_cap = 0);
+                                int reserve, int cu_cap, double& beside_us);
 // cell problems with uncoupled velocity components (k_comp.hip)
 hipError_t launch_comp_flags(hipStream_t s, const DevLevel& L, uint8_t* flags);
 hipError_t launch_inverse_comp(hipStream_t s, const DevLevel& L, int fp32, uint8_t* status, int cap);

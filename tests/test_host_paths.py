@@ -148,3 +148,18 @@ s.set_inverse_cus({cap})
 s.build_cell_inverses()
 assert fake.fake_grid(b"k_inverse_comp") == {grid}, fake.fake_grid(b"k_inverse_comp")
 """)
+
+
+@pytest.mark.parametrize("cells,levels,last", [((16, 8, 8), 4, 0), ((16, 4, 4), 2, 224)])
+def test_cells_in_launches_beside_the_chain_only(run, cells, levels, last):
+    """3d cells without factors: launches of at most 224 cells while the coarse
+    chain is expected to last (8x2x2 coarse cells: all 256), the others at once
+    (2x1x1 coarse cells, 1,024 finest ones)."""
+    run(f"""
+p = make_problem(3, {cells}, {levels}, 1, 0.01, 1e-3, 7)
+s = solver()
+s.set_hierarchy(p.levels, 3, 1)
+s.build_cell_inverses()
+g = fake.fake_grid(b"k_inverse_mfma")
+assert {last} == 0 and g > 224 or 0 < g <= {last}, g
+""")
