@@ -182,24 +182,37 @@ int stv_instance_info(stv_ctx* ctx, int inst, stv_gmres_info* info);
 /* Extract every local Jacobian J_T (the submatrix of the level matrix on the
  * cell's DoFs, Section 4.2) on levels >= 1, invert it by Gauss-Jordan
  * elimination with partial pivoting in FP64 and store it (Section 4.3);
- * factor the coarsest matrix densely (its explicit inverse) in FP64; with
- * spatial factors on the coarsest level, the diagonal blocks of its
- * time-decoupled form are inverted instead (each the real form of a complex
- * matrix) and stv_coarse_solve applies them with the time transforms, so the
- * whole inverse is never formed.
+ * factor the coarsest matrix in FP64 for the direct solve.
  * With spatial factors on a level (stv_set_kron_factors) whose cell problems
- * fit one wavefront (n_ls = 21, k + 1 <= 3) and the owned-rows layout, the
- * level's inverses are stored time-decoupled: with D^-1 C = V T V^-1 (real
- * Jordan form), J_T^-1 = (I (x) V) Q^-1 (I (x) W), Q = M_T (x) T + A_T (x) I,
- * W = V^-1 D^-1, and Q^-1 is block diagonal in time, so one row of
- * (k+1)*n_ls values per owned spatial DoF is kept instead of k+1 rows (the
- * sweep applies the same J_T^-1).  The layout is fixed by the build that
- * made the store.
+ * fit one wavefront (n_ls = 21, k + 1 = 2 or 3; n_ls = 85, k + 1 = 2) and the
+ * owned-rows layout, the level's inverses are stored time-decoupled: with
+ * D^-1 C = V T V^-1 (real Jordan form), J_T^-1 = (I (x) V) Q^-1 (I (x) W),
+ * Q = M_T (x) T + A_T (x) I, W = V^-1 D^-1, and Q^-1 is block diagonal in
+ * time, so one row per owned spatial DoF is kept instead of k+1 rows (the
+ * sweep applies the same J_T^-1).  Where moreover no cell of the level couples
+ * its velocity components, each component's block is eliminated for itself,
+ * pivots from that block, and then the pressure's Schur complement; with
+ * n_ls = 85 the blocks' inverses and the couplings to the pressure are stored
+ * instead of whole rows.  A cell whose blocks meet a small pivot, or whose
+ * blocks' inverses cancel against the couplings, makes its level eliminate the
+ * whole cell matrices instead.  The layout is fixed by the build that made the
+ * store.
+ * The coarsest matrix, with the algorithm left to the library
+ * (STV_OPT_COARSE_ALGO 0), is cut along its block structure where it has one:
+ * per time block (with spatial factors) the velocity components, divided by
+ * separators, are eliminated first, then the Schur complement of the
+ * separators and the pressure.  stv_coarse_solve applies the time blocks'
+ * whole inverses or, for large ones, the parts.  The build solves with the
+ * parts for pseudo-random right-hand sides and eliminates the whole matrix of a
+ * member whose residuals are beyond a pivoted inverse's, or whose parts do not
+ * fit in memory.  Otherwise its explicit inverse is formed or, with spatial
+ * factors, those of the diagonal blocks of its time-decoupled form (each the
+ * real form of a complex matrix).
  * storage = STV_F64 or STV_F32, optionally | STV_STORE_FULL.  The stores
  * and the build's work buffers are owned by the context and kept between
  * builds of one hierarchy (remade when the storage flags or the coarse
- * algorithm change; a changed hierarchy frees them).  Synchronises the
- * stream.  On a zero pivot returns STV_ESINGULAR and, if non-NULL, sets
+ * algorithm change, or after a build that had to eliminate whole matrices
+ * instead; a changed hierarchy frees them).  Synchronises the stream.  On a zero pivot returns STV_ESINGULAR and, if non-NULL, sets
  * *bad_level and *bad_cell (bad_cell = -1 for the coarse matrix); the
  * inverses are then unusable until the next successful build.
  * Errors: STV_ESTATE (no hierarchy), STV_EINVAL, STV_ENOMEM, STV_EHIP. */
@@ -246,7 +259,8 @@ int stv_vcycle(stv_ctx* ctx, const double* r, double* d, const stv_mg_params* p)
  * and correction of every level below the finest; with STV_POU/STV_ADDITIVE
  * also the per-cell corrections) taken from a fixed device workspace of
  * 64 MiB that the library holds on every device it runs on until the process
- * ends, instead of the context's own buffers.  The call allocates nothing,
+ * ends, instead of the context's own buffers (a coarse solve from parts keeps a
+ * second set of its border vectors for this call).  The call allocates nothing,
  * launches eagerly on the context's stream (never the captured graph) and is
  * not recorded by stv_set_timing.  Same arguments and results as stv_vcycle
  * (bitwise).  Every call on one device shares that workspace and leaves the
@@ -349,8 +363,10 @@ int stv_level_info(stv_ctx* ctx, int level, int64_t* n_sdofs, int64_t* n_cells,
 
 /* Options (take effect at the next stv_build_cell_inverses):
  *   STV_OPT_COARSE_ALGO: how the coarsest matrix is inverted by Gauss-Jordan
- *   elimination with partial pivoting: 0 = chosen by size (default: 1 up
- *   to order 256, 3 above),
+ *   elimination: 0 (default) = cut along its block structure where it has one
+ *   (with spatial factors at any order, without above order 512; see
+ *   stv_build_cell_inverses), otherwise the whole matrix by 1 up to order
+ *   256, by 3 above.  1 to 3 eliminate the whole matrix with partial pivoting:
  *   1 = one level of narrow panels, each updating the whole matrix,
  *   2 = slabs of 64 (128 above order 5120) columns eliminated by narrow
  *   panels, then one rank-64 (128) update of the rest on the matrix cores

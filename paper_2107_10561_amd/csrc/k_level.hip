@@ -608,7 +608,8 @@ hipError_t launch_interleave(hipStream_t s, const double* m, const double* a, do
 // kind bit 0: rows i .. i + D - 1 are a velocity group; bit 1: rows i .. i + D
 // a pressure group (k_spmv_group); n1[i] = row i's blocks with m != 0.  The
 // conditions are exact (equal values, equal lengths), so a group's rows give
-// the sums that the single rows give.
+// the sums that the single rows give, to rounding: C and tw are applied once
+// per row to a group's sums, once per block to a single row's.
 template <int D>
 __global__ void __launch_bounds__(256) k_group_classify(const int32_t* __restrict__ rowptr,
                                                         const int32_t* __restrict__ col,
