@@ -53,6 +53,7 @@ __device__ __forceinline__ void atomic_max_bits(unsigned long long* at, double v
 __global__ void __launch_bounds__(64) k_cc_fill(const CompCoarse* __restrict__ cc) {
   const CompCoarse& M = cc[blockIdx.z];
   const int p = blockIdx.y, e = blockIdx.x;
+  if (p == 0 && e == 0 && threadIdx.x < kCcProbeWords) M.probe_max[threadIdx.x] = 0ull;
   if (p >= M.nblk || e >= M.n_v + M.n_p) return;
   int c = 0;
   while (c < M.nc && e >= M.off[c] + M.n[c]) ++c;
@@ -330,8 +331,9 @@ __global__ void __launch_bounds__(256) k_cc_x(const CompCoarse* __restrict__ cc,
 }
 
 // d = J^-1 r from the time blocks' whole inverses, a workgroup per spatial row:
-// z = W r on the fly, y_p = x_p z_p, d = V y.  Bound by the latency of a row's
-// loads: four are in flight per thread.
+// z = W r on the fly, y_p = x_p z_p, d = V y.  Bound by the latency of the
+// descriptor, then of a row's loads: the former are all at fixed places, four of
+// the latter in flight per thread.
 template <int B>
 __global__ void __launch_bounds__(256) k_cc_apply(const CompCoarse* __restrict__ cc,
                                                   const double* __restrict__ r,
@@ -346,13 +348,12 @@ __global__ void __launch_bounds__(256) k_cc_apply(const CompCoarse* __restrict__
   for (int p = 0; p < B; ++p) {
     acc[p] = make_double2(0.0, 0.0);
     if (p >= M.nblk) continue;
-    const int f = M.first[p];
     const bool pair = M.sz[p] == 2;
     double w0[B], w1[B];
 #pragma unroll
     for (int l = 0; l < B; ++l) {
-      w0[l] = M.W[f * B + l];
-      w1[l] = pair ? M.W[(f + 1) * B + l] : 0.0;
+      w0[l] = M.w[p][0][l];
+      w1[l] = M.w[p][1][l];
     }
     constexpr int U = 4;
     for (int c0 = threadIdx.x; c0 < n; c0 += 256 * U) {
@@ -400,9 +401,8 @@ __global__ void __launch_bounds__(256) k_cc_apply(const CompCoarse* __restrict__
     if (p >= M.nblk) continue;
     const double re = (red[0][p].x + red[1][p].x) + (red[2][p].x + red[3][p].x);
     const double im = (red[0][p].y + red[1][p].y) + (red[2][p].y + red[3][p].y);
-    const int f = M.first[p];
-    out = fma(M.V[i * B + f], re, out);
-    if (M.sz[p] == 2) out = fma(M.V[i * B + f + 1], im, out);
+    out = fma(M.v[p][0][i], re, out);
+    if (M.sz[p] == 2) out = fma(M.v[p][1][i], im, out);
   }
   d[((int64_t)M.row_off + s) * B + i] = out;
 }
@@ -427,13 +427,12 @@ __global__ void __launch_bounds__(1024) k_cc_apply_t(const CompCoarse* __restric
 #pragma unroll
   for (int l = 0; l < B; ++l) out[l] = 0.0;
   for (int p = 0; p < M.nblk; ++p) {
-    const int f = M.first[p];
     const bool pair = M.sz[p] == 2;
     double v0[B], v1[B];
 #pragma unroll
     for (int i = 0; i < B; ++i) {
-      v0[i] = M.V[i * B + f];
-      v1[i] = pair ? M.V[i * B + f + 1] : 0.0;
+      v0[i] = M.v[p][0][i];
+      v1[i] = M.v[p][1][i];
     }
     double2 t = make_double2(0.0, 0.0);
 #pragma unroll 4
@@ -462,8 +461,8 @@ __global__ void __launch_bounds__(1024) k_cc_apply_t(const CompCoarse* __restric
     t = red[0][c];
 #pragma unroll
     for (int l = 0; l < B; ++l) {
-      out[l] = fma(M.W[f * B + l], t.x, out[l]);
-      if (pair) out[l] = fma(-M.W[(f + 1) * B + l], t.y, out[l]);
+      out[l] = fma(M.w[p][0][l], t.x, out[l]);
+      if (pair) out[l] = fma(-M.w[p][1][l], t.y, out[l]);
     }
   }
   if (g != 0 || (int)blockIdx.x * NC + c >= n) return;
@@ -485,8 +484,8 @@ __global__ void __launch_bounds__(1024) k_cc_apply_t(const CompCoarse* __restric
 // 1e-4 to 10): 2 to 60 and 20 to 800 units of 2^-53 for these factors, growing
 // with the order, 5 to 300 and 20 to 400 for a pivoted inverse of the whole
 // matrix; errors beyond the pivoted inverse's came with 1e4 units and more.
-// Otherwise the build eliminates the whole coarse matrix.  Four launches of a
-// few us; the right-hand sides share every load.
+// Otherwise the build eliminates the whole coarse matrix.  Three launches (four
+// without P); the right-hand sides share every load.
 constexpr int kProbe = kCcProbe;
 
 // entry e of right-hand side j: parts in [-1, 1) from a multiplicative hash
@@ -584,7 +583,8 @@ __global__ void __launch_bounds__(256) k_cc_probe_u(const CompCoarse* __restrict
   for (int j = 0; j < kProbe; ++j) y[(int64_t)j * n_s + e] = s[j];
 }
 
-// Residuals and their scale, a wavefront per row.
+// Residuals and their scale, a wavefront per row; the member's last workgroup
+// (counted in the word after the maxima) gives the verdict.
 __global__ void __launch_bounds__(256) k_cc_probe_r(const CompCoarse* __restrict__ cc) {
   __shared__ double red[4][4];   // per wavefront: residual, scale; without a diagonal the last two
   const CompCoarse& M = cc[blockIdx.z];
@@ -631,17 +631,22 @@ __global__ void __launch_bounds__(256) k_cc_probe_r(const CompCoarse* __restrict
     for (int k = 1; k < 4; ++k) v = larger(red[k][threadIdx.x], v);
     atomic_max_bits(&M.probe_max[4 * p + threadIdx.x], v);
   }
-}
-
-__global__ void k_cc_verdict(const CompCoarse* __restrict__ cc) {
-  const CompCoarse& M = cc[blockIdx.x];
-  const int p = threadIdx.x;
-  if (p >= M.nblk) return;
-  for (int k = 0; k < 2; ++k) {
-    const double r = __builtin_bit_cast(double, M.probe_max[4 * p + 2 * k]);
-    const double s = __builtin_bit_cast(double, M.probe_max[4 * p + 2 * k + 1]);
-    if (!(r <= 0x1p-53 * (4096.0 + 2.0 * (M.n_v + M.n_p)) * s && s < INFINITY))
-      *M.verdict[p][kCcMax] = 1;
+  if (threadIdx.x != 0) return;
+  __threadfence();   // this wavefront's maxima before its arrival
+  const unsigned long long all = (unsigned long long)((n_s + 3) / 4) * M.nblk;
+  if (atomicAdd(&M.probe_max[16], 1ull) != all - 1) return;
+  __threadfence();
+  for (int q = 0; q < M.nblk; ++q) {
+    bool ok = true;
+    for (int k = 0; k < 2; ++k) {
+      auto word = [&](int i) {
+        return __builtin_bit_cast(double, __hip_atomic_load(&M.probe_max[4 * q + 2 * k + i], __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT));
+      };
+      const double res = word(0), scale = word(1);
+      ok = ok && res <= 0x1p-53 * (4096.0 + 2.0 * n_s) * scale && scale < INFINITY;
+    }
+    if (!ok) *M.verdict[q][kCcMax] = 1;
   }
 }
 
@@ -912,8 +917,6 @@ static hipError_t cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
   k_cc_probe_u<<<gs, 256, 0, s>>>(cc);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   k_cc_probe_r<<<gs, 256, 0, s>>>(cc);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_cc_verdict<<<D.cnt, 64, 0, s>>>(cc);
   return hipGetLastError();
 }
 

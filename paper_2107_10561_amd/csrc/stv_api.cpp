@@ -1888,6 +1888,11 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
         R.first[p] = T.first[p];
         R.al[p] = T.t[p][0];
         R.be[p] = T.sz[p] == 2 ? T.t[p][1] : 0.0;
+        for (int k = 0; k < T.sz[p]; ++k)
+          for (int l = 0; l < b; ++l) {
+            R.v[p][k][l] = T.V[l * b + T.first[p] + k];
+            R.w[p][k][l] = T.W[(T.first[p] + k) * b + l];
+          }
       }
       c.inv_off = -2;
       ctx->h_cc[g].push_back(R);
@@ -2007,7 +2012,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     array_at.emplace_back(&p, entries);
     entries += (n + 15) & ~size_t(15);   // 256 bytes
   };
-  STV_TRY(dalloc(ctx, &ctx->cc_probe_max, 16 * mem.size()));
+  STV_TRY(dalloc(ctx, &ctx->cc_probe_max, kCcProbeWords * mem.size()));
   std::vector<size_t> next((size_t)ctx->n_levels, 0);
   for (Member& M : mem) {
     CompCoarse& R = ctx->h_cc[M.g][next[(size_t)M.g]++];
@@ -2020,7 +2025,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     list(R.ci, M.S.ci);
     list(R.cq, M.S.cq);
     const size_t nv = (size_t)R.n_v, np = (size_t)R.n_p;
-    R.probe_max = ctx->cc_probe_max + 16 * (&M - mem.data());
+    R.probe_max = ctx->cc_probe_max + kCcProbeWords * (&M - mem.data());
     array(R.probe_y, (size_t)R.nblk * kCcProbe * (nv + np));
     array(R.probe_q, (size_t)R.nblk * kCcProbe * np);
     array(R.pw, (size_t)4 * R.nblk * np);
@@ -2619,8 +2624,6 @@ static int build_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_ce
     };
     for (auto& G : ctx->vgroups) clear(G);
     for (auto& G : ctx->sgroups) clear(G);
-    if (e == hipSuccess)   // zero bits
-      e = launch_fill(side, reinterpret_cast<double*>(ctx->cc_probe_max), 16 * (int64_t)ctx->cc_slots.size(), 0.0);
     members_do(launch_cc_fill);
     for (auto& G : ctx->vgroups) eliminate(G);
     members_do(launch_cc_schur);

@@ -222,6 +222,7 @@ struct KronCoarse {
 // largest residual and its scale, twice (bit patterns).
 constexpr int kCcMax = 12;
 constexpr int kCcProbe = 4;   // right-hand sides of the trial
+constexpr int kCcProbeWords = 17;   // its maxima (four per time block), arrivals
 struct CompCoarse {
   const int32_t *rowptr, *col;
   const double* ma;
@@ -230,6 +231,7 @@ struct CompCoarse {
   int32_t n[kCcMax], off[kCcMax];
   int sz[4], first[4];
   double al[4], be[4], V[16], W[16];
+  double v[4][2][4], w[4][2][4];   // columns of V, rows of W of each block (0: no second)
   double* A[4][kCcMax + 1];
   int64_t lda[kCcMax + 1];
   const int* rpiv[4][kCcMax + 1];
