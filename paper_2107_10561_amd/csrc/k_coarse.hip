@@ -330,17 +330,18 @@ __global__ void __launch_bounds__(256) k_cc_x(const CompCoarse* __restrict__ cc,
   }
 }
 
-// d = J^-1 r from the time blocks' whole inverses, a workgroup per spatial row:
+// d = J^-1 r from the time blocks' whole inverses, a wavefront per spatial row:
 // z = W r on the fly, y_p = x_p z_p, d = V y.  Bound by the latency of the
 // descriptor, then of a row's loads: the former are all at fixed places, four of
-// the latter in flight per thread.
+// the latter in flight per lane (a workgroup per row: 63 members of 218 rows 34 ->
+// 13 us, 72 of 458 77 -> 38 us, one of 786 5.2 -> 4.9 us, one of 1,438 9.2 -> 9.6).
 template <int B>
 __global__ void __launch_bounds__(256) k_cc_apply(const CompCoarse* __restrict__ cc,
                                                   const double* __restrict__ r,
                                                   double* __restrict__ d) {
-  __shared__ double2 red[4][B];
   const CompCoarse& M = cc[blockIdx.z];
-  const int n = M.n_v + M.n_p, s = blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int n = M.n_v + M.n_p, s = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
   if (s >= n) return;
   const double* rz = r + (int64_t)M.row_off * B;
   double2 acc[B];
@@ -356,12 +357,12 @@ __global__ void __launch_bounds__(256) k_cc_apply(const CompCoarse* __restrict__
       w1[l] = M.w[p][1][l];
     }
     constexpr int U = 4;
-    for (int c0 = threadIdx.x; c0 < n; c0 += 256 * U) {
+    for (int c0 = lane; c0 < n; c0 += 64 * U) {
       double2 x[U];
       double v[U][B];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int c = min(c0 + 256 * u, n - 1);
+        const int c = min(c0 + 64 * u, n - 1);
         x[u] = cc_get(M.Xp[p], (int64_t)s * n + c, pair);
 #pragma unroll
         for (int l = 0; l < B; ++l) v[u][l] = rz[(int64_t)c * B + l];
@@ -376,35 +377,33 @@ __global__ void __launch_bounds__(256) k_cc_apply(const CompCoarse* __restrict__
         }
         const double re = fma(x[u].x, z0, fma(-x[u].y, z1, acc[p].x));
         const double im = fma(x[u].x, z1, fma(x[u].y, z0, acc[p].y));
-        const bool in = c0 + 256 * u < n;
+        const bool in = c0 + 64 * u < n;
         acc[p].x = in ? re : acc[p].x;
         acc[p].y = in ? im : acc[p].y;
       }
     }
   }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  double out[B];
+#pragma unroll
+  for (int i = 0; i < B; ++i) out[i] = 0.0;
 #pragma unroll
   for (int p = 0; p < B; ++p) {
+    if (p >= M.nblk) continue;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
       acc[p].x += __shfl_xor(acc[p].x, off, 64);
       acc[p].y += __shfl_xor(acc[p].y, off, 64);
     }
-    if (lane == 0) red[wv][p] = acc[p];
-  }
-  __syncthreads();
-  if (threadIdx.x >= B) return;
-  const int i = threadIdx.x;
-  double out = 0.0;
 #pragma unroll
-  for (int p = 0; p < B; ++p) {
-    if (p >= M.nblk) continue;
-    const double re = (red[0][p].x + red[1][p].x) + (red[2][p].x + red[3][p].x);
-    const double im = (red[0][p].y + red[1][p].y) + (red[2][p].y + red[3][p].y);
-    out = fma(M.v[p][0][i], re, out);
-    if (M.sz[p] == 2) out = fma(M.v[p][1][i], im, out);
+    for (int i = 0; i < B; ++i) {
+      out[i] = fma(M.v[p][0][i], acc[p].x, out[i]);
+      if (M.sz[p] == 2) out[i] = fma(M.v[p][1][i], acc[p].y, out[i]);
+    }
   }
-  d[((int64_t)M.row_off + s) * B + i] = out;
+  double v = out[0];
+#pragma unroll
+  for (int i = 1; i < B; ++i) v = lane == i ? out[i] : v;
+  if (lane < B) d[((int64_t)M.row_off + s) * B + lane] = v;
 }
 
 // d = J^-T r: per time block t = sum_s conj(u_s) x_p[s, .] with u = (V^T r) (its
@@ -927,7 +926,7 @@ hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
 hipError_t launch_cc_apply(hipStream_t s, const CompCoarse* cc, const CcDims& D, bool transposed,
                            const double* r, double* d) {
   if (!D.form_c) return hipErrorInvalidValue;
-  const dim3 row(D.n_s, 1, D.cnt), col((D.n_s + 15) / 16, 1, D.cnt);
+  const dim3 row((D.n_s + 3) / 4, 1, D.cnt), col((D.n_s + 15) / 16, 1, D.cnt);
 #define STV_CC(B)                                                               \
   case B:                                                                       \
     if (transposed) launch(k_cc_apply_t<B>, col, dim3(1024), 0, s, cc, r, d);   \

@@ -1903,9 +1903,10 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     // the all-rows layout, whose transposed solves need it.  Else, several time
     // components (a complex entry per spatial pair), where one launch is the
     // faster by enough to pay for the forming within some 60 cycles, whole and
-    // parts: 436 rows (0.8 MB) 4.0 and 6.6 us, 1572 (9.9) 5.2 and 9.0, 2404 (23)
-    // 7.4 and 8.8, 3348 (45) 10.9 and 15.6, 3d 2142 (18) 6.2 and 8.7, 2806 (32)
-    // 9.1 and 10.9; 4484 (80) 16.4 and 20.2, but 0.6 ms of forming; 3d 8214 (270)
+    // parts: 436 rows (0.8 MB) 4.1 and 6.6 us, 1572 (9.9) 4.9 and 9.0, 2404 (23)
+    // 7.0 and 8.8, 3348 (45) 10.9 and 15.6, 63 members of 436 (48) 13 and 19, 3d
+    // 2142 (18) 6.2 and 8.7, 2806 (32) 9.1 and 10.9; 4484 (80) 16.4 and 20.2, but
+    // 0.6 ms of forming; 72 members of 916 (242) 38 and 66, but 0.7; 3d 8214 (270)
     // 44 and 31.  One component (real entries, larger borders): small, or while
     // the whole inverse stays in the last-level cache and the parts are more than
     // half of it: 1572 rows (20 MB) 6.3 and 10.2 us, 2404 (46) 10.7 and 13.2, 3412
