@@ -44,7 +44,7 @@ def measured_traffic(workload: str, kernel: str, launches_per_level):
     """HBM bytes per launch from the counter record in profiles/ (bytes per
     launch on each level), averaged over the given launches per level, or
     None when there is no record for this workload and kernel, a level is
-    missing, or the kernel source changed since the counters were taken."""
+    missing, or a kernel source changed since the counters were taken."""
     import hashlib
     if workload not in TRAFFIC_RECORDS:
         return None
@@ -54,13 +54,12 @@ def measured_traffic(workload: str, kernel: str, launches_per_level):
         return None
     if rec.get("workload") != workload or kernel not in rec:
         return None
-    src = os.path.join(ROOT, rec["kernel_source"])
-    try:
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
-    except OSError:
-        return None
-    if sha != rec.get("kernel_source_sha256"):
-        return None
+    for src, sha in rec["kernel_sources"].items():
+        try:
+            if hashlib.sha256(open(os.path.join(ROOT, src), "rb").read()).hexdigest() != sha:
+                return None
+        except OSError:
+            return None
     per = rec[kernel]["bytes_per_launch_by_level"]
     tot = n = 0
     for g, cnt in launches_per_level.items():
