@@ -42,9 +42,9 @@ __device__ __forceinline__ void cc_put(double2* a, int64_t e, bool pair, double2
   else reinterpret_cast<double*>(a)[e] = v.x;
 }
 
-__device__ __forceinline__ void atomic_max_bits(unsigned long long* at, double v) {
+__device__ __forceinline__ unsigned long long atomic_max_bits(unsigned long long* at, double v) {
   // non-negative doubles order as their bit patterns (a NaN above infinity)
-  atomicMax(at, __builtin_bit_cast(unsigned long long, v));
+  return atomicMax(at, __builtin_bit_cast(unsigned long long, v));
 }
 
 // The dense V_c and D in real form (the matrices zeroed before): member row
@@ -628,13 +628,15 @@ __global__ void __launch_bounds__(256) k_cc_probe_r(const CompCoarse* __restrict
   if (threadIdx.x < 4) {
     double v = red[0][threadIdx.x];
     for (int k = 1; k < 4; ++k) v = larger(red[k][threadIdx.x], v);
-    atomic_max_bits(&M.probe_max[4 * p + threadIdx.x], v);
+    const unsigned long long old = atomic_max_bits(&M.probe_max[4 * p + threadIdx.x], v);
+    // The maxima have been made where their old values are back; the arrival
+    // comes after them, without a fence (which would write the L2 back, once per
+    // workgroup: a batch of 136 members 137 us).
+    asm volatile("" : : "v"(old) : "memory");
   }
   if (threadIdx.x != 0) return;
-  __threadfence();   // this wavefront's maxima before its arrival
   const unsigned long long all = (unsigned long long)((n_s + 3) / 4) * M.nblk;
   if (atomicAdd(&M.probe_max[16], 1ull) != all - 1) return;
-  __threadfence();
   for (int q = 0; q < M.nblk; ++q) {
     bool ok = true;
     for (int k = 0; k < 2; ++k) {
