@@ -479,13 +479,27 @@ __global__ void __launch_bounds__(1024) k_cc_apply_t(const CompCoarse* __restric
 // time block counts as inverted when, over the rows with a diagonal entry and
 // over those without (of another scale: the pressure) separately,
 //   max_i |z - A y|_i <= 2^-53 (4096 + 2 n) max_i (|A| |y| + |z|)_i.
-// Measured over channel operators of order 218 to 1,706 (nu 1e-6 to 1e-1, tau
-// 1e-4 to 10): 2 to 60 and 20 to 800 units of 2^-53 for these factors, growing
-// with the order, 5 to 300 and 20 to 400 for a pivoted inverse of the whole
-// matrix; errors beyond the pivoted inverse's came with 1e4 units and more.
-// Otherwise the build eliminates the whole coarse matrix.  Three launches (four
-// without P); the right-hand sides share every load.
+// Measured over channel operators of order 210 to 9,204 (nu 1e-6 to 1e-1, tau
+// 1e-4 to 10): 2 to 5e3 units of 2^-53 on the rows with a diagonal entry,
+// within the bound for all 372; on the others 20 to 4.3e4 for these factors
+// and 20 to 2e3 for a pivoted inverse of the whole matrix, although the
+// solutions are about as accurate (errors 4e-14 to 8e-12 and 2e-13 to 7e-12):
+// those rows' |A| |y| does not hold the border's part of y, G y_border, which
+// cancels against V^-1 z (29 of the 372, on cells stretched by 3 to 1 and 5 to
+// 1, are beyond the bound).  So a time block beyond it on those rows alone is
+// looked at again: e = A^-1 (z - A y) by the factors is what the residual
+// means for y, and w = A^-1 s, s_i = +-2^-53 (|A| |y| + |z|)_i, what one
+// rounding per row does; it counts as inverted when max |e| <= 128 max |w|
+// over the rows with a diagonal entry.  Measured 5 to 82 for the 29, 137 and
+// more for operators with a velocity block close to singular that the bound
+// refuses (5e2 and more where the solution has lost two digits).  Otherwise
+// the build eliminates the whole coarse matrix.  Three launches (four without
+// P), the second look two (three) where a member needs it; the right-hand
+// sides share every load.
 constexpr int kProbe = kCcProbe;
+constexpr double kProbeNoise = 128.0;
+constexpr int kProbeParts = 16, kProbeCount = 24;   // probe_max: residuals, second look, arrivals
+static_assert(kProbeCount + 2 == kCcProbeWords);
 
 // entry e of right-hand side j: parts in [-1, 1) from a multiplicative hash
 __device__ __forceinline__ double2 cc_probe(int e, int j, bool pair) {
@@ -503,6 +517,11 @@ __device__ __forceinline__ void cc_mad(double2& s, double2 a, double2 b) {
   s.y = fma(a.x, b.y, fma(a.y, b.x, s.y));
 }
 
+__device__ __forceinline__ double cc_abs1(double2 a) { return fabs(a.x) + fabs(a.y); }
+
+// the larger of the two; a NaN stays
+__device__ __forceinline__ double cc_larger(double a, double b) { return (a != a || a > b) ? a : b; }
+
 __device__ __forceinline__ void cc_wave_sum(double2 (&s)[kProbe]) {
 #pragma unroll
   for (int j = 0; j < kProbe; ++j)
@@ -513,16 +532,55 @@ __device__ __forceinline__ void cc_wave_sum(double2 (&s)[kProbe]) {
     }
 }
 
-// Border part, a wavefront per border row: y = P z, or without P first
-// q = z_border - Z z (last false), then y = S^-1 q (last true).
+// The trial's input: the right-hand sides, or the columns that k_cc_probe_r left.
+template <bool COLS>
+__device__ __forceinline__ double2 cc_probe_in(const CompCoarse& M, const double2* z, int e, int j, bool pair) {
+  return COLS ? z[(int64_t)j * (M.n_v + M.n_p) + e] : cc_probe(e, j, pair);
+}
+
+// A workgroup's N maxima into the member's words from `at`, in its first threads.
+template <int N>
+__device__ __forceinline__ void cc_probe_max(const CompCoarse& M, int at, const double (&red)[4][N]) {
+  if (threadIdx.x >= N) return;
+  double v = red[0][threadIdx.x];
+  for (int k = 1; k < 4; ++k) v = cc_larger(red[k][threadIdx.x], v);
+  const unsigned long long old = atomic_max_bits(&M.probe_max[at + threadIdx.x], v);
+  // The maxima have been made where their old values are back; the arrival
+  // comes after them, without a fence (which would write the L2 back, once per
+  // workgroup: a batch of 136 members 137 us).
+  asm volatile("" : : "v"(old) : "memory");
+}
+
+// Whether this is the last of the `all` workgroups counted in word `at`.
+__device__ __forceinline__ bool cc_probe_last(const CompCoarse& M, int at, unsigned long long all) {
+  return atomicAdd(&M.probe_max[at], 1ull) == all - 1;
+}
+
+__device__ __forceinline__ double cc_probe_word(const CompCoarse& M, int i) {
+  return __builtin_bit_cast(double, __hip_atomic_load(&M.probe_max[i], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// On rows with a diagonal entry: the larger solution of the error columns and
+// of the noise columns (lane 0 of a wavefront).
+__device__ __forceinline__ void cc_probe_parts(const double2 (&s)[kProbe], bool diag, double (&red)[2]) {
+  red[0] = diag ? cc_larger(cc_abs1(s[0]), cc_abs1(s[1])) : 0.0;
+  red[1] = diag ? cc_larger(cc_abs1(s[2]), cc_abs1(s[3])) : 0.0;
+}
+
+// Border part, a wavefront per border row (the last row may come twice): y = P z,
+// or without P first q = z_border - Z z (last false), then y = S^-1 q (last true).
+template <bool COLS>
 __global__ void __launch_bounds__(256) k_cc_probe_p(const CompCoarse* __restrict__ cc, bool last) {
+  __shared__ double red[4][2];
   const CompCoarse& M = cc[blockIdx.z];
-  const int lane = threadIdx.x & 63;
-  const int p = blockIdx.y, m = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (p >= M.nblk || m >= M.n_p) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int p = blockIdx.y, m = min((int)blockIdx.x * 4 + wv, M.n_p - 1);
+  if (p >= M.nblk || (int)blockIdx.x * 4 >= M.n_p) return;
   const bool pair = M.sz[p] == 2, form = M.P[p] != nullptr;
   const int n_s = M.n_v + M.n_p;
   double2* q = M.probe_q + (int64_t)p * kProbe * M.n_p;
+  const double2* z = M.probe_z + (int64_t)p * (kProbe + 1) * n_s;
   double2 s[kProbe] = {};
   if (last) {
     const double2* row = M.Si[p] + (int64_t)m * M.n_p;
@@ -537,39 +595,48 @@ __global__ void __launch_bounds__(256) k_cc_probe_p(const CompCoarse* __restrict
       const double2 a = form ? cc_get(M.P[p], (int64_t)m * len + e, pair)
                              : M.Z[p][(int64_t)m * len + e];
 #pragma unroll
-      for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, cc_probe(e, j, pair));
+      for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, cc_probe_in<COLS>(M, z, e, j, pair));
     }
   }
   cc_wave_sum(s);
-  if (lane != 0) return;
-  double2* y = M.probe_y + (int64_t)p * kProbe * n_s + M.n_v + m;
+  if (lane == 0) {
+    double2* y = M.probe_y + (int64_t)p * kProbe * n_s + M.n_v + m;
 #pragma unroll
-  for (int j = 0; j < kProbe; ++j) {
-    if (last || form) {
-      y[(int64_t)j * n_s] = s[j];
-    } else {
-      const double2 z = cc_probe(M.n_v + m, j, pair);
-      q[(int64_t)j * M.n_p + m] = make_double2(z.x - s[j].x, z.y - s[j].y);
+    for (int j = 0; j < kProbe; ++j) {
+      if (last || form) {
+        y[(int64_t)j * n_s] = s[j];
+      } else {
+        const double2 v = cc_probe_in<COLS>(M, z, M.n_v + m, j, pair);
+        q[(int64_t)j * M.n_p + m] = make_double2(v.x - s[j].x, v.y - s[j].y);
+      }
     }
   }
+  if (!COLS || !(last || form)) return;
+  if (lane == 0) cc_probe_parts(s, z[(int64_t)kProbe * n_s + M.n_v + m].x != 0.0, red[wv]);
+  __syncthreads();
+  cc_probe_max(M, kProbeParts + 2 * p, red);
 }
 
-// Block part, a wavefront per row: y = V^-1 z + G y_border.
+// Block part, a wavefront per row (the last row may come twice): y = V^-1 z + G y_border.
+// With COLS the member's last workgroup (counted in the last word) gives the verdict.
+template <bool COLS>
 __global__ void __launch_bounds__(256) k_cc_probe_u(const CompCoarse* __restrict__ cc) {
+  __shared__ double red[4][2];
   const CompCoarse& M = cc[blockIdx.z];
-  const int lane = threadIdx.x & 63;
-  const int p = blockIdx.y, e = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (p >= M.nblk || e >= M.n_v) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int p = blockIdx.y, e = min((int)blockIdx.x * 4 + wv, M.n_v - 1);
+  if (p >= M.nblk || (int)blockIdx.x * 4 >= M.n_v) return;
   const bool pair = M.sz[p] == 2;
   int c = 0;
   while (c + 1 < M.nc && e >= M.off[c] + M.n[c]) ++c;
   const int n = M.n[c], o = M.off[c], n_s = M.n_v + M.n_p;
   double2* y = M.probe_y + (int64_t)p * kProbe * n_s;
+  const double2* z = M.probe_z + (int64_t)p * (kProbe + 1) * n_s;
   double2 s[kProbe] = {};
   for (int k = lane; k < n; k += 64) {
     const double2 a = cc_get(M.Vi[p][c], (int64_t)(e - o) * n + k, pair);
 #pragma unroll
-    for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, cc_probe(o + k, j, pair));
+    for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, cc_probe_in<COLS>(M, z, o + k, j, pair));
   }
   for (int m = lane; m < M.n_p; m += 64) {
     const double2 a = cc_get(M.G[p], (int64_t)e * M.n_p + m, pair);
@@ -577,13 +644,27 @@ __global__ void __launch_bounds__(256) k_cc_probe_u(const CompCoarse* __restrict
     for (int j = 0; j < kProbe; ++j) cc_mad(s[j], a, y[(int64_t)j * n_s + M.n_v + m]);
   }
   cc_wave_sum(s);
-  if (lane != 0) return;
+  if (!COLS) {
+    if (lane != 0) return;
 #pragma unroll
-  for (int j = 0; j < kProbe; ++j) y[(int64_t)j * n_s + e] = s[j];
+    for (int j = 0; j < kProbe; ++j) y[(int64_t)j * n_s + e] = s[j];
+    return;
+  }
+  if (lane == 0) cc_probe_parts(s, z[(int64_t)kProbe * n_s + e].x != 0.0, red[wv]);
+  __syncthreads();
+  cc_probe_max(M, kProbeParts + 2 * p, red);
+  if (threadIdx.x != 0) return;
+  if (!cc_probe_last(M, kProbeCount + 1, (unsigned long long)((M.n_v + 3) / 4) * M.nblk)) return;
+  for (int q = 0; q < M.nblk; ++q) {
+    int* verdict = M.verdict[q][kCcMax];
+    if (*verdict != kCcBareRows) continue;
+    const double err = cc_probe_word(M, kProbeParts + 2 * q), noise = cc_probe_word(M, kProbeParts + 2 * q + 1);
+    *verdict = !(err <= kProbeNoise * noise && noise < INFINITY);
+  }
 }
 
-// Residuals and their scale, a wavefront per row; the member's last workgroup
-// (counted in the word after the maxima) gives the verdict.
+// Residuals and their scale, a wavefront per row, and the columns of the second
+// look; the member's last workgroup gives the verdict.
 __global__ void __launch_bounds__(256) k_cc_probe_r(const CompCoarse* __restrict__ cc) {
   __shared__ double red[4][4];   // per wavefront: residual, scale; without a diagonal the last two
   const CompCoarse& M = cc[blockIdx.z];
@@ -593,6 +674,7 @@ __global__ void __launch_bounds__(256) k_cc_probe_r(const CompCoarse* __restrict
   if (p >= M.nblk || (int)blockIdx.x * 4 >= n_s) return;
   const bool pair = M.sz[p] == 2;
   const double2* y = M.probe_y + (int64_t)p * kProbe * n_s;
+  double2* cols = M.probe_z + (int64_t)p * (kProbe + 1) * n_s;
   const int32_t row = M.row_off + M.order[e];
   double2 s[kProbe] = {}, w[kProbe] = {};
   bool diag = false;
@@ -604,50 +686,43 @@ __global__ void __launch_bounds__(256) k_cc_probe_r(const CompCoarse* __restrict
     for (int j = 0; j < kProbe; ++j) {
       const double2 v = y[(int64_t)j * n_s + at];
       cc_mad(s[j], a, v);
-      w[j].x = fma(fabs(a.x) + fabs(a.y), fabs(v.x) + fabs(v.y), w[j].x);
+      w[j].x = fma(cc_abs1(a), cc_abs1(v), w[j].x);
     }
   }
   cc_wave_sum(s);
   cc_wave_sum(w);
-  auto larger = [](double a, double b) { return (a != a || a > b) ? a : b; };   // a NaN stays
-  double r = 0.0, t = 0.0;
-#pragma unroll
-  for (int j = 0; j < kProbe; ++j) {
-    const double2 z = cc_probe(e, j, pair);
-    r = larger(fabs(z.x - s[j].x) + fabs(z.y - s[j].y), r);
-    t = larger(w[j].x + fabs(z.x) + fabs(z.y), t);
-  }
   diag = __any(diag);
   if (lane == 0) {
+    double r = 0.0, t = 0.0;
+#pragma unroll
+    for (int j = 0; j < kProbe; ++j) {
+      const double2 z = cc_probe(e, j, pair), v = make_double2(z.x - s[j].x, z.y - s[j].y);
+      const double scale = w[j].x + cc_abs1(z);
+      r = cc_larger(cc_abs1(v), r);
+      t = cc_larger(scale, t);
+      if (j < 2) {
+        cols[(int64_t)j * n_s + e] = v;
+        cols[(int64_t)(j + 2) * n_s + e] = make_double2(copysign(0x1p-53 * scale, z.x), 0.0);
+      }
+    }
+    cols[(int64_t)kProbe * n_s + e] = make_double2(diag ? 1.0 : 0.0, 0.0);
     red[wv][0] = diag ? r : 0.0;
     red[wv][1] = diag ? t : 0.0;
     red[wv][2] = diag ? 0.0 : r;
     red[wv][3] = diag ? 0.0 : t;
   }
   __syncthreads();
-  if (threadIdx.x < 4) {
-    double v = red[0][threadIdx.x];
-    for (int k = 1; k < 4; ++k) v = larger(red[k][threadIdx.x], v);
-    const unsigned long long old = atomic_max_bits(&M.probe_max[4 * p + threadIdx.x], v);
-    // The maxima have been made where their old values are back; the arrival
-    // comes after them, without a fence (which would write the L2 back, once per
-    // workgroup: a batch of 136 members 137 us).
-    asm volatile("" : : "v"(old) : "memory");
-  }
+  cc_probe_max(M, 4 * p, red);
   if (threadIdx.x != 0) return;
-  const unsigned long long all = (unsigned long long)((n_s + 3) / 4) * M.nblk;
-  if (atomicAdd(&M.probe_max[16], 1ull) != all - 1) return;
+  if (!cc_probe_last(M, kProbeCount, (unsigned long long)((n_s + 3) / 4) * M.nblk)) return;
   for (int q = 0; q < M.nblk; ++q) {
-    bool ok = true;
-    for (int k = 0; k < 2; ++k) {
-      auto word = [&](int i) {
-        return __builtin_bit_cast(double, __hip_atomic_load(&M.probe_max[4 * q + 2 * k + i], __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT));
-      };
-      const double res = word(0), scale = word(1);
-      ok = ok && res <= 0x1p-53 * (4096.0 + 2.0 * n_s) * scale && scale < INFINITY;
-    }
-    if (!ok) *M.verdict[q][kCcMax] = 1;
+    auto within = [&](int k) {
+      const double res = cc_probe_word(M, 4 * q + 2 * k), scale = cc_probe_word(M, 4 * q + 2 * k + 1);
+      return res <= 0x1p-53 * (4096.0 + 2.0 * n_s) * scale && scale < INFINITY;
+    };
+    int* verdict = M.verdict[q][kCcMax];
+    if (!within(0)) *verdict = 1;
+    else if (!within(1) && *verdict == 0) *verdict = kCcBareRows;
   }
 }
 
@@ -889,6 +964,19 @@ hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D)
   return cc_slices(cc, D, [&](const CompCoarse* c, const CcDims& S) { return cc_schur(s, c, S); });
 }
 
+// The factors applied to the trial's right-hand sides or columns.
+static hipError_t cc_probe_solve(hipStream_t s, const CompCoarse* cc, const CcDims& D,
+                                 void (*border)(const CompCoarse*, bool), void (*block)(const CompCoarse*)) {
+  const dim3 gb((D.n_p + 3) / 4, D.blk, D.cnt), gv((D.n_s + 3) / 4, D.blk, D.cnt);
+  for (int last = 0; last <= !D.form_p; ++last) {
+    border<<<gb, 256, 0, s>>>(cc, last != 0);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  block<<<gv, 256, 0, s>>>(cc);
+  return hipGetLastError();
+}
+
 // After the Schur chain: S^-1, P, G and the verdicts.
 static hipError_t cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
   const unsigned cols = (D.n_p + 255) / 256;
@@ -908,21 +996,19 @@ static hipError_t cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D
     k_cc_x<<<dim3(tiles, tiles, D.cnt * D.blk), 256, 0, s>>>(cc, D.blk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const dim3 gb((D.n_p + 3) / 4, D.blk, D.cnt), gs((D.n_s + 3) / 4, D.blk, D.cnt);
-  k_cc_probe_p<<<gb, 256, 0, s>>>(cc, false);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (!D.form_p) {
-    k_cc_probe_p<<<gb, 256, 0, s>>>(cc, true);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  k_cc_probe_u<<<gs, 256, 0, s>>>(cc);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_cc_probe_r<<<gs, 256, 0, s>>>(cc);
+  if ((e = cc_probe_solve(s, cc, D, k_cc_probe_p<false>, k_cc_probe_u<false>)) != hipSuccess) return e;
+  k_cc_probe_r<<<dim3((D.n_s + 3) / 4, D.blk, D.cnt), 256, 0, s>>>(cc);
   return hipGetLastError();
 }
 
 hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
   return cc_slices(cc, D, [&](const CompCoarse* c, const CcDims& S) { return cc_finish(s, c, S); });
+}
+
+hipError_t launch_cc_second(hipStream_t s, const CompCoarse* cc, const CcDims& D) {
+  return cc_slices(cc, D, [&](const CompCoarse* c, const CcDims& S) {
+    return cc_probe_solve(s, c, S, k_cc_probe_p<true>, k_cc_probe_u<true>);
+  });
 }
 
 hipError_t launch_cc_apply(hipStream_t s, const CompCoarse* cc, const CcDims& D, bool transposed,

@@ -2029,6 +2029,7 @@ static int make_component_members(stv_ctx* ctx, const std::vector<TimeSplit>& sp
     R.probe_max = ctx->cc_probe_max + kCcProbeWords * (&M - mem.data());
     array(R.probe_y, (size_t)R.nblk * kCcProbe * (nv + np));
     array(R.probe_q, (size_t)R.nblk * kCcProbe * np);
+    array(R.probe_z, (size_t)R.nblk * (kCcProbe + 1) * (nv + np));
     array(R.pw, (size_t)4 * R.nblk * np);
     for (int p = 0; p < R.nblk; ++p) {
       for (int c = 0; c <= kCcMax; ++c) {
@@ -2676,6 +2677,20 @@ static int build_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_ce
     (void)hipStreamSynchronize(ctx->side2);
     if (e == hipSuccess) e = (e1 != hipSuccess) ? e1 : e2;
   }
+  // cut members beyond the trial's bound on nothing but rows without a diagonal
+  // entry are looked at once more (few: the others pay no launch for it)
+  const int parts_at = nrep - parts;
+  if (e == hipSuccess && parts > 0 &&
+      std::any_of(ctx->h_report + parts_at, ctx->h_report + nrep, [](int v) { return v == kCcBareRows; })) {
+    Timed t(ctx, KC_COARSE_FACTOR, 0, s);
+    for (int g = 0; g < ctx->n_levels && e == hipSuccess; ++g)
+      if (!ctx->h_cc[g].empty()) e = launch_cc_second(s, ctx->d_cc[g], ctx->cc_dims[g]);
+    t.done();
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(ctx->h_report + parts_at, rep + parts_at, sizeof(int) * (size_t)parts, hipMemcpyDeviceToHost, s);
+    const hipError_t e1 = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = e1;
+  }
   if (e != hipSuccess) {
     free_inverses(ctx);
     return fail(ctx, STV_EHIP, std::string("inverse build failed: ") + hipGetErrorString(e));
@@ -2693,7 +2708,7 @@ static int build_inverses(stv_ctx* ctx, int storage, int* bad_level, int* bad_ce
     }
   for (const CcSlot& sl : ctx->cc_slots)
     if (std::any_of(sl.verdict.begin(), sl.verdict.end(),
-                    [&](int v) { return v >= 0 && ctx->h_report[nrep - parts + v] != 0; })) {
+                    [&](int v) { return v >= 0 && ctx->h_report[parts_at + v] != 0; })) {
       ctx->cc_off[sl.level].resize(ctx->h_coarse[sl.level].size(), 0);
       ctx->cc_off[sl.level][(size_t)sl.member] = 1;
       ctx->cgroups_algo = -1;

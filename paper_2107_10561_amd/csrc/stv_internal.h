@@ -218,11 +218,14 @@ struct KronCoarse {
 // block p: the eliminated real forms A (block c, or kCcMax: the Schur
 // complement) with pivot records and verdicts, the
 // inverses Vi, Si and the factors Z, G, P of the solve.  probe_*: the trial of
-// the factors: solutions, border right-hand sides, and per time block the
-// largest residual and its scale, twice (bit patterns).
+// the factors: solutions, border right-hand sides, the columns of its second
+// look (with each row's kind), and per time block the largest residual and its
+// scale, twice, and error and noise of the second look (bit patterns).
 constexpr int kCcMax = 12;
 constexpr int kCcProbe = 4;   // right-hand sides of the trial
-constexpr int kCcProbeWords = 17;   // its maxima (four per time block), arrivals
+constexpr int kCcProbeWords = 26;   // its maxima (four, then two per time block), arrivals
+// border verdict: only the rows without a diagonal entry are beyond the trial's bound
+constexpr int kCcBareRows = 2;
 struct CompCoarse {
   const int32_t *rowptr, *col;
   const double* ma;
@@ -237,7 +240,7 @@ struct CompCoarse {
   const int* rpiv[4][kCcMax + 1];
   int* verdict[4][kCcMax + 1];
   unsigned long long* probe_max;
-  double2 *probe_y, *probe_q;
+  double2 *probe_y, *probe_q, *probe_z;
   double2* Vi[4][kCcMax];
   double2 *Si[4], *Z[4], *G[4], *P[4], *Xp[4];   // Xp: the block's whole inverse, where formed
   double2* pw;     // border vectors of the solve, two sets (launch_cc_solve)
@@ -518,6 +521,8 @@ hipError_t launch_expand_blocks(hipStream_t s, int b, int32_t n_s, const int32_t
 hipError_t launch_cc_fill(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_schur(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_finish(hipStream_t s, const CompCoarse* cc, const CcDims& D);
+// the trial's second look: verdicts kCcBareRows become 0 or 1
+hipError_t launch_cc_second(hipStream_t s, const CompCoarse* cc, const CcDims& D);
 hipError_t launch_cc_apply(hipStream_t s, const CompCoarse* cc, const CcDims& D, bool transposed,
                            const double* r, double* d);
 // set: which border vectors it works with (0: the context's, 1: stv_vcycle_noalloc's)

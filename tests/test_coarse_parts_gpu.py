@@ -154,6 +154,33 @@ def test_weak_velocity_block(stv, case, kind, delta):
     s.close()
 
 
+@pytest.mark.parametrize("n,k,factors", [((8, 8), 1, True), ((8, 8), 1, False), ((8, 8), 2, True),
+                                         ((8, 8), 2, False), ((4, 4), 3, True), ((4, 4), 3, False)])
+def test_stretched_cells_stay_cut(stv, n, k, factors):
+    """Channel operators on cells stretched by 5 to 1, with residuals on the
+    rows without a diagonal entry far above those of a pivoted inverse (1e4
+    units of 2^-53 and more): their solutions are accurate, so the member stays
+    cut (another solution than the whole elimination's, as many digits)."""
+    p = make_problem(2, n, 1, k, 1e-4, 1e-3, 7)
+    L = p.levels[0]
+    J = matrix(L, L.val, p.b)
+    r = np.random.default_rng(31).standard_normal(J.shape[0])
+    out = []
+    for algo in ("auto", "tournament"):
+        s = stv.Solver(0)
+        s.set_coarse_algorithm(algo)
+        s.set_hierarchy(p.levels, 2, k)
+        if factors:
+            _, w, C, _ = fe_time.time_matrices(k)
+            m, a = spatial_factors(L)
+            s.set_kron_factors(0, m, a, np.asarray(C, dtype=np.float64), p.tau * np.asarray(w, dtype=np.float64))
+        s.build_cell_inverses()
+        out.append(coarse_solve(s, r))
+        s.close()
+    check_solve(J, r, out[0], f"stretched {n} dG({k}) factors={factors}")
+    assert not np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("factors", [True, False])
 def test_batch_of_members_far_apart(stv, factors):
     """Eight members of 16x4 coarse cells and one of 48x12: every member's
